@@ -4,153 +4,16 @@
 //
 // Weights: Z = y - Y (the K neighbour rows), G = Z Z^T, A = G + lam tr(G) I,
 // A w~ = 1 by Cholesky, w = w~ / sum(w~); uniform weights when tr(G) = 0.
-// A workgroup (one wave) forms the Gram matrices of QPW patches one after
-// the other, every lane owning one (a, b) entry; then each lane solves one
-// patch's system.
+// Up to 8 neighbours the packed Gram matrices come from the search or k_gram
+// and a thread solves one patch's system; above that (and for every match of
+// a patch) a wave forms and solves the system of one patch in registers.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "zh_internal.h"
 
 namespace zh {
-
-// (a, b) with a >= b for packed lower index p = a (a + 1) / 2 + b
-__constant__ uint8_t c_pa[136];
-__constant__ uint8_t c_pb[136];
-static bool g_pair_table_ready[64] = {false};
-
-template <typename T, int KMAX, int QPW>
-__global__ __launch_bounds__(64) void k_lle(LleArgs a) {
-    constexpr int NPM = KMAX * (KMAX + 1) / 2;
-    constexpr int GST = NPM + 1;                      // padded per-patch stride
-    __shared__ T sG[QPW * GST];
-    __shared__ T sZ[128 * KMAX];                      // Z transposed: [dim][neighbour]
-    const int lane = threadIdx.x;
-    const int D = a.D, K = a.K;
-    const int q0 = blockIdx.x * QPW;
-
-    for (int qi = 0; qi < QPW; ++qi) {
-        const int q = q0 + qi;
-        if (q >= a.Q) break;
-        const int m = a.m[q];
-        if (m <= 0) continue;
-        const float* qrow = a.qfeat + (int64_t)q * D;
-        for (int r = 0; r < m; ++r) {
-            const int64_t id = a.ids[(int64_t)q * K + r];
-            const int64_t b = id * D, bh = id * a.hs;
-            for (int t = lane; t < D; t += 64)
-                sZ[t * KMAX + r] = (T)qrow[t] - (T)join_planes(a.hi[bh + t], a.lo[b + t]);
-        }
-        __syncthreads();
-        const int np = m * (m + 1) / 2;
-        for (int p = lane; p < np; p += 64) {
-            const int ia = c_pa[p], ib = c_pb[p];
-            T g = (T)0;
-            for (int t = 0; t < D; ++t) g += sZ[t * KMAX + ia] * sZ[t * KMAX + ib];
-            sG[qi * GST + p] = g;
-        }
-        __syncthreads();
-    }
-
-    if (lane < QPW && q0 + lane < a.Q) {
-        const int q = q0 + lane;
-        const int m = a.m[q];
-        float* wout = a.w + (int64_t)q * K;
-        if (m <= 0) {
-            for (int r = 0; r < K; ++r) wout[r] = 0.0f;
-            return;
-        }
-        T* G = sG + lane * GST;
-        auto at = [&](int i, int j) -> T& { return G[i * (i + 1) / 2 + j]; };  // i >= j
-        T tau = (T)0;
-        for (int i = 0; i < m; ++i) tau += at(i, i);
-        T wv[KMAX];
-        bool redo64 = false;
-        if (tau == (T)0) {
-            for (int i = 0; i < m; ++i) wv[i] = (T)1 / (T)m;
-        } else {
-            const T reg = (T)a.lam * tau;
-            for (int i = 0; i < m; ++i) at(i, i) += reg;
-            // Cholesky A = L L^T in place (packed lower)
-            T dmin = (T)1e300, dmax = (T)0;
-            for (int j = 0; j < m; ++j) {
-                T s = at(j, j);
-                for (int k = 0; k < j; ++k) s -= at(j, k) * at(j, k);
-                const T d = sqrt(s);
-                at(j, j) = d;
-                dmin = d < dmin ? d : dmin;
-                dmax = d > dmax ? d : dmax;
-                for (int i = j + 1; i < m; ++i) {
-                    T t = at(i, j);
-                    for (int k = 0; k < j; ++k) t -= at(i, k) * at(j, k);
-                    at(i, j) = t / d;
-                }
-            }
-            // condition estimate from the Cholesky diagonal
-            if (sizeof(T) == 4 && (double)dmax * (double)dmax > 1e6 * (double)dmin * (double)dmin) redo64 = true;
-            T y[KMAX];
-            for (int i = 0; i < m; ++i) {
-                T s = (T)1;
-                for (int k = 0; k < i; ++k) s -= at(i, k) * y[k];
-                y[i] = s / at(i, i);
-            }
-            T sum = (T)0;
-            for (int i = m - 1; i >= 0; --i) {
-                T s = y[i];
-                for (int k = i + 1; k < m; ++k) s -= at(k, i) * wv[k];
-                wv[i] = s / at(i, i);
-            }
-            for (int i = 0; i < m; ++i) sum += wv[i];
-            for (int i = 0; i < m; ++i) wv[i] /= sum;
-        }
-        if (redo64) {
-            // ill-conditioned in fp32: the whole solve again in FP64
-            if (a.n_fp64) atomicAdd(a.n_fp64, 1u);
-            double Gd[KMAX * (KMAX + 1) / 2];
-            const float* qrow = a.qfeat + (int64_t)q * D;
-            for (int i = 0; i < m; ++i)
-                for (int j = 0; j <= i; ++j) {
-                    const int64_t ii = a.ids[(int64_t)q * K + i], ij = a.ids[(int64_t)q * K + j];
-                    const int64_t bi = ii * D, bj = ij * D, hi_i = ii * a.hs, hi_j = ij * a.hs;
-                    double g = 0.0;
-                    for (int t = 0; t < D; ++t) {
-                        const double zi = (double)qrow[t] - (double)join_planes(a.hi[hi_i + t], a.lo[bi + t]);
-                        const double zj = (double)qrow[t] - (double)join_planes(a.hi[hi_j + t], a.lo[bj + t]);
-                        g += zi * zj;
-                    }
-                    Gd[i * (i + 1) / 2 + j] = g;
-                }
-            double td = 0.0;
-            for (int i = 0; i < m; ++i) td += Gd[i * (i + 1) / 2 + i];
-            for (int i = 0; i < m; ++i) Gd[i * (i + 1) / 2 + i] += (double)a.lam * td;
-            for (int j = 0; j < m; ++j) {
-                double s = Gd[j * (j + 1) / 2 + j];
-                for (int k = 0; k < j; ++k) s -= Gd[j * (j + 1) / 2 + k] * Gd[j * (j + 1) / 2 + k];
-                const double d = sqrt(s);
-                Gd[j * (j + 1) / 2 + j] = d;
-                for (int i = j + 1; i < m; ++i) {
-                    double t = Gd[i * (i + 1) / 2 + j];
-                    for (int k = 0; k < j; ++k) t -= Gd[i * (i + 1) / 2 + k] * Gd[j * (j + 1) / 2 + k];
-                    Gd[i * (i + 1) / 2 + j] = t / d;
-                }
-            }
-            double yd[KMAX], xd[KMAX], sd = 0.0;
-            for (int i = 0; i < m; ++i) {
-                double s = 1.0;
-                for (int k = 0; k < i; ++k) s -= Gd[i * (i + 1) / 2 + k] * yd[k];
-                yd[i] = s / Gd[i * (i + 1) / 2 + i];
-            }
-            for (int i = m - 1; i >= 0; --i) {
-                double s = yd[i];
-                for (int k = i + 1; k < m; ++k) s -= Gd[k * (k + 1) / 2 + i] * xd[k];
-                xd[i] = s / Gd[i * (i + 1) / 2 + i];
-            }
-            for (int i = 0; i < m; ++i) sd += xd[i];
-            for (int i = 0; i < m; ++i) wv[i] = (T)(xd[i] / sd);
-        }
-        for (int r = 0; r < K; ++r) wout[r] = r < m ? (float)wv[r] : 0.0f;
-    }
-}
 
 // One halving step of a reduce-scatter over the lanes of a half wave: lanes
 // whose bit O is clear keep the first half of their N values, the others the
@@ -418,111 +281,341 @@ hipError_t launch_lle_solve(const LleArgs& a, const void* gram, int gram_fp64, h
     return hipGetLastError();
 }
 
+// ---- systems of up to 80 rows, one wave per patch ------------------------------
+// The M rows of a patch's system are cut into NB blocks of 16; the upper block
+// triangle of A = G + lam tr(G) I sits in the wave's registers as tiles U_bj
+// (b <= j) in the layout that the 16x16x4 matrix product leaves its result
+// in: lane (g = l / 16, c = l % 16) holds column c of rows row_of(i, g),
+// i < 4. In that layout a tile is directly the B operand of a product, its
+// transpose directly the A operand (the same register for step i of both), so
+// the whole block elimination
+//   W_bj = U_bb^-1 U_bj,   U_ij -= U_bi^T W_bj   (b < i <= j)
+// runs on the matrix cores without moving data between lanes. The diagonal
+// blocks are inverted in place by the symmetric sweep operator, one pivot at
+// a time (the pivot's column reaches the lanes of a row of 16 by a DPP
+// broadcast, its row the four rows by one shuffle). lam > 0 bounds the
+// condition number of A by 1 + 1 / lam, so no pivoting is needed.
+//
+// Bound: the Gram tiles' FP64 products (64 cycles each; 28 per tile at D = 100)
+// and, per block, the chain of 16 sweeps. Measured against one wave that
+// summed G entry by entry from LDS and factorised it column by column there
+// (50 KB of LDS: three waves per compute unit): 24,236 patches of up to 72
+// matches (33 on average) 6.21 -> 0.43 ms; 62,721 patches at K = 12
+// 0.81 -> 0.11 ms (both FP64, D = 100).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+template <typename T> struct Tile;
+template <> struct Tile<float> {
+    typedef f32x4 vec;
+    static __device__ __forceinline__ vec mma(float a, float b, vec c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    // row of register i in lane group g
+    static __device__ __host__ constexpr int row_of(int i, int g) { return 4 * g + i; }
+    static constexpr int reg_of(int r) { return r & 3; }
+    static constexpr int grp_of(int r) { return r >> 2; }
+};
+template <> struct Tile<double> {
+    typedef f64x4 vec;
+    static __device__ __forceinline__ vec mma(double a, double b, vec c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __host__ constexpr int row_of(int i, int g) { return 4 * i + g; }
+    static constexpr int reg_of(int r) { return r >> 2; }
+    static constexpr int grp_of(int r) { return r & 3; }
+};
+
+template <int CTRL> __device__ __forceinline__ float dpp_mov(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL> __device__ __forceinline__ double dpp_mov(double v) {
+    const int64_t b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xFFFFFFFF), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double(((int64_t)hi << 32) | (int64_t)(uint32_t)lo);
+}
+constexpr int kDppRowBcast = 0x150;   // row_newbcast:n, lane n of each row of 16 to the row
+constexpr int kDppRowRor = 0x120;     // row_ror:n
+
+__device__ __forceinline__ float lane_value(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_value(double v, int l) {
+    const int64_t b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xFFFFFFFF), l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((int64_t)hi << 32) | (int64_t)(uint32_t)lo);
+}
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
+
+// One sweep of the symmetric 16x16 tile d on pivot P (skipped past the n used
+// rows, whose diagonal is -1 already); pmin, pmax: the pivots' range.
+template <typename T, int Pv>
+__device__ __forceinline__ void sweep_pivot(typename Tile<T>::vec& d, int n, T& pmin, T& pmax) {
+    if (Pv >= n) return;
+    const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+    constexpr int ip = Tile<T>::reg_of(Pv), gp = Tile<T>::grp_of(Pv);
+    const T piv = lane_value(d[ip], 16 * gp + Pv);
+    pmin = piv < pmin ? piv : pmin;
+    pmax = piv > pmax ? piv : pmax;
+    const T inv = (T)1 / piv;
+    const T row = __shfl(d[ip], 16 * gp + c) * inv;   // a_pc / a_pp
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const T col = dpp_mov<kDppRowBcast + Pv>(d[i]);   // a_rp
+        const bool rp = Tile<T>::row_of(i, g) == Pv, cp = c == Pv;
+        const T upd = fma_t(-col, row, d[i]);
+        d[i] = rp ? (cp ? -inv : row) : (cp ? col * inv : upd);
+    }
+}
+template <typename T, int... Pv>
+__device__ __forceinline__ void sweep_tile(typename Tile<T>::vec& d, int n, T& pmin, T& pmax,
+                                           std::integer_sequence<int, Pv...>) {
+    (sweep_pivot<T, Pv>(d, n, pmin, pmax), ...);
+}
+
+// Vectors of 16 entries come in two layouts: by column (lane holds entry c)
+// and by row (register i holds entry row_of(i, g)).
+template <typename T> __device__ __forceinline__ typename Tile<T>::vec to_rows(T v) {
+    const int g = (threadIdx.x & 63) >> 4;
+    typename Tile<T>::vec r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = __shfl(v, Tile<T>::row_of(i, g));
+    return r;
+}
+// by column: (X^T r)_c
+template <typename T>
+__device__ __forceinline__ T mul_t(const typename Tile<T>::vec& X, const typename Tile<T>::vec& r) {
+    T s = X[0] * r[0];
+#pragma unroll
+    for (int i = 1; i < 4; ++i) s = fma_t(X[i], r[i], s);
+    s += __shfl_xor(s, 16);
+    return s + __shfl_xor(s, 32);
+}
+template <typename T> __device__ __forceinline__ T row_sum16(T v) {
+    v += dpp_mov<kDppRowRor + 8>(v);
+    v += dpp_mov<kDppRowRor + 4>(v);
+    v += dpp_mov<kDppRowRor + 2>(v);
+    return v + dpp_mov<kDppRowRor + 1>(v);
+}
+
+// Weights of one patch's M <= 16 NB rows xf[id[0..M)] against the query qf, by
+// column into x[b] (entry 16 b + c). Returns the squared ratio of the largest
+// to the smallest Cholesky diagonal (the pivots' ratio).
+template <typename T, int NB, bool V4>
+__device__ __forceinline__ double lle_wave(int D, int M, double lam, const float* __restrict__ qf,
+                                           const float* __restrict__ xf, const int32_t* __restrict__ id, T (&x)[NB]) {
+    typedef typename Tile<T>::vec vec;
+    const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+    const int nb = (M + 15) >> 4;
+    const float* row[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) row[b] = 16 * b + c < M ? xf + (int64_t)id[16 * b + c] * D : nullptr;
+    // Gram tiles: 16 coordinates a step, lane group g on 16 t + 4 g .. + 3
+    vec U[NB * (NB + 1) / 2];
+    auto at = [](int b, int j) constexpr { return j * (j + 1) / 2 + b; };   // b <= j
+#pragma unroll
+    for (int p = 0; p < NB * (NB + 1) / 2; ++p) U[p] = vec{0, 0, 0, 0};
+    for (int c0 = 4 * g, t = 0; t < D; t += 16, c0 += 16) {
+        float qv[4] = {0.f, 0.f, 0.f, 0.f}, xv[NB][4];
+        if (V4) {
+            const float4 v = c0 < D ? *reinterpret_cast<const float4*>(qf + c0) : make_float4(0.f, 0.f, 0.f, 0.f);
+            qv[0] = v.x, qv[1] = v.y, qv[2] = v.z, qv[3] = v.w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) qv[e] = c0 + e < D ? qf[c0 + e] : 0.0f;
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            // rows past M equal the query: zero differences
+#pragma unroll
+            for (int e = 0; e < 4; ++e) xv[b][e] = qv[e];
+            if (row[b]) {
+                if (V4) {
+                    if (c0 < D) {
+                        const float4 v = *reinterpret_cast<const float4*>(row[b] + c0);
+                        xv[b][0] = v.x, xv[b][1] = v.y, xv[b][2] = v.z, xv[b][3] = v.w;
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (c0 + e < D) xv[b][e] = row[b][c0 + e];
+                }
+            }
+        }
+        T z[NB][4];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z[b][e] = (T)qv[e] - (T)xv[b][e];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            if (j >= nb) break;
+#pragma unroll
+            for (int b = 0; b <= j; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) U[at(b, j)] = Tile<T>::mma(z[b][e], z[j][e], U[at(b, j)]);
+        }
+    }
+    // tau = tr G; the diagonal's entries sit where row_of(i, g) = c
+    T tau = (T)0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (Tile<T>::row_of(i, g) == c) tau += U[at(b, b)][i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) tau += __shfl_xor(tau, o);
+    if (tau == (T)0) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) x[b] = 16 * b + c < M ? (T)1 / (T)M : (T)0;
+        return 1.0;
+    }
+    const T reg = (T)lam * tau;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (Tile<T>::row_of(i, g) == c) U[at(b, b)][i] = 16 * b + c < M ? U[at(b, b)][i] + reg : (T)-1;
+    // elimination; U_bb becomes -U_bb^-1, x the forward-substituted right-hand side
+    T pmin = (T)INFINITY, pmax = (T)0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) x[b] = 16 * b + c < M ? (T)1 : (T)0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        if (b >= nb) break;
+        vec& S = U[at(b, b)];
+        sweep_tile<T>(S, M - 16 * b, pmin, pmax, std::make_integer_sequence<int, 16>{});
+        x[b] = -mul_t<T>(S, to_rows(x[b]));
+        const vec y = to_rows(x[b]);
+#pragma unroll
+        for (int j = b + 1; j < NB; ++j) {
+            if (j >= nb) break;
+            x[j] -= mul_t<T>(U[at(b, j)], y);
+            vec W = {0, 0, 0, 0};   // -U_bb^-1 U_bj
+#pragma unroll
+            for (int i = 0; i < 4; ++i) W = Tile<T>::mma(S[i], U[at(b, j)][i], W);
+#pragma unroll
+            for (int k = b + 1; k <= j; ++k)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) U[at(k, j)] = Tile<T>::mma(U[at(b, k)][i], W[i], U[at(k, j)]);
+        }
+    }
+    // back substitution: x_b = y_b - U_bb^-1 sum_j U_bj x_j
+#pragma unroll
+    for (int b = NB - 2; b >= 0; --b) {
+        if (b + 1 >= nb) continue;
+        vec s = {0, 0, 0, 0};
+#pragma unroll
+        for (int j = b + 1; j < NB; ++j) {
+            if (j >= nb) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = fma_t(U[at(b, j)][i], x[j], s[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] = row_sum16(s[i]);
+        x[b] += mul_t<T>(U[at(b, b)], s);
+    }
+    T sum = (T)0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) sum += 16 * b + c < M ? x[b] : (T)0;
+    sum = row_sum16(sum);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) x[b] = 16 * b + c < M ? x[b] / sum : (T)0;
+    return (double)pmax / (double)pmin;
+}
+
+// K <= 16 neighbours, four patches a workgroup. The fp32 form solves again in
+// FP64 when the Cholesky diagonals' squared ratio exceeds 1e6.
+template <typename T, bool V4>
+__global__ __launch_bounds__(256) void k_lle16(LleArgs a) {
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (q >= a.Q) return;
+    const int M = min(a.m[q], a.K);
+    float* wout = a.w + (int64_t)q * a.K;
+    if (M <= 0) {
+        if (lane < a.K) wout[lane] = 0.0f;
+        return;
+    }
+    const float* qf = a.qfeat + (int64_t)q * a.D;
+    const int32_t* id = a.ids + (int64_t)q * a.K;
+    T x[1];
+    const double cond = lle_wave<T, 1, V4>(a.D, M, a.lam, qf, a.xf, id, x);
+    float w = (float)x[0];
+    if (sizeof(T) == 4 && cond > 1e6) {
+        if (a.n_fp64 && lane == 0) atomicAdd(a.n_fp64, 1u);
+        double xd[1];
+        lle_wave<double, 1, V4>(a.D, M, a.lam, qf, a.xf, id, xd);
+        w = (float)xd[0];
+    }
+    if (lane < a.K) wout[lane] = w;
+}
+
+hipError_t launch_lle(const LleArgs& a, hipStream_t st) {
+    if (a.Q == 0) return hipSuccess;
+    if (a.D < 1 || a.D > 128 || a.K < 1 || a.K > kMaxK || !a.xf) return hipErrorInvalidValue;
+    const dim3 grid((a.Q + 3) / 4);
+    const bool v4 = a.D % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.xf) | reinterpret_cast<uintptr_t>(a.qfeat)) & 15) == 0;
+    if (a.fp64) {
+        if (v4) hipLaunchKernelGGL((k_lle16<double, true>), grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((k_lle16<double, false>), grid, dim3(256), 0, st, a);
+    } else {
+        if (v4) hipLaunchKernelGGL((k_lle16<float, true>), grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((k_lle16<float, false>), grid, dim3(256), 0, st, a);
+    }
+    return hipGetLastError();
+}
+
 // LLE over all M matches of each patch (Section 4.2: Eq. LinSys with m
-// running over every match found, M <= kAllMax): one wave per patch. The M
-// candidate rows sit in LDS (fp32, odd stride); the packed lower triangle of
-// G = Z Z^T, z_m = q - y_m, is formed in FP64 from exact differences (sums in
-// coordinate order), tau = tr G is added times lambda to the diagonal, the
-// Cholesky factor overwrites it (column by column, lanes over rows), and two
-// triangular solves give w~ = A^-1 1, w = w~ / sum w~. tau = 0 (every
-// candidate equals the query) gives uniform weights. Weights past M are 0 and
-// list entries past M are set to -1.
+// running over every match found, M <= kAllMax), FP64 from exact differences:
+// w = w~ / sum w~, uniform when tr G = 0 (every candidate equals the query).
+// Weights past M are 0 and list entries past M are set to -1.
+template <int NB, bool V4>
 __global__ __launch_bounds__(64) void k_lle_all(int Q, int D, int cap, double lam, const float* __restrict__ qfeat,
                                                 const float* __restrict__ xf, int32_t* __restrict__ cand,
                                                 const int32_t* __restrict__ ncand, float* __restrict__ w) {
-    extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x;
-    const int q = blockIdx.x;
+    const int q = xcd_block();
+    if (q >= Q) return;
     const int M = min(ncand[q], cap);
-    const int st = D | 1;
-    double* A = reinterpret_cast<double*>(smem);                        // [cap (cap + 1) / 2]
-    double* y = A + (size_t)cap * (cap + 1) / 2;                         // [cap]
-    double* sq = y + cap;                                               // [D]
-    float* rows = reinterpret_cast<float*>(sq + D);                     // [cap][st]
-    for (int i = lane; i < D; i += 64) sq[i] = (double)qfeat[(int64_t)q * D + i];
-    for (int e = lane; e < M * D; e += 64) {
-        const int r = e / D, c = e - r * D;
-        rows[r * st + c] = xf[(int64_t)cand[(int64_t)q * cap + r] * D + c];
+    int32_t* cq = cand + (int64_t)q * cap;
+    float* wq = w + (int64_t)q * cap;
+    for (int i = M + lane; i < cap; i += 64) {
+        cq[i] = -1;
+        wq[i] = 0.0f;
     }
-    for (int i = M + lane; i < cap; i += 64) cand[(int64_t)q * cap + i] = -1;   // list entries past M
-    __syncthreads();
-    // G, packed: entry (i, j <= i) at i (i + 1) / 2 + j
-    const int np = M * (M + 1) / 2;
-    for (int e = lane; e < np; e += 64) {
-        int i = (int)((sqrt(8.0 * e + 1.0) - 1.0) * 0.5);
-        while (i * (i + 1) / 2 > e) --i;
-        while ((i + 1) * (i + 2) / 2 <= e) ++i;
-        const int j = e - i * (i + 1) / 2;
-        const float* ri = rows + i * st;
-        const float* rj = rows + j * st;
-        double g = 0.0;
-        for (int c = 0; c < D; ++c) {
-            const double zi = sq[c] - (double)ri[c];
-            const double zj = sq[c] - (double)rj[c];
-            g = g + zi * zj;
-        }
-        A[e] = g;
-    }
-    __syncthreads();
-    double tau = 0.0;
-    for (int i = lane; i < M; i += 64) tau += A[i * (i + 1) / 2 + i];
+    if (M <= 0) return;
+    double x[NB];
+    lle_wave<double, NB, V4>(D, M, lam, qfeat + (int64_t)q * D, xf, cq, x);
+    if (lane < 16) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) tau += __shfl_xor(tau, o);
-    if (M > 0 && tau == 0.0) {
-        for (int i = lane; i < cap; i += 64) w[(int64_t)q * cap + i] = i < M ? (float)(1.0 / M) : 0.0f;
-        return;
+        for (int b = 0; b < NB; ++b)
+            if (16 * b + lane < M) wq[16 * b + lane] = (float)x[b];
     }
-    for (int i = lane; i < M; i += 64) A[i * (i + 1) / 2 + i] += lam * tau;
-    __syncthreads();
-    // Cholesky, right-looking: column j, then the trailing rows of later columns
-    for (int j = 0; j < M; ++j) {
-        const int dj = j * (j + 1) / 2 + j;
-        const double d = sqrt(A[dj]);
-        __syncthreads();
-        for (int i = j + 1 + lane; i < M; i += 64) A[i * (i + 1) / 2 + j] /= d;
-        if (lane == 0) A[dj] = d;
-        __syncthreads();
-        for (int i = j + 1 + lane; i < M; i += 64) {
-            const int ri = i * (i + 1) / 2;
-            const double lij = A[ri + j];
-            for (int k = j + 1; k <= i; ++k) A[ri + k] -= lij * A[k * (k + 1) / 2 + j];
-        }
-        __syncthreads();
-    }
-    // L y = 1, then L^T w~ = y (columns in turn, lanes over the other rows)
-    for (int i = lane; i < M; i += 64) y[i] = 1.0;
-    __syncthreads();
-    for (int j = 0; j < M; ++j) {
-        const double yj = y[j] / A[j * (j + 1) / 2 + j];
-        __syncthreads();
-        if (lane == 0) y[j] = yj;
-        for (int i = j + 1 + lane; i < M; i += 64) y[i] -= A[i * (i + 1) / 2 + j] * yj;
-        __syncthreads();
-    }
-    for (int j = M - 1; j >= 0; --j) {
-        const int rj = j * (j + 1) / 2;
-        const double xj = y[j] / A[rj + j];
-        __syncthreads();
-        if (lane == 0) y[j] = xj;
-        for (int i = lane; i < j; i += 64) y[i] -= A[rj + i] * xj;
-        __syncthreads();
-    }
-    double sum = 0.0;
-    for (int i = lane; i < M; i += 64) sum += y[i];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    for (int i = lane; i < cap; i += 64) w[(int64_t)q * cap + i] = i < M ? (float)(y[i] / sum) : 0.0f;
 }
 
-size_t lle_all_lds(int cap, int D) {
-    return sizeof(double) * ((size_t)cap * (cap + 1) / 2 + cap + D) + sizeof(float) * (size_t)cap * (D | 1);
+template <int NB>
+static void launch_lle_all_nb(int Q, int D, int cap, double lam, const float* qfeat, const float* xf, int32_t* cand,
+                              const int32_t* ncand, float* w, bool v4, hipStream_t st) {
+    const dim3 grid(round_grid8(Q));
+    if (v4) hipLaunchKernelGGL((k_lle_all<NB, true>), grid, dim3(64), 0, st, Q, D, cap, lam, qfeat, xf, cand, ncand, w);
+    else hipLaunchKernelGGL((k_lle_all<NB, false>), grid, dim3(64), 0, st, Q, D, cap, lam, qfeat, xf, cand, ncand, w);
 }
 
 hipError_t launch_lle_all(int Q, int D, int cap, double lam, const float* qfeat, const float* xf, int32_t* cand,
                           const int32_t* ncand, float* w, hipStream_t st) {
     if (Q == 0) return hipSuccess;
     if (cap < 1 || cap > kAllMax || D < 1 || D > 128) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_lle_all, dim3(Q), dim3(64), lle_all_lds(cap, D), st, Q, D, cap, lam, qfeat, xf, cand, ncand, w);
+    static_assert(kAllMax <= 80, "five blocks of 16 rows");
+    const bool v4 = D % 4 == 0 && ((reinterpret_cast<uintptr_t>(xf) | reinterpret_cast<uintptr_t>(qfeat)) & 15) == 0;
+    switch ((cap + 15) / 16) {
+        case 1: launch_lle_all_nb<1>(Q, D, cap, lam, qfeat, xf, cand, ncand, w, v4, st); break;
+        case 2: launch_lle_all_nb<2>(Q, D, cap, lam, qfeat, xf, cand, ncand, w, v4, st); break;
+        case 3: launch_lle_all_nb<3>(Q, D, cap, lam, qfeat, xf, cand, ncand, w, v4, st); break;
+        case 4: launch_lle_all_nb<4>(Q, D, cap, lam, qfeat, xf, cand, ncand, w, v4, st); break;
+        default: launch_lle_all_nb<5>(Q, D, cap, lam, qfeat, xf, cand, ncand, w, v4, st); break;
+    }
     return hipGetLastError();
 }
 
@@ -807,40 +900,6 @@ hipError_t launch_b_synth_blend(const BatchImage* im, int n, int64_t tiles, int6
         case 48: return b_sb_launch<4, 8>(im, n, tiles, hr_total, K, ids, m, wt, mu, resid, part, st);
         default: return hipErrorInvalidValue;
     }
-}
-
-hipError_t lle_init() {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 64 && g_pair_table_ready[dev]) return hipSuccess;
-    uint8_t pa[136], pb[136];
-    int p = 0;
-    for (int i = 0; i < 16; ++i)
-        for (int j = 0; j <= i; ++j) {
-            pa[p] = (uint8_t)i;
-            pb[p] = (uint8_t)j;
-            ++p;
-        }
-    e = hipMemcpyToSymbol(HIP_SYMBOL(c_pa), pa, sizeof(pa));
-    if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_pb), pb, sizeof(pb));
-    if (e == hipSuccess && dev < 64) g_pair_table_ready[dev] = true;
-    return e;
-}
-
-hipError_t launch_lle(const LleArgs& a, hipStream_t st) {
-    if (a.Q == 0) return hipSuccess;
-    if (a.D > 128 || a.K > kMaxK) return hipErrorInvalidValue;
-    if (a.K <= 8) {
-        const int grid = (a.Q + 63) / 64;
-        if (a.fp64) hipLaunchKernelGGL((k_lle<double, 8, 64>), dim3(grid), dim3(64), 0, st, a);
-        else hipLaunchKernelGGL((k_lle<float, 8, 64>), dim3(grid), dim3(64), 0, st, a);
-    } else {
-        const int grid = (a.Q + 15) / 16;
-        if (a.fp64) hipLaunchKernelGGL((k_lle<double, 16, 16>), dim3(grid), dim3(64), 0, st, a);
-        else hipLaunchKernelGGL((k_lle<float, 16, 16>), dim3(grid), dim3(64), 0, st, a);
-    }
-    return hipGetLastError();
 }
 
 }  // namespace zh

@@ -495,7 +495,7 @@ zh_status zh_create(zh_ctx** out, int device, void* hip_stream) {
     c->device = device;
     c->stream = (hipStream_t)hip_stream;
     if (const char* lim = std::getenv("ZH_MEM_LIMIT")) c->mem_limit = (size_t)std::strtoull(lim, nullptr, 10);
-    if (hipSetDevice(device) != hipSuccess || lle_init() != hipSuccess) {
+    if (hipSetDevice(device) != hipSuccess) {
         (void)hipGetLastError();
         delete c;
         return ZH_EDEVICE;

@@ -201,15 +201,16 @@ struct LleArgs {
     float* w;                // [Q, K]
     unsigned int* n_fp64;    // FP64 redo count (nullable)
 };
-hipError_t lle_init();  // once per device, before any launch_lle
 // packed Gram matrices [Q, 36] of the <= 8 neighbours (Z = query - rows),
 // two patches per wave; then the weights from them, one thread per patch
 hipError_t launch_gram(const LleArgs& a, void* gram, int gram_fp64, hipStream_t st);
 hipError_t launch_lle_solve(const LleArgs& a, const void* gram, int gram_fp64, hipStream_t st);
+// the weights of K <= 16 neighbours, Gram matrix and solve in one kernel, a wave per patch
 hipError_t launch_lle(const LleArgs& a, hipStream_t st);
 // LLE over all M <= cap matches of each patch: cand[Q, cap] (IDs, M = ncand
-// capped; entries past M set to -1), weights w[Q, cap] (0 past M); Gram and solves in FP64; the LDS of
-// a workgroup (packed Gram, rows) stays within 64 KB up to cap 80 at D = 100
+// capped; entries past M set to -1), weights w[Q, cap] (0 past M); Gram and
+// solves in FP64 in the registers of one wave per patch (five blocks of 16
+// rows)
 constexpr int kAllMax = 80;
 hipError_t launch_lle_all(int Q, int D, int cap, double lam, const float* qfeat, const float* xf, int32_t* cand,
                           const int32_t* ncand, float* w, hipStream_t st);

@@ -883,156 +883,227 @@ __global__ __launch_bounds__(256) void k_cand_t(int Q, int L, int64_t N, int t, 
     if (lane == 0) counts[q] = (int32_t)kept;
 }
 
-// K nearest of the t-of-L candidates, however many there are. One wave per
-// patch walks its bins as k_cand_t does (an ID kept at its first table when
-// it has at least t hits); each lane with a kept ID sums its squared l2
-// distance over the coordinates in index order in FP64 (each term rounded
-// before it is added, as the oracle's loop), and the wave merges the chunk's
-// (distance, ID) pairs into a running top K held by lanes 0..K-1: K rounds
-// of a wave minimum over both sets. IDs are distinct across chunks (first
-// occurrences only), so no pair is seen twice.
-template <int DT>
-__global__ __launch_bounds__(256) void k_knn_tofl(int Q, int L, int64_t N, int t, int Drt, int K,
-                                                  const uint2* __restrict__ bins, const uint32_t* __restrict__ tids,
-                                                  const float* __restrict__ qfeat, const float* __restrict__ xf,
-                                                  int32_t* __restrict__ counts, int32_t* __restrict__ out_ids,
-                                                  float* __restrict__ out_d, int32_t* __restrict__ out_m) {
-    __shared__ uint32_t s_off[4][64], s_cnt[4][64];
-    __shared__ int64_t s_st[4][64];
-    __shared__ double s_q[4][kL1MaxD];
-    const int D = DT ? DT : Drt;
-    const int lane = __lane_id(), wv = threadIdx.x >> 6;
-    const int q = blockIdx.x * 4 + wv;
-    if (q >= Q) return;
-    const uint2 b = lane < L ? bins[(int64_t)lane * Q + q] : make_uint2(0u, 0u);
-    int64_t incl = b.y;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int64_t v = __shfl_up(incl, o);
-        if (lane >= o) incl += v;
-    }
-    s_off[wv][lane] = b.x;
-    s_cnt[wv][lane] = b.y;
-    s_st[wv][lane] = incl - b.y;
-    for (int i = lane; i < D; i += 64) s_q[wv][i] = (double)qfeat[(int64_t)q * D + i];
-    const int64_t S = __shfl(incl, 63);
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    auto in_bin = [&](int l, uint32_t x) {
-        const uint32_t* p = tids + (int64_t)l * N + s_off[wv][l];
-        uint32_t lo = 0, hi = s_cnt[wv][l];
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (p[mid] < x) lo = mid + 1;
-            else hi = mid;
+// K nearest of the IDs that at least t of a patch's L bins hold, however many
+// there are (t = 1: of the union). One workgroup per patch.
+//
+// The bins are sorted by ID, so they are taken together in windows of
+// ascending ID ranges of at most kWinMax entries: with more entries left, every
+// bin may offer kWinMax / (bins left) of them, the window ends before the
+// smallest ID that lies just past such an offer, and each bin takes its IDs
+// below that end. A window's entries go into a hash table in LDS (open
+// addressing; a byte per slot counts the bins that hold the ID); the entry
+// that brings an ID to t bins appends it to the window's list. Each ID of the
+// list gets its squared distance as the FP64 sequential sum over the
+// coordinates in index order (each term rounded before it is added, the
+// definition), a lane per ID, and enters its wave's running K nearest, kept
+// sorted in lanes 0 .. K-1, when it beats the K-th; the four waves' lists are
+// merged at the end. IDs are distinct across windows.
+//
+// Bound: the LDS inserts of the bins' entries, then the rows of the listed
+// IDs. The form before searched every other bin for each entry (L - 1 binary
+// searches of dependent loads), and the union without a stop was sorted in
+// LDS by one wave: 14,732 patches, L = 16, 100k pairs, t = 2:
+// 14.8 -> 0.91 ms; 3,600 patches, L = 8, 20k pairs at D = 25, t = 1 (unions of
+// up to 1,600 IDs): 2.37 -> 0.06 ms.
+constexpr int kWinMax = 2048;               // entries of a window
+constexpr int kWinSlots = 2 * kWinMax;      // largest hash table: load at most 1/2
+
+// (d, id) of the lanes with `act` into the K smallest held sorted by lanes 0 .. K-1
+__device__ __forceinline__ void topk_insert(bool act, double d, int id, int K, double& bd, int& bi) {
+    const int lane = __lane_id();
+    for (;;) {
+        const uint64_t kb = (uint64_t)__double_as_longlong(bd);
+        const double kd = __longlong_as_double(
+            (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(kb >> 32), K - 1) << 32) |
+                      (uint32_t)__builtin_amdgcn_readlane((int)kb, K - 1)));
+        const int ki = __builtin_amdgcn_readlane(bi, K - 1);
+        const uint64_t todo = __ballot(act && (d < kd || (d == kd && id < ki)));
+        if (!todo) return;
+        const int src = __builtin_ctzll(todo);
+        const double nd = __shfl(d, src);
+        const int ni = __builtin_amdgcn_readlane(id, src);
+        const int at = __popcll(__ballot(lane < K && (bd < nd || (bd == nd && bi < ni))));
+        const double ud = __shfl_up(bd, 1);
+        const int ui = __shfl_up(bi, 1);
+        if (lane > at) {
+            bd = ud;
+            bi = ui;
+        } else if (lane == at) {
+            bd = nd;
+            bi = ni;
         }
-        return lo < s_cnt[wv][l] && p[lo] == x;
-    };
-    // running top K: lane k < K holds the k-th smallest (distance, ID) so far
+        if (lane == src) act = false;
+    }
+}
+
+template <int DT>
+__global__ __launch_bounds__(256) void k_bins_rank(int Q, int L, int64_t N, int t, int Drt, int K,
+                                                   const uint2* __restrict__ bins, const uint32_t* __restrict__ tids,
+                                                   const float* __restrict__ qfeat, const float* __restrict__ xf,
+                                                   int32_t* __restrict__ counts, int32_t* __restrict__ out_ids,
+                                                   float* __restrict__ out_d, int32_t* __restrict__ out_m,
+                                                   unsigned int* __restrict__ counters) {
+    __shared__ uint32_t s_key[kWinSlots];
+    __shared__ uint32_t s_cnt[kWinSlots / 4];
+    __shared__ uint32_t s_list[kWinMax];
+    __shared__ double s_q[kL1MaxD];
+    __shared__ int64_t s_ofs[64];
+    __shared__ int s_start[64];
+    __shared__ int s_nk;
+    __shared__ double s_td[4 * kMaxK];
+    __shared__ int s_ti[4 * kMaxK];
+    const int D = DT ? DT : Drt;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int q = xcd_block();
+    if (q >= Q) return;
+    for (int i = tid; i < D; i += 256) s_q[i] = (double)qfeat[(int64_t)q * D + i];
+    // every wave holds the patch's bins in its lanes: the position of the next
+    // entry and the entries left
+    const uint2 b = lane < L ? bins[(int64_t)lane * Q + q] : make_uint2(0u, 0u);
+    const uint32_t* src = tids + (int64_t)lane * N + b.x;
+    int64_t pos = (int64_t)lane * N + b.x;
+    uint32_t left = b.y;
+    if (counters && tid < 64) {
+        // patches over the limits of the LDS forms of the union search
+        const int total = wave_sum_i32((int)min(left, 8193u));
+        if (lane == 0 && total > 2048) {
+            atomicAdd(&counters[C_OVERFLOW], 1u);
+            if (total > 8192) atomicAdd(&counters[C_STREAM], 1u);
+        }
+    }
     double bd = INFINITY;
     int bi = 0x7FFFFFFF;
-    int64_t kept = 0;
-    for (int64_t e0 = 0; e0 < S; e0 += 64) {
-        const int64_t e = e0 + lane;
-        bool keep = false;
-        uint32_t x = 0;
-        if (e < S) {
-            int l = 0;
-            while (l + 1 < L && s_st[wv][l + 1] <= e) ++l;
-            x = tids[(int64_t)l * N + s_off[wv][l] + (e - s_st[wv][l])];
-            bool first = true;
-            for (int j = 0; j < l && first; ++j) first = !in_bin(j, x);
-            if (first) {
-                int hits = 1;
-                for (int j = l + 1; j < L && hits < t; ++j) hits += in_bin(j, x) ? 1 : 0;
-                keep = hits >= t;
+    int kept = 0;
+    for (bool more = true; more;) {
+        // ---- the window: `take` entries of every bin
+        uint32_t take = left;
+        more = wave_sum_i32((int)min(left, (uint32_t)kWinMax + 1u)) > kWinMax;
+        if (more) {
+            const uint32_t quota = (uint32_t)kWinMax / (uint32_t)__popcll(__ballot(left > 0));
+            const uint32_t end = wave_min_u32(left > quota ? src[quota] : 0xFFFFFFFFu);
+            uint32_t lo = 0, hi = min(left, quota);
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (src[mid] < end) lo = mid + 1;
+                else hi = mid;
             }
+            take = lo;
         }
-        const uint64_t mask = __ballot(keep);
-        kept += __popcll(mask);
-        if (!mask) continue;
-        double nd = INFINITY;
-        int ni = 0x7FFFFFFF;
-        if (keep) {
-            const float* row = xf + (int64_t)x * D;
-            double acc = 0.0;
-            if ((D & 3) == 0) {
-                const float4* r4 = reinterpret_cast<const float4*>(row);
-                for (int i = 0; i < D; i += 4) {
-                    const float4 v = r4[i >> 2];
-                    const double t0 = s_q[wv][i] - (double)v.x;
-                    acc = acc + t0 * t0;
-                    const double t1 = s_q[wv][i + 1] - (double)v.y;
-                    acc = acc + t1 * t1;
-                    const double t2 = s_q[wv][i + 2] - (double)v.z;
-                    acc = acc + t2 * t2;
-                    const double t3 = s_q[wv][i + 3] - (double)v.w;
-                    acc = acc + t3 * t3;
-                }
-            } else {
-                for (int i = 0; i < D; ++i) {
-                    const double t0 = s_q[wv][i] - (double)row[i];
-                    acc = acc + t0 * t0;
-                }
-            }
-            nd = acc;
-            ni = (int)x;
+        const int incl = wave_incl_scan((int)take);
+        const int n = __shfl(incl, 63);
+        int lg = 6;
+        while ((1 << lg) < 2 * n) ++lg;
+        __syncthreads();   // the last window's list and table are no longer read
+        if (wv == 0) {
+            s_start[lane] = incl - (int)take;
+            s_ofs[lane] = pos - (incl - (int)take);
         }
-        // K rounds: the smallest of the running top K and the chunk's pairs
-        double rd = INFINITY;
-        int ri = 0x7FFFFFFF;
-        for (int k = 0; k < K; ++k) {
-            const bool bfirst = bd < nd || (bd == nd && bi < ni);
-            double md = bfirst ? bd : nd;
-            int mi = bfirst ? bi : ni;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                const double od = __shfl_xor(md, o);
-                const int oi = __shfl_xor(mi, o);
-                if (od < md || (od == md && oi < mi)) {
-                    md = od;
-                    mi = oi;
-                }
+        for (int i = tid; i < (1 << lg); i += 256) s_key[i] = 0xFFFFFFFFu;
+        if (t > 1)
+            for (int i = tid; i < (1 << lg) / 4; i += 256) s_cnt[i] = 0u;
+        if (tid == 0) s_nk = 0;
+        __syncthreads();
+        // ---- its entries into the table
+        const uint32_t mask = (1u << lg) - 1u;
+        for (int e = tid; e < n; e += 256) {
+            int lo = 0, hi = L;   // the last bin that starts at or before e
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (s_start[mid] <= e) lo = mid;
+                else hi = mid;
             }
-            if (bi == mi && bd == md) {
-                bd = INFINITY;
-                bi = 0x7FFFFFFF;
-            } else if (ni == mi && nd == md) {
-                nd = INFINITY;
-                ni = 0x7FFFFFFF;
+            const uint32_t id = tids[s_ofs[lo] + e];
+            uint32_t slot = (id * 0x9E3779B1u) >> (32 - lg);
+            uint32_t old;
+            for (;;) {
+                old = atomicCAS(&s_key[slot], 0xFFFFFFFFu, id);
+                if (old == 0xFFFFFFFFu || old == id) break;
+                slot = (slot + 1u) & mask;
             }
-            if (lane == k) {
-                rd = md;
-                ri = mi;
+            bool list = old == 0xFFFFFFFFu;
+            if (t > 1) {
+                const int sh = 8 * (slot & 3u);
+                list = (int)((atomicAdd(&s_cnt[slot >> 2], 1u << sh) >> sh) & 0xFFu) == t - 1;
             }
+            if (list) s_list[atomicAdd(&s_nk, 1)] = id;
         }
-        bd = rd;
-        bi = ri;
+        __syncthreads();
+        // ---- distances of the listed IDs
+        const int nk = s_nk;
+        kept += nk;
+        for (int c0 = 64 * wv; c0 < nk; c0 += 256) {
+            const bool act = c0 + lane < nk;
+            const int id = act ? (int)s_list[c0 + lane] : 0;
+            double d = 0.0;
+            if (act) {
+                const float* row = xf + (int64_t)id * D;
+                if ((D & 3) == 0) {
+                    const float4* r4 = reinterpret_cast<const float4*>(row);
+#pragma unroll 5
+                    for (int i = 0; i < D; i += 4) {
+                        const float4 v = r4[i >> 2];
+                        const double t0 = s_q[i] - (double)v.x;
+                        d = d + t0 * t0;
+                        const double t1 = s_q[i + 1] - (double)v.y;
+                        d = d + t1 * t1;
+                        const double t2 = s_q[i + 2] - (double)v.z;
+                        d = d + t2 * t2;
+                        const double t3 = s_q[i + 3] - (double)v.w;
+                        d = d + t3 * t3;
+                    }
+                } else {
+#pragma unroll 5
+                    for (int i = 0; i < D; ++i) {
+                        const double t0 = s_q[i] - (double)row[i];
+                        d = d + t0 * t0;
+                    }
+                }
+                if (!(d == d)) d = INFINITY;   // not a number: last, by ID
+            }
+            topk_insert(act, d, id, K, bd, bi);
+        }
+        pos += take;
+        src += take;
+        left -= take;
     }
-    const int m = (int)(kept < K ? kept : K);
-    if (lane < m) {
-        out_ids[(int64_t)q * K + lane] = bi;
-        out_d[(int64_t)q * K + lane] = (float)bd;
-    } else if (lane < K) {
-        out_ids[(int64_t)q * K + lane] = -1;
-        out_d[(int64_t)q * K + lane] = 0.0f;
+    // ---- the K nearest of the waves' lists
+    if (lane < K) {
+        s_td[wv * K + lane] = bd;
+        s_ti[wv * K + lane] = bi;
+    }
+    __syncthreads();
+    if (wv > 0) return;
+    const bool act = lane < 4 * K;
+    const double d = act ? s_td[lane] : INFINITY;
+    const int id = act ? s_ti[lane] : 0x7FFFFFFF;
+    bd = INFINITY;
+    bi = 0x7FFFFFFF;
+    topk_insert(act, d, id, K, bd, bi);
+    const int m = kept < K ? kept : K;
+    if (lane < K) {
+        out_ids[(int64_t)q * K + lane] = lane < m ? bi : -1;
+        out_d[(int64_t)q * K + lane] = lane < m ? (float)bd : 0.0f;
     }
     if (lane == 0) {
-        counts[q] = (int32_t)kept;
+        counts[q] = kept;
         out_m[q] = m;
     }
 }
 
-hipError_t launch_knn_tofl(int Q, int L, int64_t N, int t, int D, int K, const uint2* bins, const uint32_t* tids,
-                           const float* qfeat, const float* xf, int32_t* counts, int32_t* ids, float* d, int32_t* m,
-                           hipStream_t st) {
+hipError_t launch_bins_rank(int Q, int L, int64_t N, int t, int D, int K, const uint2* bins, const uint32_t* tids,
+                            const float* qfeat, const float* xf, int32_t* counts, int32_t* ids, float* d, int32_t* m,
+                            unsigned int* counters, hipStream_t st) {
     if (Q == 0) return hipSuccess;
     if (L < 1 || L > 64 || t < 1 || t > L || K < 1 || K > kMaxK || D < 1 || D > kL1MaxD) return hipErrorInvalidValue;
-    const dim3 grid((Q + 3) / 4);
-    if (D == 100) hipLaunchKernelGGL(k_knn_tofl<100>, grid, dim3(256), 0, st, Q, L, N, t, D, K, bins, tids, qfeat, xf, counts, ids, d, m);
-    else if (D == 25) hipLaunchKernelGGL(k_knn_tofl<25>, grid, dim3(256), 0, st, Q, L, N, t, D, K, bins, tids, qfeat, xf, counts, ids, d, m);
-    else hipLaunchKernelGGL(k_knn_tofl<0>, grid, dim3(256), 0, st, Q, L, N, t, D, K, bins, tids, qfeat, xf, counts, ids, d, m);
+    if ((D & 3) == 0 && (reinterpret_cast<uintptr_t>(xf) & 15)) return hipErrorInvalidValue;
+    const dim3 grid(round_grid8(Q));
+#define ZH_BINS_RANK(DT)                                                                                              \
+    hipLaunchKernelGGL(k_bins_rank<DT>, grid, dim3(256), 0, st, Q, L, N, t, D, K, bins, tids, qfeat, xf, counts, ids, \
+                       d, m, counters)
+    if (D == 100) ZH_BINS_RANK(100);
+    else if (D == 25) ZH_BINS_RANK(25);
+    else ZH_BINS_RANK(0);
+#undef ZH_BINS_RANK
     return hipGetLastError();
 }
 

@@ -418,6 +418,17 @@ zh_status store_features(zh_ctx* c, Dict& d, const float* feat) {
 // cand_only (early stop): the candidate counts and the dump only; the
 // neighbour outputs and the Gram matrices of the last search stay as they are
 zh_status run_search(zh_ctx* c, Dict& d, int32_t* dump, int dump_cap, bool cand_only = false) {
+    if (c->opts.cap == 0 && c->opts.rerank == 0 && !dump) {
+        // the union without a stop, ranked by the FP64 distance itself. The
+        // kernels below take the bf16 pre-rank (rerank > 0) and the candidate
+        // lists (dump), whose IDs they sort.
+        c->gram_ready = false;
+        StageTimer t(c, ZH_T_SEARCH);
+        HIPCHK(c, launch_bins_rank((int)c->Q, d.L, d.n, 1, d.D, c->qK, P<uint2>(c->qbins), P<uint32_t>(d.tids),
+                                   P<float>(c->qfeat), P<float>(d.xf), P<int32_t>(c->ncand), P<int32_t>(c->ids),
+                                   P<float>(c->d2), P<int32_t>(c->m), P<unsigned int>(c->counters), c->stream));
+        return ZH_OK;
+    }
     SearchArgs a{};
     a.Q = (int)c->Q;
     a.D = d.D;
@@ -2133,9 +2144,9 @@ zh_status zh_knn_t(zh_ctx* c, int t) {
     TRY(set_device(c));
     {
         StageTimer tm(c, ZH_T_SEARCH);
-        HIPCHK(c, launch_knn_tofl((int)c->Q, d.L, d.n, t, d.D, c->qK, P<uint2>(c->qbins), P<uint32_t>(d.tids),
-                                  P<float>(c->qfeat), P<float>(d.xf), P<int32_t>(c->ncand), P<int32_t>(c->ids),
-                                  P<float>(c->d2), P<int32_t>(c->m), c->stream));
+        HIPCHK(c, launch_bins_rank((int)c->Q, d.L, d.n, t, d.D, c->qK, P<uint2>(c->qbins), P<uint32_t>(d.tids),
+                                   P<float>(c->qfeat), P<float>(d.xf), P<int32_t>(c->ncand), P<int32_t>(c->ids),
+                                   P<float>(c->d2), P<int32_t>(c->m), nullptr, c->stream));
     }
     c->gram_ready = false;   // the Gram matrices of the new neighbours are formed by zh_lle_weights
     c->stage = 1;

@@ -238,11 +238,13 @@ hipError_t launch_min_i32(int n, const int32_t* in, int cap, int32_t* out, hipSt
 hipError_t launch_knn_l1_screened(int Q, int K, int cap, const float* qfeat, const float* xf, const uint8_t* l1s,
                                   const int32_t* cand, const int32_t* ncand, int32_t* ids, float* d, int32_t* m,
                                   int32_t* ns, hipStream_t st);
-// K nearest (squared l2, sequential FP64) of each patch's t-of-L candidates,
-// any number of them; counts[Q] the t-of-L counts
-hipError_t launch_knn_tofl(int Q, int L, int64_t N, int t, int D, int K, const uint2* bins, const uint32_t* tids,
-                           const float* qfeat, const float* xf, int32_t* counts, int32_t* ids, float* d, int32_t* m,
-                           hipStream_t st);
+// K nearest (squared l2, sequential FP64) of the IDs that at least t of each
+// patch's bins hold, any number of them; counts[Q] their numbers. counters
+// (nullable): C_OVERFLOW and C_STREAM count the patches whose bins hold more
+// than 2048 and 8192 entries
+hipError_t launch_bins_rank(int Q, int L, int64_t N, int t, int D, int K, const uint2* bins, const uint32_t* tids,
+                            const float* qfeat, const float* xf, int32_t* counts, int32_t* ids, float* d, int32_t* m,
+                            unsigned int* counters, hipStream_t st);
 hipError_t launch_cand_t(int Q, int L, int64_t N, int t, const uint2* bins, const uint32_t* tids, int cap,
                          int32_t* counts, int32_t* ids, hipStream_t st);
 int64_t entropy_scratch_bytes(int L, uint64_t cap);

@@ -903,7 +903,7 @@ __global__ __launch_bounds__(256) void k_cand_t(int Q, int L, int64_t N, int t, 
 // IDs. The form before searched every other bin for each entry (L - 1 binary
 // searches of dependent loads), and the union without a stop was sorted in
 // LDS by one wave: 14,732 patches, L = 16, 100k pairs, t = 2:
-// 14.8 -> 0.91 ms; 3,600 patches, L = 8, 20k pairs at D = 25, t = 1 (unions of
+// 14.8 -> 0.56 ms; 3,600 patches, L = 8, 20k pairs at D = 25, t = 1 (unions of
 // up to 1,600 IDs): 2.37 -> 0.06 ms.
 constexpr int kWinMax = 2048;               // entries of a window
 constexpr int kWinSlots = 2 * kWinMax;      // largest hash table: load at most 1/2
@@ -954,8 +954,9 @@ __global__ __launch_bounds__(256) void k_bins_rank(int Q, int L, int64_t N, int 
     __shared__ int s_ti[4 * kMaxK];
     const int D = DT ? DT : Drt;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int q = xcd_block();
-    if (q >= Q) return;
+    // not in runs per XCD: the patches of a flat region, the longest ones, are
+    // neighbours (0.91 against 0.56 ms on the 14,732 patches above)
+    const int q = blockIdx.x;
     for (int i = tid; i < D; i += 256) s_q[i] = (double)qfeat[(int64_t)q * D + i];
     // every wave holds the patch's bins in its lanes: the position of the next
     // entry and the entries left
@@ -1096,7 +1097,7 @@ hipError_t launch_bins_rank(int Q, int L, int64_t N, int t, int D, int K, const 
     if (Q == 0) return hipSuccess;
     if (L < 1 || L > 64 || t < 1 || t > L || K < 1 || K > kMaxK || D < 1 || D > kL1MaxD) return hipErrorInvalidValue;
     if ((D & 3) == 0 && (reinterpret_cast<uintptr_t>(xf) & 15)) return hipErrorInvalidValue;
-    const dim3 grid(round_grid8(Q));
+    const dim3 grid(Q);
 #define ZH_BINS_RANK(DT)                                                                                              \
     hipLaunchKernelGGL(k_bins_rank<DT>, grid, dim3(256), 0, st, Q, L, N, t, D, K, bins, tids, qfeat, xf, counts, ids, \
                        d, m, counters)

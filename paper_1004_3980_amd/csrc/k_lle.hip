@@ -630,10 +630,22 @@ hipError_t launch_lle_all(int Q, int D, int cap, double lam, const float* qfeat,
 // tile's region: the (TI + 4) s x (TJ + 4) s HR pixels its patches cover,
 // together with the count of covering patches of every LR cell. Regions go
 // to a partial buffer; k_sb_combine then gives each HR pixel the sum of the
-// (at most four) regions that hold it, in tile order, divided by the summed
+// regions that hold it, in tile order, divided by the summed
 // count, or the bicubic of the LR image where no patch covers it. The sum
 // of a pixel is therefore taken patch row by patch row in row-major order
 // inside a tile and tile by tile across tiles.
+//
+//
+// Bound: the gather of the residual rows. The neighbours of the next row are
+// staged while the current row is added (two barriers a row; three, and the
+// lists in chunks of eight, before: 1020x1020 patches x2 556 -> 540 us, 3.4 GB
+// of rows at 6.3 TB/s; 247x259 x2 60 -> 39; 207x303 x4 at K = 12 157 -> 106).
+//
+// An image of few tiles leaves most of the chip idle for the chain of a tile's
+// rows, so its patches are written out after all (k_sb_patch, a thread per
+// load of a residual row) and summed by a thread per HR pixel (k_sb_gather) in
+// the order above, tile by tile: the same bits either way.
+constexpr int kSbThreads = 512;   // 256 take 5-15% longer
 template <int s, int TI>
 struct SbGeom {
     static constexpr int ps = kPatch * s, ps2 = ps * ps;
@@ -643,23 +655,57 @@ struct SbGeom {
     static constexpr int CY = TI + kPatch - 1, CX = TJ + kPatch - 1;   // LR cells of a region
     static constexpr int RY = CY * s, RX = CX * s;                       // HR pixels of a region
     static constexpr int64_t PART = (int64_t)RY * RX + CY * CX;         // floats + counts per tile
+    static size_t lds(int K) { return sizeof(float) * (size_t)(TJ * ps2 + PART + 2 * TJ * K + 2 * TJ); }
 };
+
+// Chunk c (VEC floats) of the synthesised patch sum_m w_m r_{n_m}, mq rows of
+// the lists id and wt, as fused multiply-adds in order from zero.
+template <int ps2, int VEC>
+__device__ __forceinline__ void synth_chunk(const float* __restrict__ resid, const int* id, const float* wt, int mq,
+                                            int c, float (&acc)[VEC]) {
+    const char* base = reinterpret_cast<const char*>(resid) + c * (VEC * 4);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[e] = 0.0f;
+    for (int r0 = 0; r0 < mq; r0 += 8) {
+        float v[8][VEC], wr[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const bool ok = r0 + r < mq;
+            wr[r] = ok ? wt[r0 + r] : 0.0f;
+            const float* x = reinterpret_cast<const float*>(
+                base + (uint64_t)(uint32_t)(ok ? id[r0 + r] : 0) * (uint32_t)(4 * ps2));
+            if constexpr (VEC == 4) {
+                const float4 t = ok ? *reinterpret_cast<const float4*>(x) : make_float4(0.f, 0.f, 0.f, 0.f);
+                v[r][0] = t.x;
+                v[r][1] = t.y;
+                v[r][2] = t.z;
+                v[r][3] = t.w;
+            } else {
+                v[r][0] = ok ? *x : 0.0f;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) acc[e] = fmaf(wr[r], v[r][e], acc[e]);
+    }
+}
 
 template <int s, int TI>
 __device__ __forceinline__ void sb_tile(const int32_t* __restrict__ ids, const int32_t* __restrict__ m,
                                         const float* __restrict__ wt, const double* __restrict__ mu,
                                         const float* __restrict__ resid, int K, int h, int w, int64_t tile,
-                                        float* __restrict__ part) {
+                                        float* __restrict__ part, float* smem) {
     using G = SbGeom<s, TI>;
     constexpr int ps = G::ps, ps2 = G::ps2, VEC = G::VEC, NCH = G::NCH, TJ = G::TJ;
-    constexpr int CX = G::CX, RY = G::RY, RX = G::RX, CY = G::CY;
-    __shared__ __align__(16) float sx[TJ * ps2];   // the synthesised patches of one patch row
-    __shared__ float sacc[RY * RX];
-    __shared__ int scnt[CY * CX];
-    __shared__ int64_t sbase[TJ * 8];              // residual row offsets of a chunk (-1: none)
-    __shared__ float swt[TJ * 8];
-    __shared__ int sflag[TJ];
-    __shared__ float smu[TJ];
+    constexpr int CX = G::CX, RX = G::RX, CY = G::CY, RY = G::RY, NT = kSbThreads;
+    float* sx = smem;                                     // [TJ][ps2] the synthesised patches of one patch row
+    float* sacc = sx + TJ * ps2;                          // [RY][RX]
+    int* scnt = reinterpret_cast<int*>(sacc + RY * RX);   // [CY][CX]
+    int* sid = scnt + CY * CX;                            // [TJ][K] neighbours and weights of one patch row
+    float* swt = reinterpret_cast<float*>(sid + TJ * K);
+    int* smq = reinterpret_cast<int*>(swt + TJ * K);      // [TJ] neighbours used, patch means
+    float* smu = reinterpret_cast<float*>(smq + TJ);
     const int tid = threadIdx.x;
     const int npi = h - kPatch + 1, npj = w - kPatch + 1;
     const int ntj = (npj + TJ - 1) / TJ;
@@ -668,84 +714,72 @@ __device__ __forceinline__ void sb_tile(const int32_t* __restrict__ ids, const i
     if (npi <= 0 || npj <= 0 || tile >= (int64_t)((npi + TI - 1) / TI) * ntj) return;
     const int ti = (int)(tile / ntj), tj = (int)(tile - (int64_t)ti * ntj);
     const int i0 = ti * TI, j0 = tj * TJ;
-    for (int e = tid; e < RY * RX; e += 256) sacc[e] = 0.0f;
-    for (int e = tid; e < CY * CX; e += 256) scnt[e] = 0;
+    const int nc = min(TJ, npj - j0);
+    auto stage = [&](int ii) {
+        const int64_t q0 = (int64_t)(i0 + ii) * npj + j0;
+        const int32_t* ip = ids + q0 * K;
+        const float* wp = wt + q0 * K;
+        for (int e = tid; e < nc * K; e += NT) {
+            sid[e] = ip[e];
+            swt[e] = wp[e];
+        }
+        for (int jj = NT - 1 - tid; jj < TJ; jj += NT) {
+            const int mq = jj < nc ? min(m[q0 + jj], K) : 0;
+            smq[jj] = mq;
+            smu[jj] = mq > 0 ? (float)mu[q0 + jj] : 0.0f;
+        }
+    };
+    stage(0);
+    for (int e = tid; e < RY * RX; e += NT) sacc[e] = 0.0f;
+    for (int e = tid; e < CY * CX; e += NT) scnt[e] = 0;
+    __syncthreads();
     for (int ii = 0; ii < TI && i0 + ii < npi; ++ii) {
-        const int64_t qrow = (int64_t)(i0 + ii) * npj;
         // ---- the patches of this row
-        for (int r0 = 0; r0 < K; r0 += 8) {
-            __syncthreads();   // the previous chunk, row or the zeroing is done
-            for (int e = tid; e < TJ * 8; e += 256) {
-                const int jj = e >> 3, r = e & 7, j = j0 + jj;
-                const int64_t q = qrow + j;
-                const int mq = j < npj ? m[q] : 0;
-                const bool ok = r0 + r < mq;
-                sbase[e] = ok ? (int64_t)ids[q * K + r0 + r] * ps2 : -1;
-                swt[e] = ok ? wt[q * K + r0 + r] : 0.0f;
-                if (r0 == 0 && r == 0) {
-                    sflag[jj] = mq > 0;
-                    smu[jj] = mq > 0 ? (float)mu[q] : 0.0f;
-                }
-            }
-            __syncthreads();
-            const bool last = r0 + 8 >= K;
-            for (int it = tid; it < TJ * NCH; it += 256) {
-                const int jj = it / NCH, c = it - jj * NCH;
-                float* dst = sx + jj * ps2 + c * VEC;
-                float acc[VEC];
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) acc[e] = r0 == 0 ? 0.0f : dst[e];
-                float v[8][VEC];
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const int64_t b = sbase[jj * 8 + r];
-                    if constexpr (VEC == 4) {
-                        const float4 x = b >= 0 ? *reinterpret_cast<const float4*>(resid + b + 4 * c)
-                                                : make_float4(0.f, 0.f, 0.f, 0.f);
-                        v[r][0] = x.x;
-                        v[r][1] = x.y;
-                        v[r][2] = x.z;
-                        v[r][3] = x.w;
-                    } else {
-                        v[r][0] = b >= 0 ? resid[b + c] : 0.0f;
-                    }
-                }
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const float wr = swt[jj * 8 + r];
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) acc[e] = fmaf(wr, v[r][e], acc[e]);
-                }
-                const float mf = last ? smu[jj] : 0.0f;
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) dst[e] = last ? mf + acc[e] : acc[e];
-            }
+        for (int it = tid; it < TJ * NCH; it += NT) {
+            const int jj = it / NCH, c = it - jj * NCH;
+            const int mq = smq[jj];
+            float acc[VEC];
+            synth_chunk<ps2, VEC>(resid, sid + jj * K, swt + jj * K, mq, c, acc);
+            float* dst = sx + jj * ps2 + c * VEC;
+            const float mf = smu[jj];
+            if constexpr (VEC == 4)
+                *reinterpret_cast<float4*>(dst) = make_float4(mf + acc[0], mf + acc[1], mf + acc[2], mf + acc[3]);
+            else
+                dst[0] = mf + acc[0];
         }
         __syncthreads();
         // ---- their values added to the region rows s ii .. s ii + 5 s
-        for (int it = tid; it < ps * RX; it += 256) {
+        uint64_t has = 0;   // patches of the row that have neighbours
+        {
+            const int jj = tid & 63;
+            has = __ballot(jj < TJ && smq[jj < TJ ? jj : 0] > 0);
+        }
+        for (int it = tid; it < ps * RX; it += NT) {
             const int u = it / RX, X = it - u * RX;
             const int cl = X / s;
             const int jlo = cl - (kPatch - 1) > 0 ? cl - (kPatch - 1) : 0, jhi = cl < TJ - 1 ? cl : TJ - 1;
             float* a = sacc + (s * ii + u) * RX + X;
             float acc = *a;
             for (int jj = jlo; jj <= jhi; ++jj)
-                if (sflag[jj]) acc += sx[jj * ps2 + u * ps + X - s * jj];
+                if ((has >> jj) & 1u) acc += sx[jj * ps2 + u * ps + X - s * jj];
             *a = acc;
         }
-        for (int it = tid; it < kPatch * CX; it += 256) {
+        for (int it = tid; it < kPatch * CX; it += NT) {
             const int cu = it / CX, cl = it - cu * CX;
             const int jlo = cl - (kPatch - 1) > 0 ? cl - (kPatch - 1) : 0, jhi = cl < TJ - 1 ? cl : TJ - 1;
-            int n = 0;
-            for (int jj = jlo; jj <= jhi; ++jj) n += sflag[jj];
-            scnt[(ii + cu) * CX + cl] += n;
+            const uint64_t cols = (2ull << jhi) - (1ull << jlo);
+            scnt[(ii + cu) * CX + cl] += __popcll(has & cols);
         }
+        if (ii + 1 < TI && i0 + ii + 1 < npi) {
+            __syncthreads();   // the flags are no longer read
+            stage(ii + 1);
+        }
+        __syncthreads();
     }
-    __syncthreads();
     float* pa = part + tile * G::PART;
     int* pc = reinterpret_cast<int*>(pa + RY * RX);
-    for (int e = tid; e < RY * RX; e += 256) pa[e] = sacc[e];
-    for (int e = tid; e < CY * CX; e += 256) pc[e] = scnt[e];
+    for (int e = tid; e < RY * RX; e += NT) pa[e] = sacc[e];
+    for (int e = tid; e < CY * CX; e += NT) pc[e] = scnt[e];
 }
 
 template <int s, int TI>
@@ -774,11 +808,12 @@ __device__ __forceinline__ float sb_pixel(const float* __restrict__ part, const 
 }
 
 template <int s, int TI>
-__global__ __launch_bounds__(256) void k_sb_tile(int K, int h, int w, const int32_t* __restrict__ ids,
-                                                 const int32_t* __restrict__ m, const float* __restrict__ wt,
-                                                 const double* __restrict__ mu, const float* __restrict__ resid,
-                                                 float* __restrict__ part) {
-    sb_tile<s, TI>(ids, m, wt, mu, resid, K, h, w, xcd_block(), part);
+__global__ __launch_bounds__(kSbThreads) void k_sb_tile(int K, int h, int w, const int32_t* __restrict__ ids,
+                                                        const int32_t* __restrict__ m, const float* __restrict__ wt,
+                                                        const double* __restrict__ mu,
+                                                        const float* __restrict__ resid, float* __restrict__ part) {
+    extern __shared__ __align__(16) float smem[];
+    sb_tile<s, TI>(ids, m, wt, mu, resid, K, h, w, xcd_block(), part, smem);
 }
 
 template <int s, int TI>
@@ -792,19 +827,96 @@ __global__ __launch_bounds__(256) void k_sb_combine(const float* __restrict__ pa
     }
 }
 
+// Images of few tiles, first kernel: the synthesised patches [Q][ps2], a
+// thread per VEC values. Lists of neighbours staged per workgroup.
+template <int s>
+__global__ __launch_bounds__(256) void k_sb_patch(int Q, int K, const int32_t* __restrict__ ids,
+                                                  const int32_t* __restrict__ m, const float* __restrict__ wt,
+                                                  const double* __restrict__ mu, const float* __restrict__ resid,
+                                                  float* __restrict__ x) {
+    using G = SbGeom<s, kSbRows>;
+    constexpr int ps2 = G::ps2, VEC = G::VEC, NCH = G::NCH;
+    const int64_t it = (int64_t)xcd_block() * 256 + threadIdx.x;
+    const int q = (int)(it / NCH), c = (int)(it - (int64_t)q * NCH);
+    if (q >= Q) return;
+    const int mq = min(m[q], K);
+    float acc[VEC];
+    synth_chunk<ps2, VEC>(resid, ids + (int64_t)q * K, wt + (int64_t)q * K, mq, c, acc);
+    const float mf = mq > 0 ? (float)mu[q] : 0.0f;   // a patch without neighbours: zeros
+    float* dst = x + (int64_t)q * ps2 + c * VEC;
+    if constexpr (VEC == 4)
+        *reinterpret_cast<float4*>(dst) = make_float4(mf + acc[0], mf + acc[1], mf + acc[2], mf + acc[3]);
+    else
+        dst[0] = mf + acc[0];
+}
+
+// Second kernel, a thread per HR pixel: the sums of its patches inside each
+// tile (from zero, rows then columns ascending), added tile by tile.
+template <int s, int TI>
+__global__ __launch_bounds__(256) void k_sb_gather(const float* __restrict__ x, const int32_t* __restrict__ m,
+                                                   const float* __restrict__ lr, int h, int w,
+                                                   float* __restrict__ hr) {
+    using G = SbGeom<s, TI>;
+    constexpr int ps = G::ps, ps2 = G::ps2, TJ = G::TJ;
+    const int W = s * w;
+    const int64_t p = (int64_t)xcd_block() * 256 + threadIdx.x;
+    if (p >= (int64_t)s * h * W) return;
+    const int Y = (int)(p / W), X = (int)(p - (int64_t)Y * W);
+    const int npi = h - kPatch + 1, npj = w - kPatch + 1;
+    const int cy = Y / s, cx = X / s;
+    const int ilo = max(0, cy - (kPatch - 1)), ihi = min(npi - 1, cy);
+    const int jlo = max(0, cx - (kPatch - 1)), jhi = min(npj - 1, cx);
+    // all values in flight; patches outside the image or without neighbours add zero
+    float v[kPatch][kPatch];
+    int cnt = 0;
+    const int64_t q0 = (int64_t)ilo * npj + jlo;
+    const float* x0 = x + q0 * ps2 + (Y - s * ilo) * ps + (X - s * jlo);
+#pragma unroll
+    for (int a = 0; a < kPatch; ++a)
+#pragma unroll
+        for (int b = 0; b < kPatch; ++b) {
+            const bool in = ilo + a <= ihi && jlo + b <= jhi;
+            v[a][b] = in ? x0[((int64_t)a * npj + b) * ps2 - s * (a * ps + b)] : 0.0f;
+            cnt += in ? (m[q0 + (int64_t)a * npj + b] > 0 ? 1 : 0) : 0;
+        }
+    // the first row and column that belong to a second tile; t0 and t1 the sums
+    // of the tiles left and right of that column
+    const int isplit = (ilo / TI + 1) * TI - ilo, jsplit = (jlo / TJ + 1) * TJ - jlo;
+    float acc = 0.0f, t0 = 0.0f, t1 = 0.0f;
+#pragma unroll
+    for (int a = 0; a < kPatch; ++a) {
+        if (a > 0) {
+            const bool next = a == isplit;
+            const float done = (acc + t0) + t1;
+            acc = next ? done : acc;
+            t0 = next ? 0.0f : t0;
+            t1 = next ? 0.0f : t1;
+        }
+#pragma unroll
+        for (int b = 0; b < kPatch; ++b) {
+            t0 += b < jsplit ? v[a][b] : 0.0f;
+            t1 += b < jsplit ? 0.0f : v[a][b];
+        }
+    }
+    acc = (acc + t0) + t1;
+    hr[p] = cnt > 0 ? acc / (float)cnt : bicubic_at(lr, h, w, s, Y, X);
+}
+
 // Batched: the tiles and HR pixels of every image of the batch, the image
 // found from its first tile (sbt_off) or HR pixel (hr_off); partial regions
 // at the image's first tile.
 template <int s, int TI>
-__global__ __launch_bounds__(256) void k_b_sb_tile(const BatchImage* __restrict__ im, int n, int64_t tiles, int K,
-                                                   const int32_t* __restrict__ ids, const int32_t* __restrict__ m,
-                                                   const float* __restrict__ wt, const double* __restrict__ mu,
-                                                   const float* __restrict__ resid, float* __restrict__ part) {
+__global__ __launch_bounds__(kSbThreads) void k_b_sb_tile(const BatchImage* __restrict__ im, int n, int64_t tiles,
+                                                          int K, const int32_t* __restrict__ ids,
+                                                          const int32_t* __restrict__ m, const float* __restrict__ wt,
+                                                          const double* __restrict__ mu,
+                                                          const float* __restrict__ resid, float* __restrict__ part) {
+    extern __shared__ __align__(16) float smem[];
     const int64_t t = xcd_block();
     if (t >= tiles) return;   // the grid is rounded up to a multiple of 8
     const BatchImage& b = im[batch_image_of<&BatchImage::sbt_off>(im, n, t)];
     sb_tile<s, TI>(ids + b.q_off * K, m + b.q_off, wt + b.q_off * K, mu + b.q_off, resid, K, b.h, b.w,
-                   t - b.sbt_off, part + b.sbt_off * SbGeom<s, TI>::PART);
+                   t - b.sbt_off, part + b.sbt_off * SbGeom<s, TI>::PART, smem);
 }
 
 template <int s, int TI>
@@ -830,31 +942,53 @@ int64_t sb_part_floats(int s, int rows) {
     return cy * s * cx * s + cy * cx;
 }
 
+// Written out below 200 tiles: there the tiles run one after the other on a
+// chip that is not full (us, written out against fused: 60x60 patches x2 11
+// and 37, 116x127 x2 20 and 40, 196x212 x2 29 and 41, 146x166 x2 with 72-row
+// lists 80 and 189), above it the patches' way through memory costs more
+// (247x259 x2 45 and 44, 316x402 x1 55 and 43, 207x303 x4 154 and 115).
+bool sb_unfused(int s, int rows, int h, int w) { return sb_tiles(s, rows, h, w) < 200; }
+
+int64_t sb_scratch_floats(int s, int rows, int h, int w) {
+    if (h < kPatch || w < kPatch) return 0;
+    if (sb_unfused(s, rows, h, w))
+        return (int64_t)(h - kPatch + 1) * (w - kPatch + 1) * (kPatch * s) * (kPatch * s);
+    return sb_tiles(s, rows, h, w) * sb_part_floats(s, rows);
+}
+
 template <int s, int TI>
 static hipError_t sb_launch(int K, int h, int w, const int32_t* ids, const int32_t* m, const float* wt,
                             const double* mu, const float* resid, float* part, const float* lr, float* hr,
                             hipStream_t st, int which) {
-    const int64_t nt = sb_tiles(s, TI, h, w);
+    using G = SbGeom<s, TI>;
+    const int64_t nt = sb_tiles(s, TI, h, w), total = (int64_t)s * h * s * w;
+    if (nt > 0 && sb_unfused(s, TI, h, w)) {
+        const int Q = (h - kPatch + 1) * (w - kPatch + 1);
+        if (which & 1)
+            hipLaunchKernelGGL(k_sb_patch<s>, dim3((unsigned)round_grid8((int)(((int64_t)Q * G::NCH + 255) / 256))),
+                               dim3(256), 0, st, Q, K, ids, m, wt, mu, resid, part);
+        if (which & 2)
+            hipLaunchKernelGGL((k_sb_gather<s, TI>), dim3((unsigned)round_grid8((int)((total + 255) / 256))), dim3(256),
+                               0, st, part, m, lr, h, w, hr);
+        return hipGetLastError();
+    }
     if (which & 1 && nt > 0) {
         if (nt > 0x7FFFFFFF) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_sb_tile<s, TI>), dim3((unsigned)round_grid8((int)nt)), dim3(256), 0, st, K, h, w, ids, m,
-                           wt, mu, resid, part);
+        hipLaunchKernelGGL((k_sb_tile<s, TI>), dim3((unsigned)round_grid8((int)nt)), dim3(kSbThreads), G::lds(K), st, K,
+                           h, w, ids, m, wt, mu, resid, part);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (which & 2) {
-        const int64_t total = (int64_t)s * h * s * w;
-        if (total > 0)
-            hipLaunchKernelGGL((k_sb_combine<s, TI>), dim3((unsigned)std::min<int64_t>((total + 255) / 256, 1 << 20)),
-                               dim3(256), 0, st, part, lr, h, w, hr);
-    }
+    if (which & 2 && total > 0)
+        hipLaunchKernelGGL((k_sb_combine<s, TI>), dim3((unsigned)std::min<int64_t>((total + 255) / 256, 1 << 20)),
+                           dim3(256), 0, st, part, lr, h, w, hr);
     return hipGetLastError();
 }
 
 hipError_t launch_synth_blend(int scale, int rows, int K, int h, int w, const int32_t* ids, const int32_t* m,
                               const float* wt, const double* mu, const float* resid, float* part, const float* lr,
                               float* hr, hipStream_t st, int which) {
-    if (K < 1 || (rows != 4 && rows != 8)) return hipErrorInvalidValue;
+    if (K < 1 || K > kAllMax || (rows != 4 && rows != 8)) return hipErrorInvalidValue;
     switch (scale * 10 + rows) {
         case 14: return sb_launch<1, 4>(K, h, w, ids, m, wt, mu, resid, part, lr, hr, st, which);
         case 18: return sb_launch<1, 8>(K, h, w, ids, m, wt, mu, resid, part, lr, hr, st, which);
@@ -874,8 +1008,9 @@ static hipError_t b_sb_launch(const BatchImage* im, int n, int64_t tiles, int64_
                               hipStream_t st) {
     if (tiles > 0) {
         if (tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_b_sb_tile<s, TI>), dim3((unsigned)round_grid8((int)tiles)), dim3(256), 0, st, im, n, tiles,
-                           K, ids, m, wt, mu, resid, part);
+        const size_t lds = SbGeom<s, TI>::lds(K);
+        hipLaunchKernelGGL((k_b_sb_tile<s, TI>), dim3((unsigned)round_grid8((int)tiles)), dim3(kSbThreads),
+                           lds, st, im, n, tiles, K, ids, m, wt, mu, resid, part);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -888,7 +1023,7 @@ static hipError_t b_sb_launch(const BatchImage* im, int n, int64_t tiles, int64_
 hipError_t launch_b_synth_blend(const BatchImage* im, int n, int64_t tiles, int64_t hr_total, int scale, int rows,
                                 int K, const int32_t* ids, const int32_t* m, const float* wt, const double* mu,
                                 const float* resid, float* part, hipStream_t st) {
-    if (K < 1 || (rows != 4 && rows != 8)) return hipErrorInvalidValue;
+    if (K < 1 || K > kMaxK || (rows != 4 && rows != 8)) return hipErrorInvalidValue;
     switch (scale * 10 + rows) {
         case 14: return b_sb_launch<1, 4>(im, n, tiles, hr_total, K, ids, m, wt, mu, resid, part, st);
         case 18: return b_sb_launch<1, 8>(im, n, tiles, hr_total, K, ids, m, wt, mu, resid, part, st);

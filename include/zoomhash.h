@@ -374,8 +374,7 @@ zh_status zh_backward(zh_ctx* ctx, const float* g_hr, float* g_resid, float* g_l
 /* Many LR images of uneven size and zoom factor in one launch chain: for
  * each zoom factor present, the patches of all its images form one index
  * space for features, hashing, search, LLE weights and synthesis; the blend
- * and the back-projection run over the images' pixels and tiles (a
- * persistent update kernel takes (image, tile) items from a work counter).
+ * and the back-projection run over the images' pixels and tiles.
  * The chain is captured once into a HIP graph and replayed while the batch
  * (pointers, sizes, parameters, query options, tuning) stays the same; it
  * runs on a stream of the context ordered after and before the context's
@@ -399,8 +398,8 @@ zh_status zh_run_batch(zh_ctx* ctx, const zh_batch* batch);
 /* Autotuner of the batched form (Section 5: the patches are independent
  * sub-problems; the launch shapes are chosen per batch): runs the batch once,
  * then times (HIP events, best of 2) the back-projection update over the
- * batch's tiles for tile sides {16, 32} and persistent grids of {2, 4, 8}
- * workgroups per compute unit, and the fused synthesis and blend of the last
+ * batch's tiles for tile sides {16, 32} and at most {2, 4, 8}
+ * workgroups at a time on a compute unit, and the fused synthesis and blend of the last
  * zoom factor with tiles of 4 and 8 patch rows; keeps the fastest of each
  * for later zh_run_batch calls and reports them in *out (host, nullable).
  * The tile height is the context's for zh_reconstruct too: it sets how the

@@ -107,8 +107,8 @@ struct zh_ctx {
         hipGraphExec_t exec = nullptr;
         hipStream_t stream = nullptr;
         hipEvent_t ev_in = nullptr, ev_out = nullptr;
-        int tile = 32, grid_per_cu = 4;
-        Buf scr, e, counter;
+        int tile = 32, grid_per_cu = 8;
+        Buf scr, e;
     } batch;
     // back-projection record for zh_backward: 0 none, 1 one call kept, -1 more than one
     int bp_rec = 0, bp_iters = 0;
@@ -550,7 +550,6 @@ void zh_destroy(zh_ctx* c) {
     for (auto& g : c->batch.g) release(c, g.table);
     release(c, c->batch.scr);
     release(c, c->batch.e);
-    release(c, c->batch.counter);
     Buf* bufs[] = {&c->lr, &c->maps, &c->qfeat, &c->qmu, &c->qkeys, &c->qbins, &c->ids, &c->d2, &c->m,
                    &c->ncand, &c->w, &c->over, &c->sbpart, &c->e, &c->tmp, &c->counters, &c->rs_k1,
                    &c->rs_v1, &c->rs_hist, &c->slot_of, &c->idsort, &c->keys_dict, &c->gram, &c->hmask, &c->fixl, &c->fixc, &c->nsurv, &c->guides, &c->bwd, &c->bwd_k, &c->clam, &c->qrot, &c->bwd_gw, &c->bwd_part, &c->tools, &c->l1cand, &c->chk, &c->wall};
@@ -1711,7 +1710,6 @@ zh_status batch_plan(zh_ctx* c, const zh_batch* b) {
     }
     const int64_t K = b->K;
     TRY(ensure(c, B.e, sizeof(float) * (size_t)std::max<int64_t>(lr_max, 1)));
-    TRY(ensure(c, B.counter, 16));
     TRY(ensure(c, c->maps, sizeof(float) * 4 * (size_t)std::max<int64_t>(lr_max, 1)));
     TRY(ensure(c, c->qfeat, sizeof(float) * (size_t)q_max * D_max));
     TRY(ensure(c, c->qmu, sizeof(double) * (size_t)q_max));
@@ -1744,8 +1742,6 @@ zh_status batch_chain(zh_ctx* c, const zh_batch* b, hipStream_t st) {
     c->stream = st;
     c->timing = false;
     zh_status rc = ZH_OK;
-    int ncu = 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || ncu < 1) ncu = 256;
     for (int s = 1; s <= kMaxScale && rc == ZH_OK; ++s) {
         auto& g = B.g[s];
         if (!g.n) continue;
@@ -1811,8 +1807,8 @@ zh_status batch_chain(zh_ctx* c, const zh_batch* b, hipStream_t st) {
             const Taps tg = gauss_taps(1.0);
             for (int t = 0; t < b->bp_iters; ++t) {
                 HIPCHK(c, launch_b_degrade_residual(tab, g.n, g.lr_total, g.dtiles, s, tg, t & 1, P<float>(B.e), st));
-                HIPCHK(c, launch_b_bp_update(tab, g.n, g.tiles, B.tile, B.grid_per_cu * ncu, s, b->sigma_s, b->sigma_r,
-                                             P<float>(B.e), t & 1, P<unsigned int>(B.counter), st));
+                HIPCHK(c, launch_b_bp_update(tab, g.n, g.tiles, B.tile, B.grid_per_cu, s, b->sigma_s, b->sigma_r,
+                                             P<float>(B.e), t & 1, st));
             }
             if (b->bp_iters & 1) HIPCHK(c, launch_b_copy_scr(tab, g.n, g.hr_total, s, st));
             return ZH_OK;
@@ -1990,8 +1986,6 @@ zh_status zh_tune_batch(zh_ctx* c, const zh_batch* b, zh_batch_tuning* out) {
     hipEvent_t e0, e1;
     HIPCHK(c, hipEventCreate(&e0));
     HIPCHK(c, hipEventCreate(&e1));
-    int ncu = 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || ncu < 1) ncu = 256;
     const int keep_tile = B.tile, keep_mult = B.grid_per_cu, keep_rows = c->sb_rows;
     zh_status rc = ZH_OK;
     auto time_once = [&](auto&& launch, float& best_ms) {
@@ -2019,8 +2013,8 @@ zh_status zh_tune_batch(zh_ctx* c, const zh_batch* b, zh_batch_tuning* out) {
                     if (launch_b_degrade_residual(tab, g.n, g.lr_total, g.dtiles, s, gauss_taps(1.0), 0, P<float>(B.e),
                                                   B.stream) !=
                             hipSuccess ||
-                        launch_b_bp_update(tab, g.n, g.tiles, tiles[ti], mults[mi] * ncu, s, b->sigma_s, b->sigma_r,
-                                           P<float>(B.e), 0, P<unsigned int>(B.counter), B.stream) != hipSuccess)
+                        launch_b_bp_update(tab, g.n, g.tiles, tiles[ti], mults[mi], s, b->sigma_s, b->sigma_r,
+                                           P<float>(B.e), 0, B.stream) != hipSuccess)
                         return false;
                 }
                 return true;

@@ -315,12 +315,11 @@ int64_t degrade_tiles(int h, int w);
 hipError_t launch_b_synth_blend(const BatchImage* im, int n, int64_t tiles, int64_t hr_total, int scale, int rows,
                                 int K, const int32_t* ids, const int32_t* m, const float* wt, const double* mu,
                                 const float* resid, float* part, hipStream_t st);
-// one back-projection update over all tiles of the batch, persistent: `grid`
-// workgroups take tiles from the counter (zeroed here by a fill kernel);
-// parity 0 reads out and writes scr, parity 1 the reverse
-hipError_t launch_b_bp_update(const BatchImage* im, int n, int64_t n_tiles, int tile, int grid, int scale,
-                              float sigma_s, float sigma_r, const float* e, int parity, unsigned int* counter,
-                              hipStream_t st);
+// one back-projection update over all tiles of the batch, a workgroup per
+// tile, at most per_cu of them on a compute unit; parity 0 reads out and writes
+// scr, parity 1 the reverse
+hipError_t launch_b_bp_update(const BatchImage* im, int n, int64_t n_tiles, int tile, int per_cu, int scale,
+                              float sigma_s, float sigma_r, const float* e, int parity, hipStream_t st);
 hipError_t launch_b_copy_scr(const BatchImage* im, int n, int64_t hr_total, int scale, hipStream_t st);
 int bp_tiles(int H, int W, int tile);
 

@@ -18,7 +18,6 @@
 // search takes from the screen; upper bounds come from exact distances.
 #include <algorithm>
 #include <cmath>
-#include <vector>
 
 #include "zh_internal.h"
 
@@ -29,136 +28,325 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 
 // ---- covariance of a row sample --------------------------------------------
-// Block b sums x_r x_r^T (FP64) over its share of the sample rows
-// r_i = floor(i n / ns); thread t owns entries t, t + 1024, ... of the D x D
-// matrix. A second kernel adds the block partials in block order.
+// Block b of kCovBlocks sums x_r x_r^T (FP64) over its share of the sample rows
+// r_i = floor(i n / ns), taken in order; kCovRows rows are staged in LDS at a
+// time. The lower triangle is cut into kCovParts parts of a thread per entry
+// (blockIdx.y), so that the chip is full. A second kernel adds the block
+// partials in block order. Bound: FP64 issue and LDS reads, 65536 rows at
+// D = 100: 0.62 -> 0.21 ms (whole matrix, ten entries a thread, two barriers a row
+// before).
 constexpr int kCovThreads = 1024;
 constexpr int kCovBlocks = 128;
+constexpr int kCovRows = 32;
+
+__device__ __forceinline__ int tri_row(int e) {   // row i of packed entry i (i + 1) / 2 + j, j <= i
+    int i = (int)((sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
+    while ((i + 1) * (i + 2) / 2 <= e) ++i;
+    while (i * (i + 1) / 2 > e) --i;
+    return i;
+}
 
 __global__ __launch_bounds__(kCovThreads) void k_cov_partial(const float* __restrict__ x, int64_t n, int D,
                                                              int64_t ns, double* __restrict__ part) {
-    __shared__ float row[128];
+    __shared__ float row[kCovRows][129];
     const int t = threadIdx.x;
-    const int DD = D * D;
-    constexpr int E = 128 * 128 / kCovThreads;
-    double acc[E];
-    int ri[E], ci[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        acc[e] = 0.0;
-        const int idx = t + kCovThreads * e;
-        ri[e] = idx < DD ? idx / D : 0;
-        ci[e] = idx < DD ? idx - (idx / D) * D : 0;
-    }
+    const int np = D * (D + 1) / 2, e = blockIdx.y * kCovThreads + t;
+    const int ri = e < np ? tri_row(e) : 0, ci = e < np ? e - ri * (ri + 1) / 2 : 0;
+    double acc = 0.0;
     const int64_t per = (ns + gridDim.x - 1) / gridDim.x;
     const int64_t i0 = (int64_t)blockIdx.x * per;
     const int64_t i1 = i0 + per < ns ? i0 + per : ns;
-    for (int64_t i = i0; i < i1; ++i) {
-        const int64_t r = i * n / ns;   // i < ns <= 2^16 and n < 2^31: no overflow
+    for (int64_t i = i0; i < i1; i += kCovRows) {
+        const int nr = (int)(i1 - i < kCovRows ? i1 - i : kCovRows);
         __syncthreads();
-        if (t < D) row[t] = x[r * D + t];
+        // i < ns <= 2^16 and n < 2^31: no overflow
+        for (int c = t & 127, r = t >> 7; r < nr; r += kCovThreads / 128)
+            if (c < D) row[r][c] = x[((i + r) * n / ns) * D + c];
         __syncthreads();
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-            if (t + kCovThreads * e < DD) acc[e] += (double)row[ri[e]] * (double)row[ci[e]];
+        for (int r = 0; r < nr; ++r) acc += (double)row[r][ri] * (double)row[r][ci];
     }
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int idx = t + kCovThreads * e;
-        if (idx < DD) part[(int64_t)blockIdx.x * DD + idx] = acc[e];
-    }
+    if (e < np) part[(int64_t)blockIdx.x * np + e] = acc;
 }
 
-__global__ void k_cov_sum(const double* __restrict__ part, int nblk, int DD, double* __restrict__ cov) {
+// cov: packed lower triangle
+__global__ void k_cov_sum(const double* __restrict__ part, int nblk, int np, double* __restrict__ cov) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= DD) return;
+    if (e >= np) return;
     double s = 0.0;
-    for (int b = 0; b < nblk; ++b) s += part[(int64_t)b * DD + e];
+#pragma unroll 8
+    for (int b = 0; b < nblk; ++b) s += part[(int64_t)b * np + e];
     cov[e] = s;
 }
 
-hipError_t launch_cov(const float* x, int64_t n, int D, int64_t ns, double* part, double* cov, hipStream_t st) {
-    if (D < 1 || D > 128 || ns < 1 || ns > n || ns > 65536) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_cov_partial, dim3(kCovBlocks), dim3(kCovThreads), 0, st, x, n, D, ns, part);
-    const int DD = D * D;
-    hipLaunchKernelGGL(k_cov_sum, dim3((DD + 255) / 256), dim3(256), 0, st, part, kCovBlocks, DD, cov);
-    return hipGetLastError();
+// ---- principal directions ----------------------------------------------------
+// Jacobi eigenvalue iteration on the symmetric matrix in LDS (FP64), one
+// workgroup. A sweep is N - 1 rounds of N / 2 disjoint rotations (round-robin
+// pairs; an odd D gets an idle index): the rotations of a round are formed from
+// the pairs' 2x2 blocks, then every 2x2 block of two pairs is rotated from both
+// sides at once. The rotations are recorded (c, s per round and pair) for
+// k_jacobi_vectors; an off-diagonal below 1e-9 of the diagonal ends the sweeps.
+// Any basis would do for the screen's bounds; this one makes them tight.
+//
+// Bound: the chain of rounds, two barriers each (D = 100: 1.6 ms; the
+// cyclic iteration on the host it replaces took 8 ms with the device idle).
+constexpr int kJacThreads = 1024;
+constexpr int kJacSweeps = 24;
+constexpr int kJacMaxD = 100;      // the lower triangle in rows of odd length: 81 KB of LDS
+constexpr int kJacPairs = kJacMaxD / 2;
+constexpr double kJacOff2 = 1e-18;   // squared off-diagonal against squared diagonal: Phi is rounded to fp32
+
+// entry (i, j) of the symmetric matrix: the lower triangle in rows of kJacLd
+constexpr int kJacLd = kJacMaxD | 1;
+__device__ __forceinline__ int tri_at(int i, int j) { return i >= j ? i * kJacLd + j : j * kJacLd + i; }
+// pair k of round r among N (even) indexes, smaller first
+__device__ __forceinline__ void jac_pair(int N, int r, int k, int& p, int& q) {
+    const int m = N - 1;
+    int a = k == 0 ? m : r + k, b = k == 0 ? r : r - k;
+    if (k > 0 && a >= m) a -= m;
+    if (b < 0) b += m;
+    p = a < b ? a : b;
+    q = a < b ? b : a;
 }
 
-// ---- principal directions (host) -------------------------------------------
-// Cyclic Jacobi eigenvalue iteration on the symmetric D x D matrix C (FP64);
-// the m eigenvectors of the largest eigenvalues (ties by index) become the
-// rows of Phi (fp32, unit length). Returns an upper bound on the largest
-// eigenvalue of Phi Phi^T (Gershgorin, FP64 sums of exact products), i.e. on
-// sigma^2.
-double screen_basis(const double* C, int D, int m, float* phi) {
-    std::vector<double> A(C, C + (size_t)D * D), V((size_t)D * D, 0.0);
-    for (int i = 0; i < D; ++i) V[(size_t)i * D + i] = 1.0;
-    for (int i = 0; i < D; ++i)
-        for (int j = i + 1; j < D; ++j) {
-            const double s = 0.5 * (A[(size_t)i * D + j] + A[(size_t)j * D + i]);
-            A[(size_t)i * D + j] = A[(size_t)j * D + i] = s;
+__global__ __launch_bounds__(kJacThreads) void k_jacobi(const double* __restrict__ cov, int D, double2* __restrict__ rot,
+                                                        double* __restrict__ eig, int* __restrict__ sweeps) {
+    extern __shared__ double sA[];   // [D][kJacLd]
+    __shared__ double2 cs[kJacPairs];
+    __shared__ int sp[kJacPairs], sq[kJacPairs];
+    __shared__ double red[2][kJacThreads / 64];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int N = (D + 1) & ~1, P = N / 2, np = D * (D + 1) / 2;
+    for (int e = t; e < np; e += kJacThreads) {
+        const int i = tri_row(e);
+        sA[tri_at(i, e - i * (i + 1) / 2)] = cov[e];
+    }
+    // the pairs of pairs (k >= l) of this thread, fixed over the rounds
+    const int nb = P * (P + 1) / 2;
+    constexpr int E = (kJacPairs * (kJacPairs + 1) / 2 + kJacThreads - 1) / kJacThreads;
+    int bk[E], bl[E];
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        const int e = t + u * kJacThreads;
+        bk[u] = e < nb ? tri_row(e) : -1;
+        bl[u] = e < nb ? e - bk[u] * (bk[u] + 1) / 2 : -1;
+    }
+    __syncthreads();
+    int sweep = 0;
+    for (; sweep < kJacSweeps; ++sweep) {
+        double off = 0.0, dia = 0.0;
+        for (int e = t; e < np; e += kJacThreads) {
+            const int i = tri_row(e), j = e - i * (i + 1) / 2;
+            const double v = sA[tri_at(i, j)] * sA[tri_at(i, j)];
+            if (i == j) dia += v;
+            else off += v;
         }
-    double diag2 = 0.0;
-    for (int i = 0; i < D; ++i) diag2 += A[(size_t)i * D + i] * A[(size_t)i * D + i];
-    for (int sweep = 0; sweep < 60; ++sweep) {
-        double off = 0.0;
-        for (int p = 0; p < D; ++p)
-            for (int q = p + 1; q < D; ++q) off += A[(size_t)p * D + q] * A[(size_t)p * D + q];
-        if (off <= 1e-30 * diag2) break;
-        for (int p = 0; p < D; ++p) {
-            for (int q = p + 1; q < D; ++q) {
-                const double apq = A[(size_t)p * D + q];
-                if (apq == 0.0) continue;
-                const double app = A[(size_t)p * D + p], aqq = A[(size_t)q * D + q];
-                const double theta = (aqq - app) / (2.0 * apq);
-                double t;
-                if (std::fabs(theta) > 1e150)
-                    t = 0.5 / theta;
-                else
-                    t = (theta >= 0.0 ? 1.0 : -1.0) / (std::fabs(theta) + std::sqrt(theta * theta + 1.0));
-                const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
-                for (int k = 0; k < D; ++k) {
-                    const double akp = A[(size_t)k * D + p], akq = A[(size_t)k * D + q];
-                    A[(size_t)k * D + p] = c * akp - s * akq;
-                    A[(size_t)k * D + q] = s * akp + c * akq;
+        off = wave_sum_f64(off);
+        dia = wave_sum_f64(dia);
+        if (lane == 0) {
+            red[0][wv] = off;
+            red[1][wv] = dia;
+        }
+        __syncthreads();
+        off = dia = 0.0;
+        for (int w = 0; w < kJacThreads / 64; ++w) {
+            off += red[0][w];
+            dia += red[1][w];
+        }
+        if (!(off > kJacOff2 * dia)) break;
+        for (int r = 0; r < N - 1; ++r) {
+            if (t < P) {
+                int p, q;
+                jac_pair(N, r, t, p, q);
+                double c = 1.0, s = 0.0;
+                if (q < D) {
+                    const double apq = sA[tri_at(q, p)];
+                    if (apq != 0.0) {
+                        const double theta = (sA[tri_at(q, q)] - sA[tri_at(p, p)]) / (2.0 * apq);
+                        const double tn = fabs(theta) > 1e150
+                                              ? 0.5 / theta
+                                              : copysign(1.0, theta) / (fabs(theta) + sqrt(theta * theta + 1.0));
+                        c = 1.0 / sqrt(tn * tn + 1.0);
+                        s = tn * c;
+                    }
                 }
-                for (int k = 0; k < D; ++k) {
-                    const double apk = A[(size_t)p * D + k], aqk = A[(size_t)q * D + k];
-                    A[(size_t)p * D + k] = c * apk - s * aqk;
-                    A[(size_t)q * D + k] = s * apk + c * aqk;
-                }
-                for (int k = 0; k < D; ++k) {
-                    const double vkp = V[(size_t)k * D + p], vkq = V[(size_t)k * D + q];
-                    V[(size_t)k * D + p] = c * vkp - s * vkq;
-                    V[(size_t)k * D + q] = s * vkp + c * vkq;
-                }
+                cs[t] = make_double2(c, s);
+                sp[t] = p;
+                sq[t] = q;
+                rot[((int64_t)sweep * (N - 1) + r) * P + t] = make_double2(c, s);
             }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < E; ++u) {
+                if (bk[u] < 0) continue;
+                const int p = sp[bk[u]], q = sq[bk[u]];
+                const double2 rk = cs[bk[u]];
+                if (bk[u] == bl[u]) {
+                    if (q < D) {
+                        const double app = sA[tri_at(p, p)], aqq = sA[tri_at(q, q)], apq = sA[tri_at(q, p)];
+                        const double c = rk.x, s = rk.y;
+                        sA[tri_at(p, p)] = c * c * app - 2.0 * c * s * apq + s * s * aqq;
+                        sA[tri_at(q, q)] = s * s * app + 2.0 * c * s * apq + c * c * aqq;
+                        sA[tri_at(q, p)] = 0.0;
+                    }
+                    continue;
+                }
+                const int i = sp[bl[u]], j = sq[bl[u]];
+                const double2 rl = cs[bl[u]];
+                // the idle index (D, when D is odd) is the larger of its pair
+                const bool hq = q < D, hj = j < D;
+                double a00 = sA[tri_at(p, i)], a01 = hj ? sA[tri_at(p, j)] : 0.0;
+                double a10 = hq ? sA[tri_at(q, i)] : 0.0, a11 = hq && hj ? sA[tri_at(q, j)] : 0.0;
+                const double b00 = rl.x * a00 - rl.y * a01, b01 = rl.y * a00 + rl.x * a01;
+                const double b10 = rl.x * a10 - rl.y * a11, b11 = rl.y * a10 + rl.x * a11;
+                sA[tri_at(p, i)] = rk.x * b00 - rk.y * b10;
+                if (hj) sA[tri_at(p, j)] = rk.x * b01 - rk.y * b11;
+                if (hq) sA[tri_at(q, i)] = rk.y * b00 + rk.x * b10;
+                if (hq && hj) sA[tri_at(q, j)] = rk.y * b01 + rk.x * b11;
+            }
+            __syncthreads();
         }
     }
-    std::vector<int> order(D);
-    for (int i = 0; i < D; ++i) order[i] = i;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int a, int b) { return A[(size_t)a * D + a] > A[(size_t)b * D + b]; });
-    for (int j = 0; j < m; ++j) {
+    for (int i = t; i < D; i += kJacThreads) eig[i] = sA[tri_at(i, i)];
+    if (t == 0) *sweeps = sweep;
+}
+
+// The product of the recorded rotations, V [D][D]: a wave per row, a lane per
+// pair of a round.
+__global__ __launch_bounds__(64) void k_jacobi_vectors(int D, const double2* __restrict__ rot,
+                                                       const int* __restrict__ sweeps, double* __restrict__ V) {
+    __shared__ double v[2 * kJacPairs];
+    const int i = blockIdx.x, lane = threadIdx.x;
+    const int N = (D + 1) & ~1, P = N / 2;
+    for (int j = lane; j < N; j += 64) v[j] = j == i ? 1.0 : 0.0;
+    const int rounds = *sweeps * (N - 1);
+    // the rotations of the next kAhead rounds in flight
+    constexpr int kAhead = 8;
+    double2 next[kAhead];
+    auto load = [&](int g) { return lane < P && g < rounds ? rot[(int64_t)g * P + lane] : make_double2(1.0, 0.0); };
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) next[u] = load(u);
+    __syncthreads();
+    for (int g0 = 0, r = 0; g0 < rounds; g0 += kAhead) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const double2 c = next[u];
+            next[u] = load(g0 + u + kAhead);
+            if (g0 + u < rounds) {
+                if (lane < P) {
+                    int p, q;
+                    jac_pair(N, r, lane, p, q);
+                    const double a = v[p], b = v[q];
+                    v[p] = c.x * a - c.y * b;
+                    v[q] = c.y * a + c.x * b;
+                }
+                if (++r == N - 1) r = 0;
+            }
+            // one wave: its LDS operations stay in order, and no load in flight
+            // is waited for
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    for (int j = lane; j < D; j += 64) V[(int64_t)i * D + j] = v[j];
+}
+
+// The m eigenvectors of the largest eigenvalues (ties by index) as the rows of
+// Phi (fp32, unit length): phiT [D][64] (FP64 of the fp32 values, zeros past
+// m) for the screen rows, the bf16 split [64][DP] (zeros outside) for the query
+// rotation, and in *s2 an upper bound on the largest eigenvalue of Phi Phi^T
+// (Gershgorin, FP64 sums of exact products), i.e. on sigma^2. One workgroup.
+__global__ __launch_bounds__(256) void k_screen_basis(const double* __restrict__ V, const double* __restrict__ eig,
+                                                      int D, int m, double* __restrict__ phiT,
+                                                      uint16_t* __restrict__ ph, uint16_t* __restrict__ pl,
+                                                      double* __restrict__ s2) {
+    __shared__ float phi[kScreenMax][kJacMaxD + 1];
+    __shared__ int order[kJacMaxD];
+    __shared__ double smax[4];
+    const int t = threadIdx.x;
+    const int DP = (D + 31) & ~31;
+    for (int j = t; j < D; j += 256) {
+        int rank = 0;
+        for (int k = 0; k < D; ++k) rank += eig[k] > eig[j] || (eig[k] == eig[j] && k < j) ? 1 : 0;
+        order[rank] = j;
+    }
+    __syncthreads();
+    for (int j = t; j < m; j += 256) {
         const int col = order[j];
         double nrm = 0.0;
-        for (int i = 0; i < D; ++i) nrm += V[(size_t)i * D + col] * V[(size_t)i * D + col];
-        nrm = std::sqrt(nrm);
-        for (int i = 0; i < D; ++i) phi[(size_t)j * D + i] = (float)(V[(size_t)i * D + col] / nrm);
-    }
-    double lmax = 0.0;
-    for (int i = 0; i < m; ++i) {
-        double row = 0.0;
-        for (int j = 0; j < m; ++j) {
-            double g = 0.0;
-            for (int k = 0; k < D; ++k) g += (double)phi[(size_t)i * D + k] * (double)phi[(size_t)j * D + k];
-            row += std::fabs(g);
+#pragma unroll 16
+        for (int i = 0; i < D; ++i) {
+            const double v = V[(int64_t)i * D + col];
+            nrm += v * v;
         }
-        lmax = std::max(lmax, row);
+        nrm = sqrt(nrm);
+#pragma unroll 16
+        for (int i = 0; i < D; ++i) phi[j][i] = (float)(V[(int64_t)i * D + col] / nrm);
     }
+    __syncthreads();
+    for (int e = t; e < D * kRotStride; e += 256) {
+        const int i = e / kRotStride, j = e - i * kRotStride;
+        phiT[e] = j < m ? (double)phi[j][i] : 0.0;
+    }
+    for (int e = t; e < kRotStride * DP; e += 256) {
+        const int j = e / DP, i = e - j * DP;
+        const float v = j < m && i < D ? phi[j][i] : 0.0f;
+        const uint16_t h = bf16_rne(v);
+        ph[e] = h;
+        pl[e] = bf16_rne(v - bf16_to_f(h));
+    }
+    // the row sums of |Phi Phi^T|, four threads a row
+    double row = 0.0;
+    const int i = t >> 2;
+    if (i < m)
+        for (int j = t & 3; j < m; j += 4) {
+            double g = 0.0;
+            for (int k = 0; k < D; ++k) g += (double)phi[i][k] * (double)phi[j][k];
+            row += fabs(g);
+        }
+    row += __shfl_xor(row, 1);
+    row += __shfl_xor(row, 2);
+    const double wm = wave_max_f64(row);
+    if ((t & 63) == 0) smax[t >> 6] = wm;
+    __syncthreads();
     // FP64 rounding of the Gram sums is below 1e-13 of each entry
-    return lmax * (1.0 + 1e-12) + 1e-14;
+    if (t == 0) *s2 = fmax(fmax(smax[0], smax[1]), fmax(smax[2], smax[3])) * (1.0 + 1e-12) + 1e-14;
+}
+
+// scratch: the partial matrices, the covariance, the rotations, V, the
+// eigenvalues, the bound and the sweep count, then phiT
+static int64_t basis_doubles(int D) {
+    const int64_t np = (int64_t)D * (D + 1) / 2, N = (D + 1) & ~1;
+    return kCovBlocks * np + np + 2 * (int64_t)kJacSweeps * (N - 1) * (N / 2) + (int64_t)D * D + D + 2 +
+           (int64_t)D * kRotStride + 2;
+}
+int64_t screen_basis_bytes(int D) { return 8 * basis_doubles(D); }
+
+hipError_t launch_screen_basis(const float* x, int64_t n, int D, int64_t ns, int m, void* scratch, double** phiT,
+                               double** s2, uint16_t* ph, uint16_t* pl, hipStream_t st) {
+    if (D < 2 || D > kJacMaxD || ns < 1 || ns > n || ns > 65536 || m < 1 || m > kScreenMax || m > D)
+        return hipErrorInvalidValue;
+    const int64_t np = (int64_t)D * (D + 1) / 2, N = (D + 1) & ~1;
+    // the rotations are read 16 bytes at a time: first, from the 16-byte aligned start
+    double* rot = static_cast<double*>(scratch);
+    double* part = rot + 2 * (int64_t)kJacSweeps * (N - 1) * (N / 2);
+    double* cov = part + kCovBlocks * np;
+    double* V = cov + np;
+    double* eig = V + (int64_t)D * D;
+    *s2 = eig + D;
+    int* sweeps = reinterpret_cast<int*>(*s2 + 1);
+    *phiT = *s2 + 2;
+    hipLaunchKernelGGL(k_cov_partial, dim3(kCovBlocks, (unsigned)((np + kCovThreads - 1) / kCovThreads)),
+                       dim3(kCovThreads), 0, st, x, n, D, ns, part);
+    hipLaunchKernelGGL(k_cov_sum, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, part, kCovBlocks, (int)np, cov);
+    const size_t lds = sizeof(double) * (size_t)D * kJacLd;
+    const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(k_jacobi),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (ea != hipSuccess) return ea;
+    hipLaunchKernelGGL(k_jacobi, dim3(1), dim3(kJacThreads), lds, st, cov, D,
+                       reinterpret_cast<double2*>(rot), eig, sweeps);
+    hipLaunchKernelGGL(k_jacobi_vectors, dim3(D), dim3(64), 0, st, D, reinterpret_cast<const double2*>(rot), sweeps, V);
+    hipLaunchKernelGGL(k_screen_basis, dim3(1), dim3(256), 0, st, V, eig, D, m, *phiT, ph, pl, *s2);
+    return hipGetLastError();
 }
 
 // Bound coefficient of the split-bf16 MFMA projection of a query onto Phi:
@@ -176,12 +364,16 @@ float rotate_bound_coeff(int D) {
 }
 
 // ---- screen rows of the dictionary -----------------------------------------
-// One wave per row: lane j < m forms y_j = sum_i phi_ji x_i in FP64 (phi^T in
-// LDS). The row scale s_x is max_j |y_j| / 127 rounded up to bf16, so every
+// y = Phi x of 16 rows a wave on the FP64 matrix cores (phi^T in LDS; lane
+// (g = l / 16, c = l % 16) carries coordinates 16 t + 4 g + e of row c as the A
+// operand and of direction 16 ct + c as the B operand, and receives direction
+// 16 ct + c of rows 4 i + g). The row scale s_x is max_j |y_j| / 127 rounded up to bf16, so every
 // code c_j = rint(y_j / s_x) lies in [-127, 127] and y~_j = s_x c_j is exact
-// in fp32; the wave adds (y~_j - y_j)^2 and y~_j^2. The FP64 sum itself is
-// within D 2^-53 sum_i |phi_ji x_i| <= 1e-13 |x|_1 of the exact product,
-// which is added to rho_x.
+// in fp32; the 16 lanes of a row add (y~_j - y_j)^2 and y~_j^2. The FP64 sums
+// themselves are within D 2^-53 sum_i |phi_ji x_i| <= 1e-13 |x|_1 of the exact product,
+// which is added to rho_x. Bound: FP64 products (64 cycles each, 112 per 16
+// rows at D = 100). 300k rows: 0.61 -> 0.16 ms (a row at a time on the vector units,
+// both factors from LDS, before).
 __device__ __forceinline__ uint32_t f32_up_bits(double v) {   // fp32 >= v >= 0
     float f = (float)v;
     if ((double)f < v) f = __uint_as_float(__float_as_uint(f) + 1u);
@@ -192,44 +384,98 @@ __device__ __forceinline__ uint16_t bf16_up(double v) {         // bf16 >= v >= 
     if (b & 0xFFFFu) b = (b | 0xFFFFu) + 1u;
     return (uint16_t)(b >> 16);
 }
-__global__ __launch_bounds__(256) void k_screen_rows(const float* __restrict__ x, int64_t n, int D, int m,
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+// v of lane l + n mod 16 of the same row of 16 lanes
+template <int N>
+__device__ __forceinline__ double row_ror(double v) {
+    const int64_t b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xFFFFFFFF), 0x120 + N, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x120 + N, 0xF, 0xF, true);
+    return __longlong_as_double(((int64_t)hi << 32) | (int64_t)(uint32_t)lo);
+}
+__device__ __forceinline__ double row16_sum(double v) {
+    v += row_ror<8>(v);
+    v += row_ror<4>(v);
+    v += row_ror<2>(v);
+    return v + row_ror<1>(v);
+}
+__device__ __forceinline__ double row16_max(double v) {
+    v = fmax(v, row_ror<8>(v));
+    v = fmax(v, row_ror<4>(v));
+    v = fmax(v, row_ror<2>(v));
+    return fmax(v, row_ror<1>(v));
+}
+
+template <bool V4>
+__global__ __launch_bounds__(256) void k_screen_rows(const float* __restrict__ x, int64_t n, int D,
                                                      const double* __restrict__ phiT, uint8_t* __restrict__ sc) {
-    extern __shared__ double sphi[];   // [D][64]
-    __shared__ double sx[4][128];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int e = threadIdx.x; e < D * 64; e += 256) sphi[e] = phiT[e];
+    extern __shared__ double sphi[];   // [round16(D)][64]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, c = lane & 15;
+    const int DR = (D + 15) & ~15;
+    for (int e = threadIdx.x; e < DR * 64; e += 256) sphi[e] = e < D * 64 ? phiT[e] : 0.0;
     __syncthreads();
-    const int64_t nw = (int64_t)gridDim.x * 4;
-    for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < n; r += nw) {
+    for (int64_t r0 = ((int64_t)blockIdx.x * 4 + wave) * 16; r0 < n; r0 += (int64_t)gridDim.x * 64) {
+        const bool ok = r0 + c < n;
+        const float* xr = x + (ok ? r0 + c : n - 1) * D;
+        f64x4 acc[4];
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) acc[ct] = f64x4{0.0, 0.0, 0.0, 0.0};
         double l1 = 0.0;
-        for (int i = lane; i < 128; i += 64) {
-            const double v = i < D ? (double)x[r * D + i] : 0.0;
-            sx[wave][i] = v;
-            l1 += fabs(v);
+        for (int c0 = 4 * g; c0 < DR; c0 += 16) {
+            float xv[4] = {0.f, 0.f, 0.f, 0.f};
+            if (V4) {
+                if (c0 < D) {
+                    const float4 v = *reinterpret_cast<const float4*>(xr + c0);
+                    xv[0] = v.x, xv[1] = v.y, xv[2] = v.z, xv[3] = v.w;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (c0 + e < D) xv[e] = xr[c0 + e];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double a = (double)xv[e];
+                l1 += fabs(a);
+#pragma unroll
+                for (int ct = 0; ct < 4; ++ct)
+                    acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, sphi[(c0 + e) * 64 + 16 * ct + c], acc[ct], 0, 0, 0);
+            }
         }
-        l1 = wave_sum_f64(l1);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        double y = 0.0;
-        for (int i = 0; i < D; ++i) y += sphi[i * 64 + lane] * sx[wave][i];
-        if (lane >= m) y = 0.0;
-        const double amax = wave_max_f64(fabs(y));
-        const uint16_t sb = bf16_up(amax / 127.0);
-        const double sxf = (double)bf16_to_f(sb);
-        const double cq = sxf > 0.0 ? rint(y / sxf) : 0.0;
-        const int code = (int)fmin(127.0, fmax(-127.0, cq));
-        const double yt = sxf * (double)code;
-        const double err = yt - y;
-        const double rho2 = wave_sum_f64(err * err);
-        const double n2 = wave_sum_f64(yt * yt);
-        const double rho = sqrt(rho2) * (1.0 + 1e-12) + 1e-13 * l1 + 1e-300;
-        const uint64_t tail = (uint64_t)__float_as_uint((float)n2) | ((uint64_t)sb << 32) | ((uint64_t)bf16_up(rho) << 48);
-        const uint8_t v = lane < kScreenMax ? (uint8_t)(int8_t)code : (uint8_t)(tail >> (8 * (lane - kScreenMax)));
-        sc[r * kScreenBytes + lane] = v;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        l1 += __shfl_xor(l1, 16);
+        l1 += __shfl_xor(l1, 32);   // of row c
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 4 * i + g;
+            double am = 0.0;
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) am = fmax(am, fabs(acc[ct][i]));
+            const uint16_t sb = bf16_up(row16_max(am) / 127.0);
+            const double sxf = (double)bf16_to_f(sb);
+            double rho2 = 0.0, n2 = 0.0;
+            int code[4];
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) {
+                const double y = acc[ct][i];
+                const double cq = sxf > 0.0 ? rint(y / sxf) : 0.0;
+                code[ct] = (int)fmin(127.0, fmax(-127.0, cq));
+                const double yt = sxf * (double)code[ct];
+                const double err = yt - y;
+                rho2 += err * err;
+                n2 += yt * yt;
+            }
+            rho2 = row16_sum(rho2);
+            n2 = row16_sum(n2);
+            const double rho = sqrt(rho2) * (1.0 + 1e-12) + 1e-13 * __shfl(l1, r) + 1e-300;
+            const uint64_t tail =
+                (uint64_t)__float_as_uint((float)n2) | ((uint64_t)sb << 32) | ((uint64_t)bf16_up(rho) << 48);
+            if (r0 + r < n) {
+                uint8_t* out = sc + (r0 + r) * kScreenBytes + c;
+#pragma unroll
+                for (int ct = 0; ct < 3; ++ct) out[16 * ct] = (uint8_t)(int8_t)code[ct];
+                out[48] = c < kScreenMax - 48 ? (uint8_t)(int8_t)code[3] : (uint8_t)(tail >> (8 * (c - (kScreenMax - 48))));
+            }
+        }
     }
 }
 
@@ -238,9 +484,12 @@ hipError_t launch_screen_rows(const float* x, int64_t n, int D, int m, const dou
     static_assert(kScreenMax + 8 == kScreenBytes && kScreenBytes == 64, "screen row: 56 codes and 8 tail bytes");
     if (n == 0) return hipSuccess;
     if (D < 1 || D > 128 || m < 1 || m > kScreenMax || m > D) return hipErrorInvalidValue;
-    const int64_t blocks = std::min<int64_t>((n + 3) / 4, 4096);
-    hipLaunchKernelGGL(k_screen_rows, dim3((unsigned)blocks), dim3(256), sizeof(double) * D * 64, st, x, n, D, m,
-                       phiT, sc);
+    const int64_t blocks = std::min<int64_t>((n + 63) / 64, 2048);
+    const size_t lds = sizeof(double) * (size_t)((D + 15) & ~15) * 64;
+    if (D % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0)
+        hipLaunchKernelGGL(k_screen_rows<true>, dim3((unsigned)blocks), dim3(256), lds, st, x, n, D, phiT, sc);
+    else
+        hipLaunchKernelGGL(k_screen_rows<false>, dim3((unsigned)blocks), dim3(256), lds, st, x, n, D, phiT, sc);
     return hipGetLastError();
 }
 

@@ -12,6 +12,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/zoomhash.h"
@@ -232,12 +233,14 @@ struct SplitMix {
     }
 };
 
+// Tables are independent streams: large parameter sets are drawn by several
+// host threads (48,000 values take 1.1 ms on one), which changes no value.
 void hash_params(uint64_t seed, int L, int k, int D, double w, std::vector<float>& alpha,
                  std::vector<float>& beta) {
     alpha.assign((size_t)L * k * D, 0.f);
     beta.assign((size_t)L * k, 0.f);
     const double eps = 1e-3;
-    for (int l = 0; l < L; ++l) {
+    auto table = [&](int l) {
         SplitMix g{fmix64(seed + kGolden * (uint64_t)(l + 1))};
         for (int j = 0; j < k; ++j)
             for (int i = 0; i < D; ++i) {
@@ -247,7 +250,21 @@ void hash_params(uint64_t seed, int L, int k, int D, double w, std::vector<float
                 alpha[((size_t)l * k + j) * D + i] = (float)(a / b);
             }
         for (int j = 0; j < k; ++j) beta[(size_t)l * k + j] = (float)(g.uniform() * w);
+    };
+    const int nt = alpha.size() < 8192 ? 1 : std::min(L, 8);
+    std::thread th[8];
+    int started = 1;
+    try {
+        for (; started < nt; ++started)
+            th[started] = std::thread([&, started] {
+                for (int l = started; l < L; l += nt) table(l);
+            });
+    } catch (...) {   // no further thread to be had: their tables are drawn below
     }
+    for (int t = 0; t < nt; ++t)
+        if (t == 0 || t >= started)
+            for (int l = t; l < L; l += nt) table(l);
+    for (int t = 1; t < started; ++t) th[t].join();
 }
 
 uint16_t bf16_rne_host(float x) {
@@ -331,62 +348,70 @@ zh_status hash_scratch(zh_ctx* c, HashArgs& ha) {
 }
 
 // Screen plane of a dictionary: FP64 covariance of up to 65536 evenly spaced
-// rows, its leading eigenvectors as Phi (host), the bf16 split of Phi for the
-// query rotation and the screen row of every entry.
-zh_status build_screen(zh_ctx* c, Dict& d, const float* feat) {
-    const int D = d.D, m = screen_dims(D);
+// rows, its leading eigenvectors as Phi, the bf16 split of Phi for the query
+// rotation and the screen row of every entry; enqueued on `st` only, the bound
+// on sigma_max(Phi)^2 is taken over by finish_screen.
+zh_status start_screen(zh_ctx* c, Dict& d, const float* feat, hipStream_t st, double** s2) {
+    const int D = d.D, m = screen_dims(D), DP = (D + 31) & ~31;
     const int64_t n = d.n;
-    const int64_t ns = std::min<int64_t>(n, 65536);
-    Buf part, cov, phit;
-    zh_status st = ZH_OK;
-    std::vector<double> C((size_t)D * D), phiT((size_t)D * kRotStride, 0.0);
-    std::vector<float> phi((size_t)m * D);
-    const int DP = (D + 31) & ~31;
-    std::vector<uint16_t> ph((size_t)kRotStride * DP, 0), pl((size_t)kRotStride * DP, 0);
-    double s2 = 0.0;
-    if ((st = ensure(c, part, sizeof(double) * 128 * (size_t)D * D)) != ZH_OK) goto out;
-    if ((st = ensure(c, cov, sizeof(double) * (size_t)D * D)) != ZH_OK) goto out;
-    if ((st = ensure(c, phit, sizeof(double) * (size_t)D * kRotStride)) != ZH_OK) goto out;
-    if (launch_cov(feat, n, D, ns, P<double>(part), P<double>(cov), c->stream) != hipSuccess ||
-        hipMemcpyAsync(C.data(), cov.p, sizeof(double) * (size_t)D * D, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
-        hipStreamSynchronize(c->stream) != hipSuccess) {
-        (void)hipGetLastError();
-        st = fail(c, ZH_EDEVICE, "zh_build_tables: covariance of the screen failed");
-        goto out;
-    }
-    s2 = screen_basis(C.data(), D, m, phi.data());
-    {
-        const double v = (1.0 / s2) * (1.0 - 1e-9);
-        float f = (float)v;
-        if ((double)f > v) f = std::nextafter(f, 0.0f);
-        d.inv_s2 = f;
-    }
+    TRY(ensure(c, c->tools, (size_t)screen_basis_bytes(D)));
+    TRY(ensure(c, d.sc, (size_t)kScreenBytes * (size_t)n));
+    TRY(ensure(c, d.phi_hi, sizeof(uint16_t) * (size_t)kRotStride * DP));
+    TRY(ensure(c, d.phi_lo, sizeof(uint16_t) * (size_t)kRotStride * DP));
     d.rot_c1 = rotate_bound_coeff(D);
-    for (int j = 0; j < m; ++j)
-        for (int i = 0; i < D; ++i) {
-            const float v = phi[(size_t)j * D + i];
-            phiT[(size_t)i * kRotStride + j] = (double)v;
-            const uint16_t h = bf16_rne_host(v);
-            ph[(size_t)j * DP + i] = h;
-            pl[(size_t)j * DP + i] = bf16_rne_host(v - bf16_f_host(h));
-        }
-    if ((st = ensure(c, d.sc, (size_t)kScreenBytes * (size_t)n)) != ZH_OK) goto out;
-    if ((st = ensure(c, d.phi_hi, sizeof(uint16_t) * ph.size())) != ZH_OK) goto out;
-    if ((st = ensure(c, d.phi_lo, sizeof(uint16_t) * pl.size())) != ZH_OK) goto out;
-    if (hipMemcpyAsync(phit.p, phiT.data(), sizeof(double) * phiT.size(), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-        hipMemcpyAsync(d.phi_hi.p, ph.data(), sizeof(uint16_t) * ph.size(), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-        hipMemcpyAsync(d.phi_lo.p, pl.data(), sizeof(uint16_t) * pl.size(), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-        launch_screen_rows(feat, n, D, m, P<double>(phit), P<uint8_t>(d.sc), c->stream) != hipSuccess ||
-        hipStreamSynchronize(c->stream) != hipSuccess) {
-        (void)hipGetLastError();
-        st = fail(c, ZH_EDEVICE, "zh_build_tables: screen rows failed");
-        goto out;
+    double* phiT = nullptr;
+    HIPCHK(c, launch_screen_basis(feat, n, D, std::min<int64_t>(n, 65536), m, c->tools.p, &phiT, s2,
+                                  P<uint16_t>(d.phi_hi), P<uint16_t>(d.phi_lo), st));
+    HIPCHK(c, launch_screen_rows(feat, n, D, m, phiT, P<uint8_t>(d.sc), st));
+    return ZH_OK;
+}
+
+// The context's second stream, and its events, made at first use.
+zh_status batch_stream(zh_ctx* c) {
+    auto& B = c->batch;
+    if (!B.stream) {
+        HIPCHK(c, hipStreamCreateWithFlags(&B.stream, hipStreamNonBlocking));
+        HIPCHK(c, hipEventCreateWithFlags(&B.ev_in, hipEventDisableTiming));
+        HIPCHK(c, hipEventCreateWithFlags(&B.ev_out, hipEventDisableTiming));
     }
-out:
-    release(c, part);
-    release(c, cov);
-    release(c, phit);
-    return st;
+    return ZH_OK;
+}
+
+// Work on the context's second stream, after what the context's stream holds
+// when it is opened; the context's stream goes on after it when it is joined or
+// the scope is left in any way (memory of the caller may be reused then).
+struct SideStream {
+    zh_ctx* c;
+    bool open = false;
+    explicit SideStream(zh_ctx* c_) : c(c_) {}
+    zh_status start() {
+        TRY(batch_stream(c));
+        HIPCHK(c, hipEventRecord(c->batch.ev_in, c->stream));
+        HIPCHK(c, hipStreamWaitEvent(c->batch.stream, c->batch.ev_in, 0));
+        open = true;
+        return ZH_OK;
+    }
+    zh_status join() {
+        if (!open) return ZH_OK;
+        open = false;
+        HIPCHK(c, hipEventRecord(c->batch.ev_out, c->batch.stream));
+        HIPCHK(c, hipStreamWaitEvent(c->stream, c->batch.ev_out, 0));
+        return ZH_OK;
+    }
+    ~SideStream() {
+        if (open && join() != ZH_OK) (void)hipStreamSynchronize(c->batch.stream);
+    }
+};
+
+zh_status finish_screen(zh_ctx* c, Dict& d, const double* s2_dev) {
+    double s2 = 0.0;
+    HIPCHK(c, hipMemcpyAsync(&s2, s2_dev, sizeof(s2), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    const double v = (1.0 / s2) * (1.0 - 1e-9);
+    float f = (float)v;
+    if ((double)f > v) f = std::nextafter(f, 0.0f);
+    d.inv_s2 = f;
+    return ZH_OK;
 }
 
 // Content hash of `bytes` bytes of device memory (a multiple of 4), salted by the section.
@@ -407,11 +432,12 @@ zh_status store_features(zh_ctx* c, Dict& d, const float* feat) {
     const int D = d.D;
     TRY(ensure(c, d.hi, sizeof(uint16_t) * (size_t)n * hi_stride(D) + 64));
     TRY(ensure(c, d.lo, sizeof(uint16_t) * (size_t)n * D + 64));
-    HIPCHK(c, hipMemsetAsync(d.hi.p, 0, d.hi.bytes, c->stream));
-    HIPCHK(c, hipMemsetAsync(d.lo.p, 0, d.lo.bytes, c->stream));
-    HIPCHK(c, launch_split_planes(feat, n, D, P<uint16_t>(d.hi), P<uint16_t>(d.lo), c->stream));
     TRY(ensure(c, d.xf, sizeof(float) * (size_t)n * D + 64));
-    HIPCHK(c, hipMemcpyAsync(d.xf.p, feat, sizeof(float) * (size_t)n * D, hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(c, launch_split_planes(feat, n, D, P<uint16_t>(d.hi), P<uint16_t>(d.lo), P<float>(d.xf), c->stream));
+    // the slack past the last rows, which wide loads may touch
+    const size_t he = sizeof(uint16_t) * (size_t)n * hi_stride(D), le = sizeof(uint16_t) * (size_t)n * D;
+    HIPCHK(c, hipMemsetAsync(static_cast<char*>(d.hi.p) + he, 0, 64, c->stream));
+    HIPCHK(c, hipMemsetAsync(static_cast<char*>(d.lo.p) + le, 0, 64, c->stream));
     return ZH_OK;
 }
 
@@ -688,7 +714,12 @@ zh_status zh_build_tables(zh_ctx* c, const zh_dictionary* dict, int L, int k, fl
     d.cap = cap;
     TRY(store_features(c, d, dict->feat));
     TRY(device_hash(c, dict->feat, sizeof(float) * (uint64_t)n * D, 0, &d.feat_hash));
-    TRY(build_screen(c, d, dict->feat));
+    double* s2_dev = nullptr;
+    // on the second stream: the basis is one workgroup's chain, beside which the
+    // keys and tables below are formed
+    SideStream side(c);
+    TRY(side.start());
+    TRY(start_screen(c, d, dict->feat, c->batch.stream, &s2_dev));
     // hash parameters
     hash_params(seed, L, k, D, (double)w, d.h_alpha, d.h_beta);
     const int m = L * k;
@@ -747,41 +778,54 @@ zh_status zh_build_tables(zh_ctx* c, const zh_dictionary* dict, int L, int k, fl
     ha.w = w;
     ha.prec = c->opts.proj;
     ha.keys = P<uint64_t>(c->keys_dict);
+    ha.keys_tmajor = 1;
     ha.codes = nullptr;
     ha.n_fixed = P<unsigned int>(c->counters) + C_CODEFIX;
     TRY(hash_scratch(c, ha));
     HIPCHK(c, launch_hash(ha, c->stream));
-    // directory and bins, table by table
+    // directory and bins, G tables at a time (about 8M entries: enough to fill
+    // the chip, 128 MB of scratch; one table at a time when that is not to be had)
     TRY(ensure(c, d.dir, sizeof(Slot) * (size_t)L * cap));
     const uint64_t fw = dir_filter_words(cap);
     TRY(ensure(c, d.dfilt, sizeof(uint32_t) * (size_t)L * fw));
     HIPCHK(c, hipMemsetAsync(d.dfilt.p, 0, sizeof(uint32_t) * (size_t)L * fw, c->stream));
     TRY(ensure(c, d.tids, sizeof(uint32_t) * (size_t)L * n));
-    TRY(ensure(c, c->slot_of, sizeof(uint32_t) * (size_t)n));
-    TRY(ensure(c, c->idsort, sizeof(uint32_t) * (size_t)n));
-    TRY(ensure(c, c->rs_k1, sizeof(uint32_t) * (size_t)n));
-    TRY(ensure(c, c->rs_v1, sizeof(uint32_t) * (size_t)n));
-    const int64_t hs = radix_hist_size(n);
-    TRY(ensure(c, c->rs_hist, sizeof(uint32_t) * (size_t)hs));
-    int bits = 0;
+    int bits = 1;
     while ((1ull << bits) < cap) ++bits;
-    HIPCHK(c, launch_dir_clear(P<Slot>(d.dir), (uint64_t)L * cap, c->stream));
-    for (int l = 0; l < L; ++l) {
-        Slot* dl = P<Slot>(d.dir) + (size_t)l * cap;
-        HIPCHK(c, launch_dir_insert(P<uint64_t>(c->keys_dict), n, L, l, dl, cap,
-                                    P<uint32_t>(d.dfilt) + (size_t)l * fw, P<uint32_t>(c->slot_of),
-                                    P<uint32_t>(c->idsort), c->stream));
-        bool in_first = true;
-        HIPCHK(c, radix_sort_pairs(P<uint32_t>(c->slot_of), P<uint32_t>(c->idsort), P<uint32_t>(c->rs_k1),
-                                   P<uint32_t>(c->rs_v1), n, bits, P<uint32_t>(c->rs_hist), hs, c->stream, &in_first));
-        const uint32_t* sk = in_first ? P<uint32_t>(c->slot_of) : P<uint32_t>(c->rs_k1);
-        const uint32_t* sv = in_first ? P<uint32_t>(c->idsort) : P<uint32_t>(c->rs_v1);
-        HIPCHK(c, launch_dir_offsets(sk, n, dl, c->stream));
-        HIPCHK(c, hipMemcpyAsync(P<uint32_t>(d.tids) + (size_t)l * n, sv, sizeof(uint32_t) * (size_t)n,
-                                 hipMemcpyDeviceToDevice, c->stream));
+    int G = (int)std::min<int64_t>(L, std::max<int64_t>(1, ((int64_t)8 << 20) / n));
+    Buf* scr[5] = {&c->slot_of, &c->idsort, &c->rs_k1, &c->rs_v1, &c->rs_hist};
+    auto sort_scratch = [&]() -> zh_status {
+        for (int i = 0; i < 4; ++i) TRY(ensure(c, *scr[i], sizeof(uint32_t) * (size_t)G * n));
+        return ensure(c, *scr[4], sizeof(uint32_t) * (size_t)radix_hist_size(n, G, bits));
+    };
+    {
+        zh_status ss = sort_scratch();
+        if (ss == ZH_ENOMEM && G > 1) {
+            for (Buf* b : scr) release(c, *b);
+            G = 1;
+            ss = sort_scratch();
+        }
+        if (ss != ZH_OK) return ss;
     }
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    HIPCHK(c, launch_dir_clear(P<Slot>(d.dir), (uint64_t)L * cap, c->stream));
+    for (int l = 0; l < L; l += G) {
+        const int g = std::min(G, L - l);
+        Slot* dl = P<Slot>(d.dir) + (size_t)l * cap;
+        HIPCHK(c, launch_dir_insert(P<uint64_t>(c->keys_dict) + (size_t)l * n, n, g, dl, cap,
+                                    P<uint32_t>(d.dfilt) + (size_t)l * fw, P<uint32_t>(c->slot_of), c->stream));
+        uint32_t *sk = nullptr, *sv = nullptr;
+        HIPCHK(c, radix_sort_pairs(P<uint32_t>(c->slot_of), P<uint32_t>(c->idsort), P<uint32_t>(c->rs_k1),
+                                   P<uint32_t>(c->rs_v1), true, P<uint32_t>(d.tids) + (size_t)l * n, n, g, bits,
+                                   P<uint32_t>(c->rs_hist), radix_hist_size(n, G, bits), c->stream, &sk, &sv));
+        HIPCHK(c, launch_dir_offsets(sk, n, g, dl, cap, c->stream));
+    }
+    TRY(side.join());
+    TRY(finish_screen(c, d, s2_dev));   // synchronises
     release(c, c->keys_dict);
+    if (c->mem_limit) {   // scratch of the build: not held against the limit of later calls
+        for (Buf* b : scr) release(c, *b);
+        release(c, c->tools);
+    }
     d.valid = true;
     return ZH_OK;
 }
@@ -1585,7 +1629,7 @@ zh_status zh_backward(zh_ctx* c, const float* g_hr, float* g_resid, float* g_lam
     const uint32_t none = (uint32_t)d.n;
     int bits = 1;
     while (bits < 32 && (1ull << bits) <= (uint64_t)d.n) ++bits;
-    const int64_t hsz = radix_hist_size(E > 0 ? E : 1);
+    const int64_t hsz = radix_hist_size(E > 0 ? E : 1, 1, bits);
     TRY(ensure(c, c->bwd_k, sizeof(uint32_t) * (size_t)(4 * (E > 0 ? E : 1) + hsz)));
     uint32_t* k0 = P<uint32_t>(c->bwd_k);
     uint32_t* v0 = k0 + E;
@@ -1595,13 +1639,13 @@ zh_status zh_backward(zh_ctx* c, const float* g_hr, float* g_resid, float* g_lam
     HIPCHK(c, hipMemsetAsync(g_resid, 0, sizeof(float) * (size_t)d.n * ps2, c->stream));
     if (E > 0) {
         HIPCHK(c, launch_nbr_pairs(P<int32_t>(c->ids), P<int32_t>(c->m), (int)Q, K, none, k0, v0, c->stream));
-        bool first = true;
-        HIPCHK(c, radix_sort_pairs(k0, v0, k1, v1, E, bits, hist, hsz, c->stream, &first));
+        uint32_t *sk = nullptr, *sv = nullptr;
+        HIPCHK(c, radix_sort_pairs(k0, v0, k1, v1, false, nullptr, E, 1, bits, hist, hsz, c->stream, &sk, &sv));
         const int64_t nchunk = (E + 63) / 64;
         TRY(ensure(c, c->bwd_part, sizeof(float) * 2 * (size_t)ps2 * nchunk + 8 * (size_t)nchunk));
         float* part = P<float>(c->bwd_part);
         void* info = part + 2 * (size_t)ps2 * nchunk;
-        HIPCHK(c, launch_dict_grad(first ? k0 : k1, first ? v0 : v1, E, none, P<float>(c->w), gp, w, s, K, g_resid,
+        HIPCHK(c, launch_dict_grad(sk, sv, E, none, P<float>(c->w), gp, w, s, K, g_resid,
                                    part, info, c->stream));
     }
     return ZH_OK;
@@ -1817,16 +1861,6 @@ zh_status batch_chain(zh_ctx* c, const zh_batch* b, hipStream_t st) {
     c->stream = saved;
     c->timing = timing;
     return rc;
-}
-
-zh_status batch_stream(zh_ctx* c) {
-    auto& B = c->batch;
-    if (!B.stream) {
-        HIPCHK(c, hipStreamCreateWithFlags(&B.stream, hipStreamNonBlocking));
-        HIPCHK(c, hipEventCreateWithFlags(&B.ev_in, hipEventDisableTiming));
-        HIPCHK(c, hipEventCreateWithFlags(&B.ev_out, hipEventDisableTiming));
-    }
-    return ZH_OK;
 }
 
 }  // namespace

@@ -47,7 +47,7 @@ hipError_t launch_check_positions(const int32_t* pos, int64_t n, int n_img, int 
 hipError_t launch_dict_cut(const float* hr, const float* lr, const float* maps, int H, int W,
                            int scale, const int32_t* pos, int64_t n, int mode, float* feat,
                            float* resid, hipStream_t st);
-hipError_t launch_split_planes(const float* x, int64_t n, int D, uint16_t* hi, uint16_t* lo,
+hipError_t launch_split_planes(const float* x, int64_t n, int D, uint16_t* hi, uint16_t* lo, float* xf,
                                hipStream_t st);
 hipError_t launch_bicubic(const float* lr, int h, int w, int scale, float* out, hipStream_t st);
 // FP64 bicubic upsampling rounded to fp32 (the interpolated LR images of the
@@ -111,15 +111,22 @@ void hash_bound_coeffs(int prec, int D, double w, const float* beta, int m, floa
 
 // ---- table build (k_table.hip) ----------------------------------------------
 hipError_t launch_dir_clear(Slot* dir, uint64_t count, hipStream_t st);
-// also sets the key bits of the table's presence filter (cleared beforehand)
-hipError_t launch_dir_insert(const uint64_t* keys, int64_t n, int L, int l, Slot* dir,
-                             uint64_t cap, uint32_t* filter, uint32_t* slot_of, uint32_t* ids, hipStream_t st);
-hipError_t launch_dir_offsets(const uint32_t* sorted_slot, int64_t n, Slot* dir, hipStream_t st);
-// stable LSD radix sort of (key, val) pairs on the low `bits` bits of key
-hipError_t radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, int64_t n,
-                            int bits, uint32_t* hist, int64_t hist_cap, hipStream_t st,
-                            bool* result_in_first);
-int64_t radix_hist_size(int64_t n);
+// keys [tables, n] into the directories [tables, cap], setting the key bits of
+// the presence filters (cleared beforehand); slot_of [tables, n]
+hipError_t launch_dir_insert(const uint64_t* keys, int64_t n, int tables, Slot* dir, uint64_t cap, uint32_t* filter,
+                             uint32_t* slot_of, hipStream_t st);
+// offsets and sizes of the bins from the sorted slots [tables, n]
+hipError_t launch_dir_offsets(const uint32_t* sorted_slot, int64_t n, int tables, Slot* dir, uint64_t cap,
+                              hipStream_t st);
+// stable LSD radix sort, table by table, of the (key, value) pairs [tables, n]
+// in k0, v0 on the low `bits` bits of the key (higher bits zero); index_values:
+// the values are the indexes 0 .. n - 1 of each table and v0 is scratch only.
+// k1, v1: scratch of the same size; vfinal (nullable) receives the values.
+// hist: radix_hist_size(n, tables, bits) words
+hipError_t radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, bool index_values,
+                            uint32_t* vfinal, int64_t n, int tables, int bits, uint32_t* hist, int64_t hist_cap,
+                            hipStream_t st, uint32_t** keys_out, uint32_t** vals_out);
+int64_t radix_hist_size(int64_t n, int tables, int bits);
 // adds the content hash of n_words 32-bit words at p into *out (cleared by
 // the caller): sum_i fmix64((i G + salt) ^ word_i) mod 2^64, G = kGolden
 hipError_t launch_hash_words(const void* p, int64_t n_words, uint64_t salt, unsigned long long* out,
@@ -172,11 +179,13 @@ constexpr int kScreenMax = 56;
 constexpr int kScreenBytes = 64;
 __host__ __device__ inline int screen_dims(int D) { return D < kScreenMax ? D : kScreenMax; }
 constexpr int kRotStride = 64;   // floats per coded query row (k_rotate)
-// FP64 sum of x x^T over ns rows r_i = floor(i n / ns) (ns <= 65536); part holds
-// 128 partial D x D matrices
-hipError_t launch_cov(const float* x, int64_t n, int D, int64_t ns, double* part, double* cov, hipStream_t st);
-// rows of Phi (m x D fp32) from the covariance; returns a bound on sigma_max(Phi)^2
-double screen_basis(const double* C, int D, int m, float* phi);
+// the screen's basis from the FP64 covariance of the ns rows
+// r_i = floor(i n / ns) (ns <= 65536): Phi split into bf16 [64][round32(D)]
+// planes, and in the scratch (screen_basis_bytes) phiT, FP64 [D][64], and *s2, a
+// bound on sigma_max(Phi)^2 (device)
+int64_t screen_basis_bytes(int D);
+hipError_t launch_screen_basis(const float* x, int64_t n, int D, int64_t ns, int m, void* scratch, double** phiT,
+                               double** s2, uint16_t* ph, uint16_t* pl, hipStream_t st);
 float rotate_bound_coeff(int D);
 // screen rows [n, kScreenBytes] from x [n, D]; phiT is FP64 [D][64]
 hipError_t launch_screen_rows(const float* x, int64_t n, int D, int m, const double* phiT, uint8_t* sc,

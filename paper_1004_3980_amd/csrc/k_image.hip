@@ -158,15 +158,6 @@ __global__ void k_gradient_maps(const float* __restrict__ lr, int n_img, int h, 
     }
 }
 
-// Batched: every LR pixel of every image; maps of image b at 4 lr_off.
-__global__ void k_b_gradient_maps(const BatchImage* __restrict__ im, int n, int64_t total, float* __restrict__ maps) {
-    for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const BatchImage& b = im[batch_image_of<&BatchImage::lr_off>(im, n, idx)];
-        gradient_maps_at(b.lr, b.h, b.w, (int)(idx - b.lr_off), maps + 4 * b.lr_off);
-    }
-}
-
 // Patch mean: FP64 sum over the 25 pixels in row-major order, then / 25.
 __device__ __forceinline__ double patch_mean(const float* __restrict__ I, int w, int i, int j) {
     double s = 0.0;
@@ -176,35 +167,64 @@ __device__ __forceinline__ double patch_mean(const float* __restrict__ I, int w,
 }
 
 // One workgroup per segment of up to 64 consecutive patches of one patch row:
-// the first threads form the segment's patch means (patch_mean), the rows
-// under the segment are staged in LDS, then the threads write the
-// segment's features in memory order (coalesced): the map values (gradient
-// mode) or the pixels minus the FP64 mean, rounded to fp32.
+// the LR rows under the segment (two more on every side for the gradients,
+// clamped indices: replicate border) are staged in LDS, the first threads form
+// the segment's patch means (the sum of patch_mean), all of them the gradient
+// maps under it (the values of gradient_maps_at) in LDS, then the threads write
+// the segment's features in memory order (coalesced): the map values (gradient
+// mode) or the pixels minus the FP64 mean, rounded to fp32. copy (nullable)
+// receives the LR image, each pixel from the segment whose first patch row and
+// columns hold it; counters (nullable) are cleared by the first segment. Bound:
+// the feature rows' writes (1024^2 at D = 100: 416 MB). Features, maps in a
+// kernel of their own, copy and clearing, then this: 1024^2 119 -> 93 us,
+// 251x263 24 -> 9.9.
 template <int MODE>
-__device__ __forceinline__ void query_features_seg(const float* __restrict__ lr, const float* __restrict__ maps,
-                                                   int h, int w, int i, int j0, float* __restrict__ feat,
-                                                   double* __restrict__ mu) {
+__device__ __forceinline__ void query_features_seg(const float* __restrict__ lr, int h, int w, int i, int j0,
+                                                   float* __restrict__ feat, double* __restrict__ mu,
+                                                   float* __restrict__ copy) {
     constexpr int D = MODE == 0 ? 25 : 100;
-    constexpr int NCH = MODE == 0 ? 1 : 4;        // image, or the four gradient maps
     constexpr int SW = kFeatSeg + kPatch - 1;     // columns under a segment of patches
+    constexpr int B = MODE == 0 ? 0 : 2;          // border of the staged LR rows
+    constexpr int SR = kPatch + 2 * B, SC = SW + 2 * B;
     __shared__ double smu[kFeatSeg];
-    __shared__ float stile[NCH * kPatch * SW];    // the 5 rows of each channel under the segment
+    __shared__ float slr[SR * SC];
+    __shared__ float stile[MODE == 0 ? 1 : 4 * kPatch * SW];   // the 5 rows of each gradient map
     const int nj = w - kPatch + 1;
     const int np = nj - j0 < kFeatSeg ? nj - j0 : kFeatSeg;
     const int64_t q0 = (int64_t)i * nj + j0;
     const int t = threadIdx.x;
+    const int ncols = np + kPatch - 1;
+    for (int e = t; e < SR * SC; e += 256) {
+        const int a = e / SC, c = e - a * SC;
+        if (c < ncols + 2 * B) slr[e] = lr[(int64_t)clampi(i - B + a, 0, h - 1) * w + clampi(j0 - B + c, 0, w - 1)];
+    }
+    __syncthreads();
+    if (copy) {
+        const bool lastc = j0 + np == nj, lastr = i + kPatch == h;
+        const int cols = lastc ? ncols : np, rows = lastr ? kPatch : 1;
+        for (int e = t; e < rows * cols; e += 256) {
+            const int a = e / cols, c = e - a * cols;
+            copy[(int64_t)(i + a) * w + j0 + c] = slr[(B + a) * SC + B + c];
+        }
+    }
     if (t < np) {
-        const double m = patch_mean(lr, w, i, j0 + t);
+        double s = 0.0;
+        for (int a = 0; a < kPatch; ++a)
+            for (int b = 0; b < kPatch; ++b) s = s + (double)slr[(B + a) * SC + B + t + b];
+        const double m = s / (double)(kPatch * kPatch);
         smu[t] = m;
         mu[q0 + t] = m;
     }
-    const int64_t plane = (int64_t)h * w;
-    const int ncols = np + kPatch - 1;
-    // coalesced reads of the rows i .. i + 4 of every channel, columns j0 ..
-    for (int e = t; e < NCH * kPatch * SW; e += 256) {
-        const int ca = e / SW, c = e - ca * SW;
-        const int ch = ca / kPatch, a = ca - ch * kPatch;
-        if (c < ncols) stile[e] = (MODE == 0 ? lr : maps + ch * plane)[(int64_t)(i + a) * w + j0 + c];
+    if (MODE == 1) {
+        for (int e = t; e < kPatch * SW; e += 256) {
+            const int a = e / SW, c = e - a * SW;
+            const float* p = slr + (B + a) * SC + B + c;
+            const double x0 = (double)p[0];
+            stile[e] = (float)((double)p[1] - (double)p[-1]);
+            stile[kPatch * SW + e] = (float)((double)p[SC] - (double)p[-SC]);
+            stile[2 * kPatch * SW + e] = (float)((2.0 * x0 - (double)p[-2]) - (double)p[2]);
+            stile[3 * kPatch * SW + e] = (float)((2.0 * x0 - (double)p[-2 * SC]) - (double)p[2 * SC]);
+        }
     }
     __syncthreads();
     if (MODE == 0) {
@@ -212,7 +232,7 @@ __device__ __forceinline__ void query_features_seg(const float* __restrict__ lr,
         for (int l = t; l < np * D; l += 256) {
             const int p = l / D, e = l - p * D;
             const int a = e / kPatch, b = e - a * kPatch;
-            feat[q0 * D + l] = (float)((double)stile[a * SW + p + b] - smu[p]);
+            feat[q0 * D + l] = (float)((double)slr[a * SC + p + b] - smu[p]);
         }
     } else {
         // 16-byte stores: D = 100 keeps a group of four inside one patch row
@@ -232,27 +252,33 @@ __device__ __forceinline__ void query_features_seg(const float* __restrict__ lr,
     }
 }
 
+__device__ __forceinline__ void clear_counters_once(uint32_t* counters) {
+    if (counters && blockIdx.x == 0 && threadIdx.x < kNumCounters) counters[threadIdx.x] = 0u;
+}
+
 template <int MODE>
-__global__ __launch_bounds__(256) void k_query_features(const float* __restrict__ lr, const float* __restrict__ maps,
-                                                        int h, int w, float* __restrict__ feat,
-                                                        double* __restrict__ mu) {
+__global__ __launch_bounds__(256) void k_query_features(const float* __restrict__ lr, int h, int w,
+                                                        float* __restrict__ feat, double* __restrict__ mu,
+                                                        float* __restrict__ copy, uint32_t* __restrict__ counters) {
+    clear_counters_once(counters);
     const int nseg = (w - kPatch + 1 + kFeatSeg - 1) / kFeatSeg;
     const int i = blockIdx.x / nseg, j0 = (blockIdx.x - i * nseg) * kFeatSeg;
-    query_features_seg<MODE>(lr, maps, h, w, i, j0, feat, mu);
+    query_features_seg<MODE>(lr, h, w, i, j0, feat, mu, copy);
 }
 
 // Batched: one workgroup per segment of every image (the image from the
 // table's segment offsets), the single-image code on the image's arrays.
 template <int MODE>
 __global__ __launch_bounds__(256) void k_b_query_features(const BatchImage* __restrict__ im, int n,
-                                                          const float* __restrict__ maps, float* __restrict__ feat,
-                                                          double* __restrict__ mu) {
+                                                          float* __restrict__ feat, double* __restrict__ mu,
+                                                          uint32_t* __restrict__ counters) {
     constexpr int D = MODE == 0 ? 25 : 100;
+    clear_counters_once(counters);
     const BatchImage& b = im[batch_image_of<&BatchImage::fblk_off>(im, n, blockIdx.x)];
     const int64_t lb = blockIdx.x - b.fblk_off;
     const int nseg = (b.w - kPatch + 1 + kFeatSeg - 1) / kFeatSeg;
     const int i = (int)(lb / nseg), j0 = (int)(lb - (int64_t)i * nseg) * kFeatSeg;
-    query_features_seg<MODE>(b.lr, maps + 4 * b.lr_off, b.h, b.w, i, j0, feat + b.q_off * D, mu + b.q_off);
+    query_features_seg<MODE>(b.lr, b.h, b.w, i, j0, feat + b.q_off * D, mu + b.q_off, nullptr);
 }
 
 // Training pairs at positions (image, i, j): features, and the HR patch
@@ -401,34 +427,27 @@ hipError_t launch_gradient_maps(const float* lr, int n_img, int h, int w, float*
     return hipGetLastError();
 }
 
-hipError_t launch_query_features(const float* lr, const float* maps, int h, int w, int mode,
-                                 float* feat, double* mu, hipStream_t st) {
+hipError_t launch_query_features(const float* lr, int h, int w, int mode, float* feat, double* mu, float* copy,
+                                 uint32_t* counters, hipStream_t st) {
     const int ni = h - kPatch + 1, nj = w - kPatch + 1;
-    if (ni < 1 || nj < 1) return hipSuccess;
+    if (ni < 1 || nj < 1) return hipErrorInvalidValue;
     const int64_t blocks = feature_segments(h, w);
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
     if (mode == 0)
-        hipLaunchKernelGGL(k_query_features<0>, grid, dim3(256), 0, st, lr, maps, h, w, feat, mu);
+        hipLaunchKernelGGL(k_query_features<0>, grid, dim3(256), 0, st, lr, h, w, feat, mu, copy, counters);
     else
-        hipLaunchKernelGGL(k_query_features<1>, grid, dim3(256), 0, st, lr, maps, h, w, feat, mu);
+        hipLaunchKernelGGL(k_query_features<1>, grid, dim3(256), 0, st, lr, h, w, feat, mu, copy, counters);
     return hipGetLastError();
 }
 
-hipError_t launch_b_gradient_maps(const BatchImage* im, int n, int64_t lr_total, float* maps, hipStream_t st) {
-    if (lr_total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_b_gradient_maps, dim3(grid_for(lr_total, 256)), dim3(256), 0, st, im, n, lr_total, maps);
-    return hipGetLastError();
-}
-
-hipError_t launch_b_query_features(const BatchImage* im, int n, int64_t seg_total, int mode, const float* maps,
-                                   float* feat, double* mu, hipStream_t st) {
-    if (seg_total == 0) return hipSuccess;
-    if (seg_total > 0x7FFFFFFF) return hipErrorInvalidValue;
+hipError_t launch_b_query_features(const BatchImage* im, int n, int64_t seg_total, int mode, float* feat, double* mu,
+                                   uint32_t* counters, hipStream_t st) {
+    if (seg_total < 1 || seg_total > 0x7FFFFFFF) return hipErrorInvalidValue;
     if (mode == 0)
-        hipLaunchKernelGGL(k_b_query_features<0>, dim3((unsigned)seg_total), dim3(256), 0, st, im, n, maps, feat, mu);
+        hipLaunchKernelGGL(k_b_query_features<0>, dim3((unsigned)seg_total), dim3(256), 0, st, im, n, feat, mu, counters);
     else
-        hipLaunchKernelGGL(k_b_query_features<1>, dim3((unsigned)seg_total), dim3(256), 0, st, im, n, maps, feat, mu);
+        hipLaunchKernelGGL(k_b_query_features<1>, dim3((unsigned)seg_total), dim3(256), 0, st, im, n, feat, mu, counters);
     return hipGetLastError();
 }
 

@@ -115,7 +115,7 @@ struct zh_ctx {
     int bp_rec = 0, bp_iters = 0;
     float bp_sigma_s = 0.f, bp_sigma_r = 0.f;
     int64_t Q = 0;
-    Buf lr, maps, qfeat, qmu, qkeys, qbins, ids, d2, m, ncand, w, over, sbpart, e, tmp, counters, gram, hmask, fixl, fixc, nsurv, guides, bwd, bwd_k, clam;
+    Buf lr, qfeat, qmu, qkeys, qbins, ids, d2, m, ncand, w, over, sbpart, e, tmp, counters, gram, hmask, fixl, fixc, nsurv, guides, bwd, bwd_k, clam;
     Buf qrot;                     // [Q, 64] rotated queries of the screen
     Buf chk;                      // flag of the training-position check
     Buf bwd_gw;                   // [Q, 8] FP64 scratch of the lambda adjoint
@@ -576,7 +576,7 @@ void zh_destroy(zh_ctx* c) {
     for (auto& g : c->batch.g) release(c, g.table);
     release(c, c->batch.scr);
     release(c, c->batch.e);
-    Buf* bufs[] = {&c->lr, &c->maps, &c->qfeat, &c->qmu, &c->qkeys, &c->qbins, &c->ids, &c->d2, &c->m,
+    Buf* bufs[] = {&c->lr, &c->qfeat, &c->qmu, &c->qkeys, &c->qbins, &c->ids, &c->d2, &c->m,
                    &c->ncand, &c->w, &c->over, &c->sbpart, &c->e, &c->tmp, &c->counters, &c->rs_k1,
                    &c->rs_v1, &c->rs_hist, &c->slot_of, &c->idsort, &c->keys_dict, &c->gram, &c->hmask, &c->fixl, &c->fixc, &c->nsurv, &c->guides, &c->bwd, &c->bwd_k, &c->clam, &c->qrot, &c->bwd_gw, &c->bwd_part, &c->tools, &c->l1cand, &c->chk, &c->wall};
     for (Buf* b : bufs) release(c, *b);
@@ -672,14 +672,12 @@ zh_status zh_features(zh_ctx* c, const float* lr, int h, int w, int mode, float*
         return fail(c, ZH_EINVAL, "zh_features: bad arguments");
     TRY(set_device(c));
     const int64_t Q = (int64_t)(h - 4) * (w - 4);
-    TRY(ensure(c, c->maps, sizeof(float) * 4 * (size_t)h * w));
     double* mup = mu;
     if (!mup) {
         TRY(ensure(c, c->qmu, sizeof(double) * (size_t)Q));
         mup = P<double>(c->qmu);
     }
-    if (mode == ZH_FEAT_GRAD4) HIPCHK(c, launch_gradient_maps(lr, 1, h, w, P<float>(c->maps), c->stream));
-    HIPCHK(c, launch_query_features(lr, P<float>(c->maps), h, w, mode, feat, mup, c->stream));
+    HIPCHK(c, launch_query_features(lr, h, w, mode, feat, mup, nullptr, nullptr, c->stream));
     return ZH_OK;
 }
 
@@ -1204,7 +1202,6 @@ zh_status zh_query(zh_ctx* c, const float* lr, int h, int w, int scale, int K) {
     c->stage = 0;
     const int ps2 = (kPatch * scale) * (kPatch * scale);
     TRY(ensure(c, c->lr, sizeof(float) * (size_t)h * w));
-    TRY(ensure(c, c->maps, sizeof(float) * 4 * (size_t)h * w));
     TRY(ensure(c, c->qfeat, sizeof(float) * (size_t)Q * d.D));
     TRY(ensure(c, c->qmu, sizeof(double) * (size_t)Q));
     TRY(ensure(c, c->qkeys, sizeof(uint64_t) * (size_t)Q * d.L));
@@ -1215,19 +1212,18 @@ zh_status zh_query(zh_ctx* c, const float* lr, int h, int w, int scale, int K) {
     TRY(ensure(c, c->m, sizeof(int32_t) * (size_t)Q));
     TRY(ensure(c, c->ncand, sizeof(int32_t) * (size_t)Q));
     TRY(ensure(c, c->over, 2 * sizeof(int32_t) * (size_t)Q));
-    HIPCHK(c, hipMemcpyAsync(c->lr.p, lr, sizeof(float) * (size_t)h * w, hipMemcpyDeviceToDevice, c->stream));
+    TRY(ensure(c, c->counters, kNumCounters * sizeof(uint32_t)));
     c->qh = h;
     c->qw = w;
     c->qscale = scale;
     c->qK = K;
     c->Q = Q;
     c->all_m = false;
-    TRY(clear_counters(c));
     {
+        // features, the context's copy of the LR image, the counters cleared
         StageTimer t(c, ZH_T_FEATURES);
-        if (d.mode == ZH_FEAT_GRAD4) HIPCHK(c, launch_gradient_maps(P<float>(c->lr), 1, h, w, P<float>(c->maps), c->stream));
-        HIPCHK(c, launch_query_features(P<float>(c->lr), P<float>(c->maps), h, w, d.mode, P<float>(c->qfeat),
-                                        P<double>(c->qmu), c->stream));
+        HIPCHK(c, launch_query_features(lr, h, w, d.mode, P<float>(c->qfeat), P<double>(c->qmu), P<float>(c->lr),
+                                        P<uint32_t>(c->counters), c->stream));
     }
     HashArgs ha{};
     ha.feat = P<float>(c->qfeat);
@@ -1754,7 +1750,6 @@ zh_status batch_plan(zh_ctx* c, const zh_batch* b) {
     }
     const int64_t K = b->K;
     TRY(ensure(c, B.e, sizeof(float) * (size_t)std::max<int64_t>(lr_max, 1)));
-    TRY(ensure(c, c->maps, sizeof(float) * 4 * (size_t)std::max<int64_t>(lr_max, 1)));
     TRY(ensure(c, c->qfeat, sizeof(float) * (size_t)q_max * D_max));
     TRY(ensure(c, c->qmu, sizeof(double) * (size_t)q_max));
     TRY(ensure(c, c->qkeys, sizeof(uint64_t) * (size_t)q_max * L_max));
@@ -1796,10 +1791,8 @@ zh_status batch_chain(zh_ctx* c, const zh_batch* b, hipStream_t st) {
             c->Q = g.q_total;
             c->qK = K;
             c->qscale = s;
-            TRY(clear_counters(c));
-            if (d.mode == ZH_FEAT_GRAD4) HIPCHK(c, launch_b_gradient_maps(tab, g.n, g.lr_total, P<float>(c->maps), st));
-            HIPCHK(c, launch_b_query_features(tab, g.n, g.fsegs, d.mode, P<float>(c->maps), P<float>(c->qfeat),
-                                              P<double>(c->qmu), st));
+            HIPCHK(c, launch_b_query_features(tab, g.n, g.fsegs, d.mode, P<float>(c->qfeat), P<double>(c->qmu),
+                                              P<uint32_t>(c->counters), st));
             HashArgs ha{};
             ha.feat = P<float>(c->qfeat);
             ha.n = g.q_total;

@@ -37,9 +37,11 @@ hipError_t launch_degrade_residual(const float* hr, int H, int W, int scale, con
                                    const float* lr_ref, float* e, hipStream_t st);
 hipError_t launch_gradient_maps(const float* lr, int n_img, int h, int w, float* maps,
                                 hipStream_t st);
-// features of every stride-1 patch of one LR image (row-major patch order)
-hipError_t launch_query_features(const float* lr, const float* maps, int h, int w, int mode,
-                                 float* feat, double* mu, hipStream_t st);
+// features and means of every stride-1 patch of one LR image (row-major patch
+// order); copy (nullable) receives the image, counters (nullable, kNumCounters)
+// are cleared
+hipError_t launch_query_features(const float* lr, int h, int w, int mode, float* feat, double* mu, float* copy,
+                                 uint32_t* counters, hipStream_t st);
 // flag[0] set to 1 when a position (image, i, j) of pos[n, 3] is outside
 // [0, n_img) x [0, imax] x [0, jmax]
 hipError_t launch_check_positions(const int32_t* pos, int64_t n, int n_img, int imax, int jmax, uint32_t* flag,
@@ -311,10 +313,9 @@ __device__ __forceinline__ int batch_image_of(const BatchImage* im, int n, int64
     }
     return lo;
 }
-hipError_t launch_b_gradient_maps(const BatchImage* im, int n, int64_t lr_total, float* maps, hipStream_t st);
 // one workgroup per feature segment (64 patches of a patch row) of every image
-hipError_t launch_b_query_features(const BatchImage* im, int n, int64_t seg_total, int mode, const float* maps,
-                                   float* feat, double* mu, hipStream_t st);
+hipError_t launch_b_query_features(const BatchImage* im, int n, int64_t seg_total, int mode, float* feat, double* mu,
+                                   uint32_t* counters, hipStream_t st);
 // LR error of every image: `tiles` LR tiles in all (degrade_tiles per image)
 hipError_t launch_b_degrade_residual(const BatchImage* im, int n, int64_t lr_total, int64_t tiles, int scale,
                                      const Taps& t, int parity, float* e, hipStream_t st);

@@ -43,7 +43,7 @@ struct Dict {
     const float* resid = nullptr; // borrowed
     Buf hi, lo;                   // [n, hi_stride(D)] and [n, D] split planes (64 bytes of slack at the end)
     Buf alpha, beta, bc0[2], ahi, alo;   // ahi, alo: bf16 split of fl(alpha / w)
-    Buf bw;                       // [L k] fl(beta / w)
+    Buf himg[2];                         // hash rows as the kernels of each precision stage them
     float bc1[2] = {0.f, 0.f}, bc2[2] = {0.f, 0.f};
     Buf dir;                      // [L, cap] Slot
     Buf dfilt;                    // [L, dir_filter_words(cap)] presence bits of the keys
@@ -293,22 +293,22 @@ Taps gauss_taps(double sigma) {
     return t;
 }
 
-// fl(beta / w) of the host copy of beta, to the device (synchronous)
-zh_status upload_beta_w(zh_ctx* c, Dict& d) {
-    std::vector<float> bw(d.h_beta.size());
-    for (size_t j = 0; j < bw.size(); ++j) bw[j] = d.h_beta[j] / d.w;
-    TRY(ensure(c, d.bw, sizeof(float) * std::max<size_t>(bw.size(), 1)));
-    HIPCHK(c, hipMemcpyAsync(d.bw.p, bw.data(), sizeof(float) * bw.size(), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+// The hash rows as k_hash stages them, for both precisions.
+zh_status make_hash_images(zh_ctx* c, Dict& d) {
+    for (int pr = 0; pr < 2; ++pr) {
+        TRY(ensure(c, d.himg[pr], hash_image_bytes(pr, d.D, d.L, d.k)));
+        HIPCHK(c, launch_hash_image(pr, d.D, d.L, d.k, d.w, P<float>(d.alpha), P<float>(d.beta), P<uint16_t>(d.ahi),
+                                    P<uint16_t>(d.alo), P<float>(d.bc0[pr]), P<uint64_t>(d.kmul),
+                                    P<unsigned char>(d.himg[pr]), c->stream));
+    }
     return ZH_OK;
 }
 
 void set_bounds(HashArgs& ha, Dict& d, int prec) {
-    ha.bound_c0 = P<float>(d.bc0[prec]);
-    ha.bound_c1 = d.bc1[prec];
+    ha.img = P<unsigned char>(d.himg[prec]);
+    ha.bound_c1 = hash_bound_norm_c1(prec, d.D, (double)d.w);
     ha.bound_c2 = d.bc2[prec];
     ha.inv_w = 1.0f / d.w;
-    ha.beta_w = P<float>(d.bw);
 }
 
 zh_status set_device(zh_ctx* c) {
@@ -331,17 +331,18 @@ zh_status clear_counters(zh_ctx* c) {
 }
 
 // Scratch of the hash kernels: the per-row dirty mask, and a fix list of
-// kFixSlots entries for each wave of 16 rows (384 tables at L = 24; on
-// average about 1% of the tables need a fix) with its entry counts.
+// kFixSlots entries for each 16 rows (384 tables at L = 24; on average
+// about 1% of the tables need a fix) with its entry counts.
 zh_status hash_scratch(zh_ctx* c, HashArgs& ha) {
-    TRY(ensure(c, c->hmask, sizeof(uint64_t) * (size_t)(ha.n > 0 ? ha.n : 1)));
+    hash_parts(ha);
+    TRY(ensure(c, c->hmask, sizeof(uint64_t) * (size_t)(ha.n > 0 ? ha.n : 1) * ha.parts));
     ha.dirty = P<uint64_t>(c->hmask);
     int cap = kFixSlots;
     if (const char* ev = std::getenv("ZH_HASH_FIX_CAP")) cap = std::min(kFixSlots, std::max(0, std::atoi(ev)));
-    const size_t nw = (size_t)((ha.n + 15) / 16);
-    TRY(ensure(c, c->fixl, sizeof(int32_t) * nw * cap * (size_t)(((ha.k + 2) + 3) & ~3)));
-    TRY(ensure(c, c->fixc, sizeof(uint32_t) * (nw > 0 ? nw : 1)));
-    ha.fix_list = P<int32_t>(c->fixl);
+    const size_t nw = (size_t)((ha.n + 15) / 16) * ha.parts;
+    TRY(ensure(c, c->fixl, sizeof(uint4) * nw * cap));
+    TRY(ensure(c, c->fixc, sizeof(uint32_t) * hash_count_words(ha)));
+    ha.fix_list = P<uint4>(c->fixl);
     ha.fix_cap = cap;
     ha.fix_count = P<unsigned int>(c->fixc);
     return ZH_OK;
@@ -560,7 +561,7 @@ void zh_destroy(zh_ctx* c) {
     (void)hipStreamSynchronize(c->stream);
     for (Dict& d : c->dicts) {
         release(c, d.hi); release(c, d.lo); release(c, d.alpha); release(c, d.beta); release(c, d.bc0[0]); release(c, d.bc0[1]);
-        release(c, d.ahi); release(c, d.alo); release(c, d.bw); release(c, d.dir); release(c, d.dfilt); release(c, d.tids);
+        release(c, d.ahi); release(c, d.alo); release(c, d.himg[0]); release(c, d.himg[1]); release(c, d.dir); release(c, d.dfilt); release(c, d.tids);
         release(c, d.sc); release(c, d.phi_hi); release(c, d.phi_lo); release(c, d.kmul); release(c, d.xf);
         release(c, d.l1s);
     }
@@ -752,12 +753,12 @@ zh_status zh_build_tables(zh_ctx* c, const zh_dictionary* dict, int L, int k, fl
     TRY(ensure(c, d.alo, sizeof(uint16_t) * (size_t)m * DP));
     HIPCHK(c, hipMemcpyAsync(d.alpha.p, d.h_alpha.data(), sizeof(float) * (size_t)m * D, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(d.beta.p, d.h_beta.data(), sizeof(float) * (size_t)m, hipMemcpyHostToDevice, c->stream));
-    TRY(upload_beta_w(c, d));
     for (int pr = 0; pr < 2; ++pr)
         HIPCHK(c, hipMemcpyAsync(d.bc0[pr].p, bc0[pr].data(), sizeof(float) * (size_t)m, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipMemcpyAsync(d.ahi.p, ahi.data(), sizeof(uint16_t) * (size_t)m * DP, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(d.alo.p, alo.data(), sizeof(uint16_t) * (size_t)m * DP, hipMemcpyHostToDevice, c->stream));
+    TRY(make_hash_images(c, d));
     // keys of every pair in every table
     TRY(ensure(c, c->keys_dict, sizeof(uint64_t) * (size_t)n * L));
     TRY(clear_counters(c));
@@ -768,8 +769,6 @@ zh_status zh_build_tables(zh_ctx* c, const zh_dictionary* dict, int L, int k, fl
     ha.L = L;
     ha.k = k;
     ha.alpha = P<float>(d.alpha);
-    ha.a_hi = P<uint16_t>(d.ahi);
-    ha.a_lo = P<uint16_t>(d.alo);
     ha.beta = P<float>(d.beta);
     ha.key_mul = P<uint64_t>(d.kmul);
     set_bounds(ha, d, c->opts.proj);
@@ -1036,7 +1035,7 @@ zh_status zh_load_tables(zh_ctx* c, const zh_dictionary* dict, const char* path)
     HIPCHK(c, hipMemcpyAsync(d.h_alpha.data(), d.alpha.p, sizeof(float) * m * d.D, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipMemcpyAsync(d.h_beta.data(), d.beta.p, sizeof(float) * m, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    TRY(upload_beta_w(c, d));
+    TRY(make_hash_images(c, d));
     d.valid = true;
     return ZH_OK;
 }
@@ -1069,8 +1068,6 @@ zh_status zh_hash(zh_ctx* c, int scale, const float* feat, int64_t n, int32_t* c
     ha.L = d.L;
     ha.k = d.k;
     ha.alpha = P<float>(d.alpha);
-    ha.a_hi = P<uint16_t>(d.ahi);
-    ha.a_lo = P<uint16_t>(d.alo);
     ha.beta = P<float>(d.beta);
     ha.key_mul = P<uint64_t>(d.kmul);
     set_bounds(ha, d, c->opts.proj);
@@ -1084,11 +1081,11 @@ zh_status zh_hash(zh_ctx* c, int scale, const float* feat, int64_t n, int32_t* c
     return ZH_OK;
 }
 
-// Per feature row of zh_hash_noalloc: the dirty mask (8 bytes) and its share of
-// the fix list (kFixSlots entries per 16 rows) and of the list's counts.
-static size_t noalloc_row_bytes(int k) {
-    return 8 + (size_t)kFixSlots * sizeof(int32_t) * (size_t)(((k + 2) + 3) & ~3) / 16 + 1;
-}
+// Fix-list entries per 16 rows of zh_hash_noalloc, and its bytes per feature
+// row: the dirty mask (8 bytes) and its share of the fix list and of the
+// list's counts.
+static int noalloc_fix_cap(int k) { return std::min(kFixSlots, 4 * (((k + 2) + 3) & ~3)); }
+static size_t noalloc_row_bytes(int k) { return 8 + 4 * (size_t)(((k + 2) + 3) & ~3) + 1; }
 static int64_t noalloc_max_rows(int k) {
     return (int64_t)((kNoAllocBytes - 512) / noalloc_row_bytes(k)) & ~(int64_t)15;
 }
@@ -1106,12 +1103,10 @@ zh_status zh_hash_noalloc(zh_ctx* c, int scale, const float* feat, int64_t n, in
         return fail(c, ZH_EDEVICE, "zh_hash_noalloc: no fixed scratch on device %d", c->device);
     if (n == 0) return ZH_OK;
     TRY(set_device(c));
-    // carve the scratch: dirty mask [n] u64, fix list, fix counts [ceil(n/16)]
+    // carve the scratch: dirty mask [n] u64, fix list, fix counts [ceil(n/16)], each per part
     // (every entry the kernels read is written by them first in the same
     // call, so nothing needs clearing)
     unsigned char* base = static_cast<unsigned char*>(g_noalloc_ptr[c->device]);
-    const size_t nw = (size_t)((n + 15) / 16);
-    const size_t fe = (size_t)(((d.k + 2) + 3) & ~3);
     HashArgs ha{};
     ha.feat = feat;
     ha.n = n;
@@ -1119,8 +1114,6 @@ zh_status zh_hash_noalloc(zh_ctx* c, int scale, const float* feat, int64_t n, in
     ha.L = d.L;
     ha.k = d.k;
     ha.alpha = P<float>(d.alpha);
-    ha.a_hi = P<uint16_t>(d.ahi);
-    ha.a_lo = P<uint16_t>(d.alo);
     ha.beta = P<float>(d.beta);
     ha.key_mul = P<uint64_t>(d.kmul);
     set_bounds(ha, d, c->opts.proj);
@@ -1130,10 +1123,17 @@ zh_status zh_hash_noalloc(zh_ctx* c, int scale, const float* feat, int64_t n, in
     ha.codes = codes;
     ha.n_fixed = nullptr;
     ha.dirty = reinterpret_cast<uint64_t*>(base);
-    ha.fix_cap = kFixSlots;
-    ha.fix_list = reinterpret_cast<int32_t*>(base + ((8 * (size_t)n + 255) & ~(size_t)255));
+    ha.fix_cap = noalloc_fix_cap(d.k);
+    // one part for rows that fill the scratch
+    hash_parts(ha);
+    while (ha.parts > 1 && ((n + 15) & ~(int64_t)15) * ha.parts > nmax) {
+        ha.part_stages *= 2;
+        ha.parts = (ha.parts + 1) / 2;
+    }
+    const size_t nw = (size_t)((n + 15) / 16) * ha.parts;
+    ha.fix_list = reinterpret_cast<uint4*>(base + ((8 * (size_t)n * ha.parts + 255) & ~(size_t)255));
     ha.fix_count = reinterpret_cast<unsigned int*>(reinterpret_cast<unsigned char*>(ha.fix_list) +
-                                                  ((nw * kFixSlots * fe * sizeof(int32_t) + 255) & ~(size_t)255));
+                                                  ((nw * ha.fix_cap * sizeof(uint4) + 255) & ~(size_t)255));
     HIPCHK(c, launch_hash(ha, c->stream));
     return ZH_OK;
 }
@@ -1232,8 +1232,6 @@ zh_status zh_query(zh_ctx* c, const float* lr, int h, int w, int scale, int K) {
     ha.L = d.L;
     ha.k = d.k;
     ha.alpha = P<float>(d.alpha);
-    ha.a_hi = P<uint16_t>(d.ahi);
-    ha.a_lo = P<uint16_t>(d.alo);
     ha.beta = P<float>(d.beta);
     ha.key_mul = P<uint64_t>(d.kmul);
     set_bounds(ha, d, c->opts.proj);
@@ -1692,7 +1690,7 @@ std::vector<uint64_t> batch_signature(zh_ctx* c, const zh_batch* b) {
 // Image tables and every buffer the chain needs, sized before any capture.
 zh_status batch_plan(zh_ctx* c, const zh_batch* b) {
     auto& B = c->batch;
-    int64_t q_max = 0, lr_max = 0, hr_max = 0, part_max = 0, L_max = 0, k_max = 0, D_max = 0;
+    int64_t q_max = 0, lr_max = 0, hr_max = 0, part_max = 0, L_max = 0, D_max = 0;
     std::vector<BatchImage> tabs[kMaxScale + 1];
     for (int s = 1; s <= kMaxScale; ++s) {
         auto& g = B.g[s];
@@ -1736,7 +1734,6 @@ zh_status batch_plan(zh_ctx* c, const zh_batch* b) {
         hr_max = std::max(hr_max, hr);
         part_max = std::max<int64_t>(part_max, g.sbtiles * sb_part_floats(s, c->sb_rows));
         L_max = std::max<int64_t>(L_max, d.L);
-        k_max = std::max<int64_t>(k_max, d.k);
         D_max = std::max<int64_t>(D_max, d.D);
     }
     // the groups run one after another and share the scratch
@@ -1765,11 +1762,16 @@ zh_status batch_plan(zh_ctx* c, const zh_batch* b) {
     TRY(ensure(c, c->sbpart, sizeof(float) * (size_t)std::max<int64_t>(part_max, 1)));
     TRY(ensure(c, c->counters, kNumCounters * sizeof(uint32_t)));
     if (K <= 8) TRY(ensure(c, c->gram, (c->opts.lle_fp64 ? 8 : 4) * (size_t)q_max * 36));
-    HashArgs ha{};
-    ha.n = q_max;
-    ha.L = (int)L_max;
-    ha.k = (int)k_max;
-    TRY(hash_scratch(c, ha));
+    for (int s = 1; s <= kMaxScale; ++s)
+        for (int pr = 0; B.g[s].n && pr < 2; ++pr) {
+            HashArgs ha{};
+            ha.n = B.g[s].q_total;
+            ha.D = c->dicts[s].D;
+            ha.L = c->dicts[s].L;
+            ha.k = c->dicts[s].k;
+            ha.prec = pr;
+            TRY(hash_scratch(c, ha));
+        }
     return ZH_OK;
 }
 
@@ -1800,8 +1802,6 @@ zh_status batch_chain(zh_ctx* c, const zh_batch* b, hipStream_t st) {
             ha.L = d.L;
             ha.k = d.k;
             ha.alpha = P<float>(d.alpha);
-            ha.a_hi = P<uint16_t>(d.ahi);
-            ha.a_lo = P<uint16_t>(d.alo);
             ha.beta = P<float>(d.beta);
             ha.key_mul = P<uint64_t>(d.kmul);
             set_bounds(ha, d, c->opts.proj);
@@ -2203,7 +2203,7 @@ zh_status zh_stats(zh_ctx* c, zh_stats_t* out) {
     out->truncated = h[C_TRUNC];
     uint64_t db = 0;
     for (const Dict& d : c->dicts)
-        db += d.hi.bytes + d.lo.bytes + d.dir.bytes + d.dfilt.bytes + d.tids.bytes + d.alpha.bytes + d.ahi.bytes + d.alo.bytes +
+        db += d.hi.bytes + d.lo.bytes + d.dir.bytes + d.dfilt.bytes + d.tids.bytes + d.alpha.bytes + d.ahi.bytes + d.alo.bytes + d.himg[0].bytes + d.himg[1].bytes +
               d.l1s.bytes;
     out->dict_bytes = db;
     return ZH_OK;

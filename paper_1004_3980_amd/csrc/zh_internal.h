@@ -15,8 +15,7 @@ constexpr int kMaxTaps = 33;    // longest 1-D Gaussian the kernels accept
 constexpr int kMaxK = 16;       // neighbours per patch
 constexpr int kMaxL = 64;       // hash tables
 constexpr int kMaxKHash = 32;   // hashes per table
-constexpr int32_t kCodeUnset = (int32_t)0x80000000;   // MFMA codes lie within +-2^23
-constexpr int kFixSlots = 16;                        // fix-list entries per wave of 16 rows
+constexpr int kFixSlots = 32;                        // fix-list entries per 16 rows
 
 // Device counters of the last query (uint32 each): patches deferred to the
 // large-union search, FP64 re-ranks, patches beyond the large-union limit
@@ -63,12 +62,9 @@ struct HashArgs {
     int D;
     int L, k;
     const float* alpha;      // [L*k, D] fp32
-    const uint16_t* a_hi;    // [L*k, DP] bf16 high parts of fl(alpha / w) (split projection), DP = D rounded to 32
-    const uint16_t* a_lo;    // [L*k, DP] bf16 low parts
+    const unsigned char* img;  // hash rows as the kernel stages them (launch_hash_image of this prec)
     const float* beta;       // [L*k]
-    const float* beta_w;     // [L*k] fl(beta / w) (split path; its a_hi, a_lo split fl(alpha / w))
-    const float* bound_c0;   // [L*k] per-hash constant term of the code error bound
-    float bound_c1;          // coefficient of the |alpha|.|v| MFMA value in the bound
+    float bound_c1;          // coefficient of sum |alpha_i v_i| in the bound (hash_bound_norm_c1)
     float bound_c2;          // coefficient of |alpha.v| (fp32 path)
     float inv_w;             // fp32 1/w
     float w;
@@ -77,12 +73,16 @@ struct HashArgs {
     uint64_t* keys;          // [n, L], or [L, n] when keys_tmajor
     int keys_tmajor;         // keys (and bins) stored table by table
     int32_t* codes;          // [n, L*k] or null
-    unsigned int* n_fixed;   // count of codes recomputed in FP64 (nullable)
-    uint64_t* dirty;         // [n] scratch: per row, bit l set when table l must be recomputed in full
-    int32_t* fix_list;       // scratch: per wave of 16 rows, fix_cap entries (row, table, k codes;
-                             // kCodeUnset where the FP64 definition must decide)
-    int fix_cap;             // entries per wave (<= kFixSlots); tables beyond go to `dirty`
-    unsigned int* fix_count; // [ceil(n/16)] entries written by each wave
+    unsigned int* n_fixed;   // count of codes recomputed in FP64 (nullable; needs the counts of the workgroups
+                             // behind fix_count)
+    unsigned int* n_open;    // set by the launch: codes that each of the open_blocks workgroups left open
+    int64_t open_blocks;
+    int parts = 1, part_stages = 0;  // the tables in `parts` shares of part_stages stages (hash_parts)
+    uint64_t* dirty;         // [parts, n] scratch: per row, bit l set when table l must be recomputed in full
+    uint4* fix_list;         // scratch: per part and 16 rows, fix_cap entries (table and row, mask of the codes that
+                             // the FP64 definition must decide, key sum of the others)
+    int fix_cap;             // entries per 16 rows (<= kFixSlots); tables beyond go to `dirty`
+    unsigned int* fix_count; // [parts, ceil(n/16)] entries written, and whether the 16 rows' masks in `dirty` are
     const Slot* dir;         // bin directories [L, dir_cap], or null: no lookup
     uint64_t dir_cap;
     const uint32_t* dir_filter;  // [L, dir_cap / 8] presence bits of the keys (dir_filter_bit)
@@ -107,6 +107,15 @@ __device__ __forceinline__ int64_t key_pos(const HashArgs& a, int64_t row, int l
 hipError_t launch_hash(const HashArgs& a, hipStream_t st);   // codes and keys, then the bin lookup
 hipError_t launch_hash_codes(const HashArgs& a, hipStream_t st);   // codes and keys (with their FP64 fixes)
 hipError_t launch_probe(const HashArgs& a, hipStream_t st);        // the bins of the keys (a.bins set)
+// The hash rows of all tables laid out for k_hash of precision prec (D = 25 or
+// 100): its size, and the kernel that fills it from the parameters
+size_t hash_image_bytes(int prec, int D, int L, int k);
+hipError_t launch_hash_image(int prec, int D, int L, int k, float w, const float* alpha, const float* beta,
+                             const uint16_t* a_hi, const uint16_t* a_lo, const float* c0, const uint64_t* key_mul,
+                             unsigned char* img, hipStream_t st);
+void hash_parts(HashArgs& a);   // sets parts and part_stages from n, D, L, k and prec
+size_t hash_count_words(const HashArgs& a);   // words of fix_count and the counts of the workgroups behind it
+float hash_bound_norm_c1(int prec, int D, double w);
 // bound coefficients for the MFMA projection of precision `prec` (host)
 void hash_bound_coeffs(int prec, int D, double w, const float* beta, int m, float* c0, float* c1,
                        float* c2);

@@ -265,16 +265,6 @@ __global__ __launch_bounds__(256) void k_b_bp_update(const BatchImage* __restric
                              parity ? b.out : b.scr, (local / tx) * T, (local % tx) * T);
 }
 
-// Results of an odd number of iterations are in scr: copy them to out.
-__global__ void k_b_copy_scr(const BatchImage* __restrict__ im, int n, int64_t total, int s) {
-    for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const BatchImage& b = im[batch_image_of<&BatchImage::hr_off>(im, n, idx)];
-        const int64_t r = idx - b.hr_off;
-        b.out[r] = b.scr[r];
-    }
-}
-
 // K<T, RM, S, ...> for a radius (at most kBpSmallR, or up to kBpMaxR) and a zoom factor
 template <int T, int RM, int S> constexpr auto kUpdate = k_bp_update<T, RM, S, false>;
 template <int T, int RM, int S> constexpr auto kTerms = k_bp_update<T, RM, S, true>;
@@ -332,14 +322,6 @@ hipError_t launch_b_bp_update(const BatchImage* im, int n, int64_t n_tiles, int 
         if (share > fa.sharedSizeBytes) lds = share - fa.sharedSizeBytes;
     }
     hipLaunchKernelGGL(k, dim3((unsigned)n_tiles), dim3(256), lds, st, im, n, R, sigma_s, inv_2sr2(sigma_r), e, parity);
-    return hipGetLastError();
-}
-
-hipError_t launch_b_copy_scr(const BatchImage* im, int n, int64_t hr_total, int scale, hipStream_t st) {
-    if (hr_total == 0) return hipSuccess;
-    int64_t g = (hr_total + 255) / 256;
-    if (g > 65536) g = 65536;
-    hipLaunchKernelGGL(k_b_copy_scr, dim3((unsigned)g), dim3(256), 0, st, im, n, hr_total, scale);
     return hipGetLastError();
 }
 

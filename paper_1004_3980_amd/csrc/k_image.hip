@@ -37,94 +37,96 @@ __global__ void k_degrade(const float* __restrict__ hr, int n_img, int H, int W,
     }
 }
 
-__global__ void k_degrade_residual(const float* __restrict__ hr, int H, int W, int scale, Taps t,
-                                   const float* __restrict__ lr_ref, float* __restrict__ e) {
-    const int h = (H + scale - 1) / scale, w = (W + scale - 1) / scale;
-    const int64_t total = (int64_t)h * w;
-    for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int i = (int)(idx / w), j = (int)(idx % w);
-        e[idx] = (float)((double)lr_ref[idx] - blur_at(hr, H, W, scale * i, scale * j, t));
-    }
-}
-
-// The same LR error by LR tiles of kDrI x kDrJ: the HR rows and columns under
-// a tile (clamped indices: replicate border) are staged in LDS, the
-// horizontal FP64 sums are formed once per (HR row, LR column) and shared by
-// the LR rows that use them, then the vertical sums; each value is the
-// blur_at sum to the bit (same products, same order).
-constexpr int kDrI = 8, kDrJ = 32;
-// The LR tile with origin (i0, j0) of an h x w LR error (h, w from H, W).
-__device__ __forceinline__ void degrade_tile(const float* __restrict__ hr, int H, int W, int scale, const Taps& t,
+// LR error of back-projection (blur of sigma 1: kDrR = 3 taps a side) by LR
+// tiles of kDrI x kDrJ, image sides S h x S w: the HR rows and columns under a
+// tile (clamped indices: replicate border) are staged in LDS, the horizontal
+// FP64 sums are formed once per (HR row, LR column) and shared by the LR rows
+// that use them, then the vertical sums; each value is the blur_at sum to the
+// bit (same products, same order). copy (nullable) receives the HR image, each
+// tile its own pixels. Bound: latency on small images, FP64 issue on large ones
+// (14 products and sums an HR row and LR column). An iteration's error before
+// (zoom factor and radius at run time) and now, the first of three with the
+// copy: 128^2 6.1 -> 4.6 us, 502x526 6.2 -> 4.8, 2048^2 16.6 -> 11.4, 844x1228
+// x4 11.5 -> 5.6; a copy of its own took 6.6 us at 2048^2.
+constexpr int kDrI = 8, kDrJ = 32, kDrR = 3;
+template <int S>
+__device__ __forceinline__ void degrade_tile(const float* __restrict__ hr, int h, int w, const Taps& t,
                                              const float* __restrict__ lr_ref, float* __restrict__ e, int i0, int j0,
-                                             unsigned char* smem) {
-    const int h = (H + scale - 1) / scale, w = (W + scale - 1) / scale;
-    const int R = t.R;
-    const int ny = scale * (kDrI - 1) + 2 * R + 1, nx = scale * (kDrJ - 1) + 2 * R + 1;
-    double* hrow = reinterpret_cast<double*>(smem);                       // [ny][kDrJ]
-    float* sh = reinterpret_cast<float*>(smem + sizeof(double) * ny * kDrJ);   // [ny][nx]
-    const int y0 = scale * i0 - R, x0 = scale * j0 - R;
-    for (int q = threadIdx.x; q < ny * nx; q += blockDim.x) {
-        const int r = q / nx, c = q % nx;
-        sh[q] = hr[(int64_t)clampi(y0 + r, 0, H - 1) * W + clampi(x0 + c, 0, W - 1)];
+                                             float* __restrict__ copy) {
+    constexpr int R = kDrR, NY = S * (kDrI - 1) + 2 * R + 1, NX = S * (kDrJ - 1) + 2 * R + 1, NT = 256;
+    __shared__ double hrow[NY * kDrJ];
+    __shared__ float sh[NY * NX];
+    const int H = S * h, W = S * w;
+    const int y0 = S * i0 - R, x0 = S * j0 - R;
+    const int ii = threadIdx.x / kDrJ, jj = threadIdx.x % kDrJ;
+    const int i = i0 + ii, j = j0 + jj;
+    const bool in = i < h && j < w;
+    const float ref = in ? lr_ref[(int64_t)i * w + j] : 0.0f;
+    {
+        constexpr int U = (NY * NX + NT - 1) / NT;
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = threadIdx.x + NT * u, r = q / NX, c = q - r * NX;
+            v[u] = hr[(int64_t)clampi(y0 + (r < NY ? r : 0), 0, H - 1) * W + clampi(x0 + c, 0, W - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = threadIdx.x + NT * u;
+            if (q < NY * NX) sh[q] = v[u];
+        }
+        if (copy) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int q = threadIdx.x + NT * u, r = q / NX, c = q - r * NX;
+                const int Y = y0 + r, X = x0 + c;
+                if (r >= R && r < R + S * kDrI && c >= R && c < R + S * kDrJ && r < NY && Y < H && X < W)
+                    copy[(int64_t)Y * W + X] = v[u];
+            }
+        }
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < ny * kDrJ; q += blockDim.x) {
-        const int r = q / kDrJ, jj = q % kDrJ;
-        const float* row = sh + r * nx + scale * jj;
+#pragma unroll
+    for (int u = 0; u < (NY * kDrJ + NT - 1) / NT; ++u) {
+        const int q = threadIdx.x + NT * u;
+        if (q >= NY * kDrJ) break;
+        const float* row = sh + (q / kDrJ) * NX + S * (q % kDrJ);
         double v = 0.0;
+#pragma unroll
         for (int b = 0; b <= 2 * R; ++b) v = v + t.g[b] * (double)row[b];
         hrow[q] = v;
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < kDrI * kDrJ; q += blockDim.x) {
-        const int ii = q / kDrJ, jj = q % kDrJ;
-        const int i = i0 + ii, j = j0 + jj;
-        if (i >= h || j >= w) continue;
-        double acc = 0.0;
-        for (int a = 0; a <= 2 * R; ++a) acc = acc + t.g[a] * hrow[(scale * ii + a) * kDrJ + jj];
-        e[(int64_t)i * w + j] = (float)((double)lr_ref[(int64_t)i * w + j] - acc);
-    }
+    if (!in) return;
+    double acc = 0.0;
+#pragma unroll
+    for (int a = 0; a <= 2 * R; ++a) acc = acc + t.g[a] * hrow[(S * ii + a) * kDrJ + jj];
+    e[(int64_t)i * w + j] = (float)((double)ref - acc);
+}
+static_assert(kDrI * kDrJ == 256, "a thread for each LR pixel of a tile");
+
+template <int S>
+__global__ __launch_bounds__(256) void k_degrade_residual(const float* __restrict__ hr, int h, int w, Taps t,
+                                                          const float* __restrict__ lr_ref, float* __restrict__ e,
+                                                          float* __restrict__ copy) {
+    degrade_tile<S>(hr, h, w, t, lr_ref, e, blockIdx.y * kDrI, blockIdx.x * kDrJ, copy);
 }
 
-__global__ __launch_bounds__(256) void k_degrade_residual_t(const float* __restrict__ hr, int H, int W, int scale,
-                                                            Taps t, const float* __restrict__ lr_ref,
-                                                            float* __restrict__ e) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    degrade_tile(hr, H, W, scale, t, lr_ref, e, blockIdx.y * kDrI, blockIdx.x * kDrJ, smem);
-}
-
-// Batched, by tiles: workgroup b takes tile b of the concatenated tile lists
-// of the images (the current estimate in out for parity 0, scr for parity 1;
-// image b's error at e + lr_off); the grid may be rounded up past the last tile.
-__global__ __launch_bounds__(256) void k_b_degrade_residual_t(const BatchImage* __restrict__ im, int n, int64_t tiles,
-                                                              int scale, Taps t, int parity, float* __restrict__ e) {
-    extern __shared__ __align__(16) unsigned char smem[];
+// Batched: workgroup b takes tile b of the concatenated tile lists of the
+// images (the current estimate in out for parity 0, scr for parity 1; copy:
+// it is in out and copied to scr); image b's error at e + lr_off.
+template <int S>
+__global__ __launch_bounds__(256) void k_b_degrade_residual(const BatchImage* __restrict__ im, int n, Taps t, int parity,
+                                                            int copy, float* __restrict__ e) {
     const int64_t tile = blockIdx.x;
-    if (tile >= tiles) return;
     const BatchImage& b = im[batch_image_of<&BatchImage::dtile_off>(im, n, tile)];
     const int local = (int)(tile - b.dtile_off);
     const int tx = (b.w + kDrJ - 1) / kDrJ;
-    const float* hr = parity ? b.scr : b.out;
-    degrade_tile(hr, scale * b.h, scale * b.w, scale, t, b.lr, e + b.lr_off, (local / tx) * kDrI, (local % tx) * kDrJ,
-                 smem);
+    degrade_tile<S>(parity ? b.scr : b.out, b.h, b.w, t, b.lr, e + b.lr_off, (local / tx) * kDrI, (local % tx) * kDrJ,
+                    copy ? b.scr : nullptr);
 }
 
 int64_t degrade_tiles(int h, int w) { return (int64_t)((h + kDrI - 1) / kDrI) * ((w + kDrJ - 1) / kDrJ); }
-
-// Batched: LR error of every image, the current estimate in out (parity 0)
-// or scr (parity 1); image b's error at e + lr_off.
-__global__ void k_b_degrade_residual(const BatchImage* __restrict__ im, int n, int64_t total, int scale, Taps t,
-                                     int parity, float* __restrict__ e) {
-    for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const BatchImage& b = im[batch_image_of<&BatchImage::lr_off>(im, n, idx)];
-        const int r = (int)(idx - b.lr_off);
-        const int i = r / b.w, j = r % b.w;
-        const float* hr = parity ? b.scr : b.out;
-        e[idx] = (float)((double)b.lr[r] - blur_at(hr, scale * b.h, scale * b.w, scale * i, scale * j, t));
-    }
-}
 
 // Four gradient maps per image, fp32 [n_img, 4, h, w]:
 //   dx = I(c+1) - I(c-1), dy likewise along rows,
@@ -404,19 +406,13 @@ hipError_t launch_degrade(const float* hr, int n_img, int H, int W, int scale, c
     return hipGetLastError();
 }
 
-hipError_t launch_degrade_residual(const float* hr, int H, int W, int scale, const Taps& t,
-                                   const float* lr_ref, float* e, hipStream_t st) {
-    const int h = (H + scale - 1) / scale, w = (W + scale - 1) / scale;
-    const size_t lds = sizeof(double) * (size_t)(scale * (kDrI - 1) + 2 * t.R + 1) * kDrJ +
-                       sizeof(float) * (size_t)(scale * (kDrI - 1) + 2 * t.R + 1) * (scale * (kDrJ - 1) + 2 * t.R + 1);
-    if (lds <= 48 * 1024 && h > 0 && w > 0) {
-        const dim3 grid((unsigned)((w + kDrJ - 1) / kDrJ), (unsigned)((h + kDrI - 1) / kDrI));
-        hipLaunchKernelGGL(k_degrade_residual_t, grid, dim3(256), lds, st, hr, H, W, scale, t, lr_ref, e);
-        return hipGetLastError();
-    }
-    const int64_t total = (int64_t)h * w;
-    hipLaunchKernelGGL(k_degrade_residual, dim3(grid_for(total, 256)), dim3(256), 0, st, hr, H, W,
-                       scale, t, lr_ref, e);
+hipError_t launch_degrade_residual(const float* hr, int h, int w, int scale, const Taps& t, const float* lr_ref,
+                                   float* e, float* copy, hipStream_t st) {
+    if (h < 1 || w < 1 || t.R != kDrR || scale < 1 || scale > kMaxScale) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((w + kDrJ - 1) / kDrJ), (unsigned)((h + kDrI - 1) / kDrI));
+    auto k = scale == 1 ? k_degrade_residual<1> : scale == 2 ? k_degrade_residual<2>
+             : scale == 3 ? k_degrade_residual<3> : k_degrade_residual<4>;
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, st, hr, h, w, t, lr_ref, e, copy);
     return hipGetLastError();
 }
 
@@ -451,18 +447,13 @@ hipError_t launch_b_query_features(const BatchImage* im, int n, int64_t seg_tota
     return hipGetLastError();
 }
 
-hipError_t launch_b_degrade_residual(const BatchImage* im, int n, int64_t lr_total, int64_t tiles, int scale,
-                                     const Taps& t, int parity, float* e, hipStream_t st) {
-    if (lr_total == 0) return hipSuccess;
-    const size_t lds = sizeof(double) * (size_t)(scale * (kDrI - 1) + 2 * t.R + 1) * kDrJ +
-                       sizeof(float) * (size_t)(scale * (kDrI - 1) + 2 * t.R + 1) * (scale * (kDrJ - 1) + 2 * t.R + 1);
-    if (lds <= 48 * 1024 && tiles > 0 && tiles <= 0x7FFFFFFF) {
-        hipLaunchKernelGGL(k_b_degrade_residual_t, dim3((unsigned)tiles), dim3(256), lds, st, im, n, tiles, scale, t,
-                           parity, e);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_b_degrade_residual, dim3(grid_for(lr_total, 256)), dim3(256), 0, st, im, n, lr_total, scale,
-                       t, parity, e);
+hipError_t launch_b_degrade_residual(const BatchImage* im, int n, int64_t tiles, int scale, const Taps& t, int parity,
+                                     bool copy, float* e, hipStream_t st) {
+    if (tiles == 0) return hipSuccess;
+    if (tiles > 0x7FFFFFFF || t.R != kDrR || scale < 1 || scale > kMaxScale) return hipErrorInvalidValue;
+    auto k = scale == 1 ? k_b_degrade_residual<1> : scale == 2 ? k_b_degrade_residual<2>
+             : scale == 3 ? k_b_degrade_residual<3> : k_b_degrade_residual<4>;
+    hipLaunchKernelGGL(k, dim3((unsigned)tiles), dim3(256), 0, st, im, n, t, parity, copy ? 1 : 0, e);
     return hipGetLastError();
 }
 

@@ -96,7 +96,7 @@ struct zh_ctx {
     // batched form: plan of the last batch, its captured graph, tuning
     struct BatchGroup {
         int n = 0;
-        int64_t q_total = 0, lr_total = 0, hr_total = 0, tiles = 0;
+        int64_t q_total = 0, hr_total = 0, tiles = 0;
         int64_t fsegs = 0;              // feature segments of all images
         int64_t sbtiles = 0;            // tiles of the fused synthesis and blend of all images
         int64_t dtiles = 0;             // LR-error tiles of all images
@@ -1369,34 +1369,44 @@ namespace {
 zh_status backproject_steps(zh_ctx* c, float* hr, const float* lr, int h, int w, int s, int iters, float sigma_s,
                             float sigma_r, bool record) {
     const int H = s * h, W = s * w;
+    const size_t HW = (size_t)H * W;
     TRY(ensure(c, c->e, sizeof(float) * (size_t)h * w));
-    TRY(ensure(c, c->tmp, sizeof(float) * (size_t)H * W));
     const Taps g = gauss_taps(1.0);
-    float* a = hr;
-    float* b = P<float>(c->tmp);
     if (record) {
-        TRY(ensure(c, c->guides, sizeof(float) * (size_t)H * W * (size_t)(iters > 0 ? iters : 1)));
+        TRY(ensure(c, c->guides, sizeof(float) * HW * (size_t)(iters > 0 ? iters : 1)));
         c->bp_rec = 1;
         c->bp_iters = iters;
         c->bp_sigma_s = sigma_s;
         c->bp_sigma_r = sigma_r;
+    } else {
+        TRY(ensure(c, c->tmp, sizeof(float) * HW));
     }
+    // The steps go through the guides and end in hr, or between hr and the
+    // temporary image: the first step's estimate is where the first update
+    // reads it once that step's LR error is formed.
+    const bool copy0 = record || (iters & 1);
     for (int t = 0; t < iters; ++t) {
-        if (record)
-            HIPCHK(c, hipMemcpyAsync(P<float>(c->guides) + (size_t)t * H * W, a, sizeof(float) * (size_t)H * W,
-                                     hipMemcpyDeviceToDevice, c->stream));
+        const float* in;
+        float* out;
+        if (record) {
+            in = P<float>(c->guides) + t * HW;
+            out = t + 1 < iters ? P<float>(c->guides) + (t + 1) * HW : hr;
+        } else {
+            in = (iters - t) & 1 ? P<float>(c->tmp) : hr;
+            out = (iters - t) & 1 ? hr : P<float>(c->tmp);
+        }
         {
             StageTimer t1(c, ZH_T_BP_ERROR);
-            HIPCHK(c, launch_degrade_residual(a, H, W, s, g, lr, P<float>(c->e), c->stream));
+            if (t == 0 && copy0)
+                HIPCHK(c, launch_degrade_residual(hr, h, w, s, g, lr, P<float>(c->e), const_cast<float*>(in), c->stream));
+            else
+                HIPCHK(c, launch_degrade_residual(in, h, w, s, g, lr, P<float>(c->e), nullptr, c->stream));
         }
         {
             StageTimer t2(c, ZH_T_BP_UPDATE);
-            HIPCHK(c, launch_bp_update(a, P<float>(c->e), H, W, h, w, s, sigma_s, sigma_r, b, c->stream));
+            HIPCHK(c, launch_bp_update(in, P<float>(c->e), H, W, h, w, s, sigma_s, sigma_r, out, c->stream));
         }
-        float* t2 = a; a = b; b = t2;
     }
-    if (a != hr)
-        HIPCHK(c, hipMemcpyAsync(hr, a, sizeof(float) * (size_t)H * W, hipMemcpyDeviceToDevice, c->stream));
     return ZH_OK;
 }
 
@@ -1535,7 +1545,7 @@ zh_status zh_backward(zh_ctx* c, const float* g_hr, float* g_resid, float* g_lam
         const bool range = std::isfinite(sr);
         for (int t = T - 1; t >= 0; --t) {
             const float* I = P<float>(c->guides) + (size_t)t * HW;
-            HIPCHK(c, launch_degrade_residual(I, H, W, s, g, P<float>(c->lr), P<float>(c->e), c->stream));
+            HIPCHK(c, launch_degrade_residual(I, h, w, s, g, P<float>(c->lr), P<float>(c->e), nullptr, c->stream));
             HIPCHK(c, launch_bp_terms(I, P<float>(c->e), H, W, h, w, s, ss, sr, FSa, c->stream));
             // v = Blur^T Dec^T Up^T N^T (S gamma)
             AxisAdjArgs a = gx;
@@ -1720,7 +1730,6 @@ zh_status batch_plan(zh_ctx* c, const zh_batch* b) {
         }
         g.n = (int)tabs[s].size();
         g.q_total = q;
-        g.lr_total = lr;
         g.hr_total = hr;
         g.tiles = tiles;
         g.fsegs = fsegs;
@@ -1842,12 +1851,14 @@ zh_status batch_chain(zh_ctx* c, const zh_batch* b, hipStream_t st) {
                                            P<int32_t>(c->m), P<float>(c->w), P<double>(c->qmu), d.resid,
                                            P<float>(c->sbpart), st));
             const Taps tg = gauss_taps(1.0);
+            // an odd number of steps starts in scr, so that the last ends in out
+            const int odd = b->bp_iters & 1;
             for (int t = 0; t < b->bp_iters; ++t) {
-                HIPCHK(c, launch_b_degrade_residual(tab, g.n, g.lr_total, g.dtiles, s, tg, t & 1, P<float>(B.e), st));
+                HIPCHK(c, launch_b_degrade_residual(tab, g.n, g.dtiles, s, tg, t == 0 ? 0 : (t + odd) & 1, t == 0 && odd,
+                                                    P<float>(B.e), st));
                 HIPCHK(c, launch_b_bp_update(tab, g.n, g.tiles, B.tile, B.grid_per_cu, s, b->sigma_s, b->sigma_r,
-                                             P<float>(B.e), t & 1, st));
+                                             P<float>(B.e), (t + odd) & 1, st));
             }
-            if (b->bp_iters & 1) HIPCHK(c, launch_b_copy_scr(tab, g.n, g.hr_total, s, st));
             return ZH_OK;
         }();
     }
@@ -2037,8 +2048,7 @@ zh_status zh_tune_batch(zh_ctx* c, const zh_batch* b, zh_batch_tuning* out) {
                     auto& g = B.g[s];
                     if (!g.n) continue;
                     const BatchImage* tab = P<BatchImage>(g.table);
-                    if (launch_b_degrade_residual(tab, g.n, g.lr_total, g.dtiles, s, gauss_taps(1.0), 0, P<float>(B.e),
-                                                  B.stream) !=
+                    if (launch_b_degrade_residual(tab, g.n, g.dtiles, s, gauss_taps(1.0), 0, false, P<float>(B.e), B.stream) !=
                             hipSuccess ||
                         launch_b_bp_update(tab, g.n, g.tiles, tiles[ti], mults[mi], s, b->sigma_s, b->sigma_r,
                                            P<float>(B.e), 0, B.stream) != hipSuccess)

@@ -31,9 +31,10 @@ struct Taps {                   // normalised 1-D Gaussian, offsets -R..R
 // ---- image kernels (k_image.hip) -------------------------------------------
 hipError_t launch_degrade(const float* hr, int n_img, int H, int W, int scale, const Taps& t,
                           float* lr, hipStream_t st);
-// e = lr_ref - degrade(hr), fp32 [h, w]
-hipError_t launch_degrade_residual(const float* hr, int H, int W, int scale, const Taps& t,
-                                   const float* lr_ref, float* e, hipStream_t st);
+// e = lr_ref - degrade(hr), fp32 [h, w], hr [scale h, scale w], taps of sigma 1;
+// copy (nullable) receives hr
+hipError_t launch_degrade_residual(const float* hr, int h, int w, int scale, const Taps& t, const float* lr_ref,
+                                   float* e, float* copy, hipStream_t st);
 hipError_t launch_gradient_maps(const float* lr, int n_img, int h, int w, float* maps,
                                 hipStream_t st);
 // features and means of every stride-1 patch of one LR image (row-major patch
@@ -325,9 +326,10 @@ __device__ __forceinline__ int batch_image_of(const BatchImage* im, int n, int64
 // one workgroup per feature segment (64 patches of a patch row) of every image
 hipError_t launch_b_query_features(const BatchImage* im, int n, int64_t seg_total, int mode, float* feat, double* mu,
                                    uint32_t* counters, hipStream_t st);
-// LR error of every image: `tiles` LR tiles in all (degrade_tiles per image)
-hipError_t launch_b_degrade_residual(const BatchImage* im, int n, int64_t lr_total, int64_t tiles, int scale,
-                                     const Taps& t, int parity, float* e, hipStream_t st);
+// LR error of every image: `tiles` LR tiles in all (degrade_tiles per image);
+// the estimate in out (parity 0) or scr (parity 1), or in out and copied to scr
+hipError_t launch_b_degrade_residual(const BatchImage* im, int n, int64_t tiles, int scale, const Taps& t, int parity,
+                                     bool copy, float* e, hipStream_t st);
 int64_t degrade_tiles(int h, int w);
 // fused synthesis and blend of every image: `tiles` tiles of `rows` patch
 // rows (offsets sbt_off), then the combine over the hr_total HR pixels
@@ -339,7 +341,6 @@ hipError_t launch_b_synth_blend(const BatchImage* im, int n, int64_t tiles, int6
 // scr, parity 1 the reverse
 hipError_t launch_b_bp_update(const BatchImage* im, int n, int64_t n_tiles, int tile, int per_cu, int scale,
                               float sigma_s, float sigma_r, const float* e, int parity, hipStream_t st);
-hipError_t launch_b_copy_scr(const BatchImage* im, int n, int64_t hr_total, int scale, hipStream_t st);
 int bp_tiles(int H, int W, int tile);
 
 // ---- adjoint (k_backward.hip) -------------------------------------------------

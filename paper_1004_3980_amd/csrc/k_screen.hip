@@ -504,83 +504,138 @@ hipError_t launch_screen_rows(const float* x, int64_t n, int D, int m, const dou
 // [-127, 127]. Output row (kRotStride floats): the h codes (64 bytes, zeros
 // past m), the l codes (64 bytes), then s_q, |y^|^2 (fp32 of the FP64 sum)
 // and rho_q >= |y^ - Phi q| (the rotation bound plus |y^ - y_q|, rounded up).
-template <int NS>
-__global__ __launch_bounds__(256) void k_rotate(const float* __restrict__ feat, int64_t n, int D,
+//
+// D = 100: the last four coordinates take one MFMA step for their three products
+// ((hi, hi, lo) of Phi against (hi, lo, hi) of the row), not one each. h and l
+// go through the sum 128 h + l, an integer below 2^14: its squares add up
+// exactly, and one fused multiply-add gives the coding error. Phi's rows are
+// dealt to the tiles so that a lane's codes are 16 consecutive bytes.
+// Bound: instruction issue. 1040400 rows of D = 100, the codes' errors and norms
+// element by element in FP64 and four bytes a store 200 us, now 140; 63973 rows
+// 19.0 and 15.7. With the next rows' reads ahead (154 registers against 109)
+// 159 and 19.5.
+template <int D>
+__global__ __launch_bounds__(256) void k_rotate(const float* __restrict__ feat, int64_t n,
                                                 const uint16_t* __restrict__ p_hi, const uint16_t* __restrict__ p_lo,
                                                 float c1, float* __restrict__ out) {
-    constexpr int DS = 32 * NS + 8;   // LDS row stride (halfwords): an odd number of 16-byte chunks
-    __shared__ __align__(16) uint16_t sA[2][64 * DS];
-    const int DP = 32 * NS;
-    for (int e = threadIdx.x; e < 2 * 64 * (DP / 8); e += 256) {
-        const int plane = e >= 64 * (DP / 8);
-        const int e2 = e - plane * 64 * (DP / 8);
-        const int r = e2 / (DP / 8), ch = e2 - r * (DP / 8);
-        *reinterpret_cast<u16x8*>(&sA[plane][r * DS + 8 * ch]) =
-            *reinterpret_cast<const u16x8*>((plane ? p_lo : p_hi) + (int64_t)r * DP + 8 * ch);
+    constexpr int DP = (D + 31) & ~31, TAIL = D % 32 == 4 ? 4 : 0;
+    constexpr int NS = DP / 32 - (TAIL ? 1 : 0);          // full steps
+    constexpr int HS = DP + 8, LS = 32 * NS + 8;          // LDS row strides (halfwords): odd numbers of 16-byte chunks
+    __shared__ __align__(16) uint16_t sHi[64 * HS];
+    __shared__ __align__(16) uint16_t sLo[64 * LS];
+    // row j = 16 kb + 4 tt + i of Phi is row 4 kb + i of tile tt, so that a lane
+    // ends with 16 coordinates in a row
+    auto place = [](int j) { return 16 * (j >> 2 & 3) + 4 * (j >> 4) + (j & 3); };
+    for (int e = threadIdx.x; e < 64 * (DP / 8); e += 256) {
+        const int r = e / (DP / 8), ch = e - r * (DP / 8);
+        u16x8 v = *reinterpret_cast<const u16x8*>(p_hi + (int64_t)r * DP + 8 * ch);
+        if (TAIL && ch >= 4 * NS) {
+            const u16x8 h = *reinterpret_cast<const u16x8*>(p_hi + (int64_t)r * DP + 32 * NS);
+            const u16x8 l = *reinterpret_cast<const u16x8*>(p_lo + (int64_t)r * DP + 32 * NS);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                v[u] = ch == 4 * NS ? h[u] : ch == 4 * NS + 1 ? l[u] : (uint16_t)0;
+                v[4 + u] = ch == 4 * NS ? h[u] : (uint16_t)0;
+            }
+        }
+        *reinterpret_cast<u16x8*>(&sHi[place(r) * HS + 8 * ch]) = v;
+    }
+    for (int e = threadIdx.x; e < 64 * 4 * NS; e += 256) {
+        const int r = e / (4 * NS), ch = e - r * (4 * NS);
+        *reinterpret_cast<u16x8*>(&sLo[place(r) * LS + 8 * ch]) = *reinterpret_cast<const u16x8*>(p_lo + (int64_t)r * DP + 8 * ch);
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ri = lane & 15, kb = lane >> 4;
     const u16x8 am = {0x7FFF, 0x7FFF, 0x7FFF, 0x7FFF, 0x7FFF, 0x7FFF, 0x7FFF, 0x7FFF};
     const int64_t nblk = (n + 15) / 16;
-    for (int64_t b = (int64_t)blockIdx.x * 4 + wave; b < nblk; b += (int64_t)gridDim.x * 4) {
+    // rows past the last take the last's values and are not written
+    float x[NS][8], xt[4];
+    auto load = [&](int64_t b) {
         const int64_t row = b * 16 + ri;
-        const bool rowok = row < n;
-        u16x8 bh[NS], bl[NS];
+        const float* fr = feat + (row < n ? row : n - 1) * D;
+        if (D % 4 == 0) {   // rows start on 16-byte boundaries
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            float v[8];
-            if ((D & 3) == 0) {
-                // rows start on 16-byte boundaries: two float4 loads per step
+            for (int s = 0; s < NS; ++s)
 #pragma unroll
-                for (int h4 = 0; h4 < 2; ++h4) {
-                    const int d = 32 * s + 8 * kb + 4 * h4;
-                    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (rowok && d < D) t = *reinterpret_cast<const float4*>(feat + row * D + d);
-                    v[4 * h4] = t.x;
-                    v[4 * h4 + 1] = t.y;
-                    v[4 * h4 + 2] = t.z;
-                    v[4 * h4 + 3] = t.w;
+                for (int j = 0; j < 2; ++j) {
+                    const float4 t = *reinterpret_cast<const float4*>(fr + 32 * s + 8 * kb + 4 * j);
+                    x[s][4 * j] = t.x, x[s][4 * j + 1] = t.y, x[s][4 * j + 2] = t.z, x[s][4 * j + 3] = t.w;
                 }
-            } else {
+            if (TAIL) {
+                const float4 t = *reinterpret_cast<const float4*>(fr + 32 * NS);
+                xt[0] = t.x, xt[1] = t.y, xt[2] = t.z, xt[3] = t.w;
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const int d = 32 * s + 8 * kb + e;
-                    v[e] = (rowok && d < D) ? feat[row * D + d] : 0.0f;
+                    const float t = fr[d < D ? d : 0];
+                    x[s][e] = d < D ? t : 0.0f;
                 }
-            }
-            // high part: v rounded to bf16 (nearest even, the packed
-            // conversion); low part: the exact remainder rounded likewise
+        }
+    };
+    const int64_t b0 = (int64_t)blockIdx.x * 4 + wave, step = (int64_t)gridDim.x * 4;
+    for (int64_t b = b0; b < nblk; b += step) {
+        const int64_t row = b * 16 + ri;
+        load(b);
+        u16x8 bh[NS], bl[NS], bt, bta;
+        // high part: v rounded to bf16 (nearest even, the packed conversion);
+        // low part: the exact remainder rounded likewise
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
             bf16x8 hv, lv;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                hv[e] = (__bf16)v[e];
-                lv[e] = (__bf16)(v[e] - (float)hv[e]);
+                hv[e] = (__bf16)x[s][e];
+                lv[e] = (__bf16)(x[s][e] - (float)hv[e]);
             }
             bh[s] = __builtin_bit_cast(u16x8, hv);
             bl[s] = __builtin_bit_cast(u16x8, lv);
         }
-        u16x8 bab[NS];   // |high part|, for the bound product
+        if (TAIL) {
+            bf16x8 hv, ha;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) bab[s] = bh[s] & am;
+            for (int e = 0; e < 4; ++e) {
+                const __bf16 h = (__bf16)xt[e], z = (__bf16)0.0f;
+                const __bf16 l = (__bf16)(xt[e] - (float)h);
+                hv[e] = kb < 2 ? h : z;
+                hv[4 + e] = kb == 0 ? l : z;
+                ha[e] = kb == 0 ? h : z;
+                ha[4 + e] = z;
+            }
+            bt = __builtin_bit_cast(u16x8, hv);
+            bta = __builtin_bit_cast(u16x8, ha) & am;
+        }
         float b2 = 0.0f;
-        float y[4][4];   // lane holds y_j, j = 16 tt + 4 kb + i, of feature row ri
+        float y[4][4];   // lane holds y_j, j = 16 kb + 4 tt + i, of feature row ri
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
-            // the three split products share one fp32 accumulator: the bound
-            // covers any order of the 3 DP additions
+            // the split products share one fp32 accumulator: the bound covers any
+            // order of the additions
             f32x4 cs = f32x4{0.f, 0.f, 0.f, 0.f}, cab = cs;
+            const uint16_t* Ah = sHi + (tt * 16 + ri) * HS + 8 * kb;
+            const uint16_t* Al = sLo + (tt * 16 + ri) * LS + 8 * kb;
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                const u16x8 ah = *reinterpret_cast<const u16x8*>(&sA[0][(tt * 16 + ri) * DS + 32 * s + 8 * kb]);
-                const u16x8 al = *reinterpret_cast<const u16x8*>(&sA[1][(tt * 16 + ri) * DS + 32 * s + 8 * kb]);
+                const u16x8 ah = *reinterpret_cast<const u16x8*>(Ah + 32 * s);
+                const u16x8 al = *reinterpret_cast<const u16x8*>(Al + 32 * s);
                 const bf16x8 ahb = __builtin_bit_cast(bf16x8, ah), alb = __builtin_bit_cast(bf16x8, al);
                 const bf16x8 vhb = __builtin_bit_cast(bf16x8, bh[s]), vlb = __builtin_bit_cast(bf16x8, bl[s]);
                 cs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahb, vhb, cs, 0, 0, 0);
                 cab = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ah & am),
-                                                             __builtin_bit_cast(bf16x8, bab[s]), cab, 0, 0, 0);
+                                                             __builtin_bit_cast(bf16x8, bh[s] & am), cab, 0, 0, 0);
                 cs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahb, vlb, cs, 0, 0, 0);
                 cs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alb, vhb, cs, 0, 0, 0);
+            }
+            if (TAIL) {
+                const u16x8 at = *reinterpret_cast<const u16x8*>(Ah + 32 * NS);
+                cs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, at),
+                                                             __builtin_bit_cast(bf16x8, bt), cs, 0, 0, 0);
+                cab = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, at & am),
+                                                              __builtin_bit_cast(bf16x8, bta), cab, 0, 0, 0);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -596,7 +651,6 @@ __global__ __launch_bounds__(256) void k_rotate(const float* __restrict__ feat, 
         b2 += __shfl_xor(b2, 32);
         // at most 64 terms of fp32 sums: relative error below 1e-5
         const float rho = sqrtf(b2 * (1.0f + 1e-5f)) * (1.0f + 1e-6f);
-        // int8 coding of the row; its error |y^ - y_q| is summed exactly (FP64)
         float amax = 0.0f;
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt)
@@ -605,8 +659,11 @@ __global__ __launch_bounds__(256) void k_rotate(const float* __restrict__ feat, 
         amax = fmaxf(amax, __shfl_xor(amax, 16));
         amax = fmaxf(amax, __shfl_xor(amax, 32));
         const float s_q = amax > 0.0f ? amax * (1.0f / 127.0f) : 1.0f;
-        const float inv = 1.0f / s_q;
-        double e2 = 0.0, n2 = 0.0;
+        const float inv = 1.0f / s_q, s128 = s_q * (1.0f / 128.0f);
+        // int8 coding of the row, c = 128 h + l: sum c^2 exact in FP64, the
+        // errors y - s_q c / 128 rounded once, their squares in fp32
+        double n2 = 0.0;
+        float e2 = 0.0f;
         uint32_t hw[4], lw[4];
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
@@ -616,30 +673,32 @@ __global__ __launch_bounds__(256) void k_rotate(const float* __restrict__ feat, 
                 const float t = y[tt][i] * inv;
                 const float h = fminf(127.0f, fmaxf(-127.0f, rintf(t)));
                 const float l = fminf(127.0f, fmaxf(-127.0f, rintf((t - h) * 128.0f)));
-                const double yh = (double)s_q * ((double)h + (double)l * (1.0 / 128.0));
-                const double er = (double)y[tt][i] - yh;
-                e2 += er * er;
-                n2 += yh * yh;
-                hw[tt] |= (uint32_t)(uint8_t)(int8_t)h << (8 * i);
-                lw[tt] |= (uint32_t)(uint8_t)(int8_t)l << (8 * i);
+                const float c = fmaf(h, 128.0f, l);
+                n2 = fma((double)c, (double)c, n2);
+                const float er = fmaf(-s128, c, y[tt][i]);
+                e2 = fmaf(er, er, e2);
+                // bytes h + 128 and l + 128; the flipped top bits make them int8
+                hw[tt] = __builtin_amdgcn_cvt_pk_u8_f32(h + 128.0f, i, hw[tt]);
+                lw[tt] = __builtin_amdgcn_cvt_pk_u8_f32(l + 128.0f, i, lw[tt]);
             }
+            hw[tt] ^= 0x80808080u;
+            lw[tt] ^= 0x80808080u;
         }
         e2 += __shfl_xor(e2, 16);
         e2 += __shfl_xor(e2, 32);
         n2 += __shfl_xor(n2, 16);
         n2 += __shfl_xor(n2, 32);
-        if (rowok) {
-            uint32_t* orow = reinterpret_cast<uint32_t*>(out + row * kRotStride);
-#pragma unroll
-            for (int tt = 0; tt < 4; ++tt) {
-                orow[4 * tt + kb] = hw[tt];
-                orow[16 + 4 * tt + kb] = lw[tt];
-            }
+        if (row < n) {
+            uint4* orow = reinterpret_cast<uint4*>(out + row * kRotStride);
+            orow[kb] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+            orow[4 + kb] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
             if (kb == 0) {
-                const float eps = (float)(sqrt(e2) * (1.0 + 1e-12) + 1e-300);
-                out[row * kRotStride + 32] = s_q;
-                out[row * kRotStride + 33] = (float)n2;
-                out[row * kRotStride + 34] = (rho + eps) * (1.0f + 1e-6f) + 1e-37f;
+                // 64 squares of errors rounded once, added in fp32: within 1e-5;
+                // squares that underflow leave less than 1e-18
+                const float eps = sqrtf(e2 * (1.0f + 1e-5f)) * (1.0f + 1e-6f) + 1e-18f;
+                reinterpret_cast<float4*>(orow)[8] =
+                    make_float4(s_q, (float)(n2 * ((double)s128 * (double)s128)),
+                                (rho + eps) * (1.0f + 1e-6f) + 1e-37f, 0.0f);
             }
         }
     }
@@ -648,15 +707,11 @@ __global__ __launch_bounds__(256) void k_rotate(const float* __restrict__ feat, 
 hipError_t launch_rotate(const float* feat, int64_t n, int D, const uint16_t* p_hi, const uint16_t* p_lo, float c1,
                          float* out, hipStream_t st) {
     if (n == 0) return hipSuccess;
-    if (D < 1 || D > 128) return hipErrorInvalidValue;
+    if (D != 25 && D != 100) return hipErrorInvalidValue;
     const int64_t nblk = (n + 15) / 16;
     const int blocks = (int)std::min<int64_t>((nblk + 3) / 4, 2048);
-    switch ((D + 31) / 32) {
-        case 1: hipLaunchKernelGGL(k_rotate<1>, dim3(blocks), dim3(256), 0, st, feat, n, D, p_hi, p_lo, c1, out); break;
-        case 2: hipLaunchKernelGGL(k_rotate<2>, dim3(blocks), dim3(256), 0, st, feat, n, D, p_hi, p_lo, c1, out); break;
-        case 3: hipLaunchKernelGGL(k_rotate<3>, dim3(blocks), dim3(256), 0, st, feat, n, D, p_hi, p_lo, c1, out); break;
-        default: hipLaunchKernelGGL(k_rotate<4>, dim3(blocks), dim3(256), 0, st, feat, n, D, p_hi, p_lo, c1, out); break;
-    }
+    auto k = D == 25 ? k_rotate<25> : k_rotate<100>;
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, feat, n, p_hi, p_lo, c1, out);
     return hipGetLastError();
 }
 

@@ -523,9 +523,7 @@ __device__ __forceinline__ void exact_pass(const SearchArgs& a, const float* sq,
     float p = 0.0f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) p = fmaf(z[e], z[e], p);
-    p += __shfl_xor(p, 1);
-    p += __shfl_xor(p, 2);
-    p += __shfl_xor(p, 4);
+    p = group8_sum_f32(p);
     bool exact_row = false;
     if (__ballot(cv && p == 0.0f) != 0) {
         bool eq = true;
@@ -651,10 +649,11 @@ __device__ __forceinline__ int cap_union(const SearchArgs& a, int q, uint64_t* h
         off = b.x;
         cnt = b.y;
     }
-    const int T = wave_sum_i32((int)cnt);
     // bins concatenated in table order: position i of bin l is entry
     // i - start_l of that bin
-    const int start = wave_incl_scan((int)cnt) - (int)cnt;
+    const int incl = wave_incl_scan((int)cnt);
+    const int T = __builtin_amdgcn_readlane(incl, 63);
+    const int start = incl - (int)cnt;
     if (lane < L) sbase[lane] = (int64_t)lane * a.N + off - start;
     for (int i = lane; i < hsz; i += 64) hset[i] = ~0ull;
     __syncthreads();
@@ -853,14 +852,15 @@ __global__ __launch_bounds__(64, 7) void k_search_cap(SearchArgs a) {
             __syncthreads();
             // U_K: the largest upper bound of the K exact distances
             const Bounds bd{a.dist_eps, (double)D * 1.2e-38};
+            // (the bound grows with the distance: that of the largest; equal rows
+            // bound by 0, and a NaN bounds nothing)
+            const uint32_t db = lane < K ? cdist[lane] : 0x80000000u;
+            const uint32_t dm = wave_max_u32(db <= 0x7F800000u ? db + 1u : 0u);
             double uk = 0.0;
-            if (lane < K) {
-                double dlo, dhi;
-                dist_interval(cdist[lane], bd, dlo, dhi);
-                uk = dhi;
+            if (dm != 0u) {
+                double dlo;
+                dist_interval(dm - 1u, bd, dlo, uk);
             }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) uk = fmax(uk, __shfl_xor(uk, o));
             bool sel[NSL];
             int S = 0;
 #pragma unroll

@@ -64,11 +64,6 @@ __device__ inline uint32_t wave_min_u32(uint32_t v) {
     }
     return v;
 }
-__device__ inline int wave_sum_i32(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
 __device__ inline double wave_sum_f64(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -89,14 +84,44 @@ __device__ inline float wave_sum_f32(float v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
 }
-// inclusive prefix sum over the 64 lanes
-__device__ inline int wave_incl_scan(int v) {
-    const int lane = __lane_id();
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int t = __shfl_up(v, o);
-        if (lane >= o) v += t;
-    }
+// v of the lane that the DPP control names, 0 where there is none or the row
+// (of 16 lanes) is not in the mask. Moves between lanes in the vector unit: no
+// trip through LDS as a shuffle takes.
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int dpp_or0(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+}
+// inclusive prefix sum over the 64 lanes: within rows of 16 (row_shr 1, 2, 4,
+// 8), then each row's last lane to the next row (row_bcast 15), then lane 31
+// to the upper half (row_bcast 31); every lane must be active
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += dpp_or0<0x111>(v);
+    v += dpp_or0<0x112>(v);
+    v += dpp_or0<0x114>(v);
+    v += dpp_or0<0x118>(v);
+    v += dpp_or0<0x142, 0xA>(v);
+    v += dpp_or0<0x143, 0xC>(v);
+    return v;
+}
+// sum over the 64 lanes, in every lane (a scalar); every lane must be active
+__device__ __forceinline__ int wave_sum_i32(int v) { return __builtin_amdgcn_readlane(wave_incl_scan(v), 63); }
+// largest value of the 64 lanes, as wave_sum_i32
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    auto mx = [](uint32_t a, int b) { return a > (uint32_t)b ? a : (uint32_t)b; };
+    v = mx(v, dpp_or0<0x111>((int)v));
+    v = mx(v, dpp_or0<0x112>((int)v));
+    v = mx(v, dpp_or0<0x114>((int)v));
+    v = mx(v, dpp_or0<0x118>((int)v));
+    v = mx(v, dpp_or0<0x142, 0xA>((int)v));
+    v = mx(v, dpp_or0<0x143, 0xC>((int)v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// sum over the eight lanes of an aligned group, in each of them (lanes 1 apart,
+// then 2, then the group's other half: the order of an xor butterfly)
+__device__ __forceinline__ float group8_sum_f32(float v) {
+    v += __int_as_float(dpp_or0<0xB1>(__float_as_int(v)));    // quad_perm 1 0 3 2
+    v += __int_as_float(dpp_or0<0x4E>(__float_as_int(v)));    // quad_perm 2 3 0 1
+    v += __int_as_float(dpp_or0<0x141>(__float_as_int(v)));   // row_half_mirror
     return v;
 }
 __device__ inline uint64_t lanemask_lt() {

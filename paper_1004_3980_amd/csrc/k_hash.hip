@@ -763,9 +763,11 @@ __global__ __launch_bounds__(64) void k_hash_fix(HashArgs a) {
     }
 }
 
-// Bin (offset, count) of every key, keys and bins table by table: blocks of
-// one table run together, so the lookups of the whole chip go to one
-// table's directory at a time (it stays in the last-level cache). A thread
+// Bin (offset, count) of every key, keys and bins table by table: each XCD takes
+// an eighth of the tables' blocks in order, so that a table's filter and
+// directory come into one L2 (with the blocks dealt out over the XCDs 63973
+// rows at L = 16 21.8 us, now 18.2; 3600 rows at L = 8 10.4 and 6.7; 1040400
+// rows at L = 24 the same, bound by 42M requests to the L2s in 380 us). A thread
 // takes kProbeRows rows of a block's kProbeRows * 256 and keeps their
 // lookups in flight together: keys, then filter words, then the first
 // directory slot of each key the filter lets through; a key that meets
@@ -778,7 +780,7 @@ __global__ __launch_bounds__(256) void k_probe(const uint64_t* __restrict__ keys
     const uint64_t mask = cap - 1;
     const int64_t span = 256 * kProbeRows;
     const int64_t bpt = (n + span - 1) / span;   // blocks per table
-    for (int64_t b = blockIdx.x; b < bpt * L; b += gridDim.x) {
+    for (int64_t b = xcd_block(); b < bpt * L; b += gridDim.x) {
         const int l = (int)(b / bpt);
         const int64_t row0 = (b - l * bpt) * span + threadIdx.x;
         const Slot* dl = dir + (uint64_t)l * cap;
@@ -909,6 +911,7 @@ hipError_t launch_probe(const HashArgs& a, hipStream_t st) {
     const int64_t total = a.n * a.L;
     int64_t g = (total + 256 * kProbeRows - 1) / (256 * kProbeRows);
     if (g > 65536) g = 65536;
+    g = round_grid8((int)g);
     hipLaunchKernelGGL(k_probe, dim3((unsigned)g), dim3(256), 0, st, a.keys, a.n, a.L, a.dir, a.dir_cap,
                        a.dir_filter, a.bins);
     return hipGetLastError();

@@ -899,34 +899,41 @@ __global__ __launch_bounds__(256) void k_cand_t(int Q, int L, int64_t N, int t, 
 // sorted in lanes 0 .. K-1, when it beats the K-th; the four waves' lists are
 // merged at the end. IDs are distinct across windows.
 //
-// Bound: the LDS inserts of the bins' entries, then the rows of the listed
-// IDs. The form before searched every other bin for each entry (L - 1 binary
-// searches of dependent loads), and the union without a stop was sorted in
-// LDS by one wave: 14,732 patches, L = 16, 100k pairs, t = 2:
-// 14.8 -> 0.56 ms; 3,600 patches, L = 8, 20k pairs at D = 25, t = 1 (unions of
-// up to 1,600 IDs): 2.37 -> 0.06 ms.
+// Bound: latency: the dependent reads and LDS passes of each window in turn (a
+// window of 800 entries of 16 bins about 7 us, a third of it the listed rows),
+// with as many workgroups on a compute unit as LDS allows (five; a row's reads
+// 13 or 9 instead of 5 at a time take the registers of one or two of them: 489
+// and 403 against 348 us below). The form before searched every other bin for
+// each entry (L - 1 binary searches of dependent loads), and the union without
+// a stop was sorted in LDS by one wave: 14,732 patches, L = 16, 100k pairs,
+// t = 2: 14.8 -> 0.55 ms, with the long patches first and in shares 0.37; 3,600
+// patches, L = 8, 20k pairs at D = 25, t = 1 (unions of up to 1,600 IDs): 2.37
+// -> 0.06 ms.
 constexpr int kWinMax = 2048;               // entries of a window
 constexpr int kWinSlots = 2 * kWinMax;      // largest hash table: load at most 1/2
 
-// (d, id) of the lanes with `act` into the K smallest held sorted by lanes 0 .. K-1
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+// (d, id) of the lanes with `act` into the K smallest held sorted by lanes
+// 0 .. K-1 (K <= 16: one row of lanes, shifted within the vector unit)
 __device__ __forceinline__ void topk_insert(bool act, double d, int id, int K, double& bd, int& bi) {
     const int lane = __lane_id();
     for (;;) {
-        const uint64_t kb = (uint64_t)__double_as_longlong(bd);
-        const double kd = __longlong_as_double(
-            (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(kb >> 32), K - 1) << 32) |
-                      (uint32_t)__builtin_amdgcn_readlane((int)kb, K - 1)));
+        const double kd = readlane_f64(bd, K - 1);
         const int ki = __builtin_amdgcn_readlane(bi, K - 1);
         const uint64_t todo = __ballot(act && (d < kd || (d == kd && id < ki)));
         if (!todo) return;
         const int src = __builtin_ctzll(todo);
-        const double nd = __shfl(d, src);
+        const double nd = readlane_f64(d, src);
         const int ni = __builtin_amdgcn_readlane(id, src);
         const int at = __popcll(__ballot(lane < K && (bd < nd || (bd == nd && bi < ni))));
-        const double ud = __shfl_up(bd, 1);
-        const int ui = __shfl_up(bi, 1);
+        // row_shr 1
+        const int uh = dpp_or0<0x111>(__double2hiint(bd)), ul = dpp_or0<0x111>(__double2loint(bd));
+        const int ui = dpp_or0<0x111>(bi);
         if (lane > at) {
-            bd = ud;
+            bd = __hiloint2double(uh, ul);
             bi = ui;
         } else if (lane == at) {
             bd = nd;
@@ -935,151 +942,34 @@ __device__ __forceinline__ void topk_insert(bool act, double d, int id, int K, d
         if (lane == src) act = false;
     }
 }
+// The K smallest of the first n lanes' (d, id), sorted, into lanes 0 .. K-1 (the
+// rest +inf): every lane counts the lanes before it, and those counted to
+// 0 .. K-1 hand theirs over through LDS (K places of the wave's own).
+__device__ __forceinline__ void topk_first(int n, double d, int id, int K, double* pd, int* pi, double& bd, int& bi) {
+    const int lane = __lane_id();
+    int rank = 0;
+    for (int j = 0; j < n; ++j) {
+        const double nd = readlane_f64(d, j);
+        const int ni = __builtin_amdgcn_readlane(id, j);
+        // (empty places may be equal: by lane, so that every rank has a lane)
+        rank += nd < d || (nd == d && (ni < id || (ni == id && j < lane))) ? 1 : 0;
+    }
+    if (lane < n && rank < K) {
+        pd[rank] = d;
+        pi[rank] = id;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (lane < K && lane < n) {
+        bd = pd[lane];
+        bi = pi[lane];
+    }
+}
 
-template <int DT>
-__global__ __launch_bounds__(256) void k_bins_rank(int Q, int L, int64_t N, int t, int Drt, int K,
-                                                   const uint2* __restrict__ bins, const uint32_t* __restrict__ tids,
-                                                   const float* __restrict__ qfeat, const float* __restrict__ xf,
-                                                   int32_t* __restrict__ counts, int32_t* __restrict__ out_ids,
-                                                   float* __restrict__ out_d, int32_t* __restrict__ out_m,
-                                                   unsigned int* __restrict__ counters) {
-    __shared__ uint32_t s_key[kWinSlots];
-    __shared__ uint32_t s_cnt[kWinSlots / 4];
-    __shared__ uint32_t s_list[kWinMax];
-    __shared__ double s_q[kL1MaxD];
-    __shared__ int64_t s_ofs[64];
-    __shared__ int s_start[64];
-    __shared__ int s_nk;
-    __shared__ double s_td[4 * kMaxK];
-    __shared__ int s_ti[4 * kMaxK];
-    const int D = DT ? DT : Drt;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    // not in runs per XCD: the patches of a flat region, the longest ones, are
-    // neighbours (0.91 against 0.56 ms on the 14,732 patches above)
-    const int q = blockIdx.x;
-    for (int i = tid; i < D; i += 256) s_q[i] = (double)qfeat[(int64_t)q * D + i];
-    // every wave holds the patch's bins in its lanes: the position of the next
-    // entry and the entries left
-    const uint2 b = lane < L ? bins[(int64_t)lane * Q + q] : make_uint2(0u, 0u);
-    const uint32_t* src = tids + (int64_t)lane * N + b.x;
-    int64_t pos = (int64_t)lane * N + b.x;
-    uint32_t left = b.y;
-    if (counters && tid < 64) {
-        // patches over the limits of the LDS forms of the union search
-        const int total = wave_sum_i32((int)min(left, 8193u));
-        if (lane == 0 && total > 2048) {
-            atomicAdd(&counters[C_OVERFLOW], 1u);
-            if (total > 8192) atomicAdd(&counters[C_STREAM], 1u);
-        }
-    }
-    double bd = INFINITY;
-    int bi = 0x7FFFFFFF;
-    int kept = 0;
-    for (bool more = true; more;) {
-        // ---- the window: `take` entries of every bin
-        uint32_t take = left;
-        more = wave_sum_i32((int)min(left, (uint32_t)kWinMax + 1u)) > kWinMax;
-        if (more) {
-            const uint32_t quota = (uint32_t)kWinMax / (uint32_t)__popcll(__ballot(left > 0));
-            const uint32_t end = wave_min_u32(left > quota ? src[quota] : 0xFFFFFFFFu);
-            uint32_t lo = 0, hi = min(left, quota);
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (src[mid] < end) lo = mid + 1;
-                else hi = mid;
-            }
-            take = lo;
-        }
-        const int incl = wave_incl_scan((int)take);
-        const int n = __shfl(incl, 63);
-        int lg = 6;
-        while ((1 << lg) < 2 * n) ++lg;
-        __syncthreads();   // the last window's list and table are no longer read
-        if (wv == 0) {
-            s_start[lane] = incl - (int)take;
-            s_ofs[lane] = pos - (incl - (int)take);
-        }
-        for (int i = tid; i < (1 << lg); i += 256) s_key[i] = 0xFFFFFFFFu;
-        if (t > 1)
-            for (int i = tid; i < (1 << lg) / 4; i += 256) s_cnt[i] = 0u;
-        if (tid == 0) s_nk = 0;
-        __syncthreads();
-        // ---- its entries into the table
-        const uint32_t mask = (1u << lg) - 1u;
-        for (int e = tid; e < n; e += 256) {
-            int lo = 0, hi = L;   // the last bin that starts at or before e
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (s_start[mid] <= e) lo = mid;
-                else hi = mid;
-            }
-            const uint32_t id = tids[s_ofs[lo] + e];
-            uint32_t slot = (id * 0x9E3779B1u) >> (32 - lg);
-            uint32_t old;
-            for (;;) {
-                old = atomicCAS(&s_key[slot], 0xFFFFFFFFu, id);
-                if (old == 0xFFFFFFFFu || old == id) break;
-                slot = (slot + 1u) & mask;
-            }
-            bool list = old == 0xFFFFFFFFu;
-            if (t > 1) {
-                const int sh = 8 * (slot & 3u);
-                list = (int)((atomicAdd(&s_cnt[slot >> 2], 1u << sh) >> sh) & 0xFFu) == t - 1;
-            }
-            if (list) s_list[atomicAdd(&s_nk, 1)] = id;
-        }
-        __syncthreads();
-        // ---- distances of the listed IDs
-        const int nk = s_nk;
-        kept += nk;
-        for (int c0 = 64 * wv; c0 < nk; c0 += 256) {
-            const bool act = c0 + lane < nk;
-            const int id = act ? (int)s_list[c0 + lane] : 0;
-            double d = 0.0;
-            if (act) {
-                const float* row = xf + (int64_t)id * D;
-                if ((D & 3) == 0) {
-                    const float4* r4 = reinterpret_cast<const float4*>(row);
-#pragma unroll 5
-                    for (int i = 0; i < D; i += 4) {
-                        const float4 v = r4[i >> 2];
-                        const double t0 = s_q[i] - (double)v.x;
-                        d = d + t0 * t0;
-                        const double t1 = s_q[i + 1] - (double)v.y;
-                        d = d + t1 * t1;
-                        const double t2 = s_q[i + 2] - (double)v.z;
-                        d = d + t2 * t2;
-                        const double t3 = s_q[i + 3] - (double)v.w;
-                        d = d + t3 * t3;
-                    }
-                } else {
-#pragma unroll 5
-                    for (int i = 0; i < D; ++i) {
-                        const double t0 = s_q[i] - (double)row[i];
-                        d = d + t0 * t0;
-                    }
-                }
-                if (!(d == d)) d = INFINITY;   // not a number: last, by ID
-            }
-            topk_insert(act, d, id, K, bd, bi);
-        }
-        pos += take;
-        src += take;
-        left -= take;
-    }
-    // ---- the K nearest of the waves' lists
-    if (lane < K) {
-        s_td[wv * K + lane] = bd;
-        s_ti[wv * K + lane] = bi;
-    }
-    __syncthreads();
-    if (wv > 0) return;
-    const bool act = lane < 4 * K;
-    const double d = act ? s_td[lane] : INFINITY;
-    const int id = act ? s_ti[lane] : 0x7FFFFFFF;
-    bd = INFINITY;
-    bi = 0x7FFFFFFF;
-    topk_insert(act, d, id, K, bd, bi);
+// a patch's result from its sorted list in lanes 0 .. K-1 of a wave
+__device__ __forceinline__ void write_ranked(int q, int K, int kept, double bd, int bi, int32_t* __restrict__ counts,
+                                             int32_t* __restrict__ out_ids, float* __restrict__ out_d,
+                                             int32_t* __restrict__ out_m) {
+    const int lane = __lane_id();
     const int m = kept < K ? kept : K;
     if (lane < K) {
         out_ids[(int64_t)q * K + lane] = lane < m ? bi : -1;
@@ -1091,20 +981,303 @@ __global__ __launch_bounds__(256) void k_bins_rank(int Q, int L, int64_t N, int 
     }
 }
 
+// Long patches, those with more entries than a window, are listed first, so that
+// none begins when all others end, and those of more than kLongShare entries
+// in shares by ranges of IDs (at most kLongParts), which a last launch joins.
+// The list's workgroups come before those of the other patches.
+constexpr int kLongMax = 8192, kLongParts = 16, kLongShare = 4096, kLongBlocks = 1024;
+// Patches from which the lists' two more launches (20 us for 14,732 patches) pay:
+// there the ranking went from 545 to 348 us; 3,600 patches take 56 us in all, and
+// their longest begins early enough.
+constexpr int kLongMin = 8192;
+struct LongLists {
+    unsigned int* n;     // entries (patches that did not fit are not listed and take their turn); 0 before the first launch
+    int2* item;          // [kLongMax] patch, and share + 32 shares
+    double* d;           // [kLongMax, K] nearest of a share
+    int32_t* id;
+    int32_t* kept;       // [kLongMax] IDs of a share
+    uint8_t* listed;     // [Q]
+};
+
+__global__ __launch_bounds__(256) void k_bins_long(int Q, int L, const uint2* __restrict__ bins, LongLists ll) {
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q >= Q) return;
+    uint32_t total = 0;
+#pragma unroll 8
+    for (int l = 0; l < L; ++l) total += min(bins[(int64_t)l * Q + q].y, 1u << 25);
+    bool listed = false;
+    if (total > (uint32_t)kWinMax) {
+        const int shares = (int)min((uint32_t)kLongParts, (total + kLongShare - 1) / kLongShare);
+        const unsigned at = atomicAdd(ll.n, (unsigned)shares);
+        listed = at + shares <= (unsigned)kLongMax;
+        for (int p = 0; p < shares && at + p < (unsigned)kLongMax; ++p)
+            ll.item[at + p] = make_int2(listed ? q : -1, p + 32 * shares);
+    }
+    ll.listed[q] = listed ? 1 : 0;
+}
+
+// Entries below `end` among the first n of src, ascending: seven probes a step.
+__device__ __forceinline__ uint32_t count_below(const uint32_t* __restrict__ src, uint32_t n, uint32_t end) {
+    uint32_t lo = 0, hi = n;
+    while (lo < hi) {
+        const uint32_t step = (hi - lo + 7u) >> 3;
+        uint32_t v[7], c = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < 7; ++j) {
+            const uint32_t p = lo + (j + 1u) * step - 1u;
+            v[j] = src[p < hi ? p : lo];
+            v[j] = p < hi ? v[j] : 0xFFFFFFFFu;
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < 7; ++j) c += v[j] < end ? 1u : 0u;
+        hi = c < 7u ? min(hi, lo + (c + 1u) * step - 1u) : hi;
+        lo += c * step;
+    }
+    return lo;
+}
+
+template <int D, bool LISTS>
+__global__ __launch_bounds__(256, 5) void k_bins_rank(int Q, int L, int64_t N, int t, int K,
+                                                   const uint2* __restrict__ bins, const uint32_t* __restrict__ tids,
+                                                   const float* __restrict__ qfeat, const float* __restrict__ xf,
+                                                   int32_t* __restrict__ counts, int32_t* __restrict__ out_ids,
+                                                   float* __restrict__ out_d, int32_t* __restrict__ out_m,
+                                                   unsigned int* __restrict__ counters, LongLists ll) {
+    __shared__ uint32_t s_key[kWinSlots];
+    __shared__ uint32_t s_cnt[kWinSlots / 4];
+    __shared__ uint32_t s_list[kWinMax];
+    __shared__ double s_q[D];
+    __shared__ int64_t s_ofs[64];
+    __shared__ int s_start[64];
+    __shared__ int s_nk, s_pos;
+    __shared__ double s_td[4 * kMaxK];
+    __shared__ int s_ti[4 * kMaxK];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const bool from_list = LISTS && blockIdx.x < kLongBlocks;
+    const int items = from_list ? (int)min(*ll.n, (unsigned)kLongMax) : 1;
+    for (int item = from_list ? blockIdx.x : 0; item < items; item += kLongBlocks) {
+        // not in runs per XCD: the patches of a flat region, the longest ones, are
+        // neighbours (0.91 against 0.56 ms on the 14,732 patches above)
+        const int2 it = from_list ? ll.item[item] : make_int2(0, 32);
+        const int q = from_list ? it.x : (int)blockIdx.x - (LISTS ? kLongBlocks : 0);
+        const int part = it.y & 31, shares = it.y >> 5;
+        if (LISTS && (q < 0 || (!from_list && ll.listed[q]))) continue;
+        if (LISTS) __syncthreads();   // the last item's arrays are no longer read
+        for (int i = tid; i < D; i += 256) s_q[i] = (double)qfeat[(int64_t)q * D + i];
+        // every wave holds the patch's bins in its lanes: the position of the next
+        // entry and the entries left
+        const uint2 b = lane < L ? bins[(int64_t)lane * Q + q] : make_uint2(0u, 0u);
+        const uint32_t* src = tids + (int64_t)lane * N + b.x;
+        int64_t pos = (int64_t)lane * N + b.x;
+        uint32_t left = b.y;
+        if (counters && tid < 64 && part == 0) {
+            // patches over the limits of the LDS forms of the union search
+            const int total = wave_sum_i32((int)min(left, 8193u));
+            if (lane == 0 && total > 2048) {
+                atomicAdd(&counters[C_OVERFLOW], 1u);
+                if (total > 8192) atomicAdd(&counters[C_STREAM], 1u);
+            }
+        }
+        if (LISTS && shares > 1) {
+            // the ends of the shares are quantiles of the largest bin
+            const uint32_t big = wave_max_u32(left);
+            const int bl = __builtin_ctzll(__ballot(left == big));
+            const uint32_t* bsrc = tids + (int64_t)bl * N + (uint32_t)__builtin_amdgcn_readlane((int)b.x, bl);
+            const uint32_t id0 = part == 0 ? 0u : bsrc[(uint64_t)big * part / shares];
+            const uint32_t id1 = part + 1 < shares ? bsrc[(uint64_t)big * (part + 1) / shares] : 0xFFFFFFFFu;
+            const uint32_t from = count_below(src, left, id0);
+            left = count_below(src, left, id1) - from;
+            src += from;
+            pos += from;
+        }
+        double bd = INFINITY;
+        int bi = 0x7FFFFFFF;
+        int kept = 0;
+        bool fresh = true;   // the wave's list is empty
+        for (bool more = true; more;) {
+            // ---- the window: `take` entries of every bin
+            uint32_t take = left;
+            more = wave_sum_i32((int)min(left, (uint32_t)kWinMax + 1u)) > kWinMax;
+            if (more) {
+                const uint32_t quota = (uint32_t)kWinMax / (uint32_t)__popcll(__ballot(left > 0));
+                const uint32_t end = wave_min_u32(left > quota ? src[quota] : 0xFFFFFFFFu);
+                take = count_below(src, min(left, quota), end);
+            }
+            const int incl = wave_incl_scan((int)take);
+            const int n = __shfl(incl, 63);
+            int lg = 6;
+            while ((1 << lg) < 2 * n) ++lg;
+            __syncthreads();   // the last window's list and table are no longer read
+            if (wv == 0) {
+                s_start[lane] = incl - (int)take;
+                s_ofs[lane] = pos - (incl - (int)take);
+            }
+            for (int i = tid; i < (1 << lg); i += 256) s_key[i] = 0xFFFFFFFFu;
+            if (t > 1)
+                for (int i = tid; i < (1 << lg) / 4; i += 256) s_cnt[i] = 0u;
+            if (tid == 0) s_nk = 0;
+            __syncthreads();
+            // ---- its entries into the table
+            const uint32_t mask = (1u << lg) - 1u;
+            for (int e = tid; e < n; e += 256) {
+                int lo = 0, hi = L;   // the last bin that starts at or before e
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (s_start[mid] <= e) lo = mid;
+                    else hi = mid;
+                }
+                const uint32_t id = tids[s_ofs[lo] + e];
+                uint32_t slot = (id * 0x9E3779B1u) >> (32 - lg);
+                uint32_t old;
+                for (;;) {
+                    old = atomicCAS(&s_key[slot], 0xFFFFFFFFu, id);
+                    if (old == 0xFFFFFFFFu || old == id) break;
+                    slot = (slot + 1u) & mask;
+                }
+                bool list = old == 0xFFFFFFFFu;
+                if (t > 1) {
+                    const int sh = 8 * (slot & 3u);
+                    list = (int)((atomicAdd(&s_cnt[slot >> 2], 1u << sh) >> sh) & 0xFFu) == t - 1;
+                }
+                if (list) s_list[atomicAdd(&s_nk, 1)] = id;
+            }
+            __syncthreads();
+            // ---- distances of the listed IDs
+            const int nk = s_nk;
+            kept += nk;
+            for (int c0 = 64 * wv; c0 < nk; c0 += 256) {
+                const bool act = c0 + lane < nk;
+                const int id = act ? (int)s_list[c0 + lane] : 0;
+                double d = 0.0;
+                if (act) {
+                    const float* row = xf + (int64_t)id * D;
+                    auto term = [&](int i, float x) {
+                        const double t0 = s_q[i] - (double)x;
+                        d = d + t0 * t0;
+                    };
+                    if (D == 100) {
+                        // a fifth of a row on its way at a time
+                        const float4* r4 = reinterpret_cast<const float4*>(row);
+#pragma unroll
+                        for (int h = 0; h < 25; h += 5) {
+                            float4 v[5];
+#pragma unroll
+                            for (int u = 0; u < 5; ++u)
+                                if (h + u < 25) v[u] = r4[h + u];
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int u = 0; u < 5; ++u)
+                                if (h + u < 25) {
+                                    term(4 * (h + u), v[u].x);
+                                    term(4 * (h + u) + 1, v[u].y);
+                                    term(4 * (h + u) + 2, v[u].z);
+                                    term(4 * (h + u) + 3, v[u].w);
+                                }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    } else {
+                        float v[D];
+#pragma unroll
+                        for (int i = 0; i < D; ++i) v[i] = row[i];
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int i = 0; i < D; ++i) term(i, v[i]);
+                    }
+                    if (!(d == d)) d = INFINITY;   // not a number: last, by ID
+                }
+                if (fresh)
+                    topk_first(min(64, nk - c0), d, id, K, s_td + wv * K, s_ti + wv * K, bd, bi);
+                else
+                    topk_insert(act, d, id, K, bd, bi);
+                fresh = false;
+            }
+            pos += take;
+            src += take;
+            left -= take;
+        }
+        // ---- the K nearest of the waves' lists
+        if (lane < K) {
+            s_td[wv * K + lane] = bd;
+            s_ti[wv * K + lane] = bi;
+        }
+        __syncthreads();
+        if (wv > 0) continue;
+        const bool act = lane < 4 * K;
+        const double d = act ? s_td[lane] : INFINITY;
+        const int id = act ? s_ti[lane] : 0x7FFFFFFF;
+        bd = INFINITY;
+        bi = 0x7FFFFFFF;
+        topk_first(4 * K, d, id, K, s_td, s_ti, bd, bi);
+        if (LISTS && shares > 1) {
+            if (lane < K) {
+                ll.d[(int64_t)item * K + lane] = bd;
+                ll.id[(int64_t)item * K + lane] = bi;
+            }
+            if (lane == 0) ll.kept[item] = kept;
+        } else {
+            write_ranked(q, K, kept, bd, bi, counts, out_ids, out_d, out_m);
+        }
+    }
+}
+
+// The K nearest of a patch from its shares, a wave a patch (at its first share).
+__global__ __launch_bounds__(64) void k_bins_join(int K, LongLists ll, int32_t* __restrict__ counts,
+                                                  int32_t* __restrict__ out_ids, float* __restrict__ out_d,
+                                                  int32_t* __restrict__ out_m) {
+    __shared__ double s_td[kMaxK];
+    __shared__ int s_ti[kMaxK];
+    const int lane = threadIdx.x;
+    const int n = (int)min(*ll.n, (unsigned)kLongMax);
+    for (int i = blockIdx.x; i < n; i += gridDim.x) {
+        const int2 it = ll.item[i];
+        const int shares = it.y >> 5, cand = shares * K;
+        if (it.x < 0 || shares == 1 || (it.y & 31)) continue;
+        const int kept = wave_sum_i32(lane < shares ? ll.kept[i + lane] : 0);
+        double bd = INFINITY;
+        int bi = 0x7FFFFFFF;
+        for (int c0 = 0; c0 < cand; c0 += 64) {
+            const bool act = c0 + lane < cand;
+            const double d = act ? ll.d[(int64_t)i * K + c0 + lane] : INFINITY;
+            const int id = act ? ll.id[(int64_t)i * K + c0 + lane] : 0x7FFFFFFF;
+            if (c0 == 0)
+                topk_first(min(64, cand), d, id, K, s_td, s_ti, bd, bi);
+            else
+                topk_insert(act, d, id, K, bd, bi);
+        }
+        write_ranked(it.x, K, kept, bd, bi, counts, out_ids, out_d, out_m);
+    }
+}
+
+// distances, IDs, patches and shares, counts, flags
+size_t bins_rank_scratch(int64_t Q, int K) {
+    if (Q < kLongMin) return 0;
+    return (size_t)kLongMax * ((sizeof(double) + sizeof(int32_t)) * K + sizeof(int2) + sizeof(int32_t)) + (size_t)Q;
+}
+
 hipError_t launch_bins_rank(int Q, int L, int64_t N, int t, int D, int K, const uint2* bins, const uint32_t* tids,
                             const float* qfeat, const float* xf, int32_t* counts, int32_t* ids, float* d, int32_t* m,
-                            unsigned int* counters, hipStream_t st) {
+                            unsigned int* counters, unsigned int* n_long, void* scratch, hipStream_t st) {
     if (Q == 0) return hipSuccess;
-    if (L < 1 || L > 64 || t < 1 || t > L || K < 1 || K > kMaxK || D < 1 || D > kL1MaxD) return hipErrorInvalidValue;
-    if ((D & 3) == 0 && (reinterpret_cast<uintptr_t>(xf) & 15)) return hipErrorInvalidValue;
-    const dim3 grid(Q);
-#define ZH_BINS_RANK(DT)                                                                                              \
-    hipLaunchKernelGGL(k_bins_rank<DT>, grid, dim3(256), 0, st, Q, L, N, t, D, K, bins, tids, qfeat, xf, counts, ids, \
-                       d, m, counters)
-    if (D == 100) ZH_BINS_RANK(100);
-    else if (D == 25) ZH_BINS_RANK(25);
-    else ZH_BINS_RANK(0);
-#undef ZH_BINS_RANK
+    if (L < 1 || L > 64 || t < 1 || t > L || K < 1 || K > kMaxK || (D != 25 && D != 100) ||
+        (reinterpret_cast<uintptr_t>(xf) & 15) || !n_long)
+        return hipErrorInvalidValue;
+    LongLists ll{n_long, nullptr, nullptr, nullptr, nullptr, nullptr};
+    if (!scratch || Q < kLongMin) {
+        auto k = D == 100 ? k_bins_rank<100, false> : k_bins_rank<25, false>;
+        hipLaunchKernelGGL(k, dim3(Q), dim3(256), 0, st, Q, L, N, t, K, bins, tids, qfeat, xf, counts, ids, d, m,
+                           counters, ll);
+        return hipGetLastError();
+    }
+    ll.d = static_cast<double*>(scratch);
+    ll.item = reinterpret_cast<int2*>(ll.d + (size_t)kLongMax * K);
+    ll.id = reinterpret_cast<int32_t*>(ll.item + kLongMax);
+    ll.kept = ll.id + (size_t)kLongMax * K;
+    ll.listed = reinterpret_cast<uint8_t*>(ll.kept + kLongMax);
+    hipLaunchKernelGGL(k_bins_long, dim3((Q + 255) / 256), dim3(256), 0, st, Q, L, bins, ll);
+    auto k = D == 100 ? k_bins_rank<100, true> : k_bins_rank<25, true>;
+    hipLaunchKernelGGL(k, dim3(kLongBlocks + Q), dim3(256), 0, st, Q, L, N, t, K, bins, tids, qfeat, xf, counts, ids, d,
+                       m, counters, ll);
+    hipLaunchKernelGGL(k_bins_join, dim3(1024), dim3(64), 0, st, K, ll, counts, ids, d, m);
     return hipGetLastError();
 }
 

@@ -118,6 +118,7 @@ struct zh_ctx {
     Buf lr, qfeat, qmu, qkeys, qbins, ids, d2, m, ncand, w, over, sbpart, e, tmp, counters, gram, hmask, fixl, fixc, nsurv, guides, bwd, bwd_k, clam;
     Buf qrot;                     // [Q, 64] rotated queries of the screen
     Buf chk;                      // flag of the training-position check
+    Buf longs;                    // lists of the bin-window ranking
     Buf bwd_gw;                   // [Q, 8] FP64 scratch of the lambda adjoint
     Buf bwd_part;                 // partial row gradients of the dictionary-gradient passes
     Buf tools;                    // scratch of the training-crop sampler and the entropy diagnostic
@@ -442,6 +443,18 @@ zh_status store_features(zh_ctx* c, Dict& d, const float* feat) {
     return ZH_OK;
 }
 
+// Scratch of the bin-window ranking's lists of long patches. Without it (a
+// memory limit is set, or the memory is not to be had) such patches take one
+// workgroup each.
+void make_rank_lists(zh_ctx* c, int64_t Q, int K) {
+    const size_t need = bins_rank_scratch(Q, K);
+    if (need && !c->mem_limit) (void)ensure(c, c->longs, need);
+}
+void* rank_lists(zh_ctx* c) {
+    const size_t need = bins_rank_scratch(c->Q, c->qK);
+    return need && c->longs.bytes >= need ? c->longs.p : nullptr;
+}
+
 // cand_only (early stop): the candidate counts and the dump only; the
 // neighbour outputs and the Gram matrices of the last search stay as they are
 zh_status run_search(zh_ctx* c, Dict& d, int32_t* dump, int dump_cap, bool cand_only = false) {
@@ -453,7 +466,8 @@ zh_status run_search(zh_ctx* c, Dict& d, int32_t* dump, int dump_cap, bool cand_
         StageTimer t(c, ZH_T_SEARCH);
         HIPCHK(c, launch_bins_rank((int)c->Q, d.L, d.n, 1, d.D, c->qK, P<uint2>(c->qbins), P<uint32_t>(d.tids),
                                    P<float>(c->qfeat), P<float>(d.xf), P<int32_t>(c->ncand), P<int32_t>(c->ids),
-                                   P<float>(c->d2), P<int32_t>(c->m), P<unsigned int>(c->counters), c->stream));
+                                   P<float>(c->d2), P<int32_t>(c->m), P<unsigned int>(c->counters),
+                                   P<unsigned int>(c->counters) + C_LONG, rank_lists(c), c->stream));
         return ZH_OK;
     }
     SearchArgs a{};
@@ -579,7 +593,7 @@ void zh_destroy(zh_ctx* c) {
     release(c, c->batch.e);
     Buf* bufs[] = {&c->lr, &c->qfeat, &c->qmu, &c->qkeys, &c->qbins, &c->ids, &c->d2, &c->m,
                    &c->ncand, &c->w, &c->over, &c->sbpart, &c->e, &c->tmp, &c->counters, &c->rs_k1,
-                   &c->rs_v1, &c->rs_hist, &c->slot_of, &c->idsort, &c->keys_dict, &c->gram, &c->hmask, &c->fixl, &c->fixc, &c->nsurv, &c->guides, &c->bwd, &c->bwd_k, &c->clam, &c->qrot, &c->bwd_gw, &c->bwd_part, &c->tools, &c->l1cand, &c->chk, &c->wall};
+                   &c->rs_v1, &c->rs_hist, &c->slot_of, &c->idsort, &c->keys_dict, &c->gram, &c->hmask, &c->fixl, &c->fixc, &c->nsurv, &c->guides, &c->bwd, &c->bwd_k, &c->clam, &c->qrot, &c->bwd_gw, &c->bwd_part, &c->tools, &c->l1cand, &c->chk, &c->wall, &c->longs};
     for (Buf* b : bufs) release(c, *b);
     delete c;
 }
@@ -1213,6 +1227,7 @@ zh_status zh_query(zh_ctx* c, const float* lr, int h, int w, int scale, int K) {
     TRY(ensure(c, c->ncand, sizeof(int32_t) * (size_t)Q));
     TRY(ensure(c, c->over, 2 * sizeof(int32_t) * (size_t)Q));
     TRY(ensure(c, c->counters, kNumCounters * sizeof(uint32_t)));
+    if (c->opts.cap == 0 && c->opts.rerank == 0) make_rank_lists(c, Q, K);
     c->qh = h;
     c->qw = w;
     c->qscale = scale;
@@ -1770,6 +1785,7 @@ zh_status batch_plan(zh_ctx* c, const zh_batch* b) {
     TRY(ensure(c, c->over, 2 * sizeof(int32_t) * (size_t)q_max));
     TRY(ensure(c, c->sbpart, sizeof(float) * (size_t)std::max<int64_t>(part_max, 1)));
     TRY(ensure(c, c->counters, kNumCounters * sizeof(uint32_t)));
+    if (c->opts.cap == 0 && c->opts.rerank == 0) make_rank_lists(c, q_max, (int)K);
     if (K <= 8) TRY(ensure(c, c->gram, (c->opts.lle_fp64 ? 8 : 4) * (size_t)q_max * 36));
     for (int s = 1; s <= kMaxScale; ++s)
         for (int pr = 0; B.g[s].n && pr < 2; ++pr) {
@@ -2172,10 +2188,13 @@ zh_status zh_knn_t(zh_ctx* c, int t) {
     if (t < 1 || t > d.L) return fail(c, ZH_EINVAL, "zh_knn_t: need 1 <= t <= L = %d", d.L);
     TRY(set_device(c));
     {
+        make_rank_lists(c, c->Q, c->qK);
         StageTimer tm(c, ZH_T_SEARCH);
+        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, c->stream, P<uint32_t>(c->counters) + C_LONG, 1, 0u);
         HIPCHK(c, launch_bins_rank((int)c->Q, d.L, d.n, t, d.D, c->qK, P<uint2>(c->qbins), P<uint32_t>(d.tids),
                                    P<float>(c->qfeat), P<float>(d.xf), P<int32_t>(c->ncand), P<int32_t>(c->ids),
-                                   P<float>(c->d2), P<int32_t>(c->m), nullptr, c->stream));
+                                   P<float>(c->d2), P<int32_t>(c->m), nullptr, P<unsigned int>(c->counters) + C_LONG,
+                                   rank_lists(c), c->stream));
     }
     c->gram_ready = false;   // the Gram matrices of the new neighbours are formed by zh_lle_weights
     c->stage = 1;

@@ -316,8 +316,9 @@ zh_status zh_lle_weights(zh_ctx* ctx, double lambda);
 /* LLE over all M matches (Section 4.2: Eq. LinSys and Eq. HR_Rec with m
  * running over every match the search found, not only the K nearest). Needs
  * the early stop of the last zh_query (query option cap, 1 <= cap <= 80;
- * else ZH_EUNSUPPORTED): the search runs again and lists each patch's M <=
- * cap candidates ascending; the weights minimise ||y - sum_m w_m y_m||^2
+ * else ZH_EUNSUPPORTED): lists each patch's M <= cap candidates ascending (and
+ * the neighbours are those of the search with the current options, which runs
+ * again where they are not); the weights minimise ||y - sum_m w_m y_m||^2
  * subject to sum_m w_m = 1 with lambda trace(G) added to the diagonal of the
  * M x M Gram matrix G (FP64: exact differences, Cholesky, two triangular
  * solves; uniform weights when trace(G) = 0). ids[Q, cap] and w[Q, cap]

@@ -86,6 +86,10 @@ struct zh_ctx {
     int metric = ZH_METRIC_L2;    // distance of zh_query's neighbour ranking
     // last query
     int stage = 0;                // 0 none, 1 queried, 2 weighted, 3 reconstructed
+    // ids, d2, m, nsurv and the Gram matrices are those of an early-stop search
+    // of this query with the options nbr_opts
+    bool nbr_search = false;
+    zh_query_opts nbr_opts{};
     int qh = 0, qw = 0, qscale = 0, qK = 0;
     bool all_m = false;           // the last weights are over all matches (zh_lle_all)
     int all_cap = 0;              // ... with lists of this many entries a patch
@@ -457,7 +461,8 @@ void* rank_lists(zh_ctx* c) {
 
 // cand_only (early stop): the candidate counts and the dump only; the
 // neighbour outputs and the Gram matrices of the last search stay as they are
-zh_status run_search(zh_ctx* c, Dict& d, int32_t* dump, int dump_cap, bool cand_only = false) {
+zh_status run_search(zh_ctx* c, Dict& d, int32_t* dump, int dump_cap, bool cand_only = false, bool dump_sorted = false) {
+    if (!cand_only) c->nbr_search = false;
     if (c->opts.cap == 0 && c->opts.rerank == 0 && !dump) {
         // the union without a stop, ranked by the FP64 distance itself. The
         // kernels below take the bf16 pre-rank (rerank > 0) and the candidate
@@ -494,6 +499,7 @@ zh_status run_search(zh_ctx* c, Dict& d, int32_t* dump, int dump_cap, bool cand_
     a.out_m = P<int32_t>(c->m);
     a.out_ncand = P<int32_t>(c->ncand);
     a.cand_only = cand_only && a.cap > 0 ? 1 : 0;
+    a.dump_sorted = dump_sorted ? 1 : 0;
     if (a.cap > 0 && !a.cand_only) {
         TRY(ensure(c, c->nsurv, sizeof(int32_t) * (size_t)(a.Q > 0 ? a.Q : 1)));
         a.out_nsurv = P<int32_t>(c->nsurv);
@@ -526,6 +532,8 @@ zh_status run_search(zh_ctx* c, Dict& d, int32_t* dump, int dump_cap, bool cand_
     }
     c->gram_ready = a.gram != nullptr;
     c->gram_fp64 = a.gram_fp64;
+    c->nbr_search = a.cap > 0;
+    c->nbr_opts = c->opts;
     return ZH_OK;
 }
 
@@ -1074,6 +1082,7 @@ zh_status zh_hash(zh_ctx* c, int scale, const float* feat, int64_t n, int32_t* c
         TRY(ensure(c, c->tmp, sizeof(uint64_t) * (size_t)(n > 0 ? n : 1) * d.L));
         kp = P<uint64_t>(c->tmp);
     }
+    c->nbr_search = false;   // the last search's counts go
     TRY(clear_counters(c));
     HashArgs ha{};
     ha.feat = feat;
@@ -1183,6 +1192,7 @@ zh_status rank_l1(zh_ctx* c, Dict& d) {
         d.l1s_ok = true;
     }
     TRY(ensure(c, c->nsurv, sizeof(int32_t) * (size_t)(c->Q > 0 ? c->Q : 1)));
+    c->nbr_search = false;
     TRY(run_search(c, d, P<int32_t>(c->l1cand), cap, true));
     StageTimer t(c, ZH_T_SEARCH);
     if (screened) {
@@ -1214,6 +1224,7 @@ zh_status zh_query(zh_ctx* c, const float* lr, int h, int w, int scale, int K) {
     TRY(set_device(c));
     Dict& d = c->dicts[scale];
     c->stage = 0;
+    c->nbr_search = false;
     const int ps2 = (kPatch * scale) * (kPatch * scale);
     TRY(ensure(c, c->lr, sizeof(float) * (size_t)h * w));
     TRY(ensure(c, c->qfeat, sizeof(float) * (size_t)Q * d.D));
@@ -1329,9 +1340,22 @@ zh_status zh_lle_all(zh_ctx* c, double lambda, int32_t* ids, float* w) {
     const size_t Qn = (size_t)(c->Q > 0 ? c->Q : 1);
     TRY(ensure(c, c->l1cand, sizeof(int32_t) * Qn * cap));
     TRY(ensure(c, c->wall, sizeof(float) * Qn * cap));
-    TRY(clear_counters(c));
-    // the candidate lists of the last query, ascending (the search runs again and dumps them)
-    TRY(run_search(c, d, P<int32_t>(c->l1cand), cap));
+    // The candidate lists of the last query, ascending. Where the neighbours are
+    // not those of the search with these options (they came from another
+    // ranking, or the options changed) the search runs again and dumps them;
+    // else its union alone gives them (24,236 patches: search and rotation 145 us,
+    // the union and its sort 38).
+    const zh_query_opts& o = c->nbr_opts;
+    if (c->nbr_search && o.cap == cap && o.rerank == c->opts.rerank && o.proj == c->opts.proj &&
+        o.lle_fp64 == c->opts.lle_fp64) {
+        // the counters as a search leaves them: its own, and none of the codes and solves
+        static_assert(C_LLE64 == C_CODEFIX + 1, "cleared together");
+        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, c->stream, P<uint32_t>(c->counters) + C_CODEFIX, 2, 0u);
+        TRY(run_search(c, d, P<int32_t>(c->l1cand), cap, true, true));
+    } else {
+        TRY(clear_counters(c));
+        TRY(run_search(c, d, P<int32_t>(c->l1cand), cap));
+    }
     {
         StageTimer t(c, ZH_T_LLE);
         HIPCHK(c, launch_lle_all((int)c->Q, d.D, cap, lambda, P<float>(c->qfeat), P<float>(d.xf), P<int32_t>(c->l1cand),
@@ -1892,6 +1916,7 @@ zh_status zh_run_batch(zh_ctx* c, const zh_batch* b) {
     TRY(batch_stream(c));
     auto& B = c->batch;
     c->stage = 0;
+    c->nbr_search = false;
     std::vector<uint64_t> sig = batch_signature(c, b);
     if (sig != B.sig || !B.exec) {
         if (B.exec) {
@@ -2196,6 +2221,7 @@ zh_status zh_knn_t(zh_ctx* c, int t) {
                                    P<float>(c->d2), P<int32_t>(c->m), nullptr, P<unsigned int>(c->counters) + C_LONG,
                                    rank_lists(c), c->stream));
     }
+    c->nbr_search = false;
     c->gram_ready = false;   // the Gram matrices of the new neighbours are formed by zh_lle_weights
     c->stage = 1;
     return ZH_OK;

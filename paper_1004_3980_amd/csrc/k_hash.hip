@@ -167,15 +167,18 @@ __global__ __launch_bounds__(256) void k_hash_image(const float* __restrict__ al
         }
     }
     uint16_t* nb = reinterpret_cast<uint16_t*>(T + HT::NORM);
+    __shared__ double sq[16 * D];   // squares of the rows
+    for (int e = threadIdx.x; e < 16 * D; e += 256) {
+        const int r = e / D, hr = hash_row(r);
+        const double v = hr >= 0 ? (double)alpha[(int64_t)hr * D + e - r * D] / (PREC == 1 ? (double)w : 1.0) : 0.0;
+        sq[e] = v * v;
+    }
+    __syncthreads();
     for (int e = threadIdx.x; e < 16 * 40; e += 256) {
-        const int r = e / 40, c = e - r * 40, hr = hash_row(r);
+        const int r = e / 40, c = e - r * 40;
         double ss = 0.0;
-        if (hr >= 0)
-            for (int d = 0; d < D; ++d)
-                if (HT::block_of(d) == c) {
-                    const double v = (double)alpha[(int64_t)hr * D + d] / (PREC == 1 ? (double)w : 1.0);
-                    ss = ss + v * v;
-                }
+        for (int d = 0; d < D; ++d)
+            if (HT::block_of(d) == c) ss = ss + sq[r * D + d];
         nb[e] = bf16_up((float)(sqrt(ss) * (1.0 + 1e-6)));
     }
     // A padded row has beta = 1/2 and bound 0 (never uncertain) and multiplier 0.

@@ -1555,73 +1555,42 @@ zh_status zh_backward(zh_ctx* c, const float* g_hr, float* g_resid, float* g_lam
     if (K > kMaxK || d.D > 128) return fail(c, ZH_EUNSUPPORTED, "zh_backward: K <= 16, D <= 128");
     TRY(set_device(c));
     const int64_t HW = (int64_t)H * W, Q = c->Q;
-    // workspace: gamma, F|S|a, four HR temporaries, H x w, h x w, h x W
-    TRY(ensure(c, c->bwd, sizeof(float) * (size_t)(8 * HW + (int64_t)H * w + (int64_t)h * w + (int64_t)h * W)));
-    float* gam = P<float>(c->bwd);
-    float* FSa = gam + HW;
-    float* tA = FSa + 3 * HW;
-    float* tB = tA + HW;
-    float* tC = tB + HW;
-    float* tD = tC + HW;
-    float* tHw = tD + HW;
-    float* thw = tHw + (int64_t)H * w;
-    float* thW = thw + (int64_t)h * w;
+    // workspace: F|S|a, the gradient before and after an iteration, the
+    // gradient per covered pixel, h x w
+    TRY(ensure(c, c->bwd, sizeof(float) * (size_t)(6 * HW + (int64_t)h * w)));
+    float* FSa = P<float>(c->bwd);
+    float* gs[2] = {FSa + 3 * HW, FSa + 4 * HW};
+    float* gp = FSa + 5 * HW;
+    float* thw = gp + HW;
     TRY(ensure(c, c->e, sizeof(float) * (size_t)h * w));
-    HIPCHK(c, hipMemcpyAsync(gam, g_hr, sizeof(float) * (size_t)HW, hipMemcpyDeviceToDevice, c->stream));
+    const float* gam = g_hr;
     const int T = c->bp_rec == 1 ? c->bp_iters : 0;
     if (T > 0) {
         const Taps g = gauss_taps(1.0);
         const float ss = c->bp_sigma_s, sr = c->bp_sigma_r;
         const int Rs = (int)std::ceil(3.0 * (double)ss);
-        AxisAdjArgs gx{}, bx{}, ux{}, dx{};
-        for (int dd = -Rs; dd <= Rs; ++dd) gx.taps[dd + Rs] = (float)std::exp(-(double)(dd * dd) / (2.0 * ss * ss));
-        gx.R = Rs;
-        bx.R = Rs;
-        ux.s = s;
-        dx.s = s;
-        dx.R = g.R;
-        for (int t = -g.R; t <= g.R; ++t) dx.taps[t + g.R] = (float)g.g[t + g.R];
-        const bool range = std::isfinite(sr);
+        BpAdjArgs a{};
+        a.FSa = FSa;
+        a.lr = thw;
+        a.h = h;
+        a.w = w;
+        a.R = Rs;
+        for (int dd = -Rs; dd <= Rs; ++dd) a.taps[dd + Rs] = (float)std::exp(-(double)(dd * dd) / (2.0 * ss * ss));
+        static_assert(sizeof(a.dec) == 7 * sizeof(float), "blur radius 3");
+        for (int t = -g.R; t <= g.R; ++t) a.dec[t + 3] = (float)g.g[t + g.R];
+        a.range = std::isfinite(sr) ? 1 : 0;
+        a.inv_sr2 = 1.0f / (sr * sr);
         for (int t = T - 1; t >= 0; --t) {
             const float* I = P<float>(c->guides) + (size_t)t * HW;
             HIPCHK(c, launch_degrade_residual(I, h, w, s, g, P<float>(c->lr), P<float>(c->e), nullptr, c->stream));
             HIPCHK(c, launch_bp_terms(I, P<float>(c->e), H, W, h, w, s, ss, sr, FSa, c->stream));
-            // v = Blur^T Dec^T Up^T N^T (S gamma)
-            AxisAdjArgs a = gx;
-            a.in = gam; a.mul = FSa + HW; a.out = tA; a.rows = H; a.n_in = W; a.n_out = W;
-            HIPCHK(c, launch_axis_adj(kAdjGauss, 0, a, c->stream));
-            a = gx;
-            a.in = tA; a.out = tB; a.rows = W; a.n_in = H; a.n_out = H;
-            HIPCHK(c, launch_axis_adj(kAdjGauss, 1, a, c->stream));
-            a = ux;
-            a.in = tB; a.out = tHw; a.rows = H; a.n_in = W; a.n_out = w;
-            HIPCHK(c, launch_axis_adj(kAdjUp, 0, a, c->stream));
-            a = ux;
-            a.in = tHw; a.out = thw; a.rows = w; a.n_in = H; a.n_out = h;
-            HIPCHK(c, launch_axis_adj(kAdjUp, 1, a, c->stream));
-            a = dx;
-            a.in = thw; a.out = thW; a.rows = h; a.n_in = w; a.n_out = W;
-            HIPCHK(c, launch_axis_adj(kAdjDec, 0, a, c->stream));
-            a = dx;
-            a.in = thW; a.out = tA; a.rows = W; a.n_in = h; a.n_out = H;
-            HIPCHK(c, launch_axis_adj(kAdjDec, 1, a, c->stream));
-            if (range) {
-                // z = -(a / sigma_r^2) S F gamma, then Box^T z
-                HIPCHK(c, launch_bp_adj_z(FSa, gam, HW, sr, tC, c->stream));
-                a = bx;
-                a.in = tC; a.out = tB; a.rows = H; a.n_in = W; a.n_out = W;
-                HIPCHK(c, launch_axis_adj(kAdjBox, 0, a, c->stream));
-                a = bx;
-                a.in = tB; a.out = tD; a.rows = W; a.n_in = H; a.n_out = H;
-                HIPCHK(c, launch_axis_adj(kAdjBox, 1, a, c->stream));
-                HIPCHK(c, launch_bp_adj_combine(gam, tA, tC, tD, HW, c->stream));
-            } else {
-                HIPCHK(c, launch_bp_adj_combine(gam, tA, nullptr, nullptr, HW, c->stream));
-            }
+            a.g = gam;
+            a.out = gs[t & 1];
+            HIPCHK(c, launch_bp_adj(a, s, c->stream));
+            gam = a.out;
         }
     }
     // blend: gradient per covered pixel over its count
-    float* gp = tB;
     HIPCHK(c, launch_blend_adj(gam, P<int32_t>(c->m), h, w, s, gp, c->stream));
     // lambda
     TRY(ensure(c, c->clam, sizeof(double) * (size_t)(Q > 0 ? Q : 1)));

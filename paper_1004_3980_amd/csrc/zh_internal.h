@@ -349,22 +349,20 @@ int bp_tiles(int H, int W, int tile);
 
 // ---- adjoint (k_backward.hip) -------------------------------------------------
 constexpr int kMaxAdjR = 8;
-enum { kAdjGauss = 0, kAdjBox = 1, kAdjUp = 2, kAdjDec = 3 };
-struct AxisAdjArgs {
-    const float* in;
-    const float* mul;        // optional elementwise factor of the input (same layout), nullable
-    float* out;
-    int rows;                // rows (x pass) or columns (y pass) of the other axis
-    int n_in, n_out;         // length of the axis in and out
-    int s;                   // zoom factor (bicubic and degradation)
-    int R;                   // tap radius (Gaussian, box, blur)
-    float taps[2 * kMaxAdjR + 1];   // Gaussian taps (unnormalised) or blur taps
+struct BpAdjArgs {
+    const float* g;          // [s h, s w] gradient after the iteration
+    const float* FSa;        // its terms F, S and I - Box I, [3, s h, s w]
+    float* lr;               // [h, w] scratch
+    float* out;              // [s h, s w] gradient before it (not g)
+    int h, w;
+    int R;                   // radius of the Gaussian and the box
+    int range;               // the range weight varies (finite sigma_r)
+    float inv_sr2;           // 1 / sigma_r^2
+    float taps[2 * kMaxAdjR + 1];   // Gaussian taps (unnormalised)
+    float dec[7];            // blur taps of the degradation (sigma 1)
 };
-// one pass of a transposed separable operator along x (axis 0) or y (axis 1)
-hipError_t launch_axis_adj(int op, int axis, const AxisAdjArgs& a, hipStream_t st);
-hipError_t launch_bp_adj_z(const float* FSa, const float* g, int64_t n, float sigma_r, float* z, hipStream_t st);
-hipError_t launch_bp_adj_combine(float* g, const float* v, const float* z, const float* bz, int64_t n,
-                                 hipStream_t st);
+// the adjoint of one back-projection iteration
+hipError_t launch_bp_adj(const BpAdjArgs& a, int scale, hipStream_t st);
 hipError_t launch_blend_adj(const float* g, const int32_t* m, int h, int w, int s, float* gp, hipStream_t st);
 struct BackwardArgs {
     int Q, D, K, s, w;       // patches, feature dimension, neighbours, zoom, LR width

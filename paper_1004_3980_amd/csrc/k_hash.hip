@@ -628,13 +628,7 @@ __device__ __forceinline__ double dot_fp64(const float* __restrict__ ar, const f
 // The same sum by the four lanes of a quad: lane q reads every fourth piece (16
 // bytes where the rows allow it) and forms its products; the sum goes through
 // the pieces in order, every lane adding its own to it and all taking the
-// owner's result.
-template <int OWNER>
-__device__ __forceinline__ double quad_take(double s) {
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(s), OWNER * 0x55, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(s), OWNER * 0x55, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
-}
+// owner's result (quad_take).
 template <int D, int W>   // W values a piece
 __device__ __forceinline__ double quad_dot(const float* __restrict__ ar, const float* __restrict__ vr, int q) {
     constexpr int C = D / W, T = (C + 3) / 4;

@@ -557,7 +557,11 @@ hipError_t launch_l1_screen_rows(const float* xf, int64_t n, uint8_t* l1s, hipSt
 //     (distance, ID) order is counted against all the others (IDs are
 //     distinct), else K rounds of wave minimum pick them.
 // With M <= K candidates nothing is screened.
-__global__ __launch_bounds__(64) void k_knn_l1_screened(int Q, int K, int cap, const float* __restrict__ qfeat,
+// Bound: VALU issue and the gathers. 203,636 patches at D = 100, cap 72, K = 8:
+// with a lane a survivor (300 FP64 instructions for about nine live lanes, the
+// query's values in 200 registers or spilled) 487 us; by quads 447, and held to
+// the 102 registers of five waves a SIMD 398 (six spill: 634).
+__global__ __launch_bounds__(64, 5) void k_knn_l1_screened(int Q, int K, int cap, const float* __restrict__ qfeat,
                                                       const float* __restrict__ xf, const uint8_t* __restrict__ l1s,
                                                       const int32_t* __restrict__ cand,
                                                       const int32_t* __restrict__ ncand, int32_t* __restrict__ out_ids,
@@ -569,6 +573,7 @@ __global__ __launch_bounds__(64) void k_knn_l1_screened(int Q, int K, int cap, c
     __shared__ double sq[DT];
     __shared__ float4 sqf[D4];
     __shared__ int sid[kRankMaxCand];
+    __shared__ double sd[kRankMaxCand];
     const int lane = threadIdx.x;
     const int q = xcd_block();
     if (q >= Q) return;
@@ -644,9 +649,7 @@ __global__ __launch_bounds__(64) void k_knn_l1_screened(int Q, int K, int cap, c
                         }
                     }
                 }
-                A += __shfl_xor(A, 1);
-                A += __shfl_xor(A, 2);
-                A += __shfl_xor(A, 4);
+                A = group8_sum_f32(A);
             }
             if (own) {
                 float l = fmaf(A, 1.0f - 0x1p-15f, -e);
@@ -689,36 +692,39 @@ __global__ __launch_bounds__(64) void k_knn_l1_screened(int Q, int K, int cap, c
     }
     __syncthreads();
     if (out_ns && lane == 0) out_ns[q] = ns;
-    // 4. exact distances of the survivors
+    // 4. exact distances of the survivors, four lanes each: lane qd of a quad
+    // forms the terms of every fourth four coordinates, and the sum goes
+    // through the coordinates in order (quad_take)
+    const int qd = lane & 3;
+    for (int j0 = 0; j0 < ns; j0 += 16) {
+        const int j = j0 + (lane >> 2);
+        const float4* row = reinterpret_cast<const float4*>(xf) + (int64_t)sid[j < ns ? j : j0] * D4;
+        constexpr int T = (D4 + 3) / 4;
+        float4 x[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) x[t] = row[min(4 * t + qd, D4 - 1)];
+        double acc = 0.0;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const double* qv = sq + 4 * min(4 * t + qd, D4 - 1);
+            const double p0 = fabs(qv[0] - (double)x[t].x), p1 = fabs(qv[1] - (double)x[t].y);
+            const double p2 = fabs(qv[2] - (double)x[t].z), p3 = fabs(qv[3] - (double)x[t].w);
+            auto add = [&](double s) { return (((s + p0) + p1) + p2) + p3; };
+            acc = quad_take<0>(add(acc));
+            if (4 * t + 1 < D4) acc = quad_take<1>(add(acc));
+            if (4 * t + 2 < D4) acc = quad_take<2>(add(acc));
+            if (4 * t + 3 < D4) acc = quad_take<3>(add(acc));
+        }
+        if (qd == 0 && j < ns) sd[j] = acc;
+    }
+    __syncthreads();
     double d[NCH];
     int id[NCH];
 #pragma unroll
     for (int u = 0; u < NCH; ++u) {
-        d[u] = INFINITY;
-        id[u] = 0x7FFFFFFF;
         const int j = 64 * u + lane;
-        if (64 * u < ns && j < ns) {
-            const int myid = sid[j];
-            const float4* row = reinterpret_cast<const float4*>(xf) + (int64_t)myid * D4;
-            double acc = 0.0;
-            constexpr int H = (D4 + 1) / 2;   // the row in two halves of loads in flight
-#pragma unroll
-            for (int h0 = 0; h0 < D4; h0 += H) {
-                float4 x[H];
-#pragma unroll
-                for (int t = 0; t < H; ++t)
-                    if (h0 + t < D4) x[t] = row[h0 + t];
-#pragma unroll
-                for (int t = 0; t < H; ++t) {
-                    if (h0 + t >= D4) break;
-                    const float xv[4] = {x[t].x, x[t].y, x[t].z, x[t].w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc = acc + fabs(sq[4 * (h0 + t) + e] - (double)xv[e]);
-                }
-            }
-            d[u] = acc;
-            id[u] = myid;
-        }
+        d[u] = 64 * u < ns && j < ns ? sd[j] : INFINITY;
+        id[u] = 64 * u < ns && j < ns ? sid[j] : 0x7FFFFFFF;
     }
     const int m = min(K, M);
     if (ns <= 64) {

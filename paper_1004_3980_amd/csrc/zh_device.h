@@ -116,6 +116,13 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     v = mx(v, dpp_or0<0x143, 0xC>((int)v));
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
+// s of lane OWNER of each quad, in its four lanes
+template <int OWNER>
+__device__ __forceinline__ double quad_take(double s) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(s), OWNER * 0x55, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(s), OWNER * 0x55, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
 // sum over the eight lanes of an aligned group, in each of them (lanes 1 apart,
 // then 2, then the group's other half: the order of an xor butterfly)
 __device__ __forceinline__ float group8_sum_f32(float v) {

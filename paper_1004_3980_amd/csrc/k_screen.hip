@@ -81,64 +81,146 @@ __global__ void k_cov_sum(const double* __restrict__ part, int nblk, int np, dou
 // ---- principal directions ----------------------------------------------------
 // Jacobi eigenvalue iteration on the symmetric matrix in LDS (FP64), one
 // workgroup. A sweep is N - 1 rounds of N / 2 disjoint rotations (round-robin
-// pairs; an odd D gets an idle index): the rotations of a round are formed from
-// the pairs' 2x2 blocks, then every 2x2 block of two pairs is rotated from both
-// sides at once. The rotations are recorded (c, s per round and pair) for
-// k_jacobi_vectors; an off-diagonal below 1e-9 of the diagonal ends the sweeps.
-// Any basis would do for the screen's bounds; this one makes them tight.
+// pairs; an odd D gets an idle index, a row of zeros). The matrix is kept in the
+// order of the round's pairs, pair k at positions 2k and 2k + 1, as the 2x2
+// blocks of pairs k > l; a round writes its blocks to where the next round has
+// them, in a second copy. The way from a round to the next is one permutation
+// of the positions, so a thread's block and the places of its four results hold
+// for the whole iteration. The last wave, a lane per pair, keeps the pairs' own
+// blocks in registers: it forms the next round's rotations from them and the one
+// block whose entry joins the pair, while the others apply this round's. The
+// rotations are recorded (c, s per round and pair) for k_jacobi_vectors; an
+// off-diagonal below 1e-9 of the diagonal ends the sweeps. Any basis would do
+// for the screen's bounds; this one makes them tight.
 //
-// Bound: the chain of rounds, two barriers each (D = 100: 1.6 ms; the
-// cyclic iteration on the host it replaces took 8 ms with the device idle).
+// Bound: the chain of rounds, one barrier each, beside the LDS traffic of a
+// round (8 doubles and two rotations a block). D = 100: 0.79 ms, 0.83 beside the
+// tables' build of 300k rows (1.55 and 1.6 with the matrix in one copy:
+// rotations, a barrier, updates at computed places, a barrier).
 constexpr int kJacThreads = 1024;
+constexpr int kJacApply = kJacThreads - 64;
 constexpr int kJacSweeps = 24;
-constexpr int kJacMaxD = 100;      // the lower triangle in rows of odd length: 81 KB of LDS
+constexpr int kJacMaxD = 100;
 constexpr int kJacPairs = kJacMaxD / 2;
+constexpr int kJacBlocks = kJacPairs * (kJacPairs - 1) / 2;   // four planes of doubles, twice: 78 KB of LDS
+constexpr int kJacAhead = 32;
 constexpr double kJacOff2 = 1e-18;   // squared off-diagonal against squared diagonal: Phi is rounded to fp32
 
-// entry (i, j) of the symmetric matrix: the lower triangle in rows of kJacLd
-constexpr int kJacLd = kJacMaxD | 1;
-__device__ __forceinline__ int tri_at(int i, int j) { return i >= j ? i * kJacLd + j : j * kJacLd + i; }
-// pair k of round r among N (even) indexes, smaller first
+// the pair k of round r among N (even) indexes: N - 1 with r, r + k with r - k
+// (mod N - 1)
 __device__ __forceinline__ void jac_pair(int N, int r, int k, int& p, int& q) {
     const int m = N - 1;
-    int a = k == 0 ? m : r + k, b = k == 0 ? r : r - k;
-    if (k > 0 && a >= m) a -= m;
-    if (b < 0) b += m;
-    p = a < b ? a : b;
-    q = a < b ? b : a;
+    p = k == 0 ? m : r + k;
+    q = r - k;
+    if (k > 0 && p >= m) p -= m;
+    if (q < 0) q += m;
+}
+// index at position x in the first round of a sweep
+__device__ __forceinline__ int jac_index(int N, int x) {
+    int p, q;
+    jac_pair(N, 0, x >> 1, p, q);
+    return x & 1 ? q : p;
+}
+// position in the next round of the index at position x
+__device__ __forceinline__ int jac_next(int P, int x) {
+    const int k = x >> 1;
+    if (P == 1) return x;
+    if (x & 1) return k == P - 1 ? 2 * k : x + 2;
+    return k == 0 ? 0 : k == 1 ? 1 : x - 2;
+}
+// the same with a lane per pair (P > 1, every lane active): the two values of
+// each pair to the next round's pairs
+__device__ __forceinline__ double wave_from_next(double v) {
+    return __hiloint2double(dpp_or0<0x130>(__double2hiint(v)), dpp_or0<0x130>(__double2loint(v)));
+}
+__device__ __forceinline__ double wave_from_last(double v) {
+    return __hiloint2double(dpp_or0<0x138>(__double2hiint(v)), dpp_or0<0x138>(__double2loint(v)));
+}
+__device__ __forceinline__ void jac_move(int P, int lane, double& a, double& b) {
+    const double up = wave_from_next(a), dn = wave_from_last(b);
+    a = lane == 0 ? a : lane == P - 1 ? b : up;
+    b = lane == 0 ? up : dn;
+}
+// place of entry (x, y) among the blocks; -1 inside a pair
+__device__ __forceinline__ int jac_slot(int x, int y) {
+    if (x < y) {
+        const int z = x;
+        x = y;
+        y = z;
+    }
+    const int k = x >> 1, l = y >> 1;
+    return k == l ? -1 : ((x & 1) * 2 + (y & 1)) * kJacBlocks + k * (k - 1) / 2 + l;
 }
 
 __global__ __launch_bounds__(kJacThreads) void k_jacobi(const double* __restrict__ cov, int D, double2* __restrict__ rot,
                                                         double* __restrict__ eig, int* __restrict__ sweeps) {
-    extern __shared__ double sA[];   // [D][kJacLd]
-    __shared__ double2 cs[kJacPairs];
-    __shared__ int sp[kJacPairs], sq[kJacPairs];
+    extern __shared__ double sB[];   // [2][4][kJacBlocks]
+    __shared__ double2 cs[2][kJacPairs];
     __shared__ double red[2][kJacThreads / 64];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int N = (D + 1) & ~1, P = N / 2, np = D * (D + 1) / 2;
-    for (int e = t; e < np; e += kJacThreads) {
-        const int i = tri_row(e);
-        sA[tri_at(i, e - i * (i + 1) / 2)] = cov[e];
-    }
-    // the pairs of pairs (k >= l) of this thread, fixed over the rounds
-    const int nb = P * (P + 1) / 2;
-    constexpr int E = (kJacPairs * (kJacPairs + 1) / 2 + kJacThreads - 1) / kJacThreads;
-    int bk[E], bl[E];
+    const int N = (D + 1) & ~1, P = N / 2, nblk = P * (P - 1) / 2;
+    const bool turns = wv == kJacThreads / 64 - 1, pair = turns && lane < P;
+    auto cov_at = [&](int x, int y) {
+        const int i = jac_index(N, x), j = jac_index(N, y), a = i > j ? i : j, b = i > j ? j : i;
+        return a < D ? cov[a * (a + 1) / 2 + b] : 0.0;
+    };
+    // the blocks of this thread and where their results go
+    constexpr int E = (kJacBlocks + kJacApply - 1) / kJacApply;
+    int bk[E], bl[E], to[E][4];
 #pragma unroll
     for (int u = 0; u < E; ++u) {
-        const int e = t + u * kJacThreads;
-        bk[u] = e < nb ? tri_row(e) : -1;
-        bl[u] = e < nb ? e - bk[u] * (bk[u] + 1) / 2 : -1;
+        const int e = t + u * kJacApply;
+        bk[u] = bl[u] = -1;
+        if (turns || e >= nblk) continue;
+        const int row = tri_row(e);
+        bk[u] = row + 1;
+        bl[u] = e - row * (row + 1) / 2;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int x = 2 * bk[u] + (v >> 1), y = 2 * bl[u] + (v & 1);
+            to[u][v] = jac_slot(jac_next(P, x), jac_next(P, y));
+            sB[v * kJacBlocks + e] = cov_at(x, y);
+        }
     }
+    // the pair of this lane: diagonal (da, db), off-diagonal ab and its
+    // rotation; the block and the entry that the next pair's off-diagonal is
+    // (the pair's lower position comes from pair ol, the other from ok)
+    double da = 0.0, db = 0.0, ab = 0.0, tn = 0.0, c = 1.0, s = 0.0;
+    int ok = 0, ol = 0, orow = 0, ocol = 0, oblk = 0, zero = -1;
+    auto turn = [&]() {
+        const double d = 0.5 * (db - da), h = sqrt(d * d + ab * ab);
+        tn = h > 0.0 ? copysign(1.0, d) * ab / (fabs(d) + h) : 0.0;
+        c = rsqrt(tn * tn + 1.0);
+        s = tn * c;
+    };
+    if (pair) {
+        da = cov_at(2 * lane, 2 * lane);
+        db = cov_at(2 * lane + 1, 2 * lane + 1);
+        ab = cov_at(2 * lane, 2 * lane + 1);
+        if (P > 1) {
+            ok = lane == P - 1 ? lane : lane + 1;
+            ol = lane == 0 ? 0 : lane - 1;
+            orow = lane > 0 && lane == P - 1;
+            ocol = lane > 0;
+            oblk = ok * (ok - 1) / 2 + ol;
+            zero = jac_slot(jac_next(P, 2 * lane), jac_next(P, 2 * lane + 1));
+        }
+        turn();
+        cs[0][lane] = make_double2(c, s);
+    }
+    if (turns) __builtin_amdgcn_s_setprio(3);   // the others wait for it
     __syncthreads();
-    int sweep = 0;
+    int sweep = 0, cur = 0;
     for (; sweep < kJacSweeps; ++sweep) {
-        double off = 0.0, dia = 0.0;
-        for (int e = t; e < np; e += kJacThreads) {
-            const int i = tri_row(e), j = e - i * (i + 1) / 2;
-            const double v = sA[tri_at(i, j)] * sA[tri_at(i, j)];
-            if (i == j) dia += v;
-            else off += v;
+        double off = ab * ab, dia = da * da + db * db;
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
+            if (bk[u] < 0) continue;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const double x = sB[(cur * 4 + v) * kJacBlocks + t + u * kJacApply];
+                off += x * x;
+            }
         }
         off = wave_sum_f64(off);
         dia = wave_sum_f64(dia);
@@ -154,100 +236,106 @@ __global__ __launch_bounds__(kJacThreads) void k_jacobi(const double* __restrict
         }
         if (!(off > kJacOff2 * dia)) break;
         for (int r = 0; r < N - 1; ++r) {
-            if (t < P) {
-                int p, q;
-                jac_pair(N, r, t, p, q);
-                double c = 1.0, s = 0.0;
-                if (q < D) {
-                    const double apq = sA[tri_at(q, p)];
-                    if (apq != 0.0) {
-                        const double theta = (sA[tri_at(q, q)] - sA[tri_at(p, p)]) / (2.0 * apq);
-                        const double tn = fabs(theta) > 1e150
-                                              ? 0.5 / theta
-                                              : copysign(1.0, theta) / (fabs(theta) + sqrt(theta * theta + 1.0));
-                        c = 1.0 / sqrt(tn * tn + 1.0);
-                        s = tn * c;
-                    }
-                }
-                cs[t] = make_double2(c, s);
-                sp[t] = p;
-                sq[t] = q;
-                rot[((int64_t)sweep * (N - 1) + r) * P + t] = make_double2(c, s);
-            }
-            __syncthreads();
+            const double* src = sB + cur * 4 * kJacBlocks;
+            double* dst = sB + (cur ^ 1) * 4 * kJacBlocks;
+            if (!turns) {
+                double a[E][4];
+                double2 rk[E], rl[E];
 #pragma unroll
-            for (int u = 0; u < E; ++u) {
-                if (bk[u] < 0) continue;
-                const int p = sp[bk[u]], q = sq[bk[u]];
-                const double2 rk = cs[bk[u]];
-                if (bk[u] == bl[u]) {
-                    if (q < D) {
-                        const double app = sA[tri_at(p, p)], aqq = sA[tri_at(q, q)], apq = sA[tri_at(q, p)];
-                        const double c = rk.x, s = rk.y;
-                        sA[tri_at(p, p)] = c * c * app - 2.0 * c * s * apq + s * s * aqq;
-                        sA[tri_at(q, q)] = s * s * app + 2.0 * c * s * apq + c * c * aqq;
-                        sA[tri_at(q, p)] = 0.0;
-                    }
-                    continue;
+                for (int u = 0; u < E; ++u) {
+                    if (bk[u] < 0) continue;
+                    const double* p = src + t + u * kJacApply;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) a[u][v] = p[v * kJacBlocks];
+                    rk[u] = cs[cur][bk[u]];
+                    rl[u] = cs[cur][bl[u]];
                 }
-                const int i = sp[bl[u]], j = sq[bl[u]];
-                const double2 rl = cs[bl[u]];
-                // the idle index (D, when D is odd) is the larger of its pair
-                const bool hq = q < D, hj = j < D;
-                double a00 = sA[tri_at(p, i)], a01 = hj ? sA[tri_at(p, j)] : 0.0;
-                double a10 = hq ? sA[tri_at(q, i)] : 0.0, a11 = hq && hj ? sA[tri_at(q, j)] : 0.0;
-                const double b00 = rl.x * a00 - rl.y * a01, b01 = rl.y * a00 + rl.x * a01;
-                const double b10 = rl.x * a10 - rl.y * a11, b11 = rl.y * a10 + rl.x * a11;
-                sA[tri_at(p, i)] = rk.x * b00 - rk.y * b10;
-                if (hj) sA[tri_at(p, j)] = rk.x * b01 - rk.y * b11;
-                if (hq) sA[tri_at(q, i)] = rk.y * b00 + rk.x * b10;
-                if (hq && hj) sA[tri_at(q, j)] = rk.y * b01 + rk.x * b11;
+#pragma unroll
+                for (int u = 0; u < E; ++u) {
+                    if (bk[u] < 0) continue;
+                    const double ck = rk[u].x, sk = rk[u].y, cl = rl[u].x, sl = rl[u].y;
+                    const double b00 = cl * a[u][0] - sl * a[u][1], b01 = sl * a[u][0] + cl * a[u][1];
+                    const double b10 = cl * a[u][2] - sl * a[u][3], b11 = sl * a[u][2] + cl * a[u][3];
+                    if (to[u][0] >= 0) dst[to[u][0]] = ck * b00 - sk * b10;
+                    if (to[u][1] >= 0) dst[to[u][1]] = ck * b01 - sk * b11;
+                    if (to[u][2] >= 0) dst[to[u][2]] = sk * b00 + ck * b10;
+                    if (to[u][3] >= 0) dst[to[u][3]] = sk * b01 + ck * b11;
+                }
+            } else {
+                if (pair) rot[((int64_t)sweep * (N - 1) + r) * P + lane] = make_double2(c, s);
+                const double2 rk = cs[cur][ok], rl = cs[cur][ol];
+                const double a00 = src[oblk], a01 = src[kJacBlocks + oblk];
+                const double a10 = src[2 * kJacBlocks + oblk], a11 = src[3 * kJacBlocks + oblk];
+                const double na = da - tn * ab, nb = db + tn * ab;
+                da = na;
+                db = nb;
+                ab = 0.0;
+                if (P > 1) {
+                    jac_move(P, lane, da, db);
+                    const double b0 = ocol ? rl.y * a00 + rl.x * a01 : rl.x * a00 - rl.y * a01;
+                    const double b1 = ocol ? rl.y * a10 + rl.x * a11 : rl.x * a10 - rl.y * a11;
+                    ab = orow ? rk.y * b0 + rk.x * b1 : rk.x * b0 - rk.y * b1;
+                    if (pair) dst[zero] = 0.0;
+                    else da = db = ab = 0.0;
+                }
+                turn();
+                if (pair) cs[cur ^ 1][lane] = make_double2(c, s);
             }
+            cur ^= 1;
             __syncthreads();
         }
     }
-    for (int i = t; i < D; i += kJacThreads) eig[i] = sA[tri_at(i, i)];
+    if (pair) {
+        const int i = jac_index(N, 2 * lane), j = jac_index(N, 2 * lane + 1);
+        if (i < D) eig[i] = da;
+        if (j < D) eig[j] = db;
+    }
     if (t == 0) *sweeps = sweep;
 }
 
 // The product of the recorded rotations, V [D][D]: a wave per row, a lane per
-// pair of a round.
+// pair of a round, whose two entries are in registers and move to the next
+// round's lanes (jac_next) in the vector unit. Bound: the rounds'
+// arithmetic in turn; the loads are kJacAhead rounds ahead, since the tables are
+// built beside it. D = 100: 186 -> 76 us, beside the build of 300k rows' tables
+// 0.73 -> 0.33 ms (entries in LDS, eight rounds ahead before).
 __global__ __launch_bounds__(64) void k_jacobi_vectors(int D, const double2* __restrict__ rot,
                                                        const int* __restrict__ sweeps, double* __restrict__ V) {
-    __shared__ double v[2 * kJacPairs];
     const int i = blockIdx.x, lane = threadIdx.x;
     const int N = (D + 1) & ~1, P = N / 2;
-    for (int j = lane; j < N; j += 64) v[j] = j == i ? 1.0 : 0.0;
+    const bool on = lane < P;
+    const int ia = on ? jac_index(N, 2 * lane) : -1, ib = on ? jac_index(N, 2 * lane + 1) : -1;
+    double a = ia == i ? 1.0 : 0.0, b = ib == i ? 1.0 : 0.0;
     const int rounds = *sweeps * (N - 1);
-    // the rotations of the next kAhead rounds in flight
-    constexpr int kAhead = 8;
-    double2 next[kAhead];
-    auto load = [&](int g) { return lane < P && g < rounds ? rot[(int64_t)g * P + lane] : make_double2(1.0, 0.0); };
+    // the rotations of the next kJacAhead rounds in flight
+    double2 next[kJacAhead];
+    // (past the last round: bytes of the scratch that lie behind, not used)
+    const unsigned at = on ? lane : 0;
+    auto step = [&](double2 c) {
+        const double na = c.x * a - c.y * b, nb = c.y * a + c.x * b;
+        a = na;
+        b = nb;
+        if (P > 1) jac_move(P, lane, a, b);
+    };
+    if (rounds > 0) {
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) next[u] = load(u);
-    __syncthreads();
-    for (int g0 = 0, r = 0; g0 < rounds; g0 += kAhead) {
+        for (int u = 0; u < kJacAhead; ++u) next[u] = (rot + u * P)[at];
+        int g0 = 0;
+        for (; g0 + kJacAhead <= rounds; g0 += kJacAhead) {
+            const double2* ahead = rot + (g0 + kJacAhead) * P;
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const double2 c = next[u];
-            next[u] = load(g0 + u + kAhead);
-            if (g0 + u < rounds) {
-                if (lane < P) {
-                    int p, q;
-                    jac_pair(N, r, lane, p, q);
-                    const double a = v[p], b = v[q];
-                    v[p] = c.x * a - c.y * b;
-                    v[q] = c.y * a + c.x * b;
-                }
-                if (++r == N - 1) r = 0;
+            for (int u = 0; u < kJacAhead; ++u) {
+                const double2 c = next[u];
+                next[u] = (ahead + u * P)[at];
+                step(c);
             }
-            // one wave: its LDS operations stay in order, and no load in flight
-            // is waited for
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
         }
+#pragma unroll
+        for (int u = 0; u < kJacAhead; ++u)
+            if (g0 + u < rounds) step(next[u]);
     }
-    for (int j = lane; j < D; j += 64) V[(int64_t)i * D + j] = v[j];
+    if (ia >= 0 && ia < D) V[(int64_t)i * D + ia] = a;
+    if (ib >= 0 && ib < D) V[(int64_t)i * D + ib] = b;
 }
 
 // The m eigenvectors of the largest eigenvalues (ties by index) as the rows of
@@ -270,17 +358,27 @@ __global__ __launch_bounds__(256) void k_screen_basis(const double* __restrict__
         order[rank] = j;
     }
     __syncthreads();
-    for (int j = t; j < m; j += 256) {
-        const int col = order[j];
-        double nrm = 0.0;
-#pragma unroll 16
-        for (int i = 0; i < D; ++i) {
-            const double v = V[(int64_t)i * D + col];
-            nrm += v * v;
+    // four threads a direction, all its loads in flight
+    {
+        constexpr int kPart = (kJacMaxD + 3) / 4;
+        const int j = t >> 2, col = order[j < m ? j : 0];
+        double v[kPart], nrm = 0.0;
+#pragma unroll
+        for (int u = 0; u < kPart; ++u) {
+            const int i = (t & 3) + 4 * u;
+            v[u] = V[(int64_t)(i < D ? i : 0) * D + col];
         }
+#pragma unroll
+        for (int u = 0; u < kPart; ++u)
+            if ((t & 3) + 4 * u < D) nrm += v[u] * v[u];
+        nrm += __shfl_xor(nrm, 1);
+        nrm += __shfl_xor(nrm, 2);
         nrm = sqrt(nrm);
-#pragma unroll 16
-        for (int i = 0; i < D; ++i) phi[j][i] = (float)(V[(int64_t)i * D + col] / nrm);
+        if (j < m) {
+#pragma unroll
+            for (int u = 0; u < kPart; ++u)
+                if ((t & 3) + 4 * u < D) phi[j][(t & 3) + 4 * u] = (float)(v[u] / nrm);
+        }
     }
     __syncthreads();
     for (int e = t; e < D * kRotStride; e += 256) {
@@ -328,7 +426,9 @@ hipError_t launch_screen_basis(const float* x, int64_t n, int D, int64_t ns, int
     const int64_t np = (int64_t)D * (D + 1) / 2, N = (D + 1) & ~1;
     // the rotations are read 16 bytes at a time: first, from the 16-byte aligned start
     double* rot = static_cast<double*>(scratch);
+    // k_jacobi_vectors reads up to kJacAhead rounds (8 N bytes each) into part
     double* part = rot + 2 * (int64_t)kJacSweeps * (N - 1) * (N / 2);
+    static_assert(kJacAhead * 2 <= kCovBlocks, "a round is N doubles, part at least kCovBlocks N / 2");
     double* cov = part + kCovBlocks * np;
     double* V = cov + np;
     double* eig = V + (int64_t)D * D;
@@ -338,7 +438,7 @@ hipError_t launch_screen_basis(const float* x, int64_t n, int D, int64_t ns, int
     hipLaunchKernelGGL(k_cov_partial, dim3(kCovBlocks, (unsigned)((np + kCovThreads - 1) / kCovThreads)),
                        dim3(kCovThreads), 0, st, x, n, D, ns, part);
     hipLaunchKernelGGL(k_cov_sum, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, part, kCovBlocks, (int)np, cov);
-    const size_t lds = sizeof(double) * (size_t)D * kJacLd;
+    const size_t lds = sizeof(double) * 8 * kJacBlocks;
     const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(k_jacobi),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (ea != hipSuccess) return ea;

@@ -420,15 +420,23 @@ zh_status finish_screen(zh_ctx* c, Dict& d, const double* s2_dev) {
     return ZH_OK;
 }
 
-// Content hash of `bytes` bytes of device memory (a multiple of 4), salted by the section.
-zh_status device_hash(zh_ctx* c, const void* p, uint64_t bytes, uint64_t salt, uint64_t* out) {
+// Content hash of `bytes` bytes of device memory (a multiple of 4), salted by the
+// section: enqueued, and taken over after a wait.
+zh_status start_hash(zh_ctx* c, const void* p, uint64_t bytes, uint64_t salt) {
     TRY(ensure(c, c->chk, 16));
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, c->stream, P<uint32_t>(c->chk), 4, 0u);
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, launch_hash_words(p, (int64_t)(bytes / 4), salt, P<unsigned long long>(c->chk), c->stream));
+    return ZH_OK;
+}
+zh_status finish_hash(zh_ctx* c, uint64_t* out) {
     HIPCHK(c, hipMemcpyAsync(out, c->chk.p, 8, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return ZH_OK;
+}
+zh_status device_hash(zh_ctx* c, const void* p, uint64_t bytes, uint64_t salt, uint64_t* out) {
+    TRY(start_hash(c, p, bytes, salt));
+    return finish_hash(c, out);
 }
 
 // The library's own copies of the dictionary features: the split bf16/low
@@ -734,14 +742,14 @@ zh_status zh_build_tables(zh_ctx* c, const zh_dictionary* dict, int L, int k, fl
     while (cap < 2 * (uint64_t)n) cap <<= 1;
     d.cap = cap;
     TRY(store_features(c, d, dict->feat));
-    TRY(device_hash(c, dict->feat, sizeof(float) * (uint64_t)n * D, 0, &d.feat_hash));
     double* s2_dev = nullptr;
     // on the second stream: the basis is one workgroup's chain, beside which the
     // keys and tables below are formed
     SideStream side(c);
     TRY(side.start());
     TRY(start_screen(c, d, dict->feat, c->batch.stream, &s2_dev));
-    // hash parameters
+    TRY(start_hash(c, dict->feat, sizeof(float) * (uint64_t)n * D, 0));
+    // hash parameters, formed on the host while the device works on the above
     hash_params(seed, L, k, D, (double)w, d.h_alpha, d.h_beta);
     const int m = L * k;
     const int DP = (D + 31) & ~31;
@@ -763,6 +771,7 @@ zh_status zh_build_tables(zh_ctx* c, const zh_dictionary* dict, int L, int k, fl
             for (int j = 0; j < k; ++j) km[(size_t)l * (k + 1) + j] = key_mul(l, j);
             km[(size_t)l * (k + 1) + k] = key_mul(l, 63);
         }
+        TRY(finish_hash(c, &d.feat_hash));
         TRY(ensure(c, d.kmul, sizeof(uint64_t) * km.size()));
         HIPCHK(c, hipMemcpyAsync(d.kmul.p, km.data(), sizeof(uint64_t) * km.size(), hipMemcpyHostToDevice, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));

@@ -58,3 +58,35 @@ def test_bins(n, L, k, w):
         _, c = np.unique(tables.sorted_keys[l], return_counts=True)
         p = c / n
         assert abs(got[0][2][l] + (p * np.log2(p)).sum()) <= 1e-12 * max(1.0, np.log2(max(n, 2)))
+
+
+# the screen's basis in a saved file (its last two parts: the bf16 split of Phi,
+# 64 rows): one row, fewer rows than directions, more
+@pytest.mark.parametrize("mode,D", [(0, 25), (1, 100)])
+@pytest.mark.parametrize("n", [1, 40, 5000])
+def test_screen_basis(tmp_path, mode, D, n):
+    """Rows of unit length, orthogonal, that turn the rows' covariance to its
+    largest eigenvalues in order. The split holds a row within 2^-17 of its
+    length, so products of rows are within 2^-16 and entries of Phi C Phi^T
+    within 2^-16 of the largest eigenvalue, twice over to be safe."""
+    torch, wl = _images(max(n, 2))
+    from paper_1004_3980_amd import zoomhash as zb
+    ctx = zb.Context(0)
+    hr = torch.from_numpy(wl.dictionary_images()).cuda()
+    pos = torch.from_numpy(wl.positions().astype(np.int32)).cuda()
+    feat = torch.empty((n, D), device="cuda")
+    resid = torch.empty((n, 100), device="cuda")
+    ctx.make_dictionary(hr, hr.shape[0], hr.shape[1], hr.shape[2], pos, n, 2, 1.0, mode, feat, resid)
+    ctx.build_tables(feat, resid, n, D, 2, mode, 2, 2, 8.0, 7)
+    ctx.save_tables(2, str(tmp_path / "t"))
+    m, DP = min(D, 56), (D + 31) // 32 * 32
+    raw = np.fromfile(tmp_path / "t", dtype=np.uint16)[-2 * 64 * DP:].reshape(2, 64, DP)
+    split = (raw.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    assert not raw[:, m:].any() and not raw[:, :, D:].any()
+    phi = (split[0] + split[1])[:m, :D]
+    x = feat.cpu().numpy().astype(np.float64)
+    c = x.T @ x
+    top = np.linalg.eigvalsh(c)[::-1][:m]
+    tol = 2.0 ** -15
+    assert np.abs(phi @ phi.T - np.eye(m)).max() <= tol
+    assert np.abs(phi @ c @ phi.T - np.diag(top)).max() <= tol * top[0]

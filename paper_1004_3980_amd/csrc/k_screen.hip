@@ -20,6 +20,7 @@
 #include <cmath>
 
 #include "zh_internal.h"
+#include "zh_order.h"
 
 namespace zh {
 
@@ -32,7 +33,9 @@ typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 // r_i = floor(i n / ns), taken in order; kCovRows rows are staged in LDS at a
 // time. The lower triangle is cut into kCovParts parts of a thread per entry
 // (blockIdx.y), so that the chip is full. A second kernel adds the block
-// partials in block order. Bound: FP64 issue and LDS reads, 65536 rows at
+// partials in block order. Values that are not finite count as zero, so the
+// basis is finite whatever the features hold; rows with such values get a rho_x
+// that is not a number, and the search rules them out by no bound. Bound: FP64 issue and LDS reads, 65536 rows at
 // D = 100: 0.62 -> 0.21 ms (whole matrix, ten entries a thread, two barriers a row
 // before).
 constexpr int kCovThreads = 1024;
@@ -61,7 +64,10 @@ __global__ __launch_bounds__(kCovThreads) void k_cov_partial(const float* __rest
         __syncthreads();
         // i < ns <= 2^16 and n < 2^31: no overflow
         for (int c = t & 127, r = t >> 7; r < nr; r += kCovThreads / 128)
-            if (c < D) row[r][c] = x[((i + r) * n / ns) * D + c];
+            if (c < D) {
+                const float v = x[((i + r) * n / ns) * D + c];
+                row[r][c] = fabsf(v) < INFINITY ? v : 0.0f;
+            }
         __syncthreads();
         for (int r = 0; r < nr; ++r) acc += (double)row[r][ri] * (double)row[r][ci];
     }
@@ -354,7 +360,7 @@ __global__ __launch_bounds__(256) void k_screen_basis(const double* __restrict__
     const int DP = (D + 31) & ~31;
     for (int j = t; j < D; j += 256) {
         int rank = 0;
-        for (int k = 0; k < D; ++k) rank += eig[k] > eig[j] || (eig[k] == eig[j] && k < j) ? 1 : 0;
+        for (int k = 0; k < D; ++k) rank += before_desc(eig[k], k, eig[j], j) ? 1 : 0;
         order[rank] = j;
     }
     __syncthreads();

@@ -30,6 +30,13 @@ __device__ __forceinline__ bool key_exact(uint64_t key) { return ((key >> 31) & 
 __device__ __forceinline__ uint32_t key_id(uint64_t key) { return (uint32_t)(key & 0x7FFFFFFFu); }
 __device__ __forceinline__ float key_dist(uint64_t key) { return __uint_as_float((uint32_t)(key >> 32)); }
 
+// what a candidate's fp32 distance is held as: its bits, bit 31 set for a row
+// equal to the query; a distance that is not a number counts as infinite, so that
+// it bounds nothing and ranks last, by ID
+__device__ __forceinline__ uint32_t dist_bits(float p, bool equal) {
+    return p == p ? __float_as_uint(p) | (equal ? 0x80000000u : 0u) : 0x7F800000u;
+}
+
 // Bitonic sort of s[0..n) ascending by one wave (n padded to a power of two
 // with 0xFFFFFFFF; s must have room for the padding).
 __device__ void wave_sort_u32(uint32_t* s, int n) {
@@ -157,7 +164,7 @@ __device__ void cand_distances(const float (&qv)[VEC], int D, int HS, const uint
             const uint64_t em = __ballot(eq);
             const uint32_t hm = (uint32_t)(em >> (32 * half));
             const int c = cb + 2 * u + half;
-            if (hl == 0 && cv[u]) cdist[c] = __float_as_uint(p) | (hm == 0xFFFFFFFFu ? 0x80000000u : 0u);
+            if (hl == 0 && cv[u]) cdist[c] = dist_bits(p, hm == 0xFFFFFFFFu);
         }
     }
     __syncthreads();
@@ -242,7 +249,7 @@ __device__ __forceinline__ uint64_t sort_select(const uint32_t* cids, const uint
     return k[0];
 }
 
-// FP64 sequential squared distance: the definition.
+// FP64 sequential squared distance: the definition (not a number: infinite).
 __device__ double exact_dist64(const float* __restrict__ qrow, int D, int HS, const uint16_t* __restrict__ hi,
                                const uint16_t* __restrict__ lo, uint32_t id) {
     const int64_t b = (int64_t)id * D, bh = (int64_t)id * HS;
@@ -251,7 +258,7 @@ __device__ double exact_dist64(const float* __restrict__ qrow, int D, int HS, co
         const double d = (double)qrow[i] - (double)join_planes(hi[bh + i], lo[b + i]);
         s = s + d * d;
     }
-    return s;
+    return s == s ? s : INFINITY;
 }
 
 struct Bounds {
@@ -312,7 +319,7 @@ __device__ void certify_or_fix(const SearchArgs& a, int q, const uint32_t* cids,
     double lastd = 0.0;
     uint32_t lastid = 0;
     for (int r = 0; r < Kp; ++r) {
-        double bestd = 1.0e300;
+        double bestd = INFINITY;
         uint32_t bestid = 0xFFFFFFFFu;
         for (int c = lane; c < M; c += 64) {
             const uint32_t db = cdist[c];
@@ -532,7 +539,7 @@ __device__ __forceinline__ void exact_pass(const SearchArgs& a, const float* sq,
         const uint32_t grp = (uint32_t)(__ballot(eq) >> (8 * rg)) & 0xFFu;
         exact_row = grp == 0xFFu;
     }
-    if (g == 0 && cv) cdist[c] = __float_as_uint(p) | (exact_row ? 0x80000000u : 0u);
+    if (g == 0 && cv) cdist[c] = dist_bits(p, exact_row);
     if constexpr (std::is_same<GT, float>::value) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) z[e] = cv ? z[e] : 0.0f;
@@ -853,7 +860,7 @@ __global__ __launch_bounds__(64, 7) void k_search_cap(SearchArgs a) {
             // U_K: the largest upper bound of the K exact distances
             const Bounds bd{a.dist_eps, (double)D * 1.2e-38};
             // (the bound grows with the distance: that of the largest; equal rows
-            // bound by 0, and a NaN bounds nothing)
+            // bound by 0)
             const uint32_t db = lane < K ? cdist[lane] : 0x80000000u;
             const uint32_t dm = wave_max_u32(db <= 0x7F800000u ? db + 1u : 0u);
             double uk = 0.0;
@@ -1107,7 +1114,7 @@ __global__ __launch_bounds__(64) void k_union_stream(SearchArgs a) {
                     const double z = sq[i] - (double)row[i];
                     acc = acc + z * z;
                 }
-                nd2 = acc;
+                nd2 = acc == acc ? acc : INFINITY;   // not a number: last, by ID
                 ni = (int)chunk[lane];
             }
             double rd = INFINITY;

@@ -342,7 +342,7 @@ __global__ __launch_bounds__(64) void k_knn_rank(int Q, int Drt, int K, int cap,
                     const double t = sq[i] - (double)sx[lane * st + i];
                     acc = acc + (L1 ? fabs(t) : t * t);
                 }
-                d[u] = acc;
+                d[u] = acc == acc ? acc : INFINITY;   // not a number: last, by ID
                 id[u] = myid;
             }
         }
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(64) void k_knn_rank_rows(int Q, int K, int cap, con
                     acc = acc + (L1 ? fabs(dv) : dv * dv);
                 }
             }
-            d[u] = acc;
+            d[u] = acc == acc ? acc : INFINITY;   // not a number: last, by ID
             id[u] = myid;
         }
     }
@@ -715,7 +715,7 @@ __global__ __launch_bounds__(64, 5) void k_knn_l1_screened(int Q, int K, int cap
             if (4 * t + 2 < D4) acc = quad_take<2>(add(acc));
             if (4 * t + 3 < D4) acc = quad_take<3>(add(acc));
         }
-        if (qd == 0 && j < ns) sd[j] = acc;
+        if (qd == 0 && j < ns) sd[j] = acc == acc ? acc : INFINITY;   // not a number: last, by ID
     }
     __syncthreads();
     double d[NCH];

@@ -1,5 +1,7 @@
-"""Training features that are not finite: rows of NaN and of infinities leave the
-tables, the screen's basis and the neighbours of everything else as they are."""
+"""Features that are not finite: training rows of NaN and of infinities leave the
+tables, the screen's basis and the neighbours of everything else as they are, and
+a distance that is not a number ranks last, by ID, in every search, so that each
+neighbour named is one of the candidates."""
 import numpy as np
 import pytest
 
@@ -50,9 +52,25 @@ class Tables:
         ref = lsh.codes(self.x[good], self.a, self.b, WIDTH)
         assert np.array_equal(self.codes[good], ref)
         assert np.array_equal(self.keys[good], lsh.bucket_keys(ref, L, K_HASH))
-        tables = lsh.Tables(self.keys)
+        self.tables = lsh.Tables(self.keys)
         qkeys = lsh.bucket_keys(lsh.codes(self.q, self.a, self.b, WIDTH), L, K_HASH)
-        self.cand = {t: lsh.candidates_t(tables, qkeys, t) for t in (1, 2)}
+        self.cand = {t: lsh.candidates_t(self.tables, qkeys, t) for t in (1, 2)}
+        self.qkeys = qkeys
+
+    def early(self, cap):
+        return self.tables.candidates(self.qkeys, cap)[0]
+
+    def use_image(self, lr):
+        """Another image, whose keys are the library's own."""
+        t = self.torch
+        self.lr = t.from_numpy(lr).cuda()
+        qf = t.empty((self.Q, self.D), device="cuda")
+        self.ctx.features(self.lr, self.h, self.w, self.mode, qf)
+        keys = t.empty((self.Q, L), dtype=t.int64, device="cuda")
+        self.ctx.hash(SCALE, qf, self.Q, None, keys)
+        self.ctx.sync()
+        self.q, self.qkeys = qf.cpu().numpy(), keys.cpu().numpy().view(np.uint64)
+        self.cand = {n: lsh.candidates_t(self.tables, self.qkeys, n) for n in (1, 2)}
 
     def dist(self, q, ids, l1=False):
         """Distances in FP64, what is not a number as the largest."""
@@ -71,7 +89,7 @@ class Tables:
         self.ctx.sync()
         return [v.cpu().numpy() for v in (ids, d, m, nc)]
 
-    def check(self, K, lists, l1=False):
+    def check(self, K, lists, l1=False, exact=True):
         ids, d, m, nc = self.results(K)
         bad = 0
         for q in range(self.Q):
@@ -82,6 +100,9 @@ class Tables:
             order = np.lexsort((c, dist))[:K]
             got = ids[q, :m[q]]
             assert (ids[q, m[q]:] == -1).all()
+            if not exact:
+                assert len(set(got)) == m[q] and set(got) <= set(c), q
+                continue
             if not np.array_equal(got, c[order]):
                 # equal up to the rounding of sums that the oracle takes in another order
                 assert len(set(got)) == m[q] and set(got) <= set(c), q
@@ -124,3 +145,65 @@ def test_every_row_not_finite():
         ctx.hash(SCALE, feat, 70, None, keys)
         ctx.sync()
         assert (keys == keys[0]).all()
+
+
+def _forms(t, K):
+    """Every search and ranking of one image: the neighbours against the oracle's
+    (the forms that rank by bounds or halves of the features: that they are
+    candidates), and the path behind them to its end."""
+    c, bad = t.ctx, 0
+    out = t.torch.empty((SCALE * t.h, SCALE * t.w), device="cuda")
+
+    def finish():
+        c.lle_weights(1e-3)
+        c.reconstruct(out)
+        c.sync()
+
+    for cap in (8, 40):
+        early = t.early(cap)
+        for rerank in (0, 16):
+            for fp64 in (1, 0):
+                c.set_query_opts(cap=cap, rerank=rerank, proj=1, lle_fp64=fp64)
+                c.query(t.lr, t.h, t.w, SCALE, K)
+                bad += t.check(K, early, exact=rerank == 0)
+                finish()
+        c.knn_l1()
+        t.check(K, early, l1=True)
+        finish()
+        c.lle_all(1e-3)
+        c.reconstruct(out)
+        c.set_query_metric("l1")
+        c.query(t.lr, t.h, t.w, SCALE, K)
+        t.check(K, early, l1=True)
+        finish()
+        c.set_query_metric("l2")
+    for rerank in (0, 16):
+        c.set_query_opts(cap=0, rerank=rerank, proj=1, lle_fp64=1)
+        c.query(t.lr, t.h, t.w, SCALE, K)
+        t.check(K, t.cand[1], exact=rerank == 0)
+        finish()
+    c.knn_t(2)
+    t.check(K, t.cand[2])
+    finish()
+    return bad
+
+
+@pytest.mark.parametrize("K", [3, 7, 12])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_searches(mode, K):
+    t = Tables(mode)
+    assert _forms(t, K) > 0, "no patch met a row that is not finite"
+
+
+@pytest.mark.parametrize("K", [3, 12])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_queries_not_finite(mode, K):
+    t = Tables(mode)
+    lr = t.lr.cpu().numpy()
+    lr[3, 4] = np.nan
+    lr[20, 9] = np.inf
+    lr[12:18, 15:21] = -np.inf
+    t.use_image(lr)
+    bad_rows = ~np.isfinite(t.q).all(1)
+    assert bad_rows.any() and any(len(t.cand[1][q]) for q in np.nonzero(bad_rows)[0])
+    _forms(t, K)

@@ -175,7 +175,8 @@ __device__ void gram_fp64_rows(const LleArgs& a, int q, int m, double* Gd) {
 
 // Solve (G + lam tr(G) I) w~ = 1 on the first m rows (rows m..7 are set to
 // the identity with a zero right-hand side), w = w~ / sum(w~). Returns the
-// squared ratio of the largest to the smallest Cholesky diagonal.
+// squared ratio of the largest to the smallest Cholesky diagonal, infinite where
+// a diagonal is not the root of a positive number.
 template <typename T>
 __device__ __forceinline__ double solve8(T (&A)[36], int m, double lam, T (&w)[8]) {
     T tau = (T)0;
@@ -197,6 +198,7 @@ __device__ __forceinline__ double solve8(T (&A)[36], int m, double lam, T (&w)[8
             else if (i == j) x += reg;
         }
     T dmin = (T)0, dmax = (T)0;
+    bool pos = true;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         T s = A[j * (j + 1) / 2 + j];
@@ -205,6 +207,7 @@ __device__ __forceinline__ double solve8(T (&A)[36], int m, double lam, T (&w)[8
         const T d = sqrt(s);
         A[j * (j + 1) / 2 + j] = d;
         if (j < m) {
+            pos = pos && s > (T)0;
             dmin = (j == 0 || d < dmin) ? d : dmin;
             dmax = d > dmax ? d : dmax;
         }
@@ -239,7 +242,7 @@ __device__ __forceinline__ double solve8(T (&A)[36], int m, double lam, T (&w)[8
 #pragma unroll
     for (int i = 0; i < 8; ++i) w[i] = i < m ? w[i] / sum : (T)0;
     const double r = (double)dmax / (double)dmin;
-    return r * r;
+    return pos ? r * r : (double)INFINITY;
 }
 
 template <typename T>
@@ -294,7 +297,9 @@ hipError_t launch_lle_solve(const LleArgs& a, const void* gram, int gram_fp64, h
 // blocks are inverted in place by the symmetric sweep operator, one pivot at
 // a time (the pivot's column reaches the lanes of a row of 16 by a DPP
 // broadcast, its row the four rows by one shuffle). lam > 0 bounds the
-// condition number of A by 1 + 1 / lam, so no pivoting is needed.
+// condition number of A by 1 + 1 / lam, so no pivoting is needed where the
+// precision holds lam tr(G); a pivot that rounding leaves at zero or below is told
+// to the caller.
 //
 // Bound: the Gram tiles' FP64 products (64 cycles each; 28 per tile at D = 100)
 // and, per block, the chain of 16 sweeps. Measured against one wave that
@@ -350,14 +355,15 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return fma(a, b, c); }
 
 // One sweep of the symmetric 16x16 tile d on pivot P (skipped past the n used
-// rows, whose diagonal is -1 already); pmin, pmax: the pivots' range.
+// rows, whose diagonal is -1 already); pmin, pmax: the pivots' range (a pivot that
+// is not a number makes every later one so, and pmin the last of them).
 template <typename T, int Pv>
 __device__ __forceinline__ void sweep_pivot(typename Tile<T>::vec& d, int n, T& pmin, T& pmax) {
     if (Pv >= n) return;
     const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
     constexpr int ip = Tile<T>::reg_of(Pv), gp = Tile<T>::grp_of(Pv);
     const T piv = lane_value(d[ip], 16 * gp + Pv);
-    pmin = piv < pmin ? piv : pmin;
+    pmin = piv >= pmin ? pmin : piv;
     pmax = piv > pmax ? piv : pmax;
     const T inv = (T)1 / piv;
     const T row = __shfl(d[ip], 16 * gp + c) * inv;   // a_pc / a_pp
@@ -402,7 +408,8 @@ template <typename T> __device__ __forceinline__ T row_sum16(T v) {
 
 // Weights of one patch's M <= 16 NB rows xf[id[0..M)] against the query qf, by
 // column into x[b] (entry 16 b + c). Returns the squared ratio of the largest
-// to the smallest Cholesky diagonal (the pivots' ratio).
+// to the smallest Cholesky diagonal (the pivots' ratio), infinite unless every
+// pivot is positive.
 template <typename T, int NB, bool V4>
 __device__ __forceinline__ double lle_wave(int D, int M, double lam, const float* __restrict__ qf,
                                            const float* __restrict__ xf, const int32_t* __restrict__ id, T (&x)[NB]) {
@@ -523,7 +530,7 @@ __device__ __forceinline__ double lle_wave(int D, int M, double lam, const float
     sum = row_sum16(sum);
 #pragma unroll
     for (int b = 0; b < NB; ++b) x[b] = 16 * b + c < M ? x[b] / sum : (T)0;
-    return (double)pmax / (double)pmin;
+    return pmin > (T)0 ? (double)pmax / (double)pmin : (double)INFINITY;
 }
 
 // K <= 16 neighbours, four patches a workgroup. The fp32 form solves again in

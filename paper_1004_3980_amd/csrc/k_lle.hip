@@ -649,9 +649,8 @@ hipError_t launch_lle_all(int Q, int D, int cap, double lam, const float* qfeat,
 // of rows at 6.3 TB/s; 247x259 x2 60 -> 39; 207x303 x4 at K = 12 157 -> 106).
 //
 // An image of few tiles leaves most of the chip idle for the chain of a tile's
-// rows, so its patches are written out after all (k_sb_patch, a thread per
-// load of a residual row) and summed by a thread per HR pixel (k_sb_gather) in
-// the order above, tile by tile: the same bits either way.
+// rows, so its tiles' regions are cut into their rows of LR cells, a workgroup
+// each (k_sb_row): the same sums in the same order into the same regions.
 constexpr int kSbThreads = 512;   // 256 take 5-15% longer
 template <int s, int TI>
 struct SbGeom {
@@ -666,8 +665,9 @@ struct SbGeom {
 };
 
 // Chunk c (VEC floats) of the synthesised patch sum_m w_m r_{n_m}, mq rows of
-// the lists id and wt, as fused multiply-adds in order from zero.
-template <int ps2, int VEC>
+// the lists id and wt, as fused multiply-adds in order from zero. L4: the lists
+// start on 16 bytes and hold a multiple of four entries.
+template <int ps2, int VEC, bool L4 = false>
 __device__ __forceinline__ void synth_chunk(const float* __restrict__ resid, const int* id, const float* wt, int mq,
                                             int c, float (&acc)[VEC]) {
     const char* base = reinterpret_cast<const char*>(resid) + c * (VEC * 4);
@@ -675,12 +675,23 @@ __device__ __forceinline__ void synth_chunk(const float* __restrict__ resid, con
     for (int e = 0; e < VEC; ++e) acc[e] = 0.0f;
     for (int r0 = 0; r0 < mq; r0 += 8) {
         float v[8][VEC], wr[8];
+        [[maybe_unused]] int ir[8];
+        if constexpr (L4) {
+#pragma unroll
+            for (int h = 0; h < 8; h += 4) {
+                const bool ok = r0 + h < mq;
+                const int4 i4 = ok ? *reinterpret_cast<const int4*>(id + r0 + h) : make_int4(0, 0, 0, 0);
+                const float4 w4 = ok ? *reinterpret_cast<const float4*>(wt + r0 + h) : make_float4(0.f, 0.f, 0.f, 0.f);
+                ir[h] = i4.x, ir[h + 1] = i4.y, ir[h + 2] = i4.z, ir[h + 3] = i4.w;
+                wr[h] = w4.x, wr[h + 1] = w4.y, wr[h + 2] = w4.z, wr[h + 3] = w4.w;
+            }
+        }
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
             const bool ok = r0 + r < mq;
-            wr[r] = ok ? wt[r0 + r] : 0.0f;
+            wr[r] = ok ? (L4 ? wr[r] : wt[r0 + r]) : 0.0f;
             const float* x = reinterpret_cast<const float*>(
-                base + (uint64_t)(uint32_t)(ok ? id[r0 + r] : 0) * (uint32_t)(4 * ps2));
+                base + (uint64_t)(uint32_t)(ok ? (L4 ? ir[r] : id[r0 + r]) : 0) * (uint32_t)(4 * ps2));
             if constexpr (VEC == 4) {
                 const float4 t = ok ? *reinterpret_cast<const float4*>(x) : make_float4(0.f, 0.f, 0.f, 0.f);
                 v[r][0] = t.x;
@@ -834,79 +845,77 @@ __global__ __launch_bounds__(256) void k_sb_combine(const float* __restrict__ pa
     }
 }
 
-// Images of few tiles, first kernel: the synthesised patches [Q][ps2], a
-// thread per VEC values. Lists of neighbours staged per workgroup.
-template <int s>
-__global__ __launch_bounds__(256) void k_sb_patch(int Q, int K, const int32_t* __restrict__ ids,
-                                                  const int32_t* __restrict__ m, const float* __restrict__ wt,
-                                                  const double* __restrict__ mu, const float* __restrict__ resid,
-                                                  float* __restrict__ x) {
-    using G = SbGeom<s, kSbRows>;
-    constexpr int ps2 = G::ps2, VEC = G::VEC, NCH = G::NCH;
-    const int64_t it = (int64_t)xcd_block() * 256 + threadIdx.x;
-    const int q = (int)(it / NCH), c = (int)(it - (int64_t)q * NCH);
-    if (q >= Q) return;
-    const int mq = min(m[q], K);
-    float acc[VEC];
-    synth_chunk<ps2, VEC>(resid, ids + (int64_t)q * K, wt + (int64_t)q * K, mq, c, acc);
-    const float mf = mq > 0 ? (float)mu[q] : 0.0f;   // a patch without neighbours: zeros
-    float* dst = x + (int64_t)q * ps2 + c * VEC;
-    if constexpr (VEC == 4)
-        *reinterpret_cast<float4*>(dst) = make_float4(mf + acc[0], mf + acc[1], mf + acc[2], mf + acc[3]);
-    else
-        dst[0] = mf + acc[0];
-}
-
-// Second kernel, a thread per HR pixel: the sums of its patches inside each
-// tile (from zero, rows then columns ascending), added tile by tile.
-template <int s, int TI>
-__global__ __launch_bounds__(256) void k_sb_gather(const float* __restrict__ x, const int32_t* __restrict__ m,
-                                                   const float* __restrict__ lr, int h, int w,
-                                                   float* __restrict__ hr) {
+// Images of few tiles: a workgroup takes one row of LR cells of a tile's region
+// (s HR rows) and the up to five patch rows that cover it. A patch gives each row
+// of cells s of its own rows and no HR pixel twice, so nothing is formed twice;
+// all the patches' values are formed at once (one chain of loads), then added per
+// pixel in the tile's order (patch rows, then columns, ascending from zero).
+// Bound: that chain on small images; above, lines of the pieces of residual rows and
+// of the lists in the vector cache (lists of 72 at 150 tiles x2 entry by entry 145
+// us, in 16-byte loads 88). 512 threads: with 256 the smallest images take 2-8 us more,
+// with 1024 those of 150 tiles 6 us; two rows of cells a workgroup 2-24 us more.
+template <int s, int TI, bool L4>
+__global__ __launch_bounds__(kSbThreads) void k_sb_row(int K, int h, int w, const int32_t* __restrict__ ids,
+                                                       const int32_t* __restrict__ m, const float* __restrict__ wt,
+                                                       const double* __restrict__ mu,
+                                                       const float* __restrict__ resid, float* __restrict__ part) {
     using G = SbGeom<s, TI>;
-    constexpr int ps = G::ps, ps2 = G::ps2, TJ = G::TJ;
-    const int W = s * w;
-    const int64_t p = (int64_t)xcd_block() * 256 + threadIdx.x;
-    if (p >= (int64_t)s * h * W) return;
-    const int Y = (int)(p / W), X = (int)(p - (int64_t)Y * W);
+    constexpr int ps = G::ps, ps2 = G::ps2, VEC = G::VEC, TJ = G::TJ, CY = G::CY, CX = G::CX, RX = G::RX, RY = G::RY;
+    constexpr int SEG = s * ps, NC = SEG / VEC, NT = kSbThreads;   // a patch's values in a row of cells, its loads of them
+    static_assert(SEG % VEC == 0 && TJ <= 64, "whole loads; a lane for each column");
+    __shared__ __align__(16) float sx[kPatch * TJ * SEG];
+    __shared__ int smq[kPatch][64];
     const int npi = h - kPatch + 1, npj = w - kPatch + 1;
-    const int cy = Y / s, cx = X / s;
-    const int ilo = max(0, cy - (kPatch - 1)), ihi = min(npi - 1, cy);
-    const int jlo = max(0, cx - (kPatch - 1)), jhi = min(npj - 1, cx);
-    // all values in flight; patches outside the image or without neighbours add zero
-    float v[kPatch][kPatch];
-    int cnt = 0;
-    const int64_t q0 = (int64_t)ilo * npj + jlo;
-    const float* x0 = x + q0 * ps2 + (Y - s * ilo) * ps + (X - s * jlo);
-#pragma unroll
-    for (int a = 0; a < kPatch; ++a)
-#pragma unroll
-        for (int b = 0; b < kPatch; ++b) {
-            const bool in = ilo + a <= ihi && jlo + b <= jhi;
-            v[a][b] = in ? x0[((int64_t)a * npj + b) * ps2 - s * (a * ps + b)] : 0.0f;
-            cnt += in ? (m[q0 + (int64_t)a * npj + b] > 0 ? 1 : 0) : 0;
-        }
-    // the first row and column that belong to a second tile; t0 and t1 the sums
-    // of the tiles left and right of that column
-    const int isplit = (ilo / TI + 1) * TI - ilo, jsplit = (jlo / TJ + 1) * TJ - jlo;
-    float acc = 0.0f, t0 = 0.0f, t1 = 0.0f;
-#pragma unroll
-    for (int a = 0; a < kPatch; ++a) {
-        if (a > 0) {
-            const bool next = a == isplit;
-            const float done = (acc + t0) + t1;
-            acc = next ? done : acc;
-            t0 = next ? 0.0f : t0;
-            t1 = next ? 0.0f : t1;
-        }
-#pragma unroll
-        for (int b = 0; b < kPatch; ++b) {
-            t0 += b < jsplit ? v[a][b] : 0.0f;
-            t1 += b < jsplit ? 0.0f : v[a][b];
-        }
+    const int ntj = (npj + TJ - 1) / TJ;
+    const int64_t b = xcd_block(), tile = b / CY;
+    const int cy = (int)(b - tile * CY);
+    if (tile >= (int64_t)((npi + TI - 1) / TI) * ntj) return;
+    const int i0 = (int)(tile / ntj) * TI, j0 = (int)(tile % ntj) * TJ;
+    const int nr = min(TI, npi - i0), nc = min(TJ, npj - j0);
+    const int ilo = max(0, cy - (kPatch - 1)), n = min(nr - 1, cy) - ilo + 1;
+    if (n <= 0) return;   // past the image
+    const int tid = threadIdx.x;
+    for (int it = tid; it < n * TJ * NC; it += NT) {
+        const int r = it / (TJ * NC), jc = it - r * (TJ * NC), jj = jc / NC, c = jc - jj * NC;
+        const int64_t q = (int64_t)(i0 + ilo + r) * npj + j0 + jj;
+        const int mq = jj < nc ? min(m[q], K) : 0;
+        float acc[VEC];
+        synth_chunk<ps2, VEC, L4>(resid, ids + q * K, wt + q * K, mq, (cy - ilo - r) * NC + c, acc);
+        const float mf = mq > 0 ? (float)mu[q] : 0.0f;
+        float* dst = sx + (r * TJ + jj) * SEG + c * VEC;
+        if constexpr (VEC == 4)
+            *reinterpret_cast<float4*>(dst) = make_float4(mf + acc[0], mf + acc[1], mf + acc[2], mf + acc[3]);
+        else
+            dst[0] = mf + acc[0];
+        if (c == 0) smq[r][jj] = mq;
     }
-    acc = (acc + t0) + t1;
-    hr[p] = cnt > 0 ? acc / (float)cnt : bicubic_at(lr, h, w, s, Y, X);
+    __syncthreads();
+    uint64_t has[kPatch];   // patches of each row that have neighbours
+#pragma unroll
+    for (int r = 0; r < kPatch; ++r) {
+        const int jj = tid & 63;
+        has[r] = __ballot(r < n && jj < TJ && smq[r][jj] > 0);
+    }
+    float* pa = part + tile * G::PART;
+    int* pc = reinterpret_cast<int*>(pa + RY * RX);
+    for (int it = tid; it < s * RX; it += NT) {
+        const int u = it / RX, X = it - u * RX, cl = X / s;
+        const int jlo = cl - (kPatch - 1) > 0 ? cl - (kPatch - 1) : 0, jhi = cl < TJ - 1 ? cl : TJ - 1;
+        float acc = 0.0f;
+#pragma unroll
+        for (int r = 0; r < kPatch; ++r)
+            for (int jj = jlo; jj <= jhi; ++jj)
+                if ((has[r] >> jj) & 1u) acc += sx[(r * TJ + jj) * SEG + u * ps + X - s * jj];
+        pa[(s * cy + u) * RX + X] = acc;
+    }
+    for (int cl = tid; cl < CX; cl += NT) {
+        const int jlo = cl - (kPatch - 1) > 0 ? cl - (kPatch - 1) : 0, jhi = cl < TJ - 1 ? cl : TJ - 1;
+        const uint64_t cols = (2ull << jhi) - (1ull << jlo);
+        int cnt = 0;
+#pragma unroll
+        for (int r = 0; r < kPatch; ++r) cnt += __popcll(has[r] & cols);
+        pc[cy * CX + cl] = cnt;
+    }
 }
 
 // Batched: the tiles and HR pixels of every image of the batch, the image
@@ -949,19 +958,17 @@ int64_t sb_part_floats(int s, int rows) {
     return cy * s * cx * s + cy * cx;
 }
 
-// Written out below 200 tiles: there the tiles run one after the other on a
-// chip that is not full (us, written out against fused: 60x60 patches x2 11
-// and 37, 116x127 x2 20 and 40, 196x212 x2 29 and 41, 146x166 x2 with 72-row
-// lists 80 and 189), above it the patches' way through memory costs more
-// (247x259 x2 45 and 44, 316x402 x1 55 and 43, 207x303 x4 154 and 115).
-bool sb_unfused(int s, int rows, int h, int w) { return sb_tiles(s, rows, h, w) < 200; }
-
-int64_t sb_scratch_floats(int s, int rows, int h, int w) {
-    if (h < kPatch || w < kPatch) return 0;
-    if (sb_unfused(s, rows, h, w))
-        return (int64_t)(h - kPatch + 1) * (w - kPatch + 1) * (kPatch * s) * (kPatch * s);
-    return sb_tiles(s, rows, h, w) * sb_part_floats(s, rows);
-}
+// Rows of cells below the line, whole tiles from it on: with few tiles the tiles'
+// chains leave the chip idle, with many the pieces of the residual rows cost more.
+// Lists in 16-byte loads, both kernels, us in rows and in tiles (140k pairs, caches
+// as the query leaves them): x2, K = 8, 16 tiles 17 and 37, 150 32 and 52, 217 39 and
+// 52, 333 52 and 59; lists of 72 150 tiles 99 and 192, 333 147 and 193; x3 220 tiles
+// 53 and 78, 350 73 and 81; x4 220 44 and 69, 494 81 and 79. x1 100 tiles 22 and 37,
+// 210 32 and 41, 390 48 and 45; lists of 72 210 tiles 109 and 155, 390 175 and 163.
+// Entry by entry (12k pairs, caches warm): x2, K = 8, 150 tiles 30 and 39, 217 39 and
+// 40, 333 54 and 44. (A form that wrote the patches out took x2 18, 38, 51 and 69, and
+// ten times the tiles' scratch.)
+static int64_t sb_few_tiles(int s, bool l4) { return l4 && s > 1 ? 300 : 200; }
 
 template <int s, int TI>
 static hipError_t sb_launch(int K, int h, int w, const int32_t* ids, const int32_t* m, const float* wt,
@@ -969,20 +976,16 @@ static hipError_t sb_launch(int K, int h, int w, const int32_t* ids, const int32
                             hipStream_t st, int which) {
     using G = SbGeom<s, TI>;
     const int64_t nt = sb_tiles(s, TI, h, w), total = (int64_t)s * h * s * w;
-    if (nt > 0 && sb_unfused(s, TI, h, w)) {
-        const int Q = (h - kPatch + 1) * (w - kPatch + 1);
-        if (which & 1)
-            hipLaunchKernelGGL(k_sb_patch<s>, dim3((unsigned)round_grid8((int)(((int64_t)Q * G::NCH + 255) / 256))),
-                               dim3(256), 0, st, Q, K, ids, m, wt, mu, resid, part);
-        if (which & 2)
-            hipLaunchKernelGGL((k_sb_gather<s, TI>), dim3((unsigned)round_grid8((int)((total + 255) / 256))), dim3(256),
-                               0, st, part, m, lr, h, w, hr);
-        return hipGetLastError();
-    }
     if (which & 1 && nt > 0) {
         if (nt > 0x7FFFFFFF) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_sb_tile<s, TI>), dim3((unsigned)round_grid8((int)nt)), dim3(kSbThreads), G::lds(K), st, K,
-                           h, w, ids, m, wt, mu, resid, part);
+        const bool l4 = K % 4 == 0 && ((reinterpret_cast<uintptr_t>(ids) | reinterpret_cast<uintptr_t>(wt)) & 15) == 0;
+        if (nt < sb_few_tiles(s, l4))
+            hipLaunchKernelGGL((l4 ? k_sb_row<s, TI, true> : k_sb_row<s, TI, false>),
+                               dim3((unsigned)round_grid8((int)nt * G::CY)), dim3(kSbThreads), 0, st, K, h, w, ids, m, wt,
+                               mu, resid, part);
+        else
+            hipLaunchKernelGGL((k_sb_tile<s, TI>), dim3((unsigned)round_grid8((int)nt)), dim3(kSbThreads), G::lds(K), st,
+                               K, h, w, ids, m, wt, mu, resid, part);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -1392,7 +1392,7 @@ zh_status zh_reconstruct(zh_ctx* c, float* hr_out) {
     const int32_t* cnt = P<int32_t>(c->all_m ? c->ncand : c->m);
     const float* wt = P<float>(c->all_m ? c->wall : c->w);
     const int K = c->all_m ? c->all_cap : c->qK;
-    TRY(ensure(c, c->sbpart, sizeof(float) * (size_t)sb_scratch_floats(s, c->sb_rows, c->qh, c->qw)));
+    TRY(ensure(c, c->sbpart, sizeof(float) * (size_t)(sb_tiles(s, c->sb_rows, c->qh, c->qw) * sb_part_floats(s, c->sb_rows))));
     {
         StageTimer t(c, ZH_T_SYNTH);
         HIPCHK(c, launch_synth_blend(s, c->sb_rows, K, c->qh, c->qw, ids, cnt, wt, P<double>(c->qmu), d.resid,

@@ -284,8 +284,6 @@ __host__ __device__ constexpr int sb_cols(int s) { return s <= 2 ? 40 : 16; }
 constexpr int kSbRows = 8;   // tile height of the single-image call
 int64_t sb_tiles(int s, int rows, int h, int w);
 int64_t sb_part_floats(int s, int rows);
-bool sb_unfused(int s, int rows, int h, int w);          // the patches are written out (images of few tiles)
-int64_t sb_scratch_floats(int s, int rows, int h, int w);   // floats of `part` for launch_synth_blend
 hipError_t launch_synth_blend(int scale, int rows, int K, int h, int w, const int32_t* ids, const int32_t* m,
                               const float* wt, const double* mu, const float* resid, float* part, const float* lr,
                               float* hr, hipStream_t st, int which = 3);

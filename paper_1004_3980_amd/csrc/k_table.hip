@@ -274,9 +274,9 @@ __global__ __launch_bounds__(256) void k_rs_scatter(const uint32_t* __restrict__
     }
 }
 
-hipError_t radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, bool index_values,
-                            uint32_t* vfinal, int64_t n, int tables, int bits, uint32_t* hist, int64_t hist_cap,
-                            hipStream_t st, uint32_t** keys_out, uint32_t** vals_out) {
+hipError_t radix_sort_pairs(uint32_t* k0, uint32_t* k1, uint32_t* v0, uint32_t* v1, bool index_values, int64_t n,
+                            int tables, int bits, uint32_t* hist, int64_t hist_cap, hipStream_t st,
+                            uint32_t** keys_out, uint32_t** vals_out) {
     const int width = rs_width(bits);
     const int bins = 1 << width;
     const int64_t ntiles = (n + kRsTile - 1) / kRsTile;
@@ -285,11 +285,15 @@ hipError_t radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* 
         return hipErrorInvalidValue;
     const int64_t rows = (int64_t)tables * bins;
     uint32_t* total = hist + rows * ntiles;
-    uint32_t *kin = k0, *kout = k1, *vin = index_values ? nullptr : v0, *vout = v1;
+    const int passes = (bits + width - 1) / width;
+    // the values of the last pass, and of every second before it, go to `last`
+    uint32_t* const last = index_values || passes % 2 == 0 ? v0 : v1;
+    uint32_t *kin = k0, *kout = k1, *vin = index_values ? nullptr : v0;
     const dim3 grid((unsigned)ntiles, tables);
-    for (int shift = 0; shift < bits; shift += width) {
+    for (int p = 0; p < passes; ++p) {
+        const int shift = p * width;
         const int wd = bits - shift < width ? bits - shift : width;   // bins past 2^wd stay empty
-        if (vfinal && shift + width >= bits) vout = vfinal;
+        uint32_t* vout = (passes - 1 - p) % 2 == 0 ? last : last == v0 ? v1 : v0;
         hipLaunchKernelGGL(k_rs_hist, grid, dim3(256), sizeof(uint32_t) * bins, st, kin, n, shift, width, hist,
                            (int)ntiles);
         hipLaunchKernelGGL(k_rs_scan_tiles, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, hist, rows, (int)ntiles,
@@ -301,7 +305,6 @@ hipError_t radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* 
         if (e != hipSuccess) return e;
         std::swap(kin, kout);
         vin = vout;
-        vout = vin == v1 ? v0 : v1;
     }
     *keys_out = kin;
     *vals_out = vin;

@@ -128,7 +128,7 @@ struct zh_ctx {
     Buf tools;                    // scratch of the training-crop sampler and the entropy diagnostic
     Buf l1cand;                   // [Q, cap] candidate lists of the l1 re-rank and of zh_lle_all
     Buf wall;                     // [Q, cap] weights over all matches (zh_lle_all)
-    Buf rs_k1, rs_v1, rs_hist, slot_of, idsort, keys_dict;
+    Buf keys_dict;                // keys and scratch of a build
     // stage timing
     bool timing = false;
     uint32_t timing_mask = ~0u;   // stages bracketed with events while timing is on
@@ -608,8 +608,7 @@ void zh_destroy(zh_ctx* c) {
     release(c, c->batch.scr);
     release(c, c->batch.e);
     Buf* bufs[] = {&c->lr, &c->qfeat, &c->qmu, &c->qkeys, &c->qbins, &c->ids, &c->d2, &c->m,
-                   &c->ncand, &c->w, &c->over, &c->sbpart, &c->e, &c->tmp, &c->counters, &c->rs_k1,
-                   &c->rs_v1, &c->rs_hist, &c->slot_of, &c->idsort, &c->keys_dict, &c->gram, &c->hmask, &c->fixl, &c->fixc, &c->nsurv, &c->guides, &c->bwd, &c->bwd_k, &c->clam, &c->qrot, &c->bwd_gw, &c->bwd_part, &c->tools, &c->l1cand, &c->chk, &c->wall, &c->longs};
+                   &c->ncand, &c->w, &c->over, &c->sbpart, &c->e, &c->tmp, &c->counters, &c->keys_dict, &c->gram, &c->hmask, &c->fixl, &c->fixc, &c->nsurv, &c->guides, &c->bwd, &c->bwd_k, &c->clam, &c->qrot, &c->bwd_gw, &c->bwd_part, &c->tools, &c->l1cand, &c->chk, &c->wall, &c->longs};
     for (Buf* b : bufs) release(c, *b);
     delete c;
 }
@@ -712,6 +711,9 @@ zh_status zh_features(zh_ctx* c, const float* lr, int h, int w, int mode, float*
     return ZH_OK;
 }
 
+// Entries of the tables that a build takes at a time.
+constexpr int64_t kBuildEntries = (int64_t)8 << 20;
+
 zh_status zh_build_tables(zh_ctx* c, const zh_dictionary* dict, int L, int k, float w, uint64_t seed) {
     if (!c) return ZH_EINVAL;
     if (!dict || !dict->feat || !dict->resid || dict->n < 1 || dict->n >= (1ll << 31) ||
@@ -748,6 +750,11 @@ zh_status zh_build_tables(zh_ctx* c, const zh_dictionary* dict, int L, int k, fl
     SideStream side(c);
     TRY(side.start());
     TRY(start_screen(c, d, dict->feat, c->batch.stream, &s2_dev));
+    if (c->mem_limit) {   // under a limit its scratch is given back first
+        TRY(side.join());
+        TRY(finish_screen(c, d, s2_dev));
+        release(c, c->tools);
+    }
     TRY(start_hash(c, dict->feat, sizeof(float) * (uint64_t)n * D, 0));
     // hash parameters, formed on the host while the device works on the above
     hash_params(seed, L, k, D, (double)w, d.h_alpha, d.h_beta);
@@ -786,12 +793,10 @@ zh_status zh_build_tables(zh_ctx* c, const zh_dictionary* dict, int L, int k, fl
     HIPCHK(c, hipMemcpyAsync(d.beta.p, d.h_beta.data(), sizeof(float) * (size_t)m, hipMemcpyHostToDevice, c->stream));
     for (int pr = 0; pr < 2; ++pr)
         HIPCHK(c, hipMemcpyAsync(d.bc0[pr].p, bc0[pr].data(), sizeof(float) * (size_t)m, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipMemcpyAsync(d.ahi.p, ahi.data(), sizeof(uint16_t) * (size_t)m * DP, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(d.alo.p, alo.data(), sizeof(uint16_t) * (size_t)m * DP, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));   // the host arrays end with the call, also where it fails below
     TRY(make_hash_images(c, d));
-    // keys of every pair in every table
-    TRY(ensure(c, c->keys_dict, sizeof(uint64_t) * (size_t)n * L));
     TRY(clear_counters(c));
     HashArgs ha{};
     ha.feat = dict->feat;
@@ -805,55 +810,58 @@ zh_status zh_build_tables(zh_ctx* c, const zh_dictionary* dict, int L, int k, fl
     set_bounds(ha, d, c->opts.proj);
     ha.w = w;
     ha.prec = c->opts.proj;
-    ha.keys = P<uint64_t>(c->keys_dict);
     ha.keys_tmajor = 1;
     ha.codes = nullptr;
     ha.n_fixed = P<unsigned int>(c->counters) + C_CODEFIX;
     TRY(hash_scratch(c, ha));
-    HIPCHK(c, launch_hash(ha, c->stream));
-    // directory and bins, G tables at a time (about 8M entries: enough to fill
-    // the chip, 128 MB of scratch; one table at a time when that is not to be had)
-    TRY(ensure(c, d.dir, sizeof(Slot) * (size_t)L * cap));
     const uint64_t fw = dir_filter_words(cap);
+    TRY(ensure(c, d.dir, sizeof(Slot) * (size_t)L * cap));
     TRY(ensure(c, d.dfilt, sizeof(uint32_t) * (size_t)L * fw));
-    HIPCHK(c, hipMemsetAsync(d.dfilt.p, 0, sizeof(uint32_t) * (size_t)L * fw, c->stream));
     TRY(ensure(c, d.tids, sizeof(uint32_t) * (size_t)L * n));
+    // keys of every pair in every table, and behind them the scratch of the tables
+    // below, G of them at a time (kBuildEntries entries; one table at a time when
+    // that is not to be had): held for the build only, and asked for last
     int bits = 1;
     while ((1ull << bits) < cap) ++bits;
-    int G = (int)std::min<int64_t>(L, std::max<int64_t>(1, ((int64_t)8 << 20) / n));
-    Buf* scr[5] = {&c->slot_of, &c->idsort, &c->rs_k1, &c->rs_v1, &c->rs_hist};
-    auto sort_scratch = [&]() -> zh_status {
-        for (int i = 0; i < 4; ++i) TRY(ensure(c, *scr[i], sizeof(uint32_t) * (size_t)G * n));
-        return ensure(c, *scr[4], sizeof(uint32_t) * (size_t)radix_hist_size(n, G, bits));
+    int G = (int)std::min<int64_t>(L, std::max<int64_t>(1, kBuildEntries / n));
+    auto build_scratch = [&]() {
+        return ensure(c, c->keys_dict, sizeof(uint64_t) * (size_t)n * L + sizeof(uint32_t) * (size_t)G * n +
+                                           sizeof(uint32_t) * (size_t)radix_hist_size(n, G, bits));
     };
     {
-        zh_status ss = sort_scratch();
+        zh_status ss = build_scratch();
         if (ss == ZH_ENOMEM && G > 1) {
-            for (Buf* b : scr) release(c, *b);
             G = 1;
-            ss = sort_scratch();
+            ss = build_scratch();
         }
         if (ss != ZH_OK) return ss;
     }
+    ha.keys = P<uint64_t>(c->keys_dict);
+    HIPCHK(c, launch_hash(ha, c->stream));
+    // directory and bins. The keys of a group are read once, by the insertion: the
+    // sort's second key and value arrays lie in their place, and the sorted values are
+    // the table's IDs.
+    HIPCHK(c, hipMemsetAsync(d.dfilt.p, 0, sizeof(uint32_t) * (size_t)L * fw, c->stream));
+    uint32_t* slot_of = reinterpret_cast<uint32_t*>(P<uint64_t>(c->keys_dict) + (size_t)n * L);
+    uint32_t* hist = slot_of + (size_t)G * n;
     HIPCHK(c, launch_dir_clear(P<Slot>(d.dir), (uint64_t)L * cap, c->stream));
     for (int l = 0; l < L; l += G) {
         const int g = std::min(G, L - l);
         Slot* dl = P<Slot>(d.dir) + (size_t)l * cap;
-        HIPCHK(c, launch_dir_insert(P<uint64_t>(c->keys_dict) + (size_t)l * n, n, g, dl, cap,
-                                    P<uint32_t>(d.dfilt) + (size_t)l * fw, P<uint32_t>(c->slot_of), c->stream));
+        uint64_t* keys = P<uint64_t>(c->keys_dict) + (size_t)l * n;
+        HIPCHK(c, launch_dir_insert(keys, n, g, dl, cap, P<uint32_t>(d.dfilt) + (size_t)l * fw, slot_of, c->stream));
+        uint32_t* k1 = reinterpret_cast<uint32_t*>(keys);
         uint32_t *sk = nullptr, *sv = nullptr;
-        HIPCHK(c, radix_sort_pairs(P<uint32_t>(c->slot_of), P<uint32_t>(c->idsort), P<uint32_t>(c->rs_k1),
-                                   P<uint32_t>(c->rs_v1), true, P<uint32_t>(d.tids) + (size_t)l * n, n, g, bits,
-                                   P<uint32_t>(c->rs_hist), radix_hist_size(n, G, bits), c->stream, &sk, &sv));
+        HIPCHK(c, radix_sort_pairs(slot_of, k1, P<uint32_t>(d.tids) + (size_t)l * n, k1 + (size_t)g * n, true, n, g, bits,
+                                   hist, radix_hist_size(n, G, bits), c->stream, &sk, &sv));
         HIPCHK(c, launch_dir_offsets(sk, n, g, dl, cap, c->stream));
     }
-    TRY(side.join());
-    TRY(finish_screen(c, d, s2_dev));   // synchronises
-    release(c, c->keys_dict);
-    if (c->mem_limit) {   // scratch of the build: not held against the limit of later calls
-        for (Buf* b : scr) release(c, *b);
-        release(c, c->tools);
+    if (!c->mem_limit) {
+        TRY(side.join());
+        TRY(finish_screen(c, d, s2_dev));
     }
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    release(c, c->keys_dict);
     d.valid = true;
     return ZH_OK;
 }
@@ -1661,7 +1669,7 @@ zh_status zh_backward(zh_ctx* c, const float* g_hr, float* g_resid, float* g_lam
     if (E > 0) {
         HIPCHK(c, launch_nbr_pairs(P<int32_t>(c->ids), P<int32_t>(c->m), (int)Q, K, none, k0, v0, c->stream));
         uint32_t *sk = nullptr, *sv = nullptr;
-        HIPCHK(c, radix_sort_pairs(k0, v0, k1, v1, false, nullptr, E, 1, bits, hist, hsz, c->stream, &sk, &sv));
+        HIPCHK(c, radix_sort_pairs(k0, k1, v0, v1, false, E, 1, bits, hist, hsz, c->stream, &sk, &sv));
         const int64_t nchunk = (E + 63) / 64;
         TRY(ensure(c, c->bwd_part, sizeof(float) * 2 * (size_t)ps2 * nchunk + 8 * (size_t)nchunk));
         float* part = P<float>(c->bwd_part);

@@ -131,13 +131,13 @@ hipError_t launch_dir_insert(const uint64_t* keys, int64_t n, int tables, Slot* 
 hipError_t launch_dir_offsets(const uint32_t* sorted_slot, int64_t n, int tables, Slot* dir, uint64_t cap,
                               hipStream_t st);
 // stable LSD radix sort, table by table, of the (key, value) pairs [tables, n]
-// in k0, v0 on the low `bits` bits of the key (higher bits zero); index_values:
-// the values are the indexes 0 .. n - 1 of each table and v0 is scratch only.
-// k1, v1: scratch of the same size; vfinal (nullable) receives the values.
+// in k0, v0 on the low `bits` bits of the key (higher bits zero); k1, v1: scratch
+// of the same size, and the result in one of each. index_values: the values are
+// the indexes 0 .. n - 1 of each table, v0 holds nothing and receives them sorted.
 // hist: radix_hist_size(n, tables, bits) words
-hipError_t radix_sort_pairs(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, bool index_values,
-                            uint32_t* vfinal, int64_t n, int tables, int bits, uint32_t* hist, int64_t hist_cap,
-                            hipStream_t st, uint32_t** keys_out, uint32_t** vals_out);
+hipError_t radix_sort_pairs(uint32_t* k0, uint32_t* k1, uint32_t* v0, uint32_t* v1, bool index_values, int64_t n,
+                            int tables, int bits, uint32_t* hist, int64_t hist_cap, hipStream_t st,
+                            uint32_t** keys_out, uint32_t** vals_out);
 int64_t radix_hist_size(int64_t n, int tables, int bits);
 // adds the content hash of n_words 32-bit words at p into *out (cleared by
 // the caller): sum_i fmix64((i G + salt) ^ word_i) mod 2^64, G = kGolden

@@ -845,6 +845,10 @@ __global__ __launch_bounds__(256) void k_sb_combine(const float* __restrict__ pa
     }
 }
 
+// how a workgroup reads the lists of neighbours and weights: entry by entry, in
+// 16-byte loads (lists of a multiple of four entries), or staged in LDS
+enum SbLists { kSbEntries, kSbWide, kSbStaged };
+
 // Images of few tiles: a workgroup takes one row of LR cells of a tile's region
 // (s HR rows) and the up to five patch rows that cover it. A patch gives each row
 // of cells s of its own rows and no HR pixel twice, so nothing is formed twice;
@@ -854,7 +858,7 @@ __global__ __launch_bounds__(256) void k_sb_combine(const float* __restrict__ pa
 // of the lists in the vector cache (lists of 72 at 150 tiles x2 entry by entry 145
 // us, in 16-byte loads 88). 512 threads: with 256 the smallest images take 2-8 us more,
 // with 1024 those of 150 tiles 6 us; two rows of cells a workgroup 2-24 us more.
-template <int s, int TI, bool L4>
+template <int s, int TI, SbLists LM>
 __global__ __launch_bounds__(kSbThreads) void k_sb_row(int K, int h, int w, const int32_t* __restrict__ ids,
                                                        const int32_t* __restrict__ m, const float* __restrict__ wt,
                                                        const double* __restrict__ mu,
@@ -875,12 +879,26 @@ __global__ __launch_bounds__(kSbThreads) void k_sb_row(int K, int h, int w, cons
     const int ilo = max(0, cy - (kPatch - 1)), n = min(nr - 1, cy) - ilo + 1;
     if (n <= 0) return;   // past the image
     const int tid = threadIdx.x;
+    extern __shared__ int slist[];   // kSbStaged: IDs [5][TJ][K], then weights
+    float* swt = reinterpret_cast<float*>(slist + kPatch * TJ * K);
+    if (LM == kSbStaged) {
+        for (int e = tid; e < n * TJ * K; e += NT) {
+            const int r = e / (TJ * K), o = e - r * (TJ * K);
+            const int64_t p = ((int64_t)(i0 + ilo + r) * npj + j0) * K + o;
+            if (o < nc * K) slist[e] = ids[p], swt[e] = wt[p];
+        }
+        __syncthreads();
+    }
     for (int it = tid; it < n * TJ * NC; it += NT) {
         const int r = it / (TJ * NC), jc = it - r * (TJ * NC), jj = jc / NC, c = jc - jj * NC;
         const int64_t q = (int64_t)(i0 + ilo + r) * npj + j0 + jj;
         const int mq = jj < nc ? min(m[q], K) : 0;
         float acc[VEC];
-        synth_chunk<ps2, VEC, L4>(resid, ids + q * K, wt + q * K, mq, (cy - ilo - r) * NC + c, acc);
+        const int chunk = (cy - ilo - r) * NC + c;
+        if (LM == kSbStaged)
+            synth_chunk<ps2, VEC>(resid, slist + (r * TJ + jj) * K, swt + (r * TJ + jj) * K, mq, chunk, acc);
+        else
+            synth_chunk<ps2, VEC, LM == kSbWide>(resid, ids + q * K, wt + q * K, mq, chunk, acc);
         const float mf = mq > 0 ? (float)mu[q] : 0.0f;
         float* dst = sx + (r * TJ + jj) * SEG + c * VEC;
         if constexpr (VEC == 4)
@@ -958,17 +976,25 @@ int64_t sb_part_floats(int s, int rows) {
     return cy * s * cx * s + cy * cx;
 }
 
+// Up to 16 neighbours the lists of a workgroup's patches fit beside their values in
+// LDS (25.6 KB). us entry by entry, in 16-byte loads and staged, both kernels, 140k
+// pairs, caches as the query leaves them: x2, 150 tiles, K = 5 33, -, 30, K = 8 40, 33,
+// 33, K = 15 54, -, 44; x3, 220 tiles, K = 5 64, -, 45, K = 8 78, 54, 49.
+static SbLists sb_lists(int K, const int32_t* ids, const float* wt) {
+    if (K <= kMaxK) return kSbStaged;
+    return K % 4 == 0 && ((reinterpret_cast<uintptr_t>(ids) | reinterpret_cast<uintptr_t>(wt)) & 15) == 0 ? kSbWide
+                                                                                                          : kSbEntries;
+}
 // Rows of cells below the line, whole tiles from it on: with few tiles the tiles'
 // chains leave the chip idle, with many the pieces of the residual rows cost more.
-// Lists in 16-byte loads, both kernels, us in rows and in tiles (140k pairs, caches
-// as the query leaves them): x2, K = 8, 16 tiles 17 and 37, 150 32 and 52, 217 39 and
-// 52, 333 52 and 59; lists of 72 150 tiles 99 and 192, 333 147 and 193; x3 220 tiles
-// 53 and 78, 350 73 and 81; x4 220 44 and 69, 494 81 and 79. x1 100 tiles 22 and 37,
-// 210 32 and 41, 390 48 and 45; lists of 72 210 tiles 109 and 155, 390 175 and 163.
-// Entry by entry (12k pairs, caches warm): x2, K = 8, 150 tiles 30 and 39, 217 39 and
-// 40, 333 54 and 44. (A form that wrote the patches out took x2 18, 38, 51 and 69, and
-// ten times the tiles' scratch.)
-static int64_t sb_few_tiles(int s, bool l4) { return l4 && s > 1 ? 300 : 200; }
+// us in rows and in tiles, as above: x2, K = 5, 16 tiles 17 and 37, 150 30 and 47, 217 36
+// and 48, 333 49 and 53; lists of 72 150 tiles 99 and 192, 333 147 and 193; x3, K = 5,
+// 220 tiles 45 and 68, 350 60 and 72; x4 220 40 and 62, 494 74 and 72. x1, K = 5, 100
+// tiles 21 and 34, 210 29 and 36, 390 43 and 40; lists of 72 210 tiles 109 and 155, 390
+// 175 and 163. Lists past 16 entry by entry (72, caches warm): x2 150 tiles 145 and 155,
+// 217 161 and 152. (A form that wrote the patches out took x2, K = 5, 17, 32, 47 and 64,
+// and ten times the tiles' scratch.)
+static int64_t sb_few_tiles(int s, SbLists lm) { return s > 1 && lm != kSbEntries ? 300 : 200; }
 
 template <int s, int TI>
 static hipError_t sb_launch(int K, int h, int w, const int32_t* ids, const int32_t* m, const float* wt,
@@ -978,12 +1004,14 @@ static hipError_t sb_launch(int K, int h, int w, const int32_t* ids, const int32
     const int64_t nt = sb_tiles(s, TI, h, w), total = (int64_t)s * h * s * w;
     if (which & 1 && nt > 0) {
         if (nt > 0x7FFFFFFF) return hipErrorInvalidValue;
-        const bool l4 = K % 4 == 0 && ((reinterpret_cast<uintptr_t>(ids) | reinterpret_cast<uintptr_t>(wt)) & 15) == 0;
-        if (nt < sb_few_tiles(s, l4))
-            hipLaunchKernelGGL((l4 ? k_sb_row<s, TI, true> : k_sb_row<s, TI, false>),
-                               dim3((unsigned)round_grid8((int)nt * G::CY)), dim3(kSbThreads), 0, st, K, h, w, ids, m, wt,
-                               mu, resid, part);
-        else
+        const SbLists lm = sb_lists(K, ids, wt);
+        if (nt < sb_few_tiles(s, lm)) {
+            auto k = lm == kSbStaged ? k_sb_row<s, TI, kSbStaged> : lm == kSbWide ? k_sb_row<s, TI, kSbWide>
+                                                                                  : k_sb_row<s, TI, kSbEntries>;
+            hipLaunchKernelGGL(k, dim3((unsigned)round_grid8((int)nt * G::CY)), dim3(kSbThreads),
+                               lm == kSbStaged ? 8 * (size_t)(kPatch * G::TJ * K) : 0, st, K, h, w, ids, m, wt, mu, resid,
+                               part);
+        } else
             hipLaunchKernelGGL((k_sb_tile<s, TI>), dim3((unsigned)round_grid8((int)nt)), dim3(kSbThreads), G::lds(K), st,
                                K, h, w, ids, m, wt, mu, resid, part);
         const hipError_t e = hipGetLastError();

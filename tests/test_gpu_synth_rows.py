@@ -1,8 +1,9 @@
 """Synthesis and blend of images of few tiles, a workgroup a row of LR cells of a
 tile's region: bitwise the whole tiles' sums (a batch takes those always), at the
-lines between the two forms, with lists in 16-byte loads (K a multiple of four) and
-entry by entry, on images that hold patches with neighbours and patches without.
-And the scratch: no more than the tiles' regions, also under a memory limit."""
+lines between the two forms, on images that hold patches with neighbours and patches
+without; lists past 16 entries, in 16-byte loads and entry by entry, against FP64
+sums. And the scratch: no more than the tiles' regions, also under a memory limit."""
+import numpy as np
 import pytest
 
 import synthdata
@@ -53,6 +54,42 @@ def test_rows_equal_tiles(scale, K):
     g.ctx.sync()
     for a, b, size in zip(single, outs, SIZES[scale]):
         assert torch.equal(a, b), (size, _tiles(scale, *size))
+
+
+@pytest.mark.parametrize("scale", [1, 2, 3, 4])
+@pytest.mark.parametrize("cap", [18, 20])
+def test_long_lists(scale, cap):
+    """A pixel is the mean of at most 25 patch values, each mu and a sum of cap
+    products in fp32: within (cap + 30) 2^-23 of the largest |mu| + sum |w r|."""
+    torch, g = _workload(scale, cap=cap, k=4, w=60.0)
+    h, w = 17, 49
+    lr = torch.from_numpy(synthdata.fractal_voronoi_image(77, h, w)).cuda()
+    Q, ps = (h - 4) * (w - 4), 5 * scale
+    ids = torch.empty((Q, cap), dtype=torch.int32, device="cuda")
+    wt = torch.empty((Q, cap), device="cuda")
+    out = torch.empty((scale * h, scale * w), device="cuda")
+    g.set_mode(cap=cap, rerank=0, proj=1, lle_fp64=1)
+    g.ctx.query(lr, h, w, scale, 4)
+    g.ctx.lle_all(1e-3, ids, wt)
+    g.ctx.reconstruct(out)
+    g.ctx.sync()
+    ids, wt = ids.cpu().numpy(), wt.cpu().numpy().astype(np.float64)
+    resid, img = g.resid.cpu().numpy().astype(np.float64), lr.cpu().numpy().astype(np.float64)
+    acc, cnt, size = np.zeros((scale * h, scale * w)), np.zeros((scale * h, scale * w)), 0.0
+    lengths = set()
+    for q in range(Q):
+        m = int((ids[q] >= 0).sum())
+        lengths.add(m)
+        if m == 0:
+            continue
+        i, j = divmod(q, w - 4)
+        mu, r = img[i:i + 5, j:j + 5].mean(), resid[ids[q, :m]]
+        acc[scale * i:scale * i + ps, scale * j:scale * j + ps] += mu + (wt[q, :m] @ r).reshape(ps, ps)
+        cnt[scale * i:scale * i + ps, scale * j:scale * j + ps] += 1
+        size = max(size, abs(mu) + (np.abs(wt[q, :m]) @ np.abs(r)).max())
+    assert cap in lengths and len(lengths) > 3
+    err = np.abs(out.cpu().numpy() - acc / np.maximum(cnt, 1))[cnt > 0]
+    assert err.max() <= (cap + 30) * 2.0 ** -23 * size
 
 
 @pytest.mark.parametrize("scale", [2, 4])

@@ -299,7 +299,8 @@ __global__ __launch_bounds__(256) void k_dict_cut(const float* __restrict__ hr, 
     __shared__ int64_t slr[kCutPairs], smap[kCutPairs], shr[kCutPairs];   // offsets of the patches' first pixels
     const int h = (H + scale - 1) / scale, w = (W + scale - 1) / scale;
     const int ps = kPatch * scale, ps2 = ps * ps;
-    const int64_t p0 = (int64_t)blockIdx.x * kCutPairs;
+    const int64_t p0 = block_id() * kCutPairs;
+    if (p0 >= n) return;
     const int np = (int)(n - p0 < kCutPairs ? n - p0 : kCutPairs);
     if ((int)threadIdx.x < np) {
         const int64_t p = p0 + threadIdx.x;
@@ -461,10 +462,10 @@ hipError_t launch_b_degrade_residual(const BatchImage* im, int n, int64_t tiles,
 // [0, n_img) x [0, imax] x [0, jmax]; flag is cleared by the caller
 __global__ __launch_bounds__(256) void k_check_positions(const int32_t* __restrict__ pos, int64_t n, int n_img,
                                                          int imax, int jmax, uint32_t* __restrict__ flag) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const int im = pos[3 * r], i = pos[3 * r + 1], j = pos[3 * r + 2];
-    if (im < 0 || im >= n_img || i < 0 || i > imax || j < 0 || j > jmax) flag[0] = 1u;
+    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
+        const int im = pos[3 * r], i = pos[3 * r + 1], j = pos[3 * r + 2];
+        if (im < 0 || im >= n_img || i < 0 || i > imax || j < 0 || j > jmax) flag[0] = 1u;
+    }
 }
 
 hipError_t launch_check_positions(const int32_t* pos, int64_t n, int n_img, int imax, int jmax, uint32_t* flag,
@@ -477,7 +478,7 @@ hipError_t launch_check_positions(const int32_t* pos, int64_t n, int n_img, int 
 hipError_t launch_dict_cut(const float* hr, const float* lr, const float* maps, int H, int W,
                            int scale, const int32_t* pos, int64_t n, int mode, float* feat,
                            float* resid, hipStream_t st) {
-    const dim3 grid((unsigned)((n + kCutPairs - 1) / kCutPairs));
+    const dim3 grid = grid_rows((n + kCutPairs - 1) / kCutPairs);
     if (mode == 0)
         hipLaunchKernelGGL(k_dict_cut<0>, grid, dim3(256), 0, st, hr, lr, maps, H, W, scale, pos, n, feat, resid);
     else

@@ -537,7 +537,7 @@ __device__ __forceinline__ double lle_wave(int D, int M, double lam, const float
 // FP64 when the Cholesky diagonals' squared ratio exceeds 1e6.
 template <typename T, bool V4>
 __global__ __launch_bounds__(256) void k_lle16(LleArgs a) {
-    const int q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int q = (int)block_id() * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (q >= a.Q) return;
     const int M = min(a.m[q], a.K);
     float* wout = a.w + (int64_t)q * a.K;
@@ -562,7 +562,7 @@ __global__ __launch_bounds__(256) void k_lle16(LleArgs a) {
 hipError_t launch_lle(const LleArgs& a, hipStream_t st) {
     if (a.Q == 0) return hipSuccess;
     if (a.D < 1 || a.D > 128 || a.K < 1 || a.K > kMaxK || !a.xf) return hipErrorInvalidValue;
-    const dim3 grid((a.Q + 3) / 4);
+    const dim3 grid = grid_rows((a.Q + 3) / 4);
     const bool v4 = a.D % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.xf) | reinterpret_cast<uintptr_t>(a.qfeat)) & 15) == 0;
     if (a.fp64) {
         if (v4) hipLaunchKernelGGL((k_lle16<double, true>), grid, dim3(256), 0, st, a);

@@ -155,6 +155,14 @@ __device__ inline int xcd_block() {
     if (G & 7) return blockIdx.x;
     return (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
 }
+// A grid of `blocks` workgroups (of up to 1024 threads) whose threads along x stay
+// below 2^32, past which a launch is refused; block_id numbers them, and the last
+// row may hold some past the end.
+inline dim3 grid_rows(int64_t blocks) {
+    constexpr int64_t row = 1 << 21;
+    return blocks <= row ? dim3((unsigned)blocks) : dim3((unsigned)row, (unsigned)((blocks + row - 1) / row));
+}
+__device__ __forceinline__ int64_t block_id() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 __host__ __device__ inline int round_grid8(int g) { return g >= 8 ? (g + 7) & ~7 : g; }
 
 // Higham's gamma_n = n u / (1 - n u) for unit roundoff u.

@@ -958,6 +958,7 @@ static hipError_t launch_codes(const HashArgs& a, hipStream_t st) {
     HashArgs b = a;
     b.n_open = a.n_fixed ? a.fix_count + (a.n + kRowsPerWave - 1) / kRowsPerWave * a.parts : nullptr;
     b.open_blocks = (int64_t)grid.x * grid.y;
+    if (!one_row(grid.x, 256)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, b);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

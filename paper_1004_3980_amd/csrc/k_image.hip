@@ -429,7 +429,7 @@ hipError_t launch_query_features(const float* lr, int h, int w, int mode, float*
     const int ni = h - kPatch + 1, nj = w - kPatch + 1;
     if (ni < 1 || nj < 1) return hipErrorInvalidValue;
     const int64_t blocks = feature_segments(h, w);
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+    if (!one_row(blocks, 256)) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)blocks);
     if (mode == 0)
         hipLaunchKernelGGL(k_query_features<0>, grid, dim3(256), 0, st, lr, h, w, feat, mu, copy, counters);
@@ -440,7 +440,8 @@ hipError_t launch_query_features(const float* lr, int h, int w, int mode, float*
 
 hipError_t launch_b_query_features(const BatchImage* im, int n, int64_t seg_total, int mode, float* feat, double* mu,
                                    uint32_t* counters, hipStream_t st) {
-    if (seg_total < 1 || seg_total > 0x7FFFFFFF) return hipErrorInvalidValue;
+    if (seg_total < 1) return hipErrorInvalidValue;
+    if (!one_row(seg_total, 256)) return hipErrorInvalidConfiguration;
     if (mode == 0)
         hipLaunchKernelGGL(k_b_query_features<0>, dim3((unsigned)seg_total), dim3(256), 0, st, im, n, feat, mu, counters);
     else

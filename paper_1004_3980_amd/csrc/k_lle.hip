@@ -614,6 +614,7 @@ hipError_t launch_lle_all(int Q, int D, int cap, double lam, const float* qfeat,
                           const int32_t* ncand, float* w, hipStream_t st) {
     if (Q == 0) return hipSuccess;
     if (cap < 1 || cap > kAllMax || D < 1 || D > 128) return hipErrorInvalidValue;
+    if (!one_row(round_grid8(Q), 64)) return hipErrorInvalidConfiguration;
     static_assert(kAllMax <= 80, "five blocks of 16 rows");
     const bool v4 = D % 4 == 0 && ((reinterpret_cast<uintptr_t>(xf) | reinterpret_cast<uintptr_t>(qfeat)) & 15) == 0;
     switch ((cap + 15) / 16) {

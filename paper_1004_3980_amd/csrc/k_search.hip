@@ -1211,6 +1211,7 @@ hipError_t launch_search(const SearchArgs& a_in, hipStream_t st) {
         while (cp < a.cap) cp <<= 1;
         a.cp = cp;
         if (a.gram && a.K > 8) return hipErrorInvalidValue;
+        if (!one_row(round_grid8(a.Q), 64)) return hipErrorInvalidConfiguration;
         launch_cap(a, st);
         return hipGetLastError();
     }

@@ -785,6 +785,7 @@ hipError_t launch_knn_l1_screened(int Q, int K, int cap, const float* qfeat, con
                                   int32_t* ns, hipStream_t st) {
     if (Q == 0) return hipSuccess;
     if (cap < 1 || cap > kRankMaxCand || K < 1 || K > kMaxK) return hipErrorInvalidValue;
+    if (!one_row(round_grid8(Q), 64)) return hipErrorInvalidConfiguration;
     if ((reinterpret_cast<uintptr_t>(xf) & 15) || (reinterpret_cast<uintptr_t>(l1s) & 15)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_knn_l1_screened, dim3(round_grid8(Q)), dim3(64), 0, st, Q, K, cap, qfeat, xf, l1s, cand,
                        ncand, ids, d, m, ns);
@@ -796,6 +797,7 @@ hipError_t launch_knn_rank(int Q, int D, int K, int cap, bool l1, const float* q
                            hipStream_t st) {
     if (Q == 0) return hipSuccess;
     if (cap < 1 || cap > kL1Chunk * kL1PerLane || K < 1 || K > kMaxK || D < 1 || D > kL1MaxD) return hipErrorInvalidValue;
+    if (!one_row(round_grid8(Q), 64)) return hipErrorInvalidConfiguration;
     const int grid = round_grid8(Q);   // patches in contiguous runs per XCD: neighbours share candidates in L2
 #define ZH_RANK(DT, M1) \
     hipLaunchKernelGGL((k_knn_rank<DT, M1>), dim3(grid), dim3(64), 0, st, Q, D, K, cap, qfeat, xf, cand, ncand, ids, d, m)
@@ -1293,6 +1295,7 @@ hipError_t launch_cand_t(int Q, int L, int64_t N, int t, const uint2* bins, cons
                          int32_t* counts, int32_t* ids, hipStream_t st) {
     if (Q == 0) return hipSuccess;
     if (L < 1 || L > 64 || t < 1 || t > L || cap < 1) return hipErrorInvalidValue;
+    if (!one_row(((int64_t)Q + 3) / 4, 256)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_cand_t, dim3((Q + 3) / 4), dim3(256), 0, st, Q, L, N, t, bins, tids, cap, counts, ids);
     return hipGetLastError();
 }

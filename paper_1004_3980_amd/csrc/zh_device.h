@@ -162,6 +162,9 @@ inline dim3 grid_rows(int64_t blocks) {
     constexpr int64_t row = 1 << 21;
     return blocks <= row ? dim3((unsigned)blocks) : dim3((unsigned)row, (unsigned)((blocks + row - 1) / row));
 }
+// whether a launch of one row reaches all its workgroups (past 2^32 threads it covers
+// some of them, without an error)
+inline bool one_row(int64_t blocks, int threads) { return blocks * threads < (1ll << 32); }
 __device__ __forceinline__ int64_t block_id() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 __host__ __device__ inline int round_grid8(int g) { return g >= 8 ? (g + 7) & ~7 : g; }
 

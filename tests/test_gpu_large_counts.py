@@ -75,3 +75,23 @@ def test_positions():
     ctx.make_dictionary(*args)
     ctx.sync()
     assert torch.equal(feat[57:n], feat[:n - 57]) and torch.equal(resid[57:n], resid[:n - 57])
+
+
+def test_one_row_searches_say_so():
+    """The early stop's searches take a wave a patch in one row: past 2^26 patches the
+    call fails and says so."""
+    torch, zb, ctx = _ctx()
+    h, w = 8197, 8196
+    img = torch.zeros((h, w), device="cuda")
+    ctx.set_query_opts(cap=8, rerank=0, proj=1, lle_fp64=1)
+    for metric in ("l2", "l1"):
+        ctx.set_query_metric(metric)
+        with pytest.raises(zb.ZHError) as e:
+            ctx.query(img, h, w, 1, 3)
+        assert e.value.status == zb.ZH_EDEVICE
+        with pytest.raises(zb.ZHError) as e:   # nothing stands
+            ctx.lle_weights(1e-3)
+        assert e.value.status == zb.ZH_ESTATE
+    ctx.set_query_metric("l2")
+    ctx.query(img[:40, :40].contiguous(), 40, 40, 1, 3)
+    ctx.sync()

@@ -467,6 +467,12 @@ void* rank_lists(zh_ctx* c) {
     return need && c->longs.bytes >= need ? c->longs.p : nullptr;
 }
 
+// Room for `bytes` of Gram matrices; those that a smaller buffer held are gone.
+zh_status ensure_gram(zh_ctx* c, size_t bytes) {
+    if (c->gram.bytes < bytes) c->gram_ready = false;
+    return ensure(c, c->gram, bytes);
+}
+
 // cand_only (early stop): the candidate counts and the dump only; the
 // neighbour outputs and the Gram matrices of the last search stay as they are
 zh_status run_search(zh_ctx* c, Dict& d, int32_t* dump, int dump_cap, bool cand_only = false, bool dump_sorted = false) {
@@ -516,7 +522,7 @@ zh_status run_search(zh_ctx* c, Dict& d, int32_t* dump, int dump_cap, bool cand_
         if (a.K <= 8) {
             // the search forms the Gram matrices of the neighbours as well
             a.gram_fp64 = c->opts.lle_fp64;
-            TRY(ensure(c, c->gram, (a.gram_fp64 ? 8 : 4) * (size_t)(a.Q > 0 ? a.Q : 1) * 36));
+            TRY(ensure_gram(c, (a.gram_fp64 ? 8 : 4) * (size_t)(a.Q > 0 ? a.Q : 1) * 36));
             a.gram = c->gram.p;
         }
         StageTimer t(c, ZH_T_ROTATE);
@@ -1331,9 +1337,14 @@ zh_status zh_lle_weights(zh_ctx* c, double lambda) {
     if (c->qK <= 8) {
         // packed Gram matrices, then one thread per patch solves its system
         const int f64 = c->opts.lle_fp64;
-        TRY(ensure(c, c->gram, (f64 ? 8 : 4) * (size_t)c->Q * 36));
+        TRY(ensure_gram(c, (f64 ? 8 : 4) * (size_t)c->Q * 36));
         StageTimer t(c, ZH_T_LLE);
-        if (!(c->gram_ready && c->gram_fp64 == f64)) HIPCHK(c, launch_gram(a, c->gram.p, f64, c->stream));
+        if (!(c->gram_ready && c->gram_fp64 == f64)) {
+            c->gram_ready = false;
+            HIPCHK(c, launch_gram(a, c->gram.p, f64, c->stream));
+            c->gram_ready = true;
+            c->gram_fp64 = f64;
+        }
         HIPCHK(c, launch_lle_solve(a, c->gram.p, f64, c->stream));
     } else {
         StageTimer t(c, ZH_T_LLE);
@@ -1642,7 +1653,7 @@ zh_status zh_backward(zh_ctx* c, const float* g_hr, float* g_resid, float* g_lam
             la.lo = P<uint16_t>(d.lo);
             la.hs = hi_stride(d.D);
             la.xf = P<float>(d.xf);
-            TRY(ensure(c, c->gram, sizeof(double) * (size_t)(Q > 0 ? Q : 1) * 36));
+            TRY(ensure_gram(c, sizeof(double) * (size_t)(Q > 0 ? Q : 1) * 36));
             HIPCHK(c, launch_gram(la, c->gram.p, 1, c->stream));
             c->gram_ready = true;
             c->gram_fp64 = 1;
@@ -1796,7 +1807,7 @@ zh_status batch_plan(zh_ctx* c, const zh_batch* b) {
     TRY(ensure(c, c->sbpart, sizeof(float) * (size_t)std::max<int64_t>(part_max, 1)));
     TRY(ensure(c, c->counters, kNumCounters * sizeof(uint32_t)));
     if (c->opts.cap == 0 && c->opts.rerank == 0) make_rank_lists(c, q_max, (int)K);
-    if (K <= 8) TRY(ensure(c, c->gram, (c->opts.lle_fp64 ? 8 : 4) * (size_t)q_max * 36));
+    if (K <= 8) TRY(ensure_gram(c, (c->opts.lle_fp64 ? 8 : 4) * (size_t)q_max * 36));
     for (int s = 1; s <= kMaxScale; ++s)
         for (int pr = 0; B.g[s].n && pr < 2; ++pr) {
             HashArgs ha{};

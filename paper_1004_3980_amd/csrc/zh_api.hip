@@ -1356,6 +1356,14 @@ zh_status zh_lle_weights(zh_ctx* c, double lambda) {
     return ZH_OK;
 }
 
+// The lists of zh_lle_all are about to be written over or to move: weights over
+// them no longer stand, whatever becomes of the call.
+static void drop_lists(zh_ctx* c) {
+    if (!c->all_m) return;
+    c->all_m = false;
+    c->stage = std::min(c->stage, 1);
+}
+
 zh_status zh_lle_all(zh_ctx* c, double lambda, int32_t* ids, float* w) {
     if (!c) return ZH_EINVAL;
     if (c->stage < 1) return fail(c, ZH_ESTATE, "zh_lle_all before zh_query");
@@ -1366,6 +1374,7 @@ zh_status zh_lle_all(zh_ctx* c, double lambda, int32_t* ids, float* w) {
     TRY(set_device(c));
     Dict& d = c->dicts[c->qscale];
     const size_t Qn = (size_t)(c->Q > 0 ? c->Q : 1);
+    drop_lists(c);
     TRY(ensure(c, c->l1cand, sizeof(int32_t) * Qn * cap));
     TRY(ensure(c, c->wall, sizeof(float) * Qn * cap));
     // The candidate lists of the last query, ascending. Where the neighbours are
@@ -2229,6 +2238,8 @@ zh_status zh_knn_l1(zh_ctx* c) {
     if (c->stage < 1) return fail(c, ZH_ESTATE, "zh_knn_l1 before zh_query");
     if (c->opts.cap < 1) return fail(c, ZH_EUNSUPPORTED, "zh_knn_l1 needs the early stop (query option cap > 0)");
     TRY(set_device(c));
+    c->stage = 1;   // the lists and the neighbours change
+    c->all_m = false;
     TRY(clear_counters(c));
     TRY(rank_l1(c, c->dicts[c->qscale]));
     c->gram_ready = false;   // the Gram matrices of the new neighbours are formed by zh_lle_weights

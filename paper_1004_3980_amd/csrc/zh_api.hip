@@ -709,9 +709,9 @@ zh_status zh_features(zh_ctx* c, const float* lr, int h, int w, int mode, float*
     TRY(set_device(c));
     const int64_t Q = (int64_t)(h - 4) * (w - 4);
     double* mup = mu;
-    if (!mup) {
-        TRY(ensure(c, c->qmu, sizeof(double) * (size_t)Q));
-        mup = P<double>(c->qmu);
+    if (!mup) {   // (not the means of the last query)
+        TRY(ensure(c, c->tmp, sizeof(double) * (size_t)Q));
+        mup = P<double>(c->tmp);
     }
     HIPCHK(c, launch_query_features(lr, h, w, mode, feat, mup, nullptr, nullptr, c->stream));
     return ZH_OK;

@@ -89,6 +89,7 @@ struct zh_ctx {
     // ids, d2, m, nsurv and the Gram matrices are those of an early-stop search
     // of this query with the options nbr_opts
     bool nbr_search = false;
+    bool surv = false;            // nsurv holds this query's survivors
     zh_query_opts nbr_opts{};
     int qh = 0, qw = 0, qscale = 0, qK = 0;
     bool all_m = false;           // the last weights are over all matches (zh_lle_all)
@@ -476,7 +477,7 @@ zh_status ensure_gram(zh_ctx* c, size_t bytes) {
 // cand_only (early stop): the candidate counts and the dump only; the
 // neighbour outputs and the Gram matrices of the last search stay as they are
 zh_status run_search(zh_ctx* c, Dict& d, int32_t* dump, int dump_cap, bool cand_only = false, bool dump_sorted = false) {
-    if (!cand_only) c->nbr_search = false;
+    if (!cand_only) c->nbr_search = c->surv = false;
     if (c->opts.cap == 0 && c->opts.rerank == 0 && !dump) {
         // the union without a stop, ranked by the FP64 distance itself. The
         // kernels below take the bf16 pre-rank (rerank > 0) and the candidate
@@ -546,7 +547,7 @@ zh_status run_search(zh_ctx* c, Dict& d, int32_t* dump, int dump_cap, bool cand_
     }
     c->gram_ready = a.gram != nullptr;
     c->gram_fp64 = a.gram_fp64;
-    c->nbr_search = a.cap > 0;
+    c->nbr_search = c->surv = a.cap > 0;
     c->nbr_opts = c->opts;
     return ZH_OK;
 }
@@ -1214,8 +1215,8 @@ zh_status rank_l1(zh_ctx* c, Dict& d) {
         HIPCHK(c, launch_l1_screen_rows(P<float>(d.xf), d.n, P<uint8_t>(d.l1s), c->stream));
         d.l1s_ok = true;
     }
+    c->nbr_search = c->surv = false;
     TRY(ensure(c, c->nsurv, sizeof(int32_t) * (size_t)(c->Q > 0 ? c->Q : 1)));
-    c->nbr_search = false;
     TRY(run_search(c, d, P<int32_t>(c->l1cand), cap, true));
     StageTimer t(c, ZH_T_SEARCH);
     if (screened) {
@@ -1229,6 +1230,7 @@ zh_status rank_l1(zh_ctx* c, Dict& d) {
         // every candidate reaches the exact pass: survivors = min(ncand, cap)
         HIPCHK(c, launch_min_i32((int)c->Q, P<int32_t>(c->ncand), cap, P<int32_t>(c->nsurv), c->stream));
     }
+    c->surv = true;
     return ZH_OK;
 }
 
@@ -1247,7 +1249,7 @@ zh_status zh_query(zh_ctx* c, const float* lr, int h, int w, int scale, int K) {
     TRY(set_device(c));
     Dict& d = c->dicts[scale];
     c->stage = 0;
-    c->nbr_search = false;
+    c->nbr_search = c->surv = false;
     const int ps2 = (kPatch * scale) * (kPatch * scale);
     TRY(ensure(c, c->lr, sizeof(float) * (size_t)h * w));
     TRY(ensure(c, c->qfeat, sizeof(float) * (size_t)Q * d.D));
@@ -2174,7 +2176,7 @@ zh_status zh_get_results(zh_ctx* c, int32_t* ids, float* d2, int32_t* m, float* 
 zh_status zh_survivors(zh_ctx* c, int32_t* survivors) {
     if (!c || !survivors) return ZH_EINVAL;
     if (c->stage < 1) return fail(c, ZH_ESTATE, "zh_survivors before zh_query");
-    if (c->opts.cap <= 0 || !c->nsurv.p) return fail(c, ZH_ESTATE, "zh_survivors: the last query had no early stop");
+    if (c->opts.cap <= 0 || !c->surv) return fail(c, ZH_ESTATE, "zh_survivors: the last query had no early stop");
     TRY(set_device(c));
     HIPCHK(c, hipMemcpyAsync(survivors, c->nsurv.p, (size_t)c->Q * 4, hipMemcpyDeviceToDevice, c->stream));
     return ZH_OK;

@@ -29,3 +29,32 @@ def test_features_between_query_and_image():
         g.ctx.reconstruct(hr)
     g.ctx.sync()
     assert torch.equal(ref, out)
+
+
+def test_survivors_are_of_the_last_query():
+    """Counts of survivors come from an early-stop search (or l1 ranking) of the last
+    query alone, not from an earlier one with fewer patches."""
+    torch, g = _workload()
+    from paper_1004_3980_amd import zoomhash as zb
+    big = torch.from_numpy(synthdata.fractal_voronoi_image(6, 150, 160)).cuda()
+    n = torch.empty(146 * 156, dtype=torch.int32, device="cuda")
+    c = g.ctx
+    for l1 in (False, True):
+        g.set_mode(cap=16, rerank=0, proj=1, lle_fp64=1)
+        c.query(g.lr, g.h, g.w, 2, 4)
+        if l1:
+            c.knn_l1()
+        c.survivors(n)
+        g.set_mode(cap=0, rerank=0, proj=1, lle_fp64=1)
+        c.query(big, 150, 160, 2, 4)
+        g.set_mode(cap=16, rerank=0, proj=1, lle_fp64=1)
+        with pytest.raises(zb.ZHError) as e:
+            c.survivors(n)
+        assert e.value.status == zb.ZH_ESTATE
+        c.knn_t(1)
+        with pytest.raises(zb.ZHError):
+            c.survivors(n)
+        c.knn_l1()
+        c.survivors(n)
+        c.sync()
+        assert int(n.min()) >= 0 and int(n.max()) <= 16

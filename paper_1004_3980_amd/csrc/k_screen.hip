@@ -614,11 +614,11 @@ hipError_t launch_screen_rows(const float* x, int64_t n, int D, int m, const dou
 // D = 100: the last four coordinates take one MFMA step for their three products
 // ((hi, hi, lo) of Phi against (hi, lo, hi) of the row), not one each. h and l
 // go through the sum 128 h + l, an integer below 2^14: its squares add up
-// exactly, and one fused multiply-add gives the coding error. Phi's rows are
+// exactly, and one FP64 multiply-add gives the coding error. Phi's rows are
 // dealt to the tiles so that a lane's codes are 16 consecutive bytes.
 // Bound: instruction issue. 1040400 rows of D = 100, the codes' errors and norms
-// element by element in FP64 and four bytes a store 200 us, now 140; 63973 rows
-// 19.0 and 15.7. With the next rows' reads ahead (154 registers against 109)
+// element by element and four bytes a store 200 us, now 143 (with the errors in fp32
+// 140); 63973 rows 19.0 and 15.7. With the next rows' reads ahead (154 registers against 109)
 // 159 and 19.5.
 template <int D>
 __global__ __launch_bounds__(256) void k_rotate(const float* __restrict__ feat, int64_t n,
@@ -765,11 +765,11 @@ __global__ __launch_bounds__(256) void k_rotate(const float* __restrict__ feat, 
         amax = fmaxf(amax, __shfl_xor(amax, 16));
         amax = fmaxf(amax, __shfl_xor(amax, 32));
         const float s_q = amax > 0.0f ? amax * (1.0f / 127.0f) : 1.0f;
-        const float inv = 1.0f / s_q, s128 = s_q * (1.0f / 128.0f);
-        // int8 coding of the row, c = 128 h + l: sum c^2 exact in FP64, the
-        // errors y - s_q c / 128 rounded once, their squares in fp32
-        double n2 = 0.0;
-        float e2 = 0.0f;
+        const float inv = 1.0f / s_q;
+        const double sd = (double)s_q * (1.0 / 128.0);
+        // int8 coding of the row, c = 128 h + l: sum c^2 exact in FP64, the errors
+        // y - s_q c / 128 and their squares in FP64
+        double n2 = 0.0, e2 = 0.0;
         uint32_t hw[4], lw[4];
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
@@ -781,8 +781,8 @@ __global__ __launch_bounds__(256) void k_rotate(const float* __restrict__ feat, 
                 const float l = fminf(127.0f, fmaxf(-127.0f, rintf((t - h) * 128.0f)));
                 const float c = fmaf(h, 128.0f, l);
                 n2 = fma((double)c, (double)c, n2);
-                const float er = fmaf(-s128, c, y[tt][i]);
-                e2 = fmaf(er, er, e2);
+                const double er = fma(-sd, (double)c, (double)y[tt][i]);
+                e2 = fma(er, er, e2);
                 // bytes h + 128 and l + 128; the flipped top bits make them int8
                 hw[tt] = __builtin_amdgcn_cvt_pk_u8_f32(h + 128.0f, i, hw[tt]);
                 lw[tt] = __builtin_amdgcn_cvt_pk_u8_f32(l + 128.0f, i, lw[tt]);
@@ -799,11 +799,9 @@ __global__ __launch_bounds__(256) void k_rotate(const float* __restrict__ feat, 
             orow[kb] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
             orow[4 + kb] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
             if (kb == 0) {
-                // 64 squares of errors rounded once, added in fp32: within 1e-5;
-                // squares that underflow leave less than 1e-18
-                const float eps = sqrtf(e2 * (1.0f + 1e-5f)) * (1.0f + 1e-6f) + 1e-18f;
+                const float eps = (float)(sqrt(e2) * (1.0 + 1e-12) + 1e-300);
                 reinterpret_cast<float4*>(orow)[8] =
-                    make_float4(s_q, (float)(n2 * ((double)s128 * (double)s128)),
+                    make_float4(s_q, (float)(n2 * (sd * sd)),
                                 (rho + eps) * (1.0f + 1e-6f) + 1e-37f, 0.0f);
             }
         }

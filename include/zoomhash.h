@@ -408,8 +408,8 @@ zh_status zh_run_batch(zh_ctx* ctx, const zh_batch* batch);
  * tile), so outputs may change in the last bits after tuning, and the
  * batched and single-image results stay bitwise equal. The images' outputs
  * are overwritten. When the environment names a cache file
- * (ZH_TUNE_CACHE), a previous choice for the same device (name and
- * architecture), HIP runtime version and batch (sizes, zoom factors, K,
+ * (ZH_TUNE_CACHE), a previous choice of the same kernels for the same device
+ * (name and architecture), HIP runtime version and batch (sizes, zoom factors, K,
  * iterations, query options) is taken from it without timing (from_cache =
  * 1, timings 0), and a new choice is appended to it as one JSON object per
  * line. */

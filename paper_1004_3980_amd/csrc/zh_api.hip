@@ -1963,8 +1963,13 @@ zh_status zh_run_batch(zh_ctx* c, const zh_batch* b) {
 
 namespace {
 
-// Key of a batch for the tuning cache: device, HIP runtime, and everything
-// that shapes the launches (sizes, zoom factors, K, iterations, query options).
+// Key of a batch for the tuning cache: the kernels that the choice is between,
+// device, HIP runtime, and everything that shapes the launches (sizes, zoom factors,
+// K, iterations, query options).
+// kTuneKernels: counted up with the kernels timed. 1: the update's grid was of
+// persistent workgroups; 2: a workgroup a tile, their number on a compute unit held
+// down by LDS.
+constexpr uint64_t kTuneKernels = 2;
 uint64_t tune_key(zh_ctx* c, const zh_batch* b, std::string& dev, std::string& arch, int& rt) {
     hipDeviceProp_t prop{};
     if (hipGetDeviceProperties(&prop, c->device) != hipSuccess) (void)hipGetLastError();
@@ -1972,7 +1977,7 @@ uint64_t tune_key(zh_ctx* c, const zh_batch* b, std::string& dev, std::string& a
     arch = prop.gcnArchName;
     rt = 0;
     if (hipRuntimeGetVersion(&rt) != hipSuccess) (void)hipGetLastError();
-    uint64_t h = fmix64(0x5A17ull + (uint64_t)rt);
+    uint64_t h = fmix64(0x5A17ull + (uint64_t)rt + ((kTuneKernels - 1) << 32));
     auto mix = [&](uint64_t v) { h = fmix64(h ^ (v + kGolden)); };
     for (char ch : dev) mix((uint64_t)(unsigned char)ch);
     for (char ch : arch) mix((uint64_t)(unsigned char)ch);

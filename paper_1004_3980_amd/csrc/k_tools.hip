@@ -916,9 +916,10 @@ __global__ __launch_bounds__(256) void k_cand_t(int Q, int L, int64_t N, int t, 
 // a stop was sorted in LDS by one wave: 14,732 patches, L = 16, 100k pairs,
 // t = 2: 14.8 -> 0.55 ms, with the long patches first and in shares 0.37; 3,600
 // patches, L = 8, 20k pairs at D = 25, t = 1 (unions of up to 1,600 IDs): 2.37
-// -> 0.06 ms. Patches without an entry are written at once and up to 64 IDs need no
-// merge: 207,836 patches, L = 8, unions of 0 or 1 ID 676 -> 256 us (the wave a patch
-// before 356), 44,100 patches at K = 16 with 8 IDs each 290 -> 109.
+// -> 0.06 ms. Up to 64 IDs, the first wave's alone, need no merge, and from 8192
+// patches on those of at most 64 entries take a wave each (rank_few): 207,836 patches,
+// L = 8, unions of 0 or 1 ID 676 -> 128 us (the wave a patch before all this 356),
+// 44,100 at K = 16 with 8 IDs each 290 -> 92 (3502).
 constexpr int kWinMax = 2048;               // entries of a window
 constexpr int kWinSlots = 2 * kWinMax;      // largest hash table: load at most 1/2
 
@@ -993,28 +994,32 @@ __device__ __forceinline__ void write_ranked(int q, int K, int kept, double bd, 
 
 // Long patches, those with more entries than a window, are listed first, so that
 // none begins when all others end, and those of more than kLongShare entries
-// in shares by ranges of IDs (at most kLongParts), which a last launch joins.
-// The list's workgroups come before those of the other patches.
+// in shares by ranges of IDs (at most kLongParts), which a last launch joins. The
+// other patches of more than kFewMax entries have a list of their own, which
+// kMidBlocks workgroups go through; those of fewer take a wave each in the last
+// workgroups (a workgroup a patch is bound by its launch there: 207,836 patches with
+// at most one entry 256 us).
 constexpr int kLongMax = 8192, kLongParts = 16, kLongShare = 4096, kLongBlocks = 1024;
-// Patches from which the lists' two more launches (20 us for 14,732 patches) pay:
+constexpr int kMidBlocks = 8192, kFewMax = 64;
+// Patches from which the lists' two more launches (18 us for 14,732 patches) pay:
 // there the ranking went from 545 to 348 us; 3,600 patches take 56 us in all, and
 // their longest begins early enough.
 constexpr int kLongMin = 8192;
 struct LongLists {
-    unsigned int* n;     // entries (patches that did not fit are not listed and take their turn); 0 before the first launch
+    unsigned int* n;     // entries of item, and of mid; 0 before the first launch
     int2* item;          // [kLongMax] patch, and share + 32 shares
     double* d;           // [kLongMax, K] nearest of a share
     int32_t* id;
     int32_t* kept;       // [kLongMax] IDs of a share
-    uint8_t* listed;     // [Q]
+    int32_t* mid;        // [Q] patches of more than kFewMax entries that are not in item
+    uint8_t* listed;     // [Q] whether a patch is in one of the lists
 };
 
 __global__ __launch_bounds__(256) void k_bins_long(int Q, int L, const uint2* __restrict__ bins, LongLists ll) {
     const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= Q) return;
     uint32_t total = 0;
 #pragma unroll 8
-    for (int l = 0; l < L; ++l) total += min(bins[(int64_t)l * Q + q].y, 1u << 25);
+    for (int l = 0; l < L; ++l) total += q < Q ? min(bins[(int64_t)l * Q + q].y, 1u << 25) : 0u;
     bool listed = false;
     if (total > (uint32_t)kWinMax) {
         const int shares = (int)min((uint32_t)kLongParts, (total + kLongShare - 1) / kLongShare);
@@ -1023,7 +1028,19 @@ __global__ __launch_bounds__(256) void k_bins_long(int Q, int L, const uint2* __
         for (int p = 0; p < shares && at + p < (unsigned)kLongMax; ++p)
             ll.item[at + p] = make_int2(listed ? q : -1, p + 32 * shares);
     }
-    ll.listed[q] = listed ? 1 : 0;
+    // one atomic a workgroup
+    __shared__ unsigned cnt[4], base;
+    const bool mid = !listed && total > (uint32_t)kFewMax;
+    const uint64_t bal = __ballot(mid);
+    const int wv = threadIdx.x >> 6;
+    if (__lane_id() == 0) cnt[wv] = (unsigned)__popcll(bal);
+    __syncthreads();
+    if (threadIdx.x == 0) base = atomicAdd(ll.n + 1, cnt[0] + cnt[1] + cnt[2] + cnt[3]);
+    __syncthreads();
+    unsigned at = base + (unsigned)__popcll(bal & lanemask_lt());
+    for (int v = 0; v < wv; ++v) at += cnt[v];
+    if (mid) ll.mid[at] = q;
+    if (q < Q) ll.listed[q] = listed || mid ? 1 : 0;
 }
 
 // Entries below `end` among the first n of src, ascending: seven probes a step.
@@ -1046,6 +1063,82 @@ __device__ __forceinline__ uint32_t count_below(const uint32_t* __restrict__ src
     return lo;
 }
 
+// FP64 squared distance of row `row` (the sequential sum over the coordinates in
+// index order) from the query q (LDS); not a number: infinite, last by ID.
+template <int D>
+__device__ __forceinline__ double rank_distance(const float* __restrict__ row, const double* q) {
+    double d = 0.0;
+    auto term = [&](int i, float x) {
+        const double t0 = q[i] - (double)x;
+        d = d + t0 * t0;
+    };
+    if (D == 100) {
+        // a fifth of a row on its way at a time
+        const float4* r4 = reinterpret_cast<const float4*>(row);
+#pragma unroll 1
+        for (int h = 0; h < 25; h += 5) {
+            float4 v[5];
+#pragma unroll
+            for (int u = 0; u < 5; ++u)
+                if (h + u < 25) v[u] = r4[h + u];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < 5; ++u)
+                if (h + u < 25) {
+                    term(4 * (h + u), v[u].x);
+                    term(4 * (h + u) + 1, v[u].y);
+                    term(4 * (h + u) + 2, v[u].z);
+                    term(4 * (h + u) + 3, v[u].w);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        float v[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i) v[i] = row[i];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < D; ++i) term(i, v[i]);
+    }
+    return d == d ? d : INFINITY;
+}
+
+// A patch of at most 64 entries by one wave, an entry a lane: each lane counts the
+// lanes with its ID; the first of t or more stands for it.
+template <int D>
+__device__ __forceinline__ void rank_few(int q, int64_t N, int t, int K, uint2 b, const uint32_t* __restrict__ tids,
+                                         const float* __restrict__ qfeat, const float* __restrict__ xf,
+                                         int32_t* __restrict__ counts, int32_t* __restrict__ out_ids,
+                                         float* __restrict__ out_d, int32_t* __restrict__ out_m, double* sq, double* pd,
+                                         int* pi) {
+    const int lane = __lane_id();
+    for (int i = lane; i < D; i += 64) sq[i] = (double)qfeat[(int64_t)q * D + i];   // the wave's own
+    const int incl = wave_incl_scan((int)b.y);
+    const int n = __builtin_amdgcn_readlane(incl, 63);
+    // the bin of entry `lane`: the number of bins that end at or before it
+    int l = 0;
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1)
+        if (__shfl(incl, l + s - 1) <= lane) l += s;
+    const uint32_t off = (uint32_t)__shfl((int)b.x, l) + (uint32_t)(lane - (__shfl(incl, l) - __shfl((int)b.y, l)));
+    const int id = lane < n ? (int)tids[(int64_t)l * N + off] : -1;
+    int hits = 0;
+    bool first = true;
+    for (int j = 0; j < n; ++j) {
+        const bool same = __builtin_amdgcn_readlane(id, j) == id;
+        hits += same ? 1 : 0;
+        first = first && !(same && j < lane);
+    }
+    const bool act = lane < n && first && hits >= t;
+    const int kept = __popcll(__ballot(act));
+    double d = INFINITY, bd = INFINITY;
+    int bi = 0x7FFFFFFF;
+    __builtin_amdgcn_wave_barrier();
+    if (act) d = rank_distance<D>(xf + (int64_t)id * D, sq);
+    if (kept) topk_first(n, d, act ? id : 0x7FFFFFFF, K, pd, pi, bd, bi);
+    write_ranked(q, K, kept, bd, bi, counts, out_ids, out_d, out_m);
+}
+
 template <int D, bool LISTS>
 __global__ __launch_bounds__(256, 5) void k_bins_rank(int Q, int L, int64_t N, int t, int K,
                                                    const uint2* __restrict__ bins, const uint32_t* __restrict__ tids,
@@ -1053,7 +1146,8 @@ __global__ __launch_bounds__(256, 5) void k_bins_rank(int Q, int L, int64_t N, i
                                                    int32_t* __restrict__ counts, int32_t* __restrict__ out_ids,
                                                    float* __restrict__ out_d, int32_t* __restrict__ out_m,
                                                    unsigned int* __restrict__ counters, LongLists ll) {
-    __shared__ uint32_t s_key[kWinSlots];
+    __shared__ __align__(8) uint32_t s_key[kWinSlots];
+    static_assert(sizeof(s_key) >= 4 * D * sizeof(double), "the few's queries lie there");
     __shared__ uint32_t s_cnt[kWinSlots / 4];
     __shared__ uint32_t s_list[kWinMax];
     __shared__ double s_q[D];
@@ -1064,22 +1158,36 @@ __global__ __launch_bounds__(256, 5) void k_bins_rank(int Q, int L, int64_t N, i
     __shared__ int s_ti[4 * kMaxK];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int blk = (int)block_id();
-    const bool from_list = LISTS && blk < kLongBlocks;
-    if (!from_list && blk - (LISTS ? kLongBlocks : 0) >= Q) return;
-    const int items = from_list ? (int)min(*ll.n, (unsigned)kLongMax) : 1;
-    for (int item = from_list ? blk : 0; item < items; item += kLongBlocks) {
+    const bool longs = LISTS && blk < kLongBlocks;
+    int item = blk, items = blk + 1, step = 1;
+    if (!LISTS && blk >= Q) return;
+    if (LISTS) {
+        const int mids = min(Q, kMidBlocks);
+        if (blk >= kLongBlocks + mids) {
+            const int q = __builtin_amdgcn_readfirstlane((blk - kLongBlocks - mids) * 4 + wv);
+            if (q < Q && !ll.listed[q])
+                rank_few<D>(q, N, t, K, lane < L ? bins[(int64_t)lane * Q + q] : make_uint2(0u, 0u), tids, qfeat, xf, counts,
+                            out_ids, out_d, out_m, reinterpret_cast<double*>(s_key) + wv * D, s_td + wv * kMaxK,
+                            s_ti + wv * kMaxK);
+            return;
+        }
+        item = longs ? blk : blk - kLongBlocks;
+        step = longs ? kLongBlocks : mids;
+        items = longs ? (int)min(ll.n[0], (unsigned)kLongMax) : (int)ll.n[1];
+    }
+    for (; item < items; item += step) {
         // not in runs per XCD: the patches of a flat region, the longest ones, are
         // neighbours (0.91 against 0.56 ms on the 14,732 patches above)
-        const int2 it = from_list ? ll.item[item] : make_int2(0, 32);
-        const int q = from_list ? it.x : blk - (LISTS ? kLongBlocks : 0);
+        const int2 it = longs ? ll.item[item] : make_int2(LISTS ? ll.mid[item] : item, 32);
+        const int q = it.x;
         const int part = it.y & 31, shares = it.y >> 5;
-        if (LISTS && (q < 0 || (!from_list && ll.listed[q]))) continue;
+        if (LISTS && q < 0) continue;
         // every wave holds the patch's bins in its lanes: the position of the next
         // entry and the entries left
         const uint2 b = lane < L ? bins[(int64_t)lane * Q + q] : make_uint2(0u, 0u);
-        if (__ballot(b.y > 0u) == 0) {
+        if (!LISTS && __ballot(b.y > 0u) == 0) {
             if (wv == 0) write_ranked(q, K, 0, 0.0, 0, counts, out_ids, out_d, out_m);
-            continue;
+            return;
         }
         if (LISTS) __syncthreads();   // the last item's arrays are no longer read
         for (int i = tid; i < D; i += 256) s_q[i] = (double)qfeat[(int64_t)q * D + i];
@@ -1172,9 +1280,7 @@ __global__ __launch_bounds__(256, 5) void k_bins_rank(int Q, int L, int64_t N, i
                         d = d + t0 * t0;
                     };
                     if (D == 100) {
-                        // a fifth of a row on its way at a time
                         const float4* r4 = reinterpret_cast<const float4*>(row);
-#pragma unroll
                         for (int h = 0; h < 25; h += 5) {
                             float4 v[5];
 #pragma unroll
@@ -1269,10 +1375,11 @@ __global__ __launch_bounds__(64) void k_bins_join(int K, LongLists ll, int32_t* 
     }
 }
 
-// distances, IDs, patches and shares, counts, flags
+// distances, IDs, patches and shares, counts, the other list, flags
 size_t bins_rank_scratch(int64_t Q, int K) {
     if (Q < kLongMin) return 0;
-    return (size_t)kLongMax * ((sizeof(double) + sizeof(int32_t)) * K + sizeof(int2) + sizeof(int32_t)) + (size_t)Q;
+    return (size_t)kLongMax * ((sizeof(double) + sizeof(int32_t)) * K + sizeof(int2) + sizeof(int32_t)) +
+           (sizeof(int32_t) + 1) * (size_t)Q;
 }
 
 hipError_t launch_bins_rank(int Q, int L, int64_t N, int t, int D, int K, const uint2* bins, const uint32_t* tids,
@@ -1282,7 +1389,7 @@ hipError_t launch_bins_rank(int Q, int L, int64_t N, int t, int D, int K, const 
     if (L < 1 || L > 64 || t < 1 || t > L || K < 1 || K > kMaxK || (D != 25 && D != 100) ||
         (reinterpret_cast<uintptr_t>(xf) & 15) || !n_long)
         return hipErrorInvalidValue;
-    LongLists ll{n_long, nullptr, nullptr, nullptr, nullptr, nullptr};
+    LongLists ll{n_long, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     if (!scratch || Q < kLongMin) {
         auto k = D == 100 ? k_bins_rank<100, false> : k_bins_rank<25, false>;
         hipLaunchKernelGGL(k, grid_rows(Q), dim3(256), 0, st, Q, L, N, t, K, bins, tids, qfeat, xf, counts, ids, d, m,
@@ -1293,12 +1400,13 @@ hipError_t launch_bins_rank(int Q, int L, int64_t N, int t, int D, int K, const 
     ll.item = reinterpret_cast<int2*>(ll.d + (size_t)kLongMax * K);
     ll.id = reinterpret_cast<int32_t*>(ll.item + kLongMax);
     ll.kept = ll.id + (size_t)kLongMax * K;
-    ll.listed = reinterpret_cast<uint8_t*>(ll.kept + kLongMax);
+    ll.mid = ll.kept + kLongMax;
+    ll.listed = reinterpret_cast<uint8_t*>(ll.mid + Q);
     hipLaunchKernelGGL(k_bins_long, dim3((Q + 255) / 256), dim3(256), 0, st, Q, L, bins, ll);
     auto k = D == 100 ? k_bins_rank<100, true> : k_bins_rank<25, true>;
-    hipLaunchKernelGGL(k, grid_rows((int64_t)kLongBlocks + Q), dim3(256), 0, st, Q, L, N, t, K, bins, tids, qfeat, xf, counts, ids, d,
-                       m, counters, ll);
-    hipLaunchKernelGGL(k_bins_join, dim3(1024), dim3(64), 0, st, K, ll, counts, ids, d, m);
+    hipLaunchKernelGGL(k, grid_rows((int64_t)kLongBlocks + std::min(Q, kMidBlocks) + (Q + 3) / 4), dim3(256), 0, st, Q, L, N, t, K, bins,
+                       tids, qfeat, xf, counts, ids, d, m, counters, ll);
+    hipLaunchKernelGGL(k_bins_join, dim3(4096), dim3(64), 0, st, K, ll, counts, ids, d, m);
     return hipGetLastError();
 }
 

@@ -2228,7 +2228,8 @@ zh_status zh_knn_t(zh_ctx* c, int t) {
     {
         make_rank_lists(c, c->Q, c->qK);
         StageTimer tm(c, ZH_T_SEARCH);
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, c->stream, P<uint32_t>(c->counters) + C_LONG, 1, 0u);
+        if (rank_lists(c))
+            hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, c->stream, P<uint32_t>(c->counters) + C_LONG, 2, 0u);
         HIPCHK(c, launch_bins_rank((int)c->Q, d.L, d.n, t, d.D, c->qK, P<uint2>(c->qbins), P<uint32_t>(d.tids),
                                    P<float>(c->qfeat), P<float>(d.xf), P<int32_t>(c->ncand), P<int32_t>(c->ids),
                                    P<float>(c->d2), P<int32_t>(c->m), nullptr, P<unsigned int>(c->counters) + C_LONG,

@@ -21,7 +21,7 @@ constexpr int kFixSlots = 32;                        // fix-list entries per 16 
 // large-union search, FP64 re-ranks, patches beyond the large-union limit
 // (ranked by the streaming merge), codes fixed in FP64, fp32 LLE solves redone
 // in FP64, screened patches whose survivors exceeded the exact-row limit.
-enum { C_OVERFLOW = 0, C_RANKFB = 1, C_STREAM = 2, C_CODEFIX = 3, C_LLE64 = 4, C_TRUNC = 5, C_LONG = 6, kNumCounters = 8 };
+enum { C_OVERFLOW = 0, C_RANKFB = 1, C_STREAM = 2, C_CODEFIX = 3, C_LLE64 = 4, C_TRUNC = 5, C_LONG = 6 /* and 7: the ranking's lists */, kNumCounters = 8 };
 
 struct Taps {                   // normalised 1-D Gaussian, offsets -R..R
     double g[kMaxTaps];
@@ -263,9 +263,8 @@ hipError_t launch_knn_l1_screened(int Q, int K, int cap, const float* qfeat, con
 // K nearest (squared l2, sequential FP64) of the IDs that at least t of each
 // patch's bins hold, any number of them; counts[Q] their numbers. counters
 // (nullable): C_OVERFLOW and C_STREAM count the patches whose bins hold more
-// than 2048 and 8192 entries. n_long: a counter that is 0; scratch (nullable,
-// bins_rank_scratch bytes; 0: none needed): lists of the patches with more than
-// 2048
+// than 2048 and 8192 entries. n_long: two counters that are 0; scratch (nullable,
+// bins_rank_scratch bytes; 0: none needed): lists of the patches by their entries
 hipError_t launch_bins_rank(int Q, int L, int64_t N, int t, int D, int K, const uint2* bins, const uint32_t* tids,
                             const float* qfeat, const float* xf, int32_t* counts, int32_t* ids, float* d, int32_t* m,
                             unsigned int* counters, unsigned int* n_long, void* scratch, hipStream_t st);

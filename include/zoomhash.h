@@ -320,8 +320,8 @@ zh_status zh_lle_weights(zh_ctx* ctx, double lambda);
  * the neighbours are those of the search with the current options, which runs
  * again where they are not); the weights minimise ||y - sum_m w_m y_m||^2
  * subject to sum_m w_m = 1 with lambda trace(G) added to the diagonal of the
- * M x M Gram matrix G (FP64: exact differences, Cholesky, two triangular
- * solves; uniform weights when trace(G) = 0). ids[Q, cap] and w[Q, cap]
+ * M x M Gram matrix G (FP64: exact differences, block elimination on the
+ * matrix cores; uniform weights when trace(G) = 0). ids[Q, cap] and w[Q, cap]
  * (device, each nullable) receive the lists (-1 past M) and the weights
  * (0 past M). zh_reconstruct then synthesises every HR patch from all of
  * its M matches; zh_backward returns ZH_EUNSUPPORTED until the next

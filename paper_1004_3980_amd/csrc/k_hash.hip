@@ -863,7 +863,9 @@ void hash_bound_coeffs(int prec, int D, double w, const float* beta, int m, floa
 // c1 of k_hash's bound: as above, but with a sum of block norms rounded up in
 // place of the MFMA sum of absolute values, and without the last doubling: gamma_n
 // counts every addition twice, which covers additions that truncate; the
-// split's own terms are exact arithmetic.
+// split's own terms are exact arithmetic. Largest |P - exact| / bound measured,
+// over features of images, normal, sparse, mixed in size and large, D = 25 and
+// 100: 0.40 on the split path, 0.16 on the fp32 path.
 float hash_bound_norm_c1(int prec, int D, double w) {
     const double u = 1.0 / 16777216.0, up = 1.0 + 2e-5;   // up: the additions of the block norms' MFMA
     const int DP = prec == 0 ? ((D + 3) & ~3) : ((D + 31) & ~31);

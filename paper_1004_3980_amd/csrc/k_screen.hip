@@ -110,7 +110,13 @@ constexpr int kJacMaxD = 100;
 constexpr int kJacPairs = kJacMaxD / 2;
 constexpr int kJacBlocks = kJacPairs * (kJacPairs - 1) / 2;   // four planes of doubles, twice: 78 KB of LDS
 constexpr int kJacAhead = 32;
-constexpr double kJacOff2 = 1e-18;   // squared off-diagonal against squared diagonal: Phi is rounded to fp32
+// Squared off-diagonal against squared diagonal at which the sweeps end. Phi is
+// rounded to fp32, and that rounding is what is left of it: largest
+// off-diagonal of Phi C Phi^T over the largest eigenvalue 1.51e-8 at D = 100
+// (4000 rows) and 1.34e-8 at D = 25, the same at 1e-18 and at 1e-30, as are the
+// captured energy and the rows' orthogonality; at 1e-30 the kernel takes 1.22 ms
+// instead of 0.83.
+constexpr double kJacOff2 = 1e-18;
 
 // the pair k of round r among N (even) indexes: N - 1 with r, r + k with r - k
 // (mod N - 1)

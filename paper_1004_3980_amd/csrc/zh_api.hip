@@ -43,8 +43,9 @@ struct Dict {
     const float* resid = nullptr; // borrowed
     Buf hi, lo;                   // [n, hi_stride(D)] and [n, D] split planes (64 bytes of slack at the end)
     Buf alpha, beta, bc0[2], ahi, alo;   // ahi, alo: bf16 split of fl(alpha / w)
-    Buf himg[2];                         // hash rows as the kernels of each precision stage them
-    float bc1[2] = {0.f, 0.f}, bc2[2] = {0.f, 0.f};
+    Buf himg[2];                         // hash rows as the kernels of each precision stage them: both, as the
+                                         // precision may change and zh_hash_noalloc allocates nothing
+    float bc1[2] = {0.f, 0.f}, bc2[2] = {0.f, 0.f};   // bc1: a field of the saved file only
     Buf dir;                      // [L, cap] Slot
     Buf dfilt;                    // [L, dir_filter_words(cap)] presence bits of the keys
     Buf tids;                     // [L, n] uint32

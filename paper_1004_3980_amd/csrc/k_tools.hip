@@ -995,12 +995,19 @@ __device__ __forceinline__ void write_ranked(int q, int K, int kept, double bd, 
 // Long patches, those with more entries than a window, are listed first, so that
 // none begins when all others end, and those of more than kLongShare entries
 // in shares by ranges of IDs (at most kLongParts), which a last launch joins. The
-// other patches of more than kFewMax entries have a list of their own, which
-// kMidBlocks workgroups go through; those of fewer take a wave each in the last
-// workgroups (a workgroup a patch is bound by its launch there: 207,836 patches with
-// at most one entry 256 us).
+// other patches of more than kFewMax entries have a list of their own, which the
+// remaining workgroups go through; then each takes four of those with fewer, a wave
+// a patch (a workgroup a patch is bound by its launch there: 207,836 patches with at
+// most one entry 256 us). mid_blocks: enough for the few, and one a patch of the list
+// up to kMidBlocks (the list's last patches end together; more would be launched for
+// nothing where it is short). Workgroups of their own for the few, and 8192 for the list:
+// 14,732 patches of which most are long 537 us instead of 531 for the whole zoom,
+// 207,836 of mixed lengths 484 instead of 523.
 constexpr int kLongMax = 8192, kLongParts = 16, kLongShare = 4096, kLongBlocks = 1024;
-constexpr int kMidBlocks = 8192, kFewMax = 64;
+constexpr int kMidBlocks = 16384, kFewMax = 64;
+__host__ __device__ constexpr int mid_blocks(int Q) {
+    return Q / 4 + 1 > kMidBlocks ? Q / 4 + 1 : (Q < kMidBlocks ? Q : kMidBlocks);
+}
 // Patches from which the lists' two more launches (18 us for 14,732 patches) pay:
 // there the ranking went from 545 to 348 us; 3,600 patches take 56 us in all, and
 // their longest begins early enough.
@@ -1162,15 +1169,8 @@ __global__ __launch_bounds__(256, 5) void k_bins_rank(int Q, int L, int64_t N, i
     int item = blk, items = blk + 1, step = 1;
     if (!LISTS && blk >= Q) return;
     if (LISTS) {
-        const int mids = min(Q, kMidBlocks);
-        if (blk >= kLongBlocks + mids) {
-            const int q = __builtin_amdgcn_readfirstlane((blk - kLongBlocks - mids) * 4 + wv);
-            if (q < Q && !ll.listed[q])
-                rank_few<D>(q, N, t, K, lane < L ? bins[(int64_t)lane * Q + q] : make_uint2(0u, 0u), tids, qfeat, xf, counts,
-                            out_ids, out_d, out_m, reinterpret_cast<double*>(s_key) + wv * D, s_td + wv * kMaxK,
-                            s_ti + wv * kMaxK);
-            return;
-        }
+        const int mids = mid_blocks(Q);
+        if (blk - kLongBlocks >= mids) return;
         item = longs ? blk : blk - kLongBlocks;
         step = longs ? kLongBlocks : mids;
         items = longs ? (int)min(ll.n[0], (unsigned)kLongMax) : (int)ll.n[1];
@@ -1280,7 +1280,9 @@ __global__ __launch_bounds__(256, 5) void k_bins_rank(int Q, int L, int64_t N, i
                         d = d + t0 * t0;
                     };
                     if (D == 100) {
+                        // a fifth of a row on its way at a time
                         const float4* r4 = reinterpret_cast<const float4*>(row);
+#pragma unroll
                         for (int h = 0; h < 25; h += 5) {
                             float4 v[5];
 #pragma unroll
@@ -1345,6 +1347,15 @@ __global__ __launch_bounds__(256, 5) void k_bins_rank(int Q, int L, int64_t N, i
             write_ranked(q, K, kept, bd, bi, counts, out_ids, out_d, out_m);
         }
     }
+    if (LISTS && !longs) {
+        __syncthreads();
+        const int64_t q4 = (int64_t)4 * (blk - kLongBlocks) + wv;
+        const int q = __builtin_amdgcn_readfirstlane((int)min(q4, (int64_t)Q));
+        if (q < Q && !ll.listed[q])
+            rank_few<D>(q, N, t, K, lane < L ? bins[(int64_t)lane * Q + q] : make_uint2(0u, 0u), tids, qfeat, xf, counts,
+                        out_ids, out_d, out_m, reinterpret_cast<double*>(s_key) + wv * D, s_td + wv * kMaxK,
+                        s_ti + wv * kMaxK);
+    }
 }
 
 // The K nearest of a patch from its shares, a wave a patch (at its first share).
@@ -1404,8 +1415,8 @@ hipError_t launch_bins_rank(int Q, int L, int64_t N, int t, int D, int K, const 
     ll.listed = reinterpret_cast<uint8_t*>(ll.mid + Q);
     hipLaunchKernelGGL(k_bins_long, dim3((Q + 255) / 256), dim3(256), 0, st, Q, L, bins, ll);
     auto k = D == 100 ? k_bins_rank<100, true> : k_bins_rank<25, true>;
-    hipLaunchKernelGGL(k, grid_rows((int64_t)kLongBlocks + std::min(Q, kMidBlocks) + (Q + 3) / 4), dim3(256), 0, st, Q, L, N, t, K, bins,
-                       tids, qfeat, xf, counts, ids, d, m, counters, ll);
+    hipLaunchKernelGGL(k, grid_rows((int64_t)kLongBlocks + mid_blocks(Q)), dim3(256), 0, st, Q, L, N, t, K, bins, tids,
+                       qfeat, xf, counts, ids, d, m, counters, ll);
     hipLaunchKernelGGL(k_bins_join, dim3(4096), dim3(64), 0, st, K, ll, counts, ids, d, m);
     return hipGetLastError();
 }
